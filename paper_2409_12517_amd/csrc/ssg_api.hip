@@ -48,12 +48,12 @@ void backward_gemm_shapes(const ssg_mlp_desc &desc, BackwardGemms &b) {
     b.dw3.c_f32 = dw_f32;
     // a13: dX = dU^ w1^ / (sdu sw1) + dG^ w2^ / (sdg sw2); w1^ [f,d] = [K,N]
     b.dx.epilogue = ssg::EPI_STORE; b.dx.a_fmt = ssg::kE5M2; b.dx.M = T; b.dx.N = dm; b.dx.K = f; b.dx.layout = 1;
-    b.dx.part = ssg::gemm_sum_in_one_launch_ok(dm, f) ? 3 : 1;
-    b.dx.c_f32 = b.dx.part == 3 ? desc.y_dtype == SSG_F32 : 1;
     // a14: dW1 = dU^T x^ / (sdu sx), dW2 = dG^T x^ / (sdg sx); dU^ [T,f] = [K,M], x^ [T,d] = [K,N]
     b.dw1.epilogue = ssg::EPI_STORE; b.dw1.a_fmt = ssg::kE5M2; b.dw1.M = f; b.dw1.N = dm; b.dw1.K = T; b.dw1.layout = 2;
     b.dw1.c_f32 = dw_f32;
     b.dw2 = b.dw1;
+    b.dx.part = ssg::gemm_sum_in_one_launch(b.dx, b.dw1) ? 3 : 1;
+    b.dx.c_f32 = b.dx.part == 3 ? desc.y_dtype == SSG_F32 : 1;
     if (desc.w3_layer_bf16) {
         // Section 4.3: dH = dY W3 and dW3 = dY^T h_b on bf16 operands, every operand with its contraction index contiguous
         b.dh.epilogue = ssg::EPI_SWIGLU_BWD; b.dh.a_fmt = ssg::kBF16; b.dh.layout = 0;
@@ -967,8 +967,8 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
     ssg::GemmArgs &g3 = bg.dw3;
     g3.A = wk + Wl.dy_q; g3.B = sv + L.h_q; g3.sa = wsc + W_SDY; g3.sb = desc->smooth ? nullptr : s;
     g3.col_scale = desc->smooth ? sinv : nullptr; g3.C = dW3;
-    // a13: dX.  One launch that runs both products into the same accumulators where the shape allows (whole K steps
-    // and tile columns); otherwise two launches, the first product through fp32 scratch
+    // a13: dX.  One launch that runs both products into the same accumulators, or (gemm_sum_in_one_launch) two
+    // launches, the first product through fp32 scratch
     float *dx_tmp = reinterpret_cast<float *>(wk + Wl.dx_tmp);
     ssg::GemmArgs &g4a = bg.dx;
     const bool dx_one = g4a.part == 3;

@@ -1,6 +1,8 @@
 // FP8 MFMA GEMMs for gfx950, one GEMM per launch: the plain store forms of every operand layout (the public
 // contraction entry points; y of the block) and the two forward forms with the fused SwiGLU epilogues.
 // The backward forms and the grouped launches are instantiated in ssg_gemm_bwd.hip.
+#include <algorithm>
+
 #include "ssg_col_range.h"
 #include "ssg_gemm_tile.h"
 
@@ -16,17 +18,21 @@ struct ColRangeParams {
     uint32_t *camax_bits;
     int blocks_x;
 };
-__global__ void __launch_bounds__(kThreads) gemm_swiglu_col_range_kernel(GemmParams p, ColRangeParams r) {
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[kUnits * kUnitBytes];
-    const int tiles = p.tiles_m * p.tiles_n;
-    if ((int)blockIdx.x < tiles) {
-        gemm_tile<EPI_SWIGLU, kE4M3, 0, 0>(p, (int)blockIdx.x, smem);
+template <int WB>
+__global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_swiglu_col_range_kernel(GemmParams p, ColRangeParams r) {
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB)];
+    const int tiles = p.tiles_m * p.tiles_n, gemm_blocks = (tiles + 7) / 8 * (WB == 4 ? 8 : 32);
+    if ((int)blockIdx.x < gemm_blocks) {
+        const int b = (int)blockIdx.x, vb = set_of<WB>(b) * 8 + (b & 7);
+        if (vb < tiles) gemm_tile<WB, EPI_SWIGLU, kE4M3, 0, 0>(p, vb, quarter_of<WB>(b), smem);
     } else {
-        const int b = (int)blockIdx.x - tiles;
+        const int b = (int)blockIdx.x - gemm_blocks;
         col_range_bf16_block<16>(r.src, r.rows, r.cols, r.camax_bits, b % r.blocks_x, b / r.blocks_x,
                                  reinterpret_cast<uint32_t *>(smem));
     }
 }
+
+static bool is_dual(const GemmArgs &a) { return a.epilogue == EPI_SWIGLU || a.epilogue == EPI_SWIGLU_Q; }
 
 bool gemm_args_ok(const GemmArgs &a) {
     if (a.epilogue < EPI_STORE || a.epilogue > EPI_SWIGLU_BWD_Q) return false;
@@ -34,7 +40,7 @@ bool gemm_args_ok(const GemmArgs &a) {
     if (a.a_fmt != kE4M3 && a.a_fmt != kE5M2 && a.a_fmt != kBF16) return false;
     // bf16 operands: the two forms the unquantized last layer needs, K-contiguous operands only
     if (a.a_fmt == kBF16 && (a.layout != 0 || a.part != 0 || (a.epilogue != EPI_STORE && a.epilogue != EPI_SWIGLU_BWD))) return false;
-    const bool dual = a.epilogue == EPI_SWIGLU || a.epilogue == EPI_SWIGLU_Q;
+    const bool dual = is_dual(a);
     if (dual && (!a.B2 || a.a_fmt != kE4M3 || a.layout != 0)) return false;
     if (a.epilogue == EPI_SWIGLU && (!a.C2 || !a.camax_bits)) return false;
     if (a.tail_src && (a.epilogue != EPI_SWIGLU || !a.tail_camax_bits || a.tail_rows <= 0 || a.tail_cols <= 0 ||
@@ -51,15 +57,80 @@ bool gemm_args_ok(const GemmArgs &a) {
     if ((a.part == 2) != (a.add != nullptr)) return false;
     if (a.part == 1 && !a.c_f32) return false;
     if ((a.part == 3) != (a.A_ph2 != nullptr) || (a.part == 3 && (!a.B_ph2 || !a.sa || !a.sb || !a.sa_ph2 || !a.sb_ph2))) return false;
-    if (a.part == 3 && !gemm_sum_in_one_launch_ok(a.N, a.K)) return false;
     if ((a.keep_u != nullptr) != (a.keep_g != nullptr) || (a.keep_u && a.epilogue != EPI_SWIGLU_BWD_Q)) return false;
     if (bwd && (!a.U || !a.G || !a.C2 || !a.amax_bits || !a.amax_bits2)) return false;
     return true;
 }
 
-// The one-launch form of a sum of two products has no general loop body: whole K steps (at least two) and whole
-// tile columns of the K-major B operand only.
-bool gemm_sum_in_one_launch_ok(int64_t N, int64_t K) { return K % BK == 0 && K >= 2 * BK && N % BN == 0; }
+// The large tile's form of a sum of two products has no general loop body: whole K steps only, at least two.
+static bool sum_in_large_tile_ok(int64_t K) { return K % BK == 0 && K >= 2 * BK; }
+
+// ---- which tile computes a launch --------------------------------------------------------------------------------
+// The 256 x 256 tile reads half as many operand bytes per product as the 128 x 128 one and keeps the matrix cores
+// about 90 % busy where it fills the chip (y at T = 4096, d = 4096, f = 11008: 133 us against 168); the small one has
+// four times the workgroups, two to a compute unit, whose epilogues run under each other's main loops (y at T = 2048,
+// d = 2048, f = 5504, 64 large tiles for 256 compute units: 53 us against 30).  Which wins is a matter of how many
+// tiles there are, so the time of a launch is estimated for both and the smaller one taken: over a range of training
+// steps, inference calls and contractions the choice stays within 3 % of the better of the two, and within 6 % for
+// every one of them.
+
+// Microseconds of one tile with all compute units busy, from time stamps (large tile: 1.33 per K step, 1.45 in the
+// long tiles of the one-launch sum, which all run at once; 2.5 before the first step; the epilogue: 33 with the SwiGLU
+// derivative, 42 when it also casts, 10 for U, G or an fp32 store, 6 for bf16).  Small tile, two on a compute unit:
+// 0.96 per K step, 3.5 before and after, a quarter of the large tile's epilogue.
+double gemm_tile_cost(const GemmArgs &a, int WB) {
+    const int64_t kbytes = a.a_fmt == kBF16 ? 2 * a.K : a.K;
+    const double ksteps = (double)((kbytes + BK - 1) / BK) * (a.part == 3 ? 2.0 : 1.0);
+    double epilogue = a.c_f32 ? 10.0 : 6.0;
+    if (is_dual(a)) epilogue = 10.0;
+    if (a.epilogue == EPI_SWIGLU_BWD) epilogue = 33.0;
+    if (a.epilogue == EPI_SWIGLU_BWD_Q) epilogue = 42.0;
+    if (WB == 2) return 3.5 + 0.96 * ksteps + 0.25 * epilogue;
+    return 2.5 + (a.part == 3 ? 1.45 : 1.33) * ksteps + epilogue;
+}
+
+// Estimated time of the GEMMs of `list` in one grid.
+static double grid_time(const GemmArgs *const *list, int n, int WB) {
+    double sum = 0.0, longest = 0.0;
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) {
+        const int64_t edge = tile_edge(WB), cols = is_dual(*list[i]) ? edge / 2 : edge;
+        const int64_t t = ((list[i]->M + edge - 1) / edge) * ((list[i]->N + cols - 1) / cols);
+        const double cost = gemm_tile_cost(*list[i], WB);
+        tiles += t;
+        sum += cost * (double)t;
+        longest = std::max(longest, cost);
+    }
+    if (WB == 2) {
+        // a tile that has its compute unit to itself takes 0.65 of the time of two that share one; beyond that the
+        // tiles drift out of step and the rounds blur
+        if (tiles <= kComputeUnits) return 0.65 * longest;
+        return std::max(longest, sum / (2.0 * kComputeUnits));
+    }
+    // one tile per compute unit: a single GEMM runs in whole rounds, a group's last round is filled by its other members
+    const double rounds = (double)((tiles + kComputeUnits - 1) / kComputeUnits);
+    return n == 1 ? rounds * longest : std::max(longest, sum / kComputeUnits);
+}
+
+int gemm_wave_blocks(const GemmArgs *const *list, int n) {
+    for (int i = 0; i < n; ++i) {
+        if (list[i]->a_fmt == kBF16 || list[i]->part == 1 || list[i]->part == 2) return 4;      // not built in the small tile
+        if (list[i]->part == 3 && !sum_in_large_tile_ok(list[i]->K)) return 2;
+    }
+    return grid_time(list, n, 2) < grid_time(list, n, 4) ? 2 : 4;
+}
+
+// The input gradient of a hidden width that is no multiple of 128: in one launch of small tiles together with the
+// weight gradients, or as two launches of large tiles through fp32 scratch and the weight gradients each on its own
+// (T = 4096, d = 4096, f = 11024, the whole step: 1982 us against 1870; T = 2048, d = 3072, f = 8208: 745 against 884).
+bool gemm_sum_in_one_launch(const GemmArgs &dx, const GemmArgs &dw) {
+    if (sum_in_large_tile_ok(dx.K)) return true;
+    GemmArgs sum = dx, half = dx;
+    sum.part = 3; half.part = 1; half.c_f32 = 1;
+    const GemmArgs *one[3] = {&sum, &dw, &dw}, *halves = &half, *single = &dw;
+    const double separate = 2.0 * grid_time(&halves, 1, 4) + 2.0 * std::min(grid_time(&single, 1, 4), grid_time(&single, 1, 2));
+    return grid_time(one, 3, 2) < separate;
+}
 
 int gemm_profile_tag(const GemmArgs &a) {
     // 2 * epilogue + A format; the halves of a sum of two products run as two launches get 9 and 10, the sum in
@@ -70,39 +141,46 @@ int gemm_profile_tag(const GemmArgs &a) {
     return 2 * (a.epilogue == EPI_SWIGLU_BWD_Q ? (int)EPI_SWIGLU_BWD : a.epilogue) + a.a_fmt;
 }
 
-template <int EPI, int LAY>
+template <int WB, int EPI, int LAY>
 static void launch_fmt(const GemmParams &p, int a_fmt, unsigned blocks, hipStream_t st) {
-    if (a_fmt == kE4M3) hipLaunchKernelGGL((gemm_kernel<EPI, kE4M3, 0, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((gemm_kernel<EPI, kE5M2, 0, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
+    if (a_fmt == kE4M3) hipLaunchKernelGGL((gemm_kernel<WB, EPI, kE4M3, 0, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((gemm_kernel<WB, EPI, kE5M2, 0, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
 }
 
-bool launch_gemm(const GemmArgs &a, hipStream_t st) {
-    if (!gemm_args_ok(a)) return false;
-    if (a.part != 0 || a.epilogue == EPI_SWIGLU_BWD || a.epilogue == EPI_SWIGLU_BWD_Q) return launch_gemm_bwd(a, st);
+template <int WB>
+static void launch_gemm_wb(const GemmArgs &a, hipStream_t st) {
     const GemmParams p = make_gemm_params(a);
-    const unsigned blocks = (unsigned)p.tiles_m * (unsigned)p.tiles_n;
-    profile_before(gemm_profile_tag(a), st, gemm_flops(a));
+    const unsigned blocks = (unsigned)sets_of(p) * set_workgroups(WB);
     switch (a.epilogue) {
         case EPI_STORE:
-            if (a.a_fmt == kBF16) hipLaunchKernelGGL((gemm_kernel<EPI_STORE, kBF16, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
-            else if (a.layout == 2) launch_fmt<EPI_STORE, 2>(p, a.a_fmt, blocks, st);
-            else if (a.layout == 1) launch_fmt<EPI_STORE, 1>(p, a.a_fmt, blocks, st);
-            else launch_fmt<EPI_STORE, 0>(p, a.a_fmt, blocks, st);
+            if (a.a_fmt == kBF16) hipLaunchKernelGGL((gemm_kernel<4, EPI_STORE, kBF16, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
+            else if (a.layout == 2) launch_fmt<WB, EPI_STORE, 2>(p, a.a_fmt, blocks, st);
+            else if (a.layout == 1) launch_fmt<WB, EPI_STORE, 1>(p, a.a_fmt, blocks, st);
+            else launch_fmt<WB, EPI_STORE, 0>(p, a.a_fmt, blocks, st);
             break;
         case EPI_SWIGLU:
             if (a.tail_src) {
                 ColRangeParams r{static_cast<const uint16_t *>(a.tail_src), a.tail_rows, a.tail_cols, a.tail_camax_bits,
                                  col_range_blocks_x(a.tail_cols)};
                 const unsigned extra = (unsigned)(r.blocks_x * col_range_blocks_y(a.tail_rows));
-                hipLaunchKernelGGL(gemm_swiglu_col_range_kernel, dim3(blocks + extra), dim3(kThreads), 0, st, p, r);
+                hipLaunchKernelGGL(gemm_swiglu_col_range_kernel<WB>, dim3(blocks + extra), dim3(kThreads), 0, st, p, r);
             } else {
-                hipLaunchKernelGGL((gemm_kernel<EPI_SWIGLU, kE4M3, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
+                hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU, kE4M3, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
             }
             break;
         default:   // EPI_SWIGLU_Q
-            hipLaunchKernelGGL((gemm_kernel<EPI_SWIGLU_Q, kE4M3, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
+            hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU_Q, kE4M3, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
             break;
     }
+}
+
+bool launch_gemm(const GemmArgs &a, hipStream_t st) {
+    if (!gemm_args_ok(a)) return false;
+    if (a.part != 0 || a.epilogue == EPI_SWIGLU_BWD || a.epilogue == EPI_SWIGLU_BWD_Q) return launch_gemm_bwd(a, st);
+    profile_before(gemm_profile_tag(a), st, gemm_flops(a));
+    const GemmArgs *one = &a;
+    if (gemm_wave_blocks(&one, 1) == 4) launch_gemm_wb<4>(a, st);
+    else launch_gemm_wb<2>(a, st);
     profile_after(st);
     return true;
 }

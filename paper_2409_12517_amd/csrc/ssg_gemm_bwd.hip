@@ -18,10 +18,10 @@
 
 namespace ssg {
 
-// Up to four GEMMs in one grid, one after the other in dispatch order.  Workgroups are dealt in sets of 8
-// consecutive ids (one per XCD, so that vblock % 8 stays the XCD inside each GEMM and map_tile's per-XCD patches
-// survive); member i runs sets [first[i], first[i] + sets[i]) of its GEMM -- a GEMM may be split between two
-// launches at a set boundary.
+// Up to four GEMMs in one grid, one after the other in dispatch order, all in the same tile (gemm_wave_blocks).
+// Workgroups are dealt in sets of 8 large tiles (see set_of: one per XCD, so that vblock % 8 stays the XCD inside each
+// GEMM and map_tile's per-XCD patches survive); member i runs sets [first[i], first[i] + sets[i]) of its GEMM -- a GEMM
+// may be split between two launches at a set boundary.
 struct GroupParams {
     GemmParams p[4];
     int sets[4];
@@ -29,27 +29,28 @@ struct GroupParams {
 };
 
 // dH (with the SwiGLU derivative; EPI = EPI_SWIGLU_BWD or EPI_SWIGLU_BWD_Q), then the first part of dW3: both read dY^.
-template <int EPI>
-__global__ void __launch_bounds__(kThreads) gemm_group_dh_dw3_kernel(GroupParams g) {
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[kUnits * kUnitBytes];
-    const int G = (int)(blockIdx.x >> 3), x = (int)(blockIdx.x & 7);
+template <int WB, int EPI>
+__global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_group_dh_dw3_kernel(GroupParams g) {
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB)];
+    const int G = set_of<WB>((int)blockIdx.x), x = (int)(blockIdx.x & 7), q = quarter_of<WB>((int)blockIdx.x);
     if (G < g.sets[0]) {
         const int vb = G * 8 + x;
-        if (vb < g.p[0].tiles_m * g.p[0].tiles_n) gemm_tile<EPI, kE5M2, 0, 1>(g.p[0], vb, smem);
+        if (vb < g.p[0].tiles_m * g.p[0].tiles_n) gemm_tile<WB, EPI, kE5M2, 0, 1>(g.p[0], vb, q, smem);
     } else {
         const int vb = (G - g.sets[0] + g.first[1]) * 8 + x;
-        if (vb < g.p[1].tiles_m * g.p[1].tiles_n) gemm_tile<EPI_STORE, kE5M2, 0, 2>(g.p[1], vb, smem);
+        if (vb < g.p[1].tiles_m * g.p[1].tiles_n) gemm_tile<WB, EPI_STORE, kE5M2, 0, 2>(g.p[1], vb, q, smem);
     }
 }
 
 // dX (sum of two products in one tile: the long tiles, dealt first), then dW1, dW2 and the rest of dW3.
-__global__ void __launch_bounds__(kThreads) gemm_group_dx_dw_kernel(GroupParams g) {
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[kUnits * kUnitBytes];
-    int G = (int)(blockIdx.x >> 3);
-    const int x = (int)(blockIdx.x & 7);
+template <int WB>
+__global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_group_dx_dw_kernel(GroupParams g) {
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB)];
+    int G = set_of<WB>((int)blockIdx.x);
+    const int x = (int)(blockIdx.x & 7), q = quarter_of<WB>((int)blockIdx.x);
     if (G < g.sets[0]) {
         const int vb = G * 8 + x;
-        if (vb < g.p[0].tiles_m * g.p[0].tiles_n) gemm_tile<EPI_STORE, kE5M2, 3, 1>(g.p[0], vb, smem);
+        if (vb < g.p[0].tiles_m * g.p[0].tiles_n) gemm_tile<WB, EPI_STORE, kE5M2, 3, 1>(g.p[0], vb, q, smem);
         return;
     }
     G -= g.sets[0];
@@ -57,10 +58,9 @@ __global__ void __launch_bounds__(kThreads) gemm_group_dx_dw_kernel(GroupParams 
     if (G >= g.sets[1]) { G -= g.sets[1]; m = 2; if (G >= g.sets[2]) { G -= g.sets[2]; m = 3; } }
     const GemmParams &p = g.p[m];
     const int vb = (G + g.first[m]) * 8 + x;
-    if (vb < p.tiles_m * p.tiles_n) gemm_tile<EPI_STORE, kE5M2, 0, 2>(p, vb, smem);
+    if (vb < p.tiles_m * p.tiles_n) gemm_tile<WB, EPI_STORE, kE5M2, 0, 2>(p, vb, q, smem);
 }
 
-static int sets_of(const GemmParams &p) { return (p.tiles_m * p.tiles_n + 7) / 8; }
 int gemm_tile_sets(const GemmArgs &a) { return sets_of(make_gemm_params(a)); }
 
 static bool is_wgrad(const GemmArgs &a) { return a.epilogue == EPI_STORE && a.part == 0 && a.layout == 2 && a.a_fmt == kE5M2; }
@@ -83,18 +83,6 @@ bool gemm_group_ok(const GemmArgs *const *list, int n) {
 // from its K steps and its epilogue, so the end of a launch can be predicted by replaying that dispatch.  A launch
 // whose last tiles start a round of their own pays a whole tile time for them; moving sets of the weight gradient
 // from the first launch to the second (or back) shifts work between the two launches' last rounds.
-static double tile_cost(const GemmArgs &a) {
-    const GemmParams p = make_gemm_params(a);
-    // microseconds, from per-workgroup time stamps at the Llama2-7B shape with all compute units busy: 1.33 per K
-    // step (1.45 in the long tiles of the one-launch sum, which all run at once), 2.5 before the first step, and the
-    // epilogue: 33 with the SwiGLU derivative (42 when it also casts), 10 for an fp32 store, 6 for bf16
-    const double ksteps = (double)((p.K + BK - 1) / BK) * (a.part == 3 ? 2.0 : 1.0);
-    double epilogue = a.c_f32 ? 10.0 : 6.0;
-    if (a.epilogue == EPI_SWIGLU_BWD) epilogue = 33.0;
-    if (a.epilogue == EPI_SWIGLU_BWD_Q) epilogue = 42.0;
-    return 2.5 + (a.part == 3 ? 1.45 : 1.33) * ksteps + epilogue;
-}
-
 static double replay_dispatch(const double *cost, const int *tiles, int n, int units, std::vector<double> &free_at) {
     // free_at: a min-heap of the times at which the compute units become free
     free_at.assign((size_t)units, 0.0);
@@ -119,10 +107,10 @@ int gemm_group_split_sets(const GemmArgs &dh, const GemmArgs &dw_split, const Ge
     double cost_b[4]; int tiles_b[4];
     for (int i = 0; i < n_second; ++i) {
         const GemmParams p = make_gemm_params(*second[i]);
-        cost_b[i] = tile_cost(*second[i]); tiles_b[i] = p.tiles_m * p.tiles_n;
+        cost_b[i] = gemm_tile_cost(*second[i], 4); tiles_b[i] = p.tiles_m * p.tiles_n;
     }
-    cost_b[n_second] = tile_cost(dw_split);
-    const double cost_a[2] = {tile_cost(dh), tile_cost(dw_split)};
+    cost_b[n_second] = gemm_tile_cost(dw_split, 4);
+    const double cost_a[2] = {gemm_tile_cost(dh, 4), gemm_tile_cost(dw_split, 4)};
     std::vector<double> heap;
     // the predicted time is a step function of the split.  Of the longest run of equally good splits take a point a
     // quarter of the run below its upper end: measured, the second launch behaves like a fluid (its tiles have
@@ -150,11 +138,19 @@ int gemm_group_split_sets(const GemmArgs &dh, const GemmArgs &dw_split, const Ge
     return best_lo + (best_len - 1) - (best_len - 1) / 4;
 }
 
+template <int WB>
+static void launch_group(const GroupParams &g, int n, int epilogue, dim3 grid, hipStream_t st) {
+    if (n >= 3) hipLaunchKernelGGL(gemm_group_dx_dw_kernel<WB>, grid, dim3(kThreads), 0, st, g);
+    else if (epilogue == EPI_SWIGLU_BWD) hipLaunchKernelGGL((gemm_group_dh_dw3_kernel<WB, EPI_SWIGLU_BWD>), grid, dim3(kThreads), 0, st, g);
+    else hipLaunchKernelGGL((gemm_group_dh_dw3_kernel<WB, EPI_SWIGLU_BWD_Q>), grid, dim3(kThreads), 0, st, g);
+}
+
 bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipStream_t st) {
     if (!gemm_group_ok(list, n)) return false;
     GroupParams g;
     int total = 0;
     double flops = 0.0;
+    const int wb = gemm_wave_blocks(list, n);
     for (int i = 0; i < 4; ++i) {
         g.p[i] = make_gemm_params(*list[i < n ? i : 0]);
         g.sets[i] = i < n ? sets_of(g.p[i]) : 0;
@@ -182,30 +178,36 @@ bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipSt
         total += g.sets[i];
     }
     if (total == 0) return true;
-    const dim3 grid((unsigned)total * 8u);
+    const dim3 grid((unsigned)total * set_workgroups(wb));
     profile_before(n == 2 ? 16 : 17, st, flops);
-    if (n >= 3) hipLaunchKernelGGL(gemm_group_dx_dw_kernel, grid, dim3(kThreads), 0, st, g);
-    else if (list[0]->epilogue == EPI_SWIGLU_BWD)
-        hipLaunchKernelGGL(gemm_group_dh_dw3_kernel<EPI_SWIGLU_BWD>, grid, dim3(kThreads), 0, st, g);
-    else
-        hipLaunchKernelGGL(gemm_group_dh_dw3_kernel<EPI_SWIGLU_BWD_Q>, grid, dim3(kThreads), 0, st, g);
+    if (wb == 4) launch_group<4>(g, n, list[0]->epilogue, grid, st);
+    else launch_group<2>(g, n, list[0]->epilogue, grid, st);
     profile_after(st);
     return true;
 }
 
 // The backward forms launched on their own (a.part != 0, or one of the SwiGLU-backward epilogues); the
 // argument set has passed gemm_args_ok.
+template <int WB>
+static void launch_bwd_wb(const GemmArgs &a, hipStream_t st) {
+    const GemmParams p = make_gemm_params(a);
+    const dim3 grid((unsigned)sets_of(p) * set_workgroups(WB));
+    if (a.epilogue == EPI_SWIGLU_BWD) hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU_BWD, kE5M2, 0, 1>), grid, dim3(kThreads), 0, st, p);
+    else if (a.epilogue == EPI_SWIGLU_BWD_Q) hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU_BWD_Q, kE5M2, 0, 1>), grid, dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((gemm_kernel<WB, EPI_STORE, kE5M2, 3, 1>), grid, dim3(kThreads), 0, st, p);
+}
+
 bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st) {
     const GemmParams p = make_gemm_params(a);
-    const dim3 grid((unsigned)p.tiles_m * (unsigned)p.tiles_n);
+    const dim3 grid((unsigned)sets_of(p) * set_workgroups(4));
+    const GemmArgs *one = &a;
     profile_before(gemm_profile_tag(a), st, gemm_flops(a));
     if (a.epilogue == EPI_SWIGLU_BWD && a.a_fmt == kBF16)
-        hipLaunchKernelGGL((gemm_kernel<EPI_SWIGLU_BWD, kBF16, 0, 0>), grid, dim3(kThreads), 0, st, p);
-    else if (a.epilogue == EPI_SWIGLU_BWD) hipLaunchKernelGGL((gemm_kernel<EPI_SWIGLU_BWD, kE5M2, 0, 1>), grid, dim3(kThreads), 0, st, p);
-    else if (a.epilogue == EPI_SWIGLU_BWD_Q) hipLaunchKernelGGL((gemm_kernel<EPI_SWIGLU_BWD_Q, kE5M2, 0, 1>), grid, dim3(kThreads), 0, st, p);
-    else if (a.part == 1) hipLaunchKernelGGL((gemm_kernel<EPI_STORE, kE5M2, 1, 1>), grid, dim3(kThreads), 0, st, p);
-    else if (a.part == 2) hipLaunchKernelGGL((gemm_kernel<EPI_STORE, kE5M2, 2, 1>), grid, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((gemm_kernel<EPI_STORE, kE5M2, 3, 1>), grid, dim3(kThreads), 0, st, p);
+        hipLaunchKernelGGL((gemm_kernel<4, EPI_SWIGLU_BWD, kBF16, 0, 0>), grid, dim3(kThreads), 0, st, p);
+    else if (a.part == 1) hipLaunchKernelGGL((gemm_kernel<4, EPI_STORE, kE5M2, 1, 1>), grid, dim3(kThreads), 0, st, p);
+    else if (a.part == 2) hipLaunchKernelGGL((gemm_kernel<4, EPI_STORE, kE5M2, 2, 1>), grid, dim3(kThreads), 0, st, p);
+    else if (gemm_wave_blocks(&one, 1) == 4) launch_bwd_wb<4>(a, st);
+    else launch_bwd_wb<2>(a, st);
     profile_after(st);
     return true;
 }

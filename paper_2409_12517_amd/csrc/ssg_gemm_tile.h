@@ -8,18 +8,22 @@
 // v_mfma_f32_32x32x64_f8f6f4, the only FP8 form that reaches the full rate on
 // this chip; its per-operand format selectors take E4M3 or E5M2.
 //
-// Workgroup: 256 threads = 4 waves as 2 (M) x 2 (N), one per SIMD; tile 256 x 256 x 128;
-// each wave owns 128 x 128 outputs = 4 x 4 MFMA blocks (256 accumulator registers).
-// Operand tiles are streamed global -> LDS with 16-byte direct-to-LDS loads (no staging
-// registers) into a ring of five 32 KB tiles.  A row of a tile is 128 bytes; the eight
-// 16-byte chunks of a row are stored XOR-permuted by the row index so that the lanes that
-// read the same logical chunk of different rows spread over all banks.
+// Workgroup: 256 threads = 4 waves as 2 (M) x 2 (N).  Two tile sizes, by the template parameter WB:
+//   WB = 4  256 x 256 x 128, each wave owns 128 x 128 outputs = 4 x 4 MFMA blocks (256 accumulator registers, one wave
+//           per SIMD).  Bound by the matrix cores and the power they draw: 90 % of the cycles of the main loop are MFMA.
+//   WB = 2  128 x 128 x 128, 64 x 64 outputs per wave (64 accumulator registers), two workgroups per compute unit.
+//           Bound by LDS: every 1024 MFMA cycles of a compute unit need 64 KB written and 128 KB read there (1536 cycles
+//           at 128 B); main loop about 60 % MFMA, but one workgroup's prologue and epilogue run under the other's main
+//           loop, and four times the tiles fill the chip where the large ones leave most of it idle.
+// Operand tiles are streamed global -> LDS with 16-byte direct-to-LDS loads (no staging registers) into a ring of five
+// 32 KB (16 KB) tiles.  A row of a tile is 128 bytes; the eight 16-byte chunks of a row are stored XOR-permuted by the
+// row index so that the lanes that read the same logical chunk of different rows spread over all banks.
 //
 // Epilogues:
 //   STORE       C = acc / (sa*sb) [* col_scale[n]] [+ addend], bf16 or fp32.  A sum of two
 //               products (the input gradient) runs as two launches: the first leaves its
 //               scaled product as fp32 scratch, the second adds it before rounding.
-//   SWIGLU      B tile = 128 rows of W1 and the same 128 rows of W2, so a wave
+//   SWIGLU      B tile = 128 (64) rows of W1 and the same rows of W2, so a wave
 //               holds u and g of the same (t,i): stores bf16 U, G and folds
 //               max_t |u * Swish(g)| into the per-channel maxima (Section 4.4).
 //   SWIGLU_BWD  acc -> dH (times the channel factor s_i), reads bf16 U, G, stores
@@ -37,9 +41,12 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 typedef __attribute__((address_space(1))) const void *global_void_ptr;
 
-constexpr int BM = 256, BN = 256, BK = 128;
-constexpr int kUnitBytes = BM * BK;               // one operand tile of one K step: 256 rows x 128 B = 32 KB
-constexpr int kUnits = 5;                         // ring of operand tiles in LDS: all 160 KB
+// The tile is square, 64 * WB rows and columns, WB = 4 or 2 blocks of 32 x 32 per wave and direction.
+constexpr int BK = 128;
+constexpr int tile_edge(int WB) { return 64 * WB; }
+constexpr int unit_bytes(int WB) { return tile_edge(WB) * BK; }   // one operand tile of one K step: 32 or 16 KB
+constexpr int kUnits = 5;                         // ring of operand tiles in LDS: all 160 KB, or half of them
+constexpr int smem_bytes(int WB) { return kUnits * unit_bytes(WB); }
 
 static __device__ uint4 g_zero_chunk = {0u, 0u, 0u, 0u}; // source of the zero fill of a ragged K tail (one per translation unit)
 
@@ -51,7 +58,7 @@ struct GemmParams {
     const uint16_t *U, *G;
     uint32_t *camax_bits, *amax_bits, *amax_bits2;
     int c_f32;
-    int tiles_m, tiles_n;
+    int tiles_m, tiles_n;       // in tiles of 256 x 256, also where the small tiles compute
     float *tmp;          // fp32 [M, N] scratch for the two-launch form of a sum of two products (may be null)
     const float *add;    // gemm_kernel<.., ADD>: fp32 [M, N] added before the store
     const float *q_scale, *q_scale2;        // EPI_SWIGLU_BWD_Q: scales of dU, dG
@@ -131,11 +138,10 @@ __device__ __forceinline__ Dequant inv_scale_product(const float *sa, const floa
     return d;
 }
 
-// Workgroup -> tile.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its
+// Large tile number -> its place.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its
 // own L2, so give every XCD a contiguous range of a tile order in which any 32 consecutive tiles
 // (one per CU of the XCD) form a 4 x 8 patch: 12 operand tiles fetched for 32 computed.
-// `vblock` is the workgroup's index among the workgroups of this GEMM (the launch's blockIdx.x, or the index
-// inside its share of a grouped launch, which keeps vblock % 8 = the XCD).
+// `vblock` is the tile's index among the tiles of this GEMM; vblock % 8 = the XCD.
 __device__ __forceinline__ void map_tile(const GemmParams &p, int vblock, int &tile_m, int &tile_n) {
     const int total = p.tiles_m * p.tiles_n;
     const int per_xcd = (total + 7) / 8;
@@ -156,15 +162,26 @@ __device__ __forceinline__ void map_tile(const GemmParams &p, int vblock, int &t
 }
 
 // ------------------------------------------------------------------------------------------------
-// 4 waves (one per SIMD), 128 x 128 wave tiles: 256 accumulator registers per lane (the AGPR half of
+// Large tile: 4 waves (one per SIMD), 128 x 128 wave tiles: 256 accumulator registers per lane (the AGPR half of
 // the register file); every A and B row block is read from LDS by only two waves.  With a single
-// wave per SIMD there is no partner to hide stalls, so the wave software-pipelines itself: while the
+// wave per SIMD there is no partner to hide stalls, so the wave software-pipelines itself (the small tile's waves do
+// the same, with 4 MFMAs, 4 fragments and 4 loads where 16, 8 and 8 stand here): while the
 // 16 MFMAs of one 64-wide K half run from one fragment set, the next half's fragments are read into
 // the other set, one fragment after every second MFMA, and one direct-to-LDS load of the new operand
 // tiles follows every pair of MFMAs throughout the K step.  One barrier per K step, in its middle: by
 // then every wave holds both halves of step k in registers, so the barrier both retires step k's ring
 // slots and publishes step k+1 (each wave first waits for its own DMA share).
 constexpr int kThreads = 256;
+constexpr int waves_per_simd(int WB) { return WB == 4 ? 1 : 2; }
+
+template <int N> __device__ __forceinline__ void wait_dma() {       // at most N direct-to-LDS loads still in flight
+    static_assert(N == 4 || N == 8 || N == 16, "a wait for one or two units");
+#if defined(__HIP_DEVICE_COMPILE__)
+    if (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    if (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    if (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+#endif
+}
 
 // PART (plain store only) names the role in a sum of two products run as two launches: 1 = first half (stores
 // its scaled product as fp32 scratch; the same code as 0, a separate symbol so that profiles tell it from the
@@ -172,69 +189,89 @@ constexpr int kThreads = 256;
 // is rounded and stored).  0 = an ordinary GEMM.
 // LAY names how the operands lie in memory: 0 = both with the contraction index contiguous (A [M,K], B [N,K]);
 // 1 = B "K-major" (stored [K,N], N contiguous); 2 = both K-major (A stored [K,M]).  A K-major tile is streamed
-// into LDS as 128 rows of K x 256 bytes and its MFMA fragments are read with the transposing LDS load, so the
+// into LDS as 128 rows of K x 256 (128) bytes and its MFMA fragments are read with the transposing LDS load, so the
 // backward contractions read the forward's quantized tensors as they are: no transposed copies exist.
 // PART = 3: the sum of two products in one tile -- the K loop runs twice, over (A, B) and then over (A_ph2, B_ph2)
-// of the same shapes, and the accumulators are rescaled by the ratio of the two dequantization factors in
-// between, so that one epilogue with the second factor finishes both.
-template <int EPI, int AFMT, int PART, int LAY>
-__device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock, uint8_t *smem) {
+// of the same shapes (or the other way round), and the accumulators are rescaled by the ratio of the two dequantization
+// factors in between, so that one epilogue with the last factor finishes both.
+template <int WB, int EPI, int AFMT, int PART, int LAY>
+__device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock, const int sub, uint8_t *smem) {
+    constexpr int BM = tile_edge(WB), BN = BM, WN = 32 * WB, kUnitBytes = unit_bytes(WB);
+    constexpr int NI = 2 * WB;                         // DMA instructions of 1 KB per wave and unit; fragment reads per half step
+    constexpr int kChunks = BM / 16;                   // 16-byte chunks of a K-major row
     constexpr bool ADD = PART == 2;
     constexpr bool TWO = PART == 3;
+    constexpr bool kTwoWhole = TWO && WB == 4;         // no general loop body there (see gemm_sum_in_one_launch_ok)
     static_assert(!TWO || EPI == EPI_STORE, "a sum of two products ends in the plain store epilogue");
     constexpr bool AKM = LAY == 2, BKM = LAY >= 1;
     constexpr bool kBwd = EPI == EPI_SWIGLU_BWD || EPI == EPI_SWIGLU_BWD_Q;     // dH -> dU, dG through the SwiGLU derivative
     static_assert(!(BKM && (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_Q)), "the dual-B forms take K-contiguous operands");
-    constexpr bool kDual = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_Q;     // B tile = 128 rows of W1 + 128 rows of W2
+    constexpr bool kDual = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_Q;     // B tile = half rows of W1, half of W2
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int l = tid & 63;            // (not const: see the note at the epilogue)
     const int wm = w >> 1, wn = w & 1;
     int tile_m, tile_n;
     map_tile(p, vblock, tile_m, tile_n);
-    const int64_t m0 = (int64_t)tile_m * BM;
-    const int64_t n0 = (int64_t)tile_n * (kDual ? BN / 2 : BN);
+    constexpr int kTileN = kDual ? BN / 2 : BN;
+    int64_t m0 = (int64_t)tile_m * tile_edge(4), n0 = (int64_t)tile_n * (kTileN * (4 / WB));
+    if (WB == 2) {                                    // the sub-th quarter of the large tile
+        m0 += (sub >> 1) * BM;
+        n0 += (sub & 1) * kTileN;
+        if (m0 >= p.M || n0 >= p.N) return;
+    }
 
-    // DMA slots: a unit is 32 instructions of 1 KB, 8 per wave.  K-contiguous operand: an instruction is 8 rows x
-    // 128 B (rows (8w+j)*8 + l/8).  K-major operand: 4 rows of K x 256 B (K rows (8w+j)*4 + l/16); the sixteen
-    // 16-byte chunks of a row are permuted so that a transposing read is free of bank conflicts: chunk c of K row k
-    // sits at position c ^ (k & 7) ^ (((c & 1) ^ (k >> 5 & 1)) << 3).  The 32 lanes of one K group read eight
-    // consecutive K rows of two adjacent chunks: the XOR with k & 7 spreads the rows over the eight positions of a
-    // half row, the chunk's own low bit picks the half, so the 32 words cover all 64 banks exactly once.
+    // DMA slots: a unit is 4 * NI instructions of 1 KB, NI per wave.  K-contiguous operand: an instruction is 8 rows x
+    // 128 B (rows (NI*w+j)*8 + l/8).  K-major operand: 4 rows of K x 256 B (WB = 4) or 8 x 128 B (WB = 2); the 16-byte
+    // chunks of a row are permuted so that a transposing read is free of bank conflicts.  The 32 lanes of one K group
+    // read eight consecutive K rows of two adjacent chunks, which have to cover all 64 banks once.
+    //   WB = 4 (a row is the 256-byte bank period): chunk c of K row k sits at position
+    //     c ^ (k & 7) ^ (((c & 1) ^ (k >> 5 & 1)) << 3): the XOR with k & 7 spreads the rows over the eight positions of
+    //     a half row, the chunk's own low bit picks the half.
+    //   WB = 2 (two rows are the period): position c ^ ((k >> 1 & 3) << 1): the row's parity picks the half, the XOR
+    //     spreads the four rows of one parity over four pairs of positions.
     const int lrow = l >> 3;
     const int chunk_even = (l & 7) ^ swz(lrow), chunk_odd = (l & 7) ^ swz(8 + lrow);
-    // the chunk that belongs at position `pos` of K row k (the map is its own inverse in the low three bits)
+    // the chunk that belongs at position `pos` of K row k (the maps are their own inverses in the low three bits)
     auto kmaj_chunk = [](int k, int pos) {
+        if (WB == 2) return pos ^ (((k >> 1) & 3) << 1);
         const int low = (pos ^ k) & 7;
         return low | ((((pos >> 3) ^ (k >> 5) ^ low) & 1) << 3);
     };
-    uint32_t a_lane[8], b_lane[8];
+    auto kmaj_row = [&](int j) { return (w * NI + j) * (64 / kChunks) + l / kChunks; };   // K row of this lane's chunk
+    uint32_t a_lane[NI], b_lane[NI];
     const uint8_t *b_src = p.B;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int row = (w * 8 + j) * 8 + lrow;
+    for (int j = 0; j < NI; ++j) {
+        const int row = (w * NI + j) * 8 + lrow;
         const int ck = ((j & 1) ? chunk_odd : chunk_even) * 16;
-        const int kr = (w * 8 + j) * 4 + (l >> 4);                     // K-major: K row of this lane's chunk
-        const int ckm = kmaj_chunk(kr, l & 15) * 16;                    //          and the chunk it fetches
+        const int kr = kmaj_row(j);
+        const int ckm = kmaj_chunk(kr, l % kChunks) * 16;               // K-major: the chunk this lane fetches
+        // rows (K-major: columns) beyond the matrix are clamped to its last ones: they only feed results that are
+        // not stored
         if (AKM) {
-            a_lane[j] = (uint32_t)((int64_t)kr * p.M + m0) + ckm;
+            int64_t gm = m0 + ckm;
+            gm = gm < p.M ? gm : p.M - 16;
+            a_lane[j] = (uint32_t)((int64_t)kr * p.M + gm);
         } else {
             int64_t gm = m0 + row;
             gm = gm < p.M ? gm : p.M - 1;
             a_lane[j] = (uint32_t)(gm * p.K) + ck;
         }
         if (BKM) {
-            b_lane[j] = (uint32_t)((int64_t)kr * p.N + n0) + ckm;
+            int64_t gn = n0 + ckm;
+            gn = gn < p.N ? gn : p.N - 16;
+            b_lane[j] = (uint32_t)((int64_t)kr * p.N + gn);
         } else {
             int64_t gn;
-            if (kDual) gn = n0 + (row & 127);
+            if (kDual) gn = n0 + (row & (BN / 2 - 1));
             else gn = n0 + row;
             gn = gn < p.N ? gn : p.N - 1;
             b_lane[j] = (uint32_t)(gn * p.K) + ck;
         }
     }
-    if (kDual && w >= 2) b_src = p.B2;      // waves 2, 3 fill tile rows 128..255
-    const uint32_t lds_w = (uint32_t)(w * 8) * 1024u;
+    if (kDual && w >= 2) b_src = p.B2;      // waves 2, 3 fill the upper half of the tile rows
+    const uint32_t lds_w = (uint32_t)(w * NI) * 1024u;
 
     // LDS byte offset of this lane's two 16-byte chunks of a fragment row, per K half; the row block of a
     // fragment adds a wave-uniform base and a compile-time multiple of 4 KB (an instruction immediate)
@@ -248,44 +285,49 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     // the 8-byte words whose byte j goes to output lane j, the odd lanes those for output lane 8+j; lane p of a
     // group therefore points at K row p/2 (of eight) and at half p%2 of the 16-byte chunk that holds the group's
     // 16 rows of the 32-row block.  Four such reads (K rows +0, +8, +16, +24) make one fragment.
-    uint32_t tr_a[4], tr_b[4];
+    uint32_t tr_a[WB], tr_b[WB];
     {
         const int g16 = l >> 4, kg = g16 >> 1, g1 = g16 & 1, t = (l & 15) >> 1, e = l & 1;
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb) {
+        for (int rb = 0; rb < WB; ++rb) {
             // position of chunk c in K row k = kg * 32 + t (+ multiples of 8 and 64, which do not enter)
-            const int ca = wm * 8 + rb * 2 + g1, cb = wn * 8 + rb * 2 + g1;
-            const int pa = ((ca ^ t) & 7) | ((((ca >> 3) ^ kg ^ ca) & 1) << 3);
-            const int pb = ((cb ^ t) & 7) | ((((cb >> 3) ^ kg ^ cb) & 1) << 3);
-            tr_a[rb] = (uint32_t)((kg * 32 + t) * 256 + (pa << 4) + e * 8);
-            tr_b[rb] = (uint32_t)((kg * 32 + t) * 256 + (pb << 4) + e * 8);
+            const int ca = wm * 2 * WB + rb * 2 + g1, cb = wn * 2 * WB + rb * 2 + g1;
+            auto pos = [&](int c) { return WB == 2 ? c ^ ((t >> 1) << 1) : ((c ^ t) & 7) | ((((c >> 3) ^ kg ^ c) & 1) << 3); };
+            tr_a[rb] = (uint32_t)((kg * 32 + t) * BM + (pos(ca) << 4) + e * 8);
+            tr_b[rb] = (uint32_t)((kg * 32 + t) * BM + (pos(cb) << 4) + e * 8);
         }
     }
-    const uint32_t a_wave_base = (uint32_t)(wm * 128) * BK;
-    const uint32_t b_wave_base = (uint32_t)(kDual ? wn * 64 : wn * 128) * BK;
-    auto b_block_off = [](int nb) -> uint32_t {      // SWIGLU: blocks 0, 1 from the W1 rows, 2, 3 from the W2 rows
-        return (uint32_t)(kDual ? (nb >> 1) * 128 + (nb & 1) * 32 : nb * 32) * BK;
+    const uint32_t a_wave_base = (uint32_t)(wm * WN) * BK;
+    const uint32_t b_wave_base = (uint32_t)(kDual ? wn * (WN / 2) : wn * WN) * BK;
+    auto b_block_off = [](int nb) -> uint32_t {      // SWIGLU: the first half of the blocks from the W1 rows, the others from the W2 rows
+        return (uint32_t)(kDual ? (nb / (WB / 2)) * (BN / 2) + (nb % (WB / 2)) * 32 : nb * 32) * BK;
     };
 
-    v16f acc[4][4];
+    v16f acc[WB][WB];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < WB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
+        for (int nb = 0; nb < WB; ++nb)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[mb][nb][i] = 0.0f;
 
     const int nk = (int)((p.K + BK - 1) / BK);
-    // the staging patch of the epilogue (one 32 x 128 slab of a wave's accumulators at a time), also used where a
+    // the staging patch of the epilogue (one 32-row slab of a wave's accumulators at a time), also used where a
     // sum of two products changes the units of its accumulators
-    constexpr int kPitch = 136;                        // floats; 4 rows apart lands on the other 32 banks
+    constexpr int kPitch = WN + 8;                       // floats; 4 rows apart lands on the other 32 banks
     float *stg = reinterpret_cast<float *>(smem) + w * (32 * kPitch);
     // where accumulator register i of column block nb of a slab lies in the patch
     auto stg_at = [&](int nb, int i) { return ((i >> 2) * 8 + (l >> 5) * 4 + (i & 3)) * kPitch + nb * 32 + (l & 31); };
+    // a sum of two products starts with the one whose scales are larger: its accumulators change units by a factor of
+    // at most 1, so that they cannot overflow however far apart the scales are
+    bool swapped = false;
+    if (TWO) swapped = __builtin_amdgcn_readfirstlane((double)*p.sa_ph2 * (double)*p.sb_ph2 > (double)*p.sa * (double)*p.sb) != 0;
+    const float *sa_last = TWO && !swapped ? p.sa_ph2 : p.sa, *sb_last = TWO && !swapped ? p.sb_ph2 : p.sb;
 #pragma nounroll
     for (int phase = 0; phase < (TWO ? 2 : 1); ++phase) {
-        const uint8_t *a_src = (TWO && phase == 1) ? p.A_ph2 : p.A;
-        if (TWO && phase == 1) b_src = p.B_ph2;
+        const bool second = TWO && (phase == 1) != swapped;
+        const uint8_t *a_src = second ? p.A_ph2 : p.A;
+        if (TWO) b_src = second ? p.B_ph2 : p.B;
         const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem;
         // general issue of unit u (unit u = A (even) / B (odd) tile of K step u/2, ring slot u % 5): any
         // K, zero fill of a ragged K tail
@@ -300,54 +342,46 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             const uint8_t *zero = reinterpret_cast<const uint8_t *>(&g_zero_chunk);
             const bool kmajor = is_b ? BKM : AKM;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < NI; ++j) {
                 if (kmajor) {
-                    const int kr = (w * 8 + j) * 4 + (l >> 4);
-                    const int64_t col = (is_b ? n0 : m0) + kmaj_chunk(kr, l & 15) * 16;
-                    const int64_t ld = is_b ? p.N : p.M;
-                    const bool ok = kbase + kr < Kseg && col < ld;      // extents are multiples of 16: a chunk is all in or out
-                    dma16(ok ? base + (kbase + kr) * ld + col : zero, dst + j * 1024);
-                    continue;
+                    const bool ok = kbase + kmaj_row(j) < Kseg;
+                    dma16(ok ? base + kbase * (is_b ? p.N : p.M) + (is_b ? b_lane[j] : a_lane[j]) : zero, dst + j * 1024);
+                } else {
+                    const bool ok = kbase + ((j & 1) ? chunk_odd : chunk_even) * 16 < Kseg;      // K is a multiple of 16: a chunk is all in or out
+                    dma16(ok ? base + kbase + (is_b ? b_lane[j] : a_lane[j]) : zero, dst + j * 1024);
                 }
-                const int row = (w * 8 + j) * 8 + lrow;
-                const int ck = ((j & 1) ? chunk_odd : chunk_even) * 16;
-                int64_t g = (is_b ? n0 + (kDual ? (row & 127) : row) : m0 + row);
-                const int64_t lim = is_b ? p.N : p.M;
-                g = g < lim ? g : lim - 1;
-                const bool k_ok = kbase + ck < Kseg;
-                dma16(k_ok ? base + g * Kseg + kbase + ck : zero, dst + j * 1024);
             }
         };
-        v8i fa[2][4], fb[2][4];
+        v8i fa[2][WB], fb[2][WB];
         // The i-th fragment read of a K half, in the order the MFMAs need them (B0 A0 B1 B2 B3 A1 A2 A3:
         // the first four MFMAs use A0 with B0..B3), from ring slots sa / sb; g = 0..3: A row blocks,
         // 4..7: B row blocks
         auto load_frag = [&](int set, uint32_t sa, uint32_t sb, int kh, int i) {
-            constexpr int kOrder[8] = {4, 0, 5, 6, 7, 1, 2, 3};
-            const int g = kOrder[i];
-            if ((g < 4 && AKM) || (g >= 4 && BKM)) {
+            constexpr int kOrder4[8] = {4, 0, 5, 6, 7, 1, 2, 3}, kOrder2[4] = {2, 0, 3, 1};
+            const int g = WB == 4 ? kOrder4[i] : kOrder2[i & 3];
+            if ((g < WB && AKM) || (g >= WB && BKM)) {
                 typedef int v2i_t __attribute__((ext_vector_type(2)));
                 typedef __attribute__((address_space(3))) v2i_t *lds_v2i_ptr;
-                const uint8_t *base = smem + (g < 4 ? sa * kUnitBytes + tr_a[g] : sb * kUnitBytes + tr_b[g - 4]) + kh * 64 * 256;
+                const uint8_t *base = smem + (g < WB ? sa * kUnitBytes + tr_a[g % WB] : sb * kUnitBytes + tr_b[g % WB]) + kh * 64 * BM;
                 const v2i_t q0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base));
-                const v2i_t q1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 8 * 256));
-                const v2i_t q2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 16 * 256));
-                const v2i_t q3 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 24 * 256));
+                const v2i_t q1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 8 * BM));
+                const v2i_t q2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 16 * BM));
+                const v2i_t q3 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 24 * BM));
                 const v8i f = v8i{q0.x, q0.y, q1.x, q1.y, q2.x, q2.y, q3.x, q3.y};
-                if (g < 4) fa[set][g] = f; else fb[set][g - 4] = f;
+                if (g < WB) fa[set][g % WB] = f; else fb[set][g % WB] = f;
                 return;
             }
-            const uint32_t ub = g < 4 ? sa * kUnitBytes + a_wave_base : sb * kUnitBytes + b_wave_base;   // uniform
-            const uint32_t imm = g < 4 ? (uint32_t)(g * 32 * BK) : b_block_off(g - 4);
+            const uint32_t ub = g < WB ? sa * kUnitBytes + a_wave_base : sb * kUnitBytes + b_wave_base;   // uniform
+            const uint32_t imm = g < WB ? (uint32_t)(g * 32 * BK) : b_block_off(g - WB);
             const uint4 lo = *reinterpret_cast<const uint4 *>(smem + (frag_off[kh][0] + ub) + imm);
             const uint4 hi = *reinterpret_cast<const uint4 *>(smem + (frag_off[kh][1] + ub) + imm);
             const v8i f = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-            if (g < 4) fa[set][g] = f; else fb[set][g - 4] = f;
+            if (g < WB) fa[set][g % WB] = f; else fb[set][g % WB] = f;
         };
-        auto mfma2 = [&](int set, int g) {          // MFMAs 2g and 2g+1 of the 16 of a half step
+        auto mfma_group = [&](int set, int g) {     // the g-th of the NI equal shares of a half step's WB * WB MFMAs
 #pragma unroll
-            for (int q = 2 * g; q < 2 * g + 2; ++q)
-                acc[q >> 2][q & 3] = mfma<AFMT>(fa[set][q >> 2], fb[set][q & 3], acc[q >> 2][q & 3]);
+            for (int q = (WB / 2) * g; q < (WB / 2) * (g + 1); ++q)
+                acc[q / WB][q % WB] = mfma<AFMT>(fa[set][q / WB], fb[set][q % WB], acc[q / WB][q % WB]);
         };
         // s_waitcnt lgkmcnt(0) through the builtin (gfx9 encoding: vmcnt and expcnt fields at their
         // maxima), so that the compiler's own wait bookkeeping sees it
@@ -362,34 +396,33 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         //                step k+2) into the slot of unit 2k
         // so one DMA instruction follows every pair of MFMAs throughout and the texture path never
         // sees a burst.
-        // (a K-major operand also needs its 256 tile columns to exist: the fast body does no column check)
-        const bool whole = (p.K % BK) == 0 && (!AKM || m0 + BM <= p.M) && (!BKM || n0 + BN <= p.N);
+        const int kwhole = (int)(p.K / BK);                 // K steps with all their 128 bytes; a ragged last one is zero filled
         const int64_t a_step = AKM ? (int64_t)BK * p.M : BK, b_step = BKM ? (int64_t)BK * p.N : BK;   // bytes per K step
-        if (TWO || (whole && nk >= 2)) {
+        if (kTwoWhole || kwhole >= 2) {
             // the first four units from wave-uniform bases and the lane offsets the steady state uses
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const uint32_t dst = smem_base + (uint32_t)u * kUnitBytes + lds_w;
                 const uint8_t *base = (u & 1) ? b_src + (u >> 1) * b_step : a_src + (u >> 1) * a_step;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) dma16_s(base, (u & 1) ? b_lane[j] : a_lane[j], dst + j * 1024);
+                for (int j = 0; j < NI; ++j) dma16_s(base, (u & 1) ? b_lane[j] : a_lane[j], dst + j * 1024);
             }
         } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u) issue_unit(u);
         }
-        if (nk >= 2) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");       // units 0 and 1 have landed
+        if (nk >= 2) wait_dma<2 * NI>();                                     // units 0 and 1 have landed
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-    #pragma unroll
-        for (int g = 0; g < 8; ++g) load_frag(0, 0, 1, 0, g);
+#pragma unroll
+        for (int g = 0; g < NI; ++g) load_frag(0, 0, 1, 0, g);
 
-        // Steady state: when every K step is whole, the steps whose new units exist run a body without
-        // any per-instruction check: wave-uniform source pointers, lane offsets from registers.  The
-        // last two steps, and every step of a ragged shape, take the general body.
-        // (a sum of two products is launched on whole shapes with at least two K steps only: no general body)
-        const int kfast = (TWO || whole) ? (nk > 2 ? nk - 2 : 0) : 0;
+        // Steady state: the steps whose new units are whole run a body without any per-instruction check:
+        // wave-uniform source pointers, lane offsets from registers.  The last two steps, and one more before
+        // them when the last one is ragged, take the general body.
+        // (a sum of two products in the large tile is launched on whole K steps, at least two, only: no general body)
+        const int kfast = kwhole > 2 ? kwhole - 2 : 0;
         uint32_t sa = 0, sb = 1, sp = 4;             // ring slots of units 2k, 2k+1 and 2k+4
         auto next_slot = [](uint32_t s) { const uint32_t t = s + 2; return t >= (uint32_t)kUnits ? t - kUnits : t; };
         // wave-uniform sources of the units issued during step k (K step k+2): running pointers in scalar registers
@@ -399,19 +432,19 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             const uint32_t d4 = smem_base + sp * kUnitBytes + lds_w;
             const uint32_t d5 = smem_base + sa * kUnitBytes + lds_w;
 #pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                mfma2(0, g);
+            for (int g = 0; g < NI; ++g) {
+                mfma_group(0, g);
                 load_frag(1, sa, sb, 1, g);
                 dma16_s(ua, a_lane[g], d4 + g * 1024);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // all but unit 2k+4 have landed
+            wait_dma<NI>();                                        // all but unit 2k+4 have landed
             wait_lds();
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                mfma2(1, g);
+            for (int g = 0; g < NI; ++g) {
+                mfma_group(1, g);
                 load_frag(0, sa_n, sb_n, 0, g);
                 dma16_s(ub, b_lane[g], d5 + g * 1024);
                 __builtin_amdgcn_sched_barrier(0);
@@ -421,23 +454,23 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         }
         for (int k = kfast; k < nk; ++k) {
             const uint32_t sa_n = next_slot(sa), sb_n = next_slot(sb);
-            if (!TWO) issue_unit(2 * k + 4);
+            if (!kTwoWhole) issue_unit(2 * k + 4);
 #pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                mfma2(0, g);
+            for (int g = 0; g < NI; ++g) {
+                mfma_group(0, g);
                 load_frag(1, sa, sb, 1, g);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (k + 2 < nk) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            if (k + 2 < nk) wait_dma<NI>();
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             wait_lds();
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            if (!TWO) issue_unit(2 * k + 5);
+            if (!kTwoWhole) issue_unit(2 * k + 5);
             // (after the last step the fragment reads touch a stale slot and are never used)
 #pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                mfma2(1, g);
+            for (int g = 0; g < NI; ++g) {
+                mfma_group(1, g);
                 load_frag(0, sa_n, sb_n, 0, g);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -446,32 +479,33 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (TWO && phase == 0) {
-            // The accumulators hold the first product in units of 1 / (sa sb); the second accumulates in units of
-            // 1 / (sa_ph2 sb_ph2).  They change units on a round trip through the wave's LDS patch (the ring is
+            // The accumulators hold the product done first in units of its 1 / (sa sb); the other accumulates in units
+            // of its own.  They change units on a round trip through the wave's LDS patch (the ring is
             // drained here): stored from their registers, multiplied in place by ordinary vector code, loaded
             // back.  (Multiplying them in registers makes this compiler shuffle all 256 of them through the other
             // half of the register file and spill.)
             asm volatile("" : "+v"(l));      // as at the epilogue: keep this block's lane arithmetic inside the block
-            const float rho = (float)(((double)*p.sa_ph2 * (double)*p.sb_ph2) / ((double)*p.sa * (double)*p.sb));
+            const double s1 = (double)*p.sa * (double)*p.sb, s2 = (double)*p.sa_ph2 * (double)*p.sb_ph2;
+            const float rho = (float)(swapped ? s1 / s2 : s2 / s1);
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb) {
+            for (int mb = 0; mb < WB; ++mb) {
 #pragma unroll
-                for (int nb = 0; nb < 4; ++nb)
+                for (int nb = 0; nb < WB; ++nb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
                         stg[stg_at(nb, i)] = acc[mb][nb][i];
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {
+                for (int q = 0; q < 4 * WB; ++q) {
                     const int e = (q * 64 + l) * 4;
-                    float4 *at = reinterpret_cast<float4 *>(stg + (e >> 7) * kPitch + (e & 127));
+                    float4 *at = reinterpret_cast<float4 *>(stg + e / WN * kPitch + e % WN);
                     float4 v = *at;
                     v.x *= rho; v.y *= rho; v.z *= rho; v.w *= rho;
                     *at = v;
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
-                for (int nb = 0; nb < 4; ++nb) {
+                for (int nb = 0; nb < WB; ++nb) {
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
                         acc[mb][nb][i] = stg[stg_at(nb, i)];
@@ -482,13 +516,13 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         }
     }
 
-    // ---- epilogue: per-wave LDS patch, one 32 x 128 slab (mb) at a time
+    // ---- epilogue: per-wave LDS patch, one 32 x WN slab (mb) at a time
     // (In the two-product form the loop above is executed twice; the compiler would compute the epilogue's lane
     // arithmetic before it and spill it across.  The empty statement makes the lane id opaque from here on.)
     if (TWO) asm volatile("" : "+v"(l));
     auto stage_slab = [&](int mb) {
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
+        for (int nb = 0; nb < WB; ++nb)
 #pragma unroll
             for (int i = 0; i < 16; ++i)
                 stg[stg_at(nb, i)] = acc[mb][nb][i];
@@ -514,11 +548,12 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     };
 
     if (EPI == EPI_STORE || kBwd) {
-        // lane -> (row of the slab in 8 passes of 4 rows, 8 columns c8 of the wave's 128)
-        const int c8 = (l & 15) * 8;
-        const int64_t col = n0 + wn * 128 + c8;
+        // lane -> (row of the slab in kPasses passes of kRows rows, 8 columns c8 of the wave's WN)
+        constexpr int kLanes = WN / 8, kRows = 64 / kLanes, kPasses = 32 / kRows;
+        const int c8 = (l % kLanes) * 8;
+        const int64_t col = n0 + wn * WN + c8;
         const bool col_ok = col < p.N;
-        const Dequant dq = TWO ? inv_scale_product(p.sa_ph2, p.sb_ph2) : inv_scale_product(p.sa, p.sb);
+        const Dequant dq = inv_scale_product(sa_last, sb_last);
         const float alpha = dq.a;
         const bool post = dq.post != 1.0f;               // wave-uniform, false except for extreme scales
         float f[8];
@@ -534,14 +569,14 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         float q_su = 1.0f, q_sg = 1.0f;
         if (EPI == EPI_SWIGLU_BWD_Q) {
             q_su = *p.q_scale; q_sg = *p.q_scale2;
-            if (vblock == 0 && tid == 0) { *p.q_scale_out = q_su; *p.q_scale_out2 = q_sg; }
+            if (vblock == 0 && sub == 0 && tid == 0) { *p.q_scale_out = q_su; *p.q_scale_out2 = q_sg; }
         }
-        uint4 ru[2][8], rg[2][8];
-        auto fetch_ug = [&](int mb) {                  // the slab's stored U, G (or addend): rows in 8 passes of 4
+        uint4 ru[2][kPasses], rg[2][kPasses];
+        auto fetch_ug = [&](int mb) {                  // the slab's stored U, G (or addend)
             if (!kBwd && !ADD) return;
 #pragma unroll
-            for (int pass = 0; pass < 8; ++pass) {
-                const int64_t row = m0 + wm * 128 + mb * 32 + pass * 4 + (l >> 4);
+            for (int pass = 0; pass < kPasses; ++pass) {
+                const int64_t row = m0 + wm * WN + mb * 32 + pass * kRows + l / kLanes;
                 if (col_ok && row < p.M) {
                     const size_t at = (size_t)row * (size_t)p.N + (size_t)col;
                     if (ADD) {
@@ -556,23 +591,24 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         };
         fetch_ug(0);
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-            if (mb + 1 < 4) fetch_ug(mb + 1);          // one slab ahead: the loads fly while this slab is worked
+        for (int mb = 0; mb < WB; ++mb) {
+            if (mb + 1 < WB) fetch_ug(mb + 1);          // one slab ahead: the loads fly while this slab is worked
             stage_slab(mb);
             if (EPI == EPI_STORE && !ADD && p.c_f32) {
                 // fp32 output: one 16-byte store per lane and pass, consecutive lanes on consecutive 16 bytes, so
-                // every store instruction writes two whole 512-byte row segments
-                const int c4 = (l & 31) * 4;
-                const int64_t col4 = n0 + wn * 128 + c4;
+                // every store instruction writes whole 512-byte (WB = 2: 256-byte) row segments
+                constexpr int kLanes4 = WN / 4, kRows4 = 64 / kLanes4;
+                const int c4 = (l % kLanes4) * 4;
+                const int64_t col4 = n0 + wn * WN + c4;
                 float f4[4] = {alpha, alpha, alpha, alpha};
                 if (p.col_scale && col4 < p.N) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k) f4[k] = __fmul_rn(alpha, p.col_scale[col4 + k]);
                 }
 #pragma unroll
-                for (int pass = 0; pass < 16; ++pass) {
-                    const int r = pass * 2 + (l >> 5);
-                    const int64_t row = m0 + wm * 128 + mb * 32 + r;
+                for (int pass = 0; pass < 32 / kRows4; ++pass) {
+                    const int r = pass * kRows4 + l / kLanes4;
+                    const int64_t row = m0 + wm * WN + mb * 32 + r;
                     const float4 a = *reinterpret_cast<const float4 *>(stg + r * kPitch + c4);
                     if (col4 >= p.N || row >= p.M) continue;
                     float *out = reinterpret_cast<float *>(p.C) + (size_t)row * (size_t)p.N + (size_t)col4;
@@ -588,9 +624,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                 continue;
             }
 #pragma unroll
-            for (int pass = 0; pass < 8; ++pass) {
-                const int r = pass * 4 + (l >> 4);
-                const int64_t row = m0 + wm * 128 + mb * 32 + r;
+            for (int pass = 0; pass < kPasses; ++pass) {
+                const int r = pass * kRows + l / kLanes;
+                const int64_t row = m0 + wm * WN + mb * 32 + r;
                 float v[8];
                 load8(r, c8, v);
                 if (!col_ok || row >= p.M) continue;
@@ -662,27 +698,28 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 #pragma unroll
                 for (int k = 0; k < 4; ++k) m = m > red[2 * k + tid] ? m : red[2 * k + tid];
                 uint32_t *dst = tid == 0 ? p.amax_bits : p.amax_bits2;
-                if (m) atomicMax(dst + (vblock % kAmaxSlots) * kAmaxSlotStride, m << 16);
+                if (m) atomicMax(dst + ((vblock * (16 / (WB * WB)) + sub) % kAmaxSlots) * kAmaxSlotStride, m << 16);
             }
         }
-    } else {   // EPI_SWIGLU, EPI_SWIGLU_Q: slab columns 0..63 are u, 64..127 are g of the same 64 channels
-        const int c8 = (l & 7) * 8;
-        const int64_t col = n0 + wn * 64 + c8;
+    } else {   // EPI_SWIGLU, EPI_SWIGLU_Q: the slab's first WN / 2 columns are u, the others g of the same channels
+        constexpr int kLanes = WN / 16, kRows = 64 / kLanes, kPasses = 32 / kRows;
+        const int c8 = (l % kLanes) * 8;
+        const int64_t col = n0 + wn * (WN / 2) + c8;
         const bool col_ok = col < p.N;
         const Dequant dq_u = inv_scale_product(p.sa, p.sb), dq_g = inv_scale_product(p.sa, p.sb2);
         const float alpha_u = dq_u.a, alpha_g = dq_g.a;
         const bool post = dq_u.post != 1.0f || dq_g.post != 1.0f;
         float hmaxf[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // fmaxf drops NaN
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
+        for (int mb = 0; mb < WB; ++mb) {
             stage_slab(mb);
 #pragma unroll
-            for (int pass = 0; pass < 4; ++pass) {
-                const int r = pass * 8 + (l >> 3);
-                const int64_t row = m0 + wm * 128 + mb * 32 + r;
+            for (int pass = 0; pass < kPasses; ++pass) {
+                const int r = pass * kRows + l / kLanes;
+                const int64_t row = m0 + wm * WN + mb * 32 + r;
                 float u[8], g[8];
                 load8(r, c8, u);
-                load8(r, 64 + c8, g);
+                load8(r, WN / 2 + c8, g);
                 if (!col_ok || row >= p.M) continue;
                 const size_t at = (size_t)row * (size_t)p.N + (size_t)col;
 #pragma unroll
@@ -718,11 +755,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 #pragma unroll
         for (int k = 0; k < 8; ++k)
 #pragma unroll
-            for (int off = 8; off < 64; off <<= 1) {
+            for (int off = kLanes; off < 64; off <<= 1) {
                 const uint32_t o = (uint32_t)__shfl_xor((int)hmax[k], off, 64);
                 hmax[k] = hmax[k] > o ? hmax[k] : o;
             }
-        if (EPI == EPI_SWIGLU && l < 8 && col_ok) {
+        if (EPI == EPI_SWIGLU && l < kLanes && col_ok) {
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 if (hmax[k]) atomicMax(&p.camax_bits[col + k], hmax[k]);
@@ -730,11 +767,18 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     }
 }
 
-// One GEMM per launch: workgroup b computes the tile that map_tile assigns to it.
-template <int EPI, int AFMT, int PART = 0, int LAY = 0>
-__global__ void __launch_bounds__(kThreads) gemm_kernel(GemmParams p) {
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[kUnits * kUnitBytes];
-    gemm_tile<EPI, AFMT, PART, LAY>(p, (int)blockIdx.x, smem);
+// Workgroups come in sets of 8 large tiles, one per XCD: with WB = 4 a set is 8 consecutive workgroups, with WB = 2
+// 32, the four quarters of a large tile on the same XCD one after the other (they share its operand panels).
+template <int WB> __device__ __forceinline__ int set_of(int block) { return block >> (WB == 4 ? 3 : 5); }
+template <int WB> __device__ __forceinline__ int quarter_of(int block) { return WB == 4 ? 0 : (block >> 3) & 3; }
+inline unsigned set_workgroups(int WB) { return WB == 4 ? 8u : 32u; }
+
+// One GEMM per launch.
+template <int WB, int EPI, int AFMT, int PART = 0, int LAY = 0>
+__global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_kernel(GemmParams p) {
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB)];
+    const int b = (int)blockIdx.x, vb = set_of<WB>(b) * 8 + (b & 7);
+    if (vb < p.tiles_m * p.tiles_n) gemm_tile<WB, EPI, AFMT, PART, LAY>(p, vb, quarter_of<WB>(b), smem);
 }
 
 // Host side: algorithmic flops of the whole contraction (both weight matrices of the SwiGLU forms, both products
@@ -743,6 +787,8 @@ inline double gemm_flops(const GemmArgs &a) {
     const bool dual = a.epilogue == EPI_SWIGLU || a.epilogue == EPI_SWIGLU_Q;
     return 2.0 * (double)a.M * (double)a.N * (double)a.K * (dual ? 2.0 : 1.0) * (a.part == 3 ? 2.0 : 1.0);
 }
+
+inline int sets_of(const GemmParams &p) { return (p.tiles_m * p.tiles_n + 7) / 8; }
 
 // Host side: the kernel's parameter block from the launch interface's argument set.
 inline GemmParams make_gemm_params(const GemmArgs &a) {
@@ -761,8 +807,9 @@ inline GemmParams make_gemm_params(const GemmArgs &a) {
     p.keep_u = (uint16_t *)a.keep_u; p.keep_g = (uint16_t *)a.keep_g;
     p.A_ph2 = a.A_ph2; p.B_ph2 = a.B_ph2; p.sa_ph2 = a.sa_ph2; p.sb_ph2 = a.sb_ph2;
     p.nt_store = 0;
-    p.tiles_m = (int)((a.M + BM - 1) / BM);
-    const int n_per_tile = (a.epilogue == EPI_SWIGLU || a.epilogue == EPI_SWIGLU_Q) ? BN / 2 : BN;
+    constexpr int edge = tile_edge(4);
+    p.tiles_m = (int)((a.M + edge - 1) / edge);
+    const int n_per_tile = (a.epilogue == EPI_SWIGLU || a.epilogue == EPI_SWIGLU_Q) ? edge / 2 : edge;
     p.tiles_n = (int)((a.N + n_per_tile - 1) / n_per_tile);
     return p;
 }

@@ -134,7 +134,12 @@ bool gemm_args_ok(const GemmArgs &a);
 // false (nothing launched): gemm_args_ok(a) is false
 bool launch_gemm(const GemmArgs &a, hipStream_t st);
 bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st);       // the backward forms (called by launch_gemm)
-bool gemm_sum_in_one_launch_ok(int64_t N, int64_t K);           // shapes for which part = 3 is built
+constexpr int kComputeUnits = 256;
+// Tile of a launch that runs these GEMMs in one grid: 32 x 32 blocks per wave and direction, 4 (256 x 256 tiles) or 2 (128 x 128)
+int gemm_wave_blocks(const GemmArgs *const *list, int n);
+double gemm_tile_cost(const GemmArgs &a, int WB);               // estimated microseconds of one tile
+// whether the input gradient runs as part = 3 (in one grid with weight gradients like `dw`) or as parts 1 and 2
+bool gemm_sum_in_one_launch(const GemmArgs &dx, const GemmArgs &dw);
 int gemm_profile_tag(const GemmArgs &a);
 // Several independent GEMMs in one grid, the workgroups of one following those of the other.  Built groups:
 //   { dH (EPI_SWIGLU_BWD or _Q), weight gradient (EPI_STORE, layout 2, A E5M2) }
