@@ -89,23 +89,30 @@ double gemm_tile_cost(const GemmArgs &a, int WB) {
     return 2.5 + (a.part == 3 ? 1.45 : 1.33) * ksteps + epilogue;
 }
 
+static int64_t tile_count(const GemmArgs &a, int WB) {
+    const int64_t edge = tile_edge(WB), cols = is_dual(a) ? edge / 2 : edge;
+    return ((a.M + edge - 1) / edge) * ((a.N + cols - 1) / cols);
+}
+
 // Estimated time of the GEMMs of `list` in one grid.
 static double grid_time(const GemmArgs *const *list, int n, int WB) {
     double sum = 0.0, longest = 0.0;
     int64_t tiles = 0;
     for (int i = 0; i < n; ++i) {
-        const int64_t edge = tile_edge(WB), cols = is_dual(*list[i]) ? edge / 2 : edge;
-        const int64_t t = ((list[i]->M + edge - 1) / edge) * ((list[i]->N + cols - 1) / cols);
+        const int64_t t = tile_count(*list[i], WB);
         const double cost = gemm_tile_cost(*list[i], WB);
         tiles += t;
         sum += cost * (double)t;
         longest = std::max(longest, cost);
     }
     if (WB == 2) {
-        // a tile that has its compute unit to itself takes 0.65 of the time of two that share one; beyond that the
-        // tiles drift out of step and the rounds blur
-        if (tiles <= kComputeUnits) return 0.65 * longest;
-        return std::max(longest, sum / (2.0 * kComputeUnits));
+        // a tile that has its compute unit to itself is bound by the latency of its loads: 0.44 per K step with a ring of
+        // nine, 0.58 when all compute units are at it; beyond two rounds the tiles drift out of step and the rounds blur
+        if (tiles <= kComputeUnits) return 5.5 + (longest - 5.5) * (tiles <= 160 ? 0.46 : 0.6);
+        const double blurred = std::max(longest, sum / (2.0 * kComputeUnits));
+        if (n != 1 || tiles > 3 * kComputeUnits) return blurred;
+        if (tiles > 2 * kComputeUnits) return std::max(blurred, 1.65 * longest);
+        return longest * (0.65 + 0.35 * (double)(tiles - kComputeUnits) / kComputeUnits);
     }
     // one tile per compute unit: a single GEMM runs in whole rounds, a group's last round is filled by its other members
     const double rounds = (double)((tiles + kComputeUnits - 1) / kComputeUnits);
@@ -141,22 +148,22 @@ int gemm_profile_tag(const GemmArgs &a) {
     return 2 * (a.epilogue == EPI_SWIGLU_BWD_Q ? (int)EPI_SWIGLU_BWD : a.epilogue) + a.a_fmt;
 }
 
-template <int WB, int EPI, int LAY>
+template <int WB, int UNITS, int EPI, int LAY>
 static void launch_fmt(const GemmParams &p, int a_fmt, unsigned blocks, hipStream_t st) {
-    if (a_fmt == kE4M3) hipLaunchKernelGGL((gemm_kernel<WB, EPI, kE4M3, 0, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((gemm_kernel<WB, EPI, kE5M2, 0, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
+    if (a_fmt == kE4M3) hipLaunchKernelGGL((gemm_kernel<WB, EPI, kE4M3, 0, LAY, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((gemm_kernel<WB, EPI, kE5M2, 0, LAY, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
 }
 
-template <int WB>
+template <int WB, int UNITS>
 static void launch_gemm_wb(const GemmArgs &a, hipStream_t st) {
     const GemmParams p = make_gemm_params(a);
     const unsigned blocks = (unsigned)sets_of(p) * set_workgroups(WB);
     switch (a.epilogue) {
         case EPI_STORE:
             if (a.a_fmt == kBF16) hipLaunchKernelGGL((gemm_kernel<4, EPI_STORE, kBF16, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
-            else if (a.layout == 2) launch_fmt<WB, EPI_STORE, 2>(p, a.a_fmt, blocks, st);
-            else if (a.layout == 1) launch_fmt<WB, EPI_STORE, 1>(p, a.a_fmt, blocks, st);
-            else launch_fmt<WB, EPI_STORE, 0>(p, a.a_fmt, blocks, st);
+            else if (a.layout == 2) launch_fmt<WB, UNITS, EPI_STORE, 2>(p, a.a_fmt, blocks, st);
+            else if (a.layout == 1) launch_fmt<WB, UNITS, EPI_STORE, 1>(p, a.a_fmt, blocks, st);
+            else launch_fmt<WB, UNITS, EPI_STORE, 0>(p, a.a_fmt, blocks, st);
             break;
         case EPI_SWIGLU:
             if (a.tail_src) {
@@ -165,11 +172,11 @@ static void launch_gemm_wb(const GemmArgs &a, hipStream_t st) {
                 const unsigned extra = (unsigned)(r.blocks_x * col_range_blocks_y(a.tail_rows));
                 hipLaunchKernelGGL(gemm_swiglu_col_range_kernel<WB>, dim3(blocks + extra), dim3(kThreads), 0, st, p, r);
             } else {
-                hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU, kE4M3, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
+                hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU, kE4M3, 0, 0, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
             }
             break;
         default:   // EPI_SWIGLU_Q
-            hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU_Q, kE4M3, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
+            hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU_Q, kE4M3, 0, 0, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
             break;
     }
 }
@@ -179,8 +186,14 @@ bool launch_gemm(const GemmArgs &a, hipStream_t st) {
     if (a.part != 0 || a.epilogue == EPI_SWIGLU_BWD || a.epilogue == EPI_SWIGLU_BWD_Q) return launch_gemm_bwd(a, st);
     profile_before(gemm_profile_tag(a), st, gemm_flops(a));
     const GemmArgs *one = &a;
-    if (gemm_wave_blocks(&one, 1) == 4) launch_gemm_wb<4>(a, st);
-    else launch_gemm_wb<2>(a, st);
+    const int wb = gemm_wave_blocks(&one, 1);
+    if (gemm_skinny_time(a) < grid_time(&one, 1, wb)) launch_gemm_skinny(a, st);
+    else if (wb == 4) launch_gemm_wb<4, 5>(a, st);
+    // one small tile to a compute unit, so up to 8 large tiles on an XCD of 32: the longer ring, which leaves no room
+    // for a second workgroup (M = 528, N = 2048, K = 4096, 80 tiles: 27 us with five units, 21 with nine; 65 large tiles
+    // give one XCD a second round: 28 and 34)
+    else if (tile_count(a, 4) <= kComputeUnits / 4) launch_gemm_wb<2, 9>(a, st);
+    else launch_gemm_wb<2, 5>(a, st);
     profile_after(st);
     return true;
 }

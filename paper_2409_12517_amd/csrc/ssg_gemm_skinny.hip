@@ -1,0 +1,214 @@
+// FP8 contraction of few rows for gfx950: the small batches of the inference form and small public calls.
+//
+//   C[m,n] = sum_k A[m,k] * B[n,k]      A [M,K], B [N,K] FP8 codes, K contiguous
+//
+// Bound by HBM where M is small (every byte of B is used once), and by what a compute unit can fetch (about 50 bytes per
+// clock) where it is a few hundred.  The tiles of ssg_gemm_tile.h have too few workgroups there: 32 for N = 4096, each
+// walking all of K alone.  So
+//   - a workgroup owns 16 * MB rows of A and 16 * NB rows of B (SwiGLU form: half of them from W1, half the same rows
+//     of W2) and its KW waves divide K among them; their partial sums meet in LDS and are added in a fixed order;
+//   - every wave streams its own K range through a ring of its own in LDS, STEPS steps of 128 bytes deep: nothing is
+//     shared between waves before the end, so there is no barrier in the loop, only each wave's own waits.  (Fragments
+//     loaded straight into registers take 4 times the cycles of the texture path: neighbouring lanes hold different
+//     rows, so no two of them share a 64-byte piece.);
+//   - v_mfma_f32_16x16x128_f8f6f4: 16 rows of A are no waste, and one instruction consumes a whole step.
+#include <algorithm>
+
+#include "ssg_gemm_tile.h"
+
+namespace ssg {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr int kBlockBytes = 16 * BK;          // 16 rows of one K step: two DMA instructions
+constexpr int skinny_smem(int MB, int NB, int KW, int STEPS) { return KW * STEPS * (MB + NB) * kBlockBytes; }
+
+template <int EPI, int AFMT, int MB, int NB, int KW, int STEPS>
+__global__ void __launch_bounds__(64 * KW) gemm_skinny_kernel(GemmParams p) {
+    constexpr bool kDual = EPI == EPI_SWIGLU_Q;
+    constexpr int NCOL = kDual ? NB / 2 : NB;                          // 16-column blocks of the result
+    constexpr int kStepBytes = (MB + NB) * kBlockBytes, kPitch = 16 * NB + 1;
+    static_assert(KW * MB * 16 * kPitch * 4 <= skinny_smem(MB, NB, KW, STEPS), "the partial sums reuse the rings");
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[skinny_smem(MB, NB, KW, STEPS)];
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // the row blocks that share 16 * NB rows of B run on the same XCD one after the other: B comes into its L2 once
+    const int mblocks = (int)((p.M + 16 * MB - 1) / (16 * MB)), idx = (int)(blockIdx.x >> 3);
+    const int64_t m0 = (int64_t)(idx % mblocks) * (16 * MB);
+    const int64_t n0 = ((int64_t)(idx / mblocks) * 8 + (blockIdx.x & 7)) * (16 * NCOL);
+    if (n0 >= p.N) return;
+    const int ksteps = (int)((p.K + BK - 1) / BK), per = (ksteps + KW - 1) / KW;
+    const int s0 = w * per, n = (s0 + per < ksteps ? per : ksteps - s0);      // this wave's steps; may be 0 or less
+
+    // DMA: instruction j of a step brings rows 8j .. 8j+7 of the MB + NB blocks, a lane 16 bytes; row r's chunk c lies at
+    // position c ^ swz(r), so that 16 lanes reading the same chunk of 16 rows meet no bank conflict
+    const int lrow = l >> 3;
+    uint32_t lane_off[2 * (MB + NB)];
+#pragma unroll
+    for (int j = 0; j < 2 * (MB + NB); ++j) {
+        const int row = 8 * (j & 1) + lrow, ck = ((l & 7) ^ swz(row)) * 16;
+        // rows beyond the matrix are clamped: they only feed results that are not stored
+        int64_t g;
+        if (j < 2 * MB) { g = m0 + 8 * j + lrow; g = g < p.M ? g : p.M - 1; }
+        else { g = n0 + ((j / 2 - MB) % NCOL) * 16 + row; g = g < p.N ? g : p.N - 1; }
+        lane_off[j] = (uint32_t)(g * p.K) + ck;
+    }
+    const uint32_t ring = (uint32_t)(uintptr_t)(lds_void_ptr)smem + (uint32_t)w * (STEPS * kStepBytes);
+    auto issue = [&](int s, int slot) {
+        const int64_t k = (int64_t)(s0 + s) * BK;
+        const uint32_t dst = ring + (uint32_t)slot * kStepBytes;
+        auto base = [&](int j) { return (j < 2 * MB ? p.A : !kDual || j / 2 - MB < NCOL ? p.B : p.B2) + k; };
+        if (k + BK <= p.K) {
+#pragma unroll
+            for (int j = 0; j < 2 * (MB + NB); ++j) dma16_s(base(j), lane_off[j], dst + j * 1024);
+        } else {                                      // ragged last step: zeros past K, a multiple of 16
+#pragma unroll
+            for (int j = 0; j < 2 * (MB + NB); ++j) {
+                const int ck = ((l & 7) ^ swz(8 * (j & 1) + lrow)) * 16;
+                dma16(k + ck < p.K ? base(j) + lane_off[j] : reinterpret_cast<const uint8_t *>(&g_zero_chunk), dst + j * 1024);
+            }
+        }
+    };
+    uint32_t frag_off[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) frag_off[e] = (uint32_t)((l & 15) * BK + ((((l >> 4) * 2 + e) ^ swz(l & 15)) << 4));
+    v4f acc[MB][NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s)
+        if (s < n) issue(s, s);
+    int slot = 0;
+    for (int s = 0; s < n; ++s) {
+        // step s has landed: all loads but those of the STEPS - 1 steps after it; near the end all of them
+        // (s_waitcnt's gfx9 encoding: vmcnt in bits 0..3 and 14..15, the other counters at their maxima)
+        constexpr int kAhead = (STEPS - 1) * 2 * (MB + NB);
+        static_assert(kAhead < 64, "vmcnt has six bits");
+        if (s + STEPS - 1 < n) __builtin_amdgcn_s_waitcnt(0x0F70 | (kAhead & 15) | ((kAhead >> 4) << 14));
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        asm volatile("" ::: "memory");
+        const uint8_t *at = smem + w * (STEPS * kStepBytes) + slot * kStepBytes;
+        v8i f[MB + NB];
+#pragma unroll
+        for (int b = 0; b < MB + NB; ++b) {
+            const uint4 lo = *reinterpret_cast<const uint4 *>(at + b * kBlockBytes + frag_off[0]);
+            const uint4 hi = *reinterpret_cast<const uint4 *>(at + b * kBlockBytes + frag_off[1]);
+            f[b] = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);          // the fragments are in registers: the slot is free
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + STEPS < n) issue(s + STEPS, slot);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                acc[mb][nb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(f[mb], f[MB + nb], acc[mb][nb], AFMT, 0, 0, 0, 0, 0);
+        slot = slot + 1 == STEPS ? 0 : slot + 1;
+    }
+    __syncthreads();                                 // every wave is done with its ring
+    // register i of a lane: row (l >> 4) * 4 + i, column l & 15 of its block
+    float *part = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                part[(w * (16 * MB) + mb * 16 + (l >> 4) * 4 + i) * kPitch + nb * 16 + (l & 15)] = acc[mb][nb][i];
+    __syncthreads();
+
+    const Dequant dq = inv_scale_product(p.sa, p.sb), dq2 = kDual ? inv_scale_product(p.sa, p.sb2) : dq;
+    // a thread finishes two neighbouring columns
+    for (int e = threadIdx.x; e < 16 * MB * (8 * NCOL); e += 64 * KW) {
+        const int row = e / (8 * NCOL), c = e % (8 * NCOL) * 2;
+        if (m0 + row >= p.M || n0 + c >= p.N) continue;
+        float v[2][2];
+#pragma unroll
+        for (int h = 0; h < (kDual ? 2 : 1); ++h)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const float *src = part + row * kPitch + h * (16 * NCOL) + c + k;
+                float sum = src[0];
+#pragma unroll
+                for (int q = 1; q < KW; ++q) sum = __fadd_rn(sum, src[q * (16 * MB) * kPitch]);
+                const Dequant &d = h == 0 ? dq : dq2;
+                v[h][k] = __fmul_rn(sum, d.a);
+                if (d.post != 1.0f) v[h][k] *= d.post;
+            }
+        const size_t at = (size_t)(m0 + row) * (size_t)p.N + (size_t)(n0 + c);
+        if (kDual)
+            *reinterpret_cast<uint16_t *>(reinterpret_cast<uint8_t *>(p.C) + at) =
+                (uint16_t)satcast_pk2<kE4M3>(swiglu_f32(v[0][0], v[1][0]), swiglu_f32(v[0][1], v[1][1]));
+        else if (p.c_f32) *reinterpret_cast<float2 *>(reinterpret_cast<float *>(p.C) + at) = make_float2(v[0][0], v[0][1]);
+        else *reinterpret_cast<uint32_t *>(reinterpret_cast<uint16_t *>(p.C) + at) = pack_bf16x2(v[0][0], v[0][1]);
+    }
+}
+
+template <int EPI, int AFMT, int MB, int NB, int KW, int STEPS>
+static void launch_form(const GemmParams &p, hipStream_t st) {
+    constexpr int cols = 16 * (EPI == EPI_SWIGLU_Q ? NB / 2 : NB);
+    const unsigned mblocks = (unsigned)((p.M + 16 * MB - 1) / (16 * MB)), nsets = (unsigned)((p.N + 8 * cols - 1) / (8 * cols));
+    hipLaunchKernelGGL((gemm_skinny_kernel<EPI, AFMT, MB, NB, KW, STEPS>), dim3(mblocks * nsets * 8), dim3(64 * KW), 0, st, p);
+}
+
+// The forms of the plain store: blocks of A and of B per workgroup.  Larger ones fetch fewer bytes per product, smaller
+// ones leave fewer compute units idle.
+static constexpr struct { int mb, nb; } kStoreForms[] = {{1, 1}, {1, 2}, {2, 2}, {4, 2}, {4, 4}, {6, 4}};
+
+template <int AFMT>
+static void launch_store(const GemmParams &p, int form, hipStream_t st) {
+    switch (form) {
+        case 0: launch_form<EPI_STORE, AFMT, 1, 1, 4, 5>(p, st); break;
+        case 1: launch_form<EPI_STORE, AFMT, 1, 2, 4, 3>(p, st); break;
+        case 2: launch_form<EPI_STORE, AFMT, 2, 2, 4, 2>(p, st); break;
+        case 3: launch_form<EPI_STORE, AFMT, 4, 2, 4, 3>(p, st); break;
+        case 4: launch_form<EPI_STORE, AFMT, 4, 4, 4, 2>(p, st); break;
+        default: launch_form<EPI_STORE, AFMT, 6, 4, 4, 2>(p, st); break;
+    }
+}
+
+// Microseconds of a form with B not in a cache: 4 to start and end, then each compute unit fetches 70 KB a microsecond
+// for its share of the workgroups, and the whole chip 4.2 MB a microsecond from HBM; a quarter of the smaller of the two
+// does not hide behind the larger.  (y of the inference form, N = 4096, K = 11008, estimated / measured: T = 16 form
+// {1,1} 16 / 14, T = 32 {1,2} 17 / 16, T = 64 {2,2} 17 / 19, T = 128 {4,2} 22 / 24, T = 208 {4,4} 27 / 26, T = 272
+// {6,4} 32 / 33; the 128 x 128 tile with its longer ring takes 42 to 57 for all of them.)  More workgroups than compute
+// units pay the 4 each round, and a third more per byte (1040 x 2736 x 4096, two rounds of {6,4}: 35 / 39; tile: 22).
+static double form_time(const GemmArgs &a, int form) {
+    const int64_t m = 16 * kStoreForms[form].mb, n = 16 * kStoreForms[form].nb;
+    const int64_t groups = ((a.M + m - 1) / m) * ((a.N + n - 1) / n), rounds = (groups + kComputeUnits - 1) / kComputeUnits;
+    const double fetch = (double)((m + n) * a.K) / 70e3, hbm = (double)(a.N * a.K) / 4.2e6;
+    const double busy = rounds == 1 ? fetch : (double)rounds * (1.35 * fetch + 4.0) - 4.0;
+    return 4.0 + std::max(busy, hbm) + 0.25 * std::min(busy, hbm);
+}
+
+// K-contiguous FP8 operands, the plain store without a per-column factor or the inference form's SwiGLU.  The SwiGLU
+// form: up to 128 rows (gate/up of the inference form against the 128 x 128 tile, us, d = 4096, f = 11008: T = 16 22
+// against 36, T = 64 27 against 40, T = 128 44 against 48, T = 208 53 against 43; d = 2048, f = 5504: T = 128 15 against
+// 18, T = 272 24 against 22).
+double gemm_skinny_time(const GemmArgs &a) {
+    const double never = 1e30;
+    if (a.layout != 0 || a.part != 0 || a.a_fmt == kBF16 || a.col_scale) return never;
+    if (a.epilogue == EPI_SWIGLU_Q) return a.M <= 128 ? 0.0 : never;
+    if (a.epilogue != EPI_STORE) return never;
+    double best = never;
+    for (int i = 0; i < (int)(sizeof(kStoreForms) / sizeof(kStoreForms[0])); ++i) best = std::min(best, form_time(a, i));
+    return best;
+}
+
+void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
+    const GemmParams p = make_gemm_params(a);
+    if (a.epilogue == EPI_SWIGLU_Q) {
+        if (p.M <= 16) launch_form<EPI_SWIGLU_Q, kE4M3, 1, 2, 4, 3>(p, st);
+        else launch_form<EPI_SWIGLU_Q, kE4M3, 4, 4, 2, 2>(p, st);
+        return;
+    }
+    int form = 0;
+    for (int i = 1; i < (int)(sizeof(kStoreForms) / sizeof(kStoreForms[0])); ++i)
+        if (form_time(a, i) < form_time(a, form)) form = i;
+    if (a.a_fmt == kE4M3) launch_store<kE4M3>(p, form, st);
+    else launch_store<kE5M2>(p, form, st);
+}
+
+}  // namespace ssg

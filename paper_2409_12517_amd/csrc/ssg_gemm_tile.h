@@ -45,8 +45,9 @@ typedef __attribute__((address_space(1))) const void *global_void_ptr;
 constexpr int BK = 128;
 constexpr int tile_edge(int WB) { return 64 * WB; }
 constexpr int unit_bytes(int WB) { return tile_edge(WB) * BK; }   // one operand tile of one K step: 32 or 16 KB
-constexpr int kUnits = 5;                         // ring of operand tiles in LDS: all 160 KB, or half of them
-constexpr int smem_bytes(int WB) { return kUnits * unit_bytes(WB); }
+// UNITS: ring of operand tiles in LDS, an odd number.  Five large units are all 160 KB, five small ones half of them;
+// nine small ones (144 KB) where a small tile has its compute unit to itself
+constexpr int smem_bytes(int WB, int UNITS = 5) { return UNITS * unit_bytes(WB); }
 
 static __device__ uint4 g_zero_chunk = {0u, 0u, 0u, 0u}; // source of the zero fill of a ragged K tail (one per translation unit)
 
@@ -175,11 +176,13 @@ constexpr int kThreads = 256;
 constexpr int waves_per_simd(int WB) { return WB == 4 ? 1 : 2; }
 
 template <int N> __device__ __forceinline__ void wait_dma() {       // at most N direct-to-LDS loads still in flight
-    static_assert(N == 4 || N == 8 || N == 16, "a wait for one or two units");
+    static_assert(N == 4 || N == 8 || N == 16 || N == 20 || N == 24, "whole units of 4 or 8 loads");
 #if defined(__HIP_DEVICE_COMPILE__)
     if (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     if (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
     if (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    if (N == 20) asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
+    if (N == 24) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
 #endif
 }
 
@@ -194,10 +197,11 @@ template <int N> __device__ __forceinline__ void wait_dma() {       // at most N
 // PART = 3: the sum of two products in one tile -- the K loop runs twice, over (A, B) and then over (A_ph2, B_ph2)
 // of the same shapes (or the other way round), and the accumulators are rescaled by the ratio of the two dequantization
 // factors in between, so that one epilogue with the last factor finishes both.
-template <int WB, int EPI, int AFMT, int PART, int LAY>
+template <int WB, int EPI, int AFMT, int PART, int LAY, int UNITS = 5>
 __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock, const int sub, uint8_t *smem) {
     constexpr int BM = tile_edge(WB), BN = BM, WN = 32 * WB, kUnitBytes = unit_bytes(WB);
     constexpr int NI = 2 * WB;                         // DMA instructions of 1 KB per wave and unit; fragment reads per half step
+    constexpr int kUnits = UNITS, AHEAD = (UNITS - 1) / 2;   // operand tiles are issued AHEAD K steps before their use
     constexpr int kChunks = BM / 16;                   // 16-byte chunks of a K-major row
     constexpr bool ADD = PART == 2;
     constexpr bool TWO = PART == 3;
@@ -329,7 +333,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         const uint8_t *a_src = second ? p.A_ph2 : p.A;
         if (TWO) b_src = second ? p.B_ph2 : p.B;
         const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem;
-        // general issue of unit u (unit u = A (even) / B (odd) tile of K step u/2, ring slot u % 5): any
+        // general issue of unit u (unit u = A (even) / B (odd) tile of K step u/2, ring slot u % UNITS): any
         // K, zero fill of a ragged K tail
         auto issue_unit = [&](int u) {
             const int k = u >> 1;
@@ -389,7 +393,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 
         // Schedule of a K step k (units 2k, 2k+1 in ring slots sa, sb):
         //   first half   16 MFMAs on fragment set 0 (k, K half 0); reads (k, half 1) into set 1;
-        //                issues unit 2k+4 (A of step k+2) into the slot that B of step k-1 left
+        //                issues unit 2k+4 (A of step k+2) into the slot that B of step k-1 left (units and steps as
+        //                with a ring of five; UNITS - 1 for the 4 and AHEAD for the 2 in general)
         //   barrier      each wave first waits for its share of units 2k+2, 2k+3 and for its LDS reads:
         //                step k's slots are free, step k+1 is visible to all
         //   second half  16 MFMAs on set 1; reads (k+1, half 0) into set 0; issues unit 2k+5 (B of
@@ -398,10 +403,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         // sees a burst.
         const int kwhole = (int)(p.K / BK);                 // K steps with all their 128 bytes; a ragged last one is zero filled
         const int64_t a_step = AKM ? (int64_t)BK * p.M : BK, b_step = BKM ? (int64_t)BK * p.N : BK;   // bytes per K step
-        if (kTwoWhole || kwhole >= 2) {
-            // the first four units from wave-uniform bases and the lane offsets the steady state uses
+        if (kTwoWhole || kwhole >= AHEAD) {
+            // the first UNITS - 1 units from wave-uniform bases and the lane offsets the steady state uses
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < UNITS - 1; ++u) {
                 const uint32_t dst = smem_base + (uint32_t)u * kUnitBytes + lds_w;
                 const uint8_t *base = (u & 1) ? b_src + (u >> 1) * b_step : a_src + (u >> 1) * a_step;
 #pragma unroll
@@ -409,9 +414,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             }
         } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) issue_unit(u);
+            for (int u = 0; u < UNITS - 1; ++u) issue_unit(u);
         }
-        if (nk >= 2) wait_dma<2 * NI>();                                     // units 0 and 1 have landed
+        if (nk >= AHEAD) wait_dma<(UNITS - 3) * NI>();                       // units 0 and 1 have landed
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -419,14 +424,14 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         for (int g = 0; g < NI; ++g) load_frag(0, 0, 1, 0, g);
 
         // Steady state: the steps whose new units are whole run a body without any per-instruction check:
-        // wave-uniform source pointers, lane offsets from registers.  The last two steps, and one more before
+        // wave-uniform source pointers, lane offsets from registers.  The last AHEAD steps, and one more before
         // them when the last one is ragged, take the general body.
         // (a sum of two products in the large tile is launched on whole K steps, at least two, only: no general body)
-        const int kfast = kwhole > 2 ? kwhole - 2 : 0;
-        uint32_t sa = 0, sb = 1, sp = 4;             // ring slots of units 2k, 2k+1 and 2k+4
+        const int kfast = kwhole > AHEAD ? kwhole - AHEAD : 0;
+        uint32_t sa = 0, sb = 1, sp = UNITS - 1;     // ring slots of units 2k, 2k+1 and 2k+UNITS-1
         auto next_slot = [](uint32_t s) { const uint32_t t = s + 2; return t >= (uint32_t)kUnits ? t - kUnits : t; };
-        // wave-uniform sources of the units issued during step k (K step k+2): running pointers in scalar registers
-        const uint8_t *ua = a_src + 2 * a_step, *ub = b_src + 2 * b_step;
+        // wave-uniform sources of the units issued during step k (K step k+AHEAD): running pointers in scalar registers
+        const uint8_t *ua = a_src + AHEAD * a_step, *ub = b_src + AHEAD * b_step;
         for (int k = 0; k < kfast; ++k) {
             const uint32_t sa_n = next_slot(sa), sb_n = next_slot(sb);
             const uint32_t d4 = smem_base + sp * kUnitBytes + lds_w;
@@ -438,7 +443,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                 dma16_s(ua, a_lane[g], d4 + g * 1024);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            wait_dma<NI>();                                        // all but unit 2k+4 have landed
+            wait_dma<(UNITS - 4) * NI>();                          // units 2k+2, 2k+3 and all before them have landed
             wait_lds();
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
@@ -454,19 +459,19 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         }
         for (int k = kfast; k < nk; ++k) {
             const uint32_t sa_n = next_slot(sa), sb_n = next_slot(sb);
-            if (!kTwoWhole) issue_unit(2 * k + 4);
+            if (!kTwoWhole) issue_unit(2 * k + UNITS - 1);
 #pragma unroll
             for (int g = 0; g < NI; ++g) {
                 mfma_group(0, g);
                 load_frag(1, sa, sb, 1, g);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (k + 2 < nk) wait_dma<NI>();
+            if (k + AHEAD < nk) wait_dma<(UNITS - 4) * NI>();
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             wait_lds();
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            if (!kTwoWhole) issue_unit(2 * k + 5);
+            if (!kTwoWhole) issue_unit(2 * k + UNITS);
             // (after the last step the fragment reads touch a stale slot and are never used)
 #pragma unroll
             for (int g = 0; g < NI; ++g) {
@@ -774,11 +779,11 @@ template <int WB> __device__ __forceinline__ int quarter_of(int block) { return 
 inline unsigned set_workgroups(int WB) { return WB == 4 ? 8u : 32u; }
 
 // One GEMM per launch.
-template <int WB, int EPI, int AFMT, int PART = 0, int LAY = 0>
+template <int WB, int EPI, int AFMT, int PART = 0, int LAY = 0, int UNITS = 5>
 __global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_kernel(GemmParams p) {
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB)];
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB, UNITS)];
     const int b = (int)blockIdx.x, vb = set_of<WB>(b) * 8 + (b & 7);
-    if (vb < p.tiles_m * p.tiles_n) gemm_tile<WB, EPI, AFMT, PART, LAY>(p, vb, quarter_of<WB>(b), smem);
+    if (vb < p.tiles_m * p.tiles_n) gemm_tile<WB, EPI, AFMT, PART, LAY, UNITS>(p, vb, quarter_of<WB>(b), smem);
 }
 
 // Host side: algorithmic flops of the whole contraction (both weight matrices of the SwiGLU forms, both products

@@ -133,6 +133,9 @@ struct GemmArgs {
 bool gemm_args_ok(const GemmArgs &a);
 // false (nothing launched): gemm_args_ok(a) is false
 bool launch_gemm(const GemmArgs &a, hipStream_t st);
+// few rows (ssg_gemm_skinny.hip): estimated microseconds, 1e30 for an argument set it is not built for
+double gemm_skinny_time(const GemmArgs &a);
+void launch_gemm_skinny(const GemmArgs &a, hipStream_t st);
 bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st);       // the backward forms (called by launch_gemm)
 constexpr int kComputeUnits = 256;
 // Tile of a launch that runs these GEMMs in one grid: 32 x 32 blocks per wave and direction, 4 (256 x 256 tiles) or 2 (128 x 128)

@@ -1,4 +1,5 @@
-"""GPU parity at the edges of the two GEMM tiles (128 x 128 and 256 x 256), at sizes that select either."""
+"""GPU parity at the edges of the two GEMM tiles (128 x 128 and 256 x 256), at sizes that select either,
+and of the kernel for few rows."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +12,7 @@ pytestmark = pytest.mark.gpu
 import paper_2409_12517_amd as ssg  # noqa: E402
 import gpu_util as gu  # noqa: E402
 import test_gpu_gemm as tg  # noqa: E402
+import test_gpu_infer as ti  # noqa: E402
 import test_gpu_mlp as tm  # noqa: E402
 
 SMALL = [(128, 128, 128), (16, 144, 272), (144, 112, 16), (272, 128, 400), (112, 400, 256)]
@@ -77,3 +79,45 @@ def test_input_gradient_with_scales_far_apart(f, du_exp, dg_exp):
            dec(blk.wv("dg_q", (T, f), torch.uint8), fp8.E5M2) @ dec(blk.sv("w2_q", (f, d), torch.uint8), fp8.E4M3) / (wsc[2] * sc[2]))
     assert np.isfinite(gu.f32(blk.dx)).all() and np.abs(ref).max() > 0
     gu.assert_close_gemm(gu.f32(blk.dx), ref, False, f"dX {f} {du_exp} {dg_exp}")
+
+
+# The few-rows kernel: rows per workgroup 16, 16, 32, 64, 64, 96 with 16, 32, 32, 32, 64, 64 columns (the form each
+# shape is given by its size); ragged K, a last workgroup with part of its columns, rows beyond the last one; K shorter
+# than one step for each wave; 4096 rows by 1024 columns take the 128 x 128 tile with the long ring (K ragged and whole)
+@pytest.mark.parametrize("M,N,K", [(16, 4112, 1040), (48, 2032, 1168), (64, 4080, 784), (112, 4080, 656), (176, 4080, 912),
+                                   (272, 4000, 1168), (32, 48, 16), (16, 16, 272), (4096, 1040, 400), (4096, 1024, 512)])
+@pytest.mark.parametrize("a_fmt,c_dtype", [(ssg.SSG_E4M3, ssg.SSG_F32), (ssg.SSG_E5M2, ssg.SSG_BF16)])
+def test_few_rows(M, N, K, a_fmt, c_dtype):
+    rng = np.random.default_rng(M + 3 * N + K)
+    a, b = tg._codes(rng, a_fmt, (M, K)), tg._codes(rng, ssg.SSG_E4M3, (N, K))
+    ref = fp8.decode(a, tg.FMT[a_fmt]).astype(np.float64) @ fp8.decode(b, fp8.E4M3).astype(np.float64).T / (2.0 * 0.5)
+    sa, sb = torch.tensor([2.0], device=gu.DEV), torch.tensor([0.5], device=gu.DEV)
+    C = torch.full((M + 1, N), -7.0, device=gu.DEV, dtype=torch.float32 if c_dtype == ssg.SSG_F32 else torch.bfloat16)
+    ssg.ssg_gemm_fp8(gu.dev(torch.from_numpy(a)), a_fmt, gu.dev(torch.from_numpy(b)), ssg.SSG_E4M3, M, N, K, sa, sb, C, c_dtype)
+    torch.cuda.synchronize()
+    gu.assert_close_gemm(gu.f32(C[:M]), ref, c_dtype == ssg.SSG_BF16, f"{M} {N} {K}")
+    assert bool((C[M] == -7.0).all())
+
+
+def test_few_rows_with_nan_and_extreme_scales():
+    """A NaN code reaches its own row or column only; scales whose product leaves the binary32 range."""
+    rng = np.random.default_rng(3)
+    M, N, K = 48, 96, 272
+    a, b = tg._codes(rng, ssg.SSG_E4M3, (M, K)), tg._codes(rng, ssg.SSG_E4M3, (N, K))
+    ref = fp8.decode(a, fp8.E4M3).astype(np.float64) @ fp8.decode(b, fp8.E4M3).astype(np.float64).T
+    a[5, 3], b[70, 271] = 0x7F, 0xFF
+    got = tg._run(a, ssg.SSG_E4M3, b, 1e30, 1e-30, ssg.SSG_F32)
+    assert np.isnan(got[5]).all() and np.isnan(got[:, 70]).all()
+    keep = np.ix_([i for i in range(M) if i != 5], [j for j in range(N) if j != 70])
+    assert np.abs(got[keep] - ref[keep]).max() <= 2e-3 * np.abs(ref).max()
+    got = tg._run(a, ssg.SSG_E4M3, b, 1e30, 1e6, ssg.SSG_F32)
+    assert np.abs(got[keep] * 1e36 - ref[keep]).max() <= 2e-3 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("T_inf", [16, 48, 128, 144])
+def test_few_rows_of_the_inference_form(T_inf):
+    """16 rows, 17 to 128 rows and the first batch beyond them; d and f that are no multiples of the tiles.  (f is wide
+    enough that the check's bar on codes more than a step apart, a share of 1e-4, means 4 of at least 40192 elements: a
+    product next to zero, 2^-9 apart in code, now and then crosses more than one step when its sum rounds otherwise.)"""
+    inp = synth.make_inputs(64, 272, 2512, seed=59)
+    ti.check(ti.Infer(inp, T_inf=T_inf, seed_inf=8), tm._np_inputs(inp))
