@@ -260,11 +260,11 @@ ssg_status ssg_infer_fwd(const ssg_mlp_desc *desc, const void *x, const void *pr
                          void *workspace, size_t workspace_bytes, void *stream);
 /* ssg_infer_fwd for callers that cannot allocate device memory and have no workspace to hand over: code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation.  The workspace of the call
- * (x^ [T,d], h^ [T,f], the range slots of x) lies in a static device array inside the library instead
+ * (x^ [T,d], h^ [T,f], the range words of x) lies in a static device array inside the library instead
  * (ssg_infer_noalloc_max_bytes() = 16 MiB, held by every GPU the library runs on until the process ends); a shape
  * with ssg_infer_workspace_bytes(desc) beyond that returns SSG_ERR_WORKSPACE with nothing launched.  Same kernels
- * and same results as ssg_infer_fwd; no hipMalloc, hipFree or allocating library routine is called, and the range
- * slots are cleared by a small fill kernel (no memset node).  All calls on one GPU share that GPU's array, which
+ * and same results as ssg_infer_fwd; no hipMalloc, hipFree or allocating library routine is called, and nothing
+ * is cleared with a memset node.  All calls on one GPU share that GPU's array, which
  * keeps the last call's contents: calls that overlap in time on one GPU (two streams, two threads) race and must
  * be serialised by the caller.  The array's device address is looked up once per GPU on the first call there. */
 size_t ssg_infer_noalloc_max_bytes(void);

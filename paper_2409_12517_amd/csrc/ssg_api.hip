@@ -141,7 +141,7 @@ SavedLayout saved_layout(const ssg_mlp_desc &d) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align256(bytes); return at; };
     L.scalars = take(S_COUNT * 4);
-    // slotted running maxima of x, W1, W2, then h_camax: zeroed by one contiguous clear
+    // range words of x, W1, W2; h_camax and w3_camax are adjacent: zeroed as one run
     L.partials = take(3 * ssg::kAmaxSlotWords * 4);
     L.h_camax = take(f * 4); L.w3_camax = take(f * 4);
     L.s = take(f * 4); L.sinv = take(f * 4);
@@ -166,7 +166,7 @@ WorkLayout work_layout(const ssg_mlp_desc &d) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align256(bytes); return at; };
     L.scalars = take(W_COUNT * 4);
-    L.partials = take(3 * ssg::kAmaxSlotWords * 4);     // slotted running maxima of dY, dU, dG (adjacent to the scalars)
+    L.partials = take(3 * ssg::kAmaxSlotWords * 4);     // range words of dY, slotted running maxima of dU, dG
     L.dy_q = take(T * dm);
     L.dU = take(T * f * 2); L.dG = take(T * f * 2);
     L.du_q = take(T * f); L.dg_q = take(T * f);
@@ -396,15 +396,11 @@ ssg_status infer_forward(const char *who, const ssg_mlp_desc *desc, const void *
     if (!ssg::gemm_args_ok(g) || !ssg::gemm_args_ok(g2)) return fail(SSG_ERR_ARG, "%s: internal GEMM arguments", who);
     ssg_status rc = check_entry(who);
     if (rc != SSG_OK) return rc;
-    // the range slots start at zero (a fill kernel, not a memset: the call may be under graph capture)
-    ssg::launch_fill_u32(reinterpret_cast<uint32_t *>(wk), (Wl.x_q - Wl.scalars) / 4, 0u, st);
     // x^ = Q(x)
-    ssg::launch_amax(x, ssg::SRC_BF16, (size_t)(T * dm), slots, ssg::kAmaxSlots, st);
     ssg::CastArgs c;
     c.src = x; c.kind = ssg::SRC_BF16; c.rows = T; c.cols = dm; c.fmt = ssg::kE4M3; c.pow2 = desc->rnd == SSG_ROUND_POW2;
-    c.amax = reinterpret_cast<float *>(slots); c.amax_slots = ssg::kAmaxSlots; c.amax_out = wsc + 1; c.scale_out = wsc + 0;
-    c.dst = wk + Wl.x_q;
-    ssg::launch_cast(c, st);
+    c.range_words = slots; c.amax_out = wsc + 1; c.scale_out = wsc + 0; c.dst = wk + Wl.x_q;
+    ssg::launch_quantize_batch(&c, 1, ssg::ZeroWords{}, st);
     ssg::launch_gemm(g, st);
     ssg::launch_gemm(g2, st);
     return check_launch(who);
@@ -784,13 +780,15 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
     if (!ssg::gemm_args_ok(g) || !ssg::gemm_args_ok(g2)) return fail(SSG_ERR_ARG, "ssg_mlp_fwd: internal GEMM arguments");
     if ((rc = check_entry("ssg_mlp_fwd")) != SSG_OK) return rc;
 
-    // zero the running maxima of this call; with cached weights the slots that belong to W1, W2 and
-    // W3 (their scales, ranges and W3's per-channel maxima) are left as the earlier call wrote them
-    const uint32_t per_call = (1u << S_AMAX_W3S) | (1u << S_HMAX);
+    // zeroed by the call's first kernel: h's per-channel maxima and (unless cached: then they are left as the earlier call
+    // wrote them) W3's, the range of s^-1 * w3 and of h
     uint32_t *part = reinterpret_cast<uint32_t *>(b + L.partials);
     uint32_t *part_x = part, *part_w1 = part + ssg::kAmaxSlotWords, *part_w2 = part + 2 * ssg::kAmaxSlotWords;
-    ssg::launch_reset(scb, per_call, part, (size_t)((L.h_camax - L.partials) / 4) + (size_t)f,
-                      reinterpret_cast<uint32_t *>(w3_camax), cached ? 0 : (size_t)f, st);
+    ssg::ZeroWords zero;
+    zero.p[0] = reinterpret_cast<uint32_t *>(h_camax);
+    zero.n[0] = (unsigned)((cached ? 0 : (L.w3_camax - L.h_camax) / 4) + (size_t)f);
+    static_assert(S_HMAX > S_AMAX_W3S && S_AMAX_W3S > S_AMAX_W2, "one run of words, from here to the end of the scalars");
+    zero.p[1] = scb + S_AMAX_W3S; zero.n[1] = S_COUNT - S_AMAX_W3S;
     if (desc->h_counters) ssg::launch_fill_u32(reinterpret_cast<uint32_t *>(desc->h_counters), 4, 0u, st);
 
     // a1 + a2: per-tensor range (Section 2), then Q (Eq. 2); row-major only: the backward contractions
@@ -804,7 +802,6 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
     auto state_slots = [&](int j) { return state + ssg::kScalingHeaderWords + (size_t)j * ssg::kAmaxSlotWords; };
     // x and (unless cached) W1, W2 go through one range launch and one cast launch together
     ssg::CastArgs casts[3];
-    const void *srcs[3]; size_t counts[3]; uint32_t *slot_ptrs[3];
     int n_in = 0;
     auto add_input = [&](const void *src, int64_t rows, int64_t cols, uint32_t *part, int k, float *amax_out,
                          float *scale_out, uint8_t *dst) {
@@ -814,9 +811,8 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
         if (delayed) {
             c.scale_in = state_scale(k); c.record = state_slots(k);
         } else {
-            c.amax = reinterpret_cast<float *>(part); c.amax_out = amax_out;
+            c.range_words = part; c.amax_out = amax_out;
         }
-        srcs[n_in] = src; counts[n_in] = (size_t)(rows * cols); slot_ptrs[n_in] = part;
         ++n_in;
     };
     add_input(x, T, dm, part_x, 0, sc + S_AMAX_X, sc + S_SX, b + L.x_q);
@@ -824,8 +820,9 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
         add_input(W1, f, dm, part_w1, 1, sc + S_AMAX_W1, sc + S_SW1, b + L.w1_q);
         add_input(W2, f, dm, part_w2, 2, sc + S_AMAX_W2, sc + S_SW2, b + L.w2_q);
     }
-    if (!delayed) ssg::launch_amax_batch(srcs, counts, slot_ptrs, n_in, st);
-    ssg::launch_cast_batch(casts, n_in, st);
+    int range_count = 0;
+    if (delayed) ssg::launch_cast_batch(casts, n_in, zero, st);
+    else range_count = ssg::launch_quantize_batch(casts, n_in, zero, st);
     if (!cached) {
         // per-channel range of w3 as a launch of its own (unless it rides in the GEMM below)
         if (!bf16_last && !w3_range_in_gemm)
@@ -843,6 +840,7 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
         if (state) {
             ssg::ScalingUpdate u;
             u.pow2 = pow2;
+            for (int &n : u.range_count) n = range_count;
             u.slots[0] = part_x; u.tensor[0] = 0; u.fmt[0] = ssg::kE4M3; u.count = 1;
             if (!cached) {
                 u.slots[1] = part_w1; u.tensor[1] = 1; u.fmt[1] = ssg::kE4M3;
@@ -883,6 +881,7 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
         // enter this call's ranges into the history; the scales written here serve the next call
         ssg::ScalingUpdate u;
         u.pow2 = pow2;
+        for (int &n : u.range_count) n = range_count;
         u.slots[0] = delayed ? state_slots(0) : part_x; u.tensor[0] = 0; u.fmt[0] = ssg::kE4M3; u.count = 1;
         if (!cached) {
             u.slots[1] = delayed ? state_slots(1) : part_w1; u.tensor[1] = 1; u.fmt[1] = ssg::kE4M3;
@@ -1006,23 +1005,29 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
     const int dw3_sets = ssg::gemm_tile_sets(g3);
     const int dw3_split = grouped ? dw3_split_sets(g, g3, group_b) : dw3_sets;
 
-    ssg::launch_fill_u32(wscb, (Wl.partials - Wl.scalars) / 4 + 3 * ssg::kAmaxSlotWords, 0u, st);
-
+    // zeroed by the call's first kernel: the slots of dU's and dG's ranges, and the scalars that nothing writes under
+    // delayed scaling (under current scaling every scalar of the view is written)
+    ssg::ZeroWords zero;
+    zero.p[0] = part_du; zero.n[0] = 2 * ssg::kAmaxSlotWords;
+    static_assert(W_AMAX_DU == W_AMAX_DY + 1 && W_AMAX_DG == W_AMAX_DY + 2, "one run of words");
+    zero.p[1] = wscb + W_AMAX_DY; zero.n[1] = delayed ? 3 : 0;
+    int dy_range_count = 0;
     // a9: upstream gradient to E5M2 (Section 6.2)
     ssg::CastArgs c;
     c.src = dy; c.kind = ssg::SRC_BF16; c.rows = T; c.cols = dm; c.fmt = ssg::kE5M2; c.pow2 = pow2;
-    c.amax_slots = ssg::kAmaxSlots; c.scale_out = wsc + W_SDY; c.dst = wk + Wl.dy_q;
+    c.scale_out = wsc + W_SDY; c.dst = wk + Wl.dy_q;
     if (bf16_last) {
         // dY is used as the bf16 tensor it is; only its transposed copy is needed (for dW3)
+        ssg::launch_fill_u32(wscb, W_COUNT, 0u, st);
+        ssg::launch_fill_u32(zero.p[0], zero.n[0], 0u, st);
         ssg::launch_transpose_bf16(dy, T, dm, wk + Wl.dyT, st);
     } else if (delayed) {
         c.scale_in = state_scale(3); c.record = state_dy_slots;
+        ssg::launch_cast_batch(&c, 1, zero, st);
     } else {
-        ssg::launch_amax(dy, ssg::SRC_BF16, (size_t)(T * dm), part_dy, ssg::kAmaxSlots, st);
-        c.amax = reinterpret_cast<float *>(part_dy); c.amax_out = wsc + W_AMAX_DY;
+        c.range_words = part_dy; c.amax_out = wsc + W_AMAX_DY;
+        dy_range_count = ssg::launch_quantize_batch(&c, 1, zero, st);
     }
-    if (!bf16_last) ssg::launch_cast(c, st);
-    c.record = nullptr;
 
     if (grouped) ssg::launch_gemm_group(group_a, 2, dw3_split, st);
     else ssg::launch_gemm(g, st);
@@ -1038,7 +1043,7 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
         gc[0].scale_out = wsc + W_SDU; gc[0].dst = wk + Wl.du_q;
         gc[1].src = wk + Wl.dG; gc[1].amax = reinterpret_cast<float *>(part_dg); gc[1].amax_out = wsc + W_AMAX_DG;
         gc[1].scale_out = wsc + W_SDG; gc[1].dst = wk + Wl.dg_q;
-        ssg::launch_cast_batch(gc, 2, st);
+        ssg::launch_cast_batch(gc, 2, ssg::ZeroWords{}, st);
     }
     if (grouped) {
         if (dw3_split < dw3_sets) ssg::launch_gemm_group(group_b, 4, dw3_split, st);
@@ -1056,7 +1061,7 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
     if (state) {
         ssg::ScalingUpdate u;
         u.pow2 = pow2; u.count = 3;
-        u.slots[0] = delayed ? state_dy_slots : part_dy; u.tensor[0] = 3; u.fmt[0] = ssg::kE5M2;
+        u.slots[0] = delayed ? state_dy_slots : part_dy; u.tensor[0] = 3; u.fmt[0] = ssg::kE5M2; u.range_count[0] = dy_range_count;
         u.slots[1] = part_du; u.tensor[1] = 4; u.fmt[1] = ssg::kE5M2;
         u.slots[2] = part_dg; u.tensor[2] = 5; u.fmt[2] = ssg::kE5M2;
         if (bf16_last) {                 // dY is not quantized: no range of it was taken

@@ -11,8 +11,11 @@ enum SrcKind { SRC_BF16 = 0, SRC_F32 = 1, SRC_SWIGLU = 2 };
 
 // ---- elementwise / reduction passes (ssg_quant.hip) -------------------------
 void launch_fill_u32(uint32_t *p, size_t n, uint32_t value, hipStream_t st);
-// zero scalar slots selected by mask (bit i -> scalars[i], i < 32) and two vectors (either may be empty)
-void launch_reset(uint32_t *scalars, uint32_t mask, uint32_t *v1, size_t n1, uint32_t *v2, size_t n2, hipStream_t st);
+// up to two runs of words that a kernel zeroes on the side for the kernels after it
+struct ZeroWords {
+    uint32_t *p[2] = {nullptr, nullptr};
+    unsigned n[2] = {0, 0};
+};
 
 // Running maxima of |x| as float bits, spread over `slots` words that are kAmaxSlotStride words
 // (one cache line) apart and must be zeroed by the caller: workgroup b folds into slot b % slots.
@@ -23,9 +26,6 @@ constexpr int kAmaxSlots = 64;
 constexpr int kAmaxSlotStride = 32;
 constexpr size_t kAmaxSlotWords = (size_t)kAmaxSlots * kAmaxSlotStride;
 void launch_amax(const void *src, SrcKind kind, size_t n, uint32_t *amax_bits, int slots, hipStream_t st);
-// up to three bf16 tensors in one launch, each into its own kAmaxSlots slotted words
-void launch_amax_batch(const void *const *src, const size_t *n, uint32_t *const *amax_bits, int count, hipStream_t st);
-
 struct CastArgs {
     const void *src = nullptr;       // bf16 / f32 [rows, cols]; U for SRC_SWIGLU
     const void *src2 = nullptr;      // G for SRC_SWIGLU
@@ -35,6 +35,8 @@ struct CastArgs {
     const float *col_scale = nullptr;   // optional per-column factor applied first (one fp32 multiply)
     const float *amax = nullptr;     // per-tensor: scale = scale_from_amax(max over amax_slots slots) ...
     int amax_slots = 1;
+    int range_count = 0;             // > 0: `amax` is this many packed words instead of slots
+    uint32_t *range_words = nullptr; // launch_quantize_batch: kAmaxSlotWords words of scratch for the range of src
     float *amax_out = nullptr;       // where the reduced amax is recorded (may be null)
     const float *scale_in = nullptr; // ... or a given scale; both null = no per-tensor factor
     int pow2 = 0;
@@ -48,7 +50,11 @@ struct CastArgs {
 };
 void launch_cast(const CastArgs &a, hipStream_t st);
 // up to three casts of the same form (source kind, format, optional parts) in one launch; others are launched singly
-void launch_cast_batch(const CastArgs *list, int n, hipStream_t st);
+void launch_cast_batch(const CastArgs *list, int n, const ZeroWords &zero, hipStream_t st);
+// Q of up to three bf16 tensors from their own ranges (rows, cols, fmt, pow2, src, dst, amax_out, scale_out, range_words
+// given; one format), in one launch for small tensors, else a range and a cast launch.  Returns how many packed words of
+// each range_words hold its range afterwards.
+int launch_quantize_batch(CastArgs *list, int n, const ZeroWords &zero, hipStream_t st);
 // the smooth cast of h (from bf16 U, G) and the fold + cast of w3 in one launch (falls back to two for any other pair)
 void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, hipStream_t st);
 
@@ -176,7 +182,8 @@ constexpr int kScalingTensors = 6, kScalingHistory = 16, kScalingStride = 32;
 constexpr size_t kScalingHeaderWords = 256;
 constexpr size_t kScalingWords = kScalingHeaderWords + 4 * kAmaxSlotWords;
 struct ScalingUpdate {
-    uint32_t *slots[3] = {nullptr, nullptr, nullptr};   // slotted range words of the call just made (cleared afterwards)
+    uint32_t *slots[3] = {nullptr, nullptr, nullptr};   // slotted range words of the call just made (cleared afterwards),
+    int range_count[3] = {0, 0, 0};                     // or this many packed words
     int tensor[3] = {0, 0, 0};
     int fmt[3] = {0, 0, 0};
     int count = 0;

@@ -25,20 +25,12 @@ void launch_fill_u32(uint32_t *p, size_t n, uint32_t value, hipStream_t st) {
     profile_after(st);
 }
 
-// Zero selected scalar slots (bit i of mask -> slot i) and up to two vectors in one launch.
-__global__ void __launch_bounds__(256)
-reset_kernel(uint32_t *scalars, uint32_t mask, uint32_t *v1, size_t n1, uint32_t *v2, size_t n2) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < 32 && ((mask >> i) & 1u)) scalars[i] = 0u;
-    if (i < n1) v1[i] = 0u;
-    if (i < n2) v2[i] = 0u;
-}
-void launch_reset(uint32_t *scalars, uint32_t mask, uint32_t *v1, size_t n1, uint32_t *v2, size_t n2, hipStream_t st) {
-    size_t n = n1 > n2 ? n1 : n2;
-    if (n < 32) n = 32;
-    profile_before(kTagSmall, st, 4.0 * (double)(n1 + n2));
-    hipLaunchKernelGGL(reset_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, scalars, mask, v1, n1, v2, n2);
-    profile_after(st);
+// Words that later kernels of the call accumulate into are zeroed on the side by its first kernel: a launch of their
+// own costs 4.7 us (kernel to kernel) for a few thousand words.
+__device__ __forceinline__ void zero_words(const ZeroWords &z, const unsigned first, const unsigned stride) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        for (unsigned i = first; i < z.n[k]; i += stride) z.p[k][i] = 0u;
 }
 
 // ------------------------------------------------------------------ loaders
@@ -91,6 +83,17 @@ struct LoadSwiglu {          // h = u * Swish(g) from stored bf16 U, G
 };
 
 // ------------------------------------------------------------------ amax
+// the largest of words 4t .. 4t+3 of `count` packed range words (the array itself is longer)
+__device__ __forceinline__ uint32_t range_word_max(const uint32_t *words, int count, int t) {
+    if (4 * t >= count) return 0u;
+    const uint4 q = *reinterpret_cast<const uint4 *>(words + 4 * t);
+    uint32_t m = q.x;
+    if (4 * t + 1 < count) m = m > q.y ? m : q.y;
+    if (4 * t + 2 < count) m = m > q.z ? m : q.z;
+    if (4 * t + 3 < count) m = m > q.w ? m : q.w;
+    return m;
+}
+
 template <class Loader>
 __global__ void __launch_bounds__(256) amax_kernel(Loader ld, size_t n8, uint32_t *amax_bits, int slots) {
     uint32_t m = 0;
@@ -134,17 +137,24 @@ __global__ void __launch_bounds__(256) amax_kernel(Loader ld, size_t n8, uint32_
 // lane), grid-stride.  Measured on a 90 MB tensor: 13 us (6.9 TB/s) against 27-41 us for the generic kernel above
 // (which widens every element to fp32 and walks 32 KB units); more loads per lane or larger workgroups are slower.
 constexpr int kAmaxBf16Loads = 4;
+constexpr unsigned kAmaxBlocks = 1024;
+static_assert(kAmaxBlocks <= kAmaxSlotWords && kAmaxBlocks == 4 * 256, "one packed word per workgroup, four per consumer thread");
 struct AmaxBatch {
     const ssg_u32x4 *src[3];
     size_t n16[3];
     uint32_t *amax_bits[3];
+    ZeroWords zero;
 };
 // (up to three tensors per launch, blockIdx.y picks one: the ranges of x, W1, W2 share a launch)
+// PACKED: workgroup b stores its maximum as word b (nothing has to be zeroed before; the consumer takes the maximum over
+// all gridDim.x words); otherwise it is folded into slot b % slots.
+template <bool PACKED>
 __global__ void __launch_bounds__(256)
 amax_bf16_kernel(const AmaxBatch batch, int slots) {
     const ssg_u32x4 *__restrict__ src = batch.src[blockIdx.y];
     const size_t n16 = batch.n16[blockIdx.y];
     uint32_t *amax_bits = batch.amax_bits[blockIdx.y];
+    if (PACKED && blockIdx.y == 0) zero_words(batch.zero, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
     ssg_i16x2 m = {0x7f, 0x7f};
     const size_t run = (size_t)kAmaxBf16Loads * 256;
     for (size_t base = (size_t)blockIdx.x * run; base < n16; base += (size_t)gridDim.x * run) {
@@ -166,29 +176,34 @@ amax_bf16_kernel(const AmaxBatch batch, int slots) {
     if (threadIdx.x == 0) {
         for (int w = 1; w < 4; ++w) r = r > part[w] ? r : part[w];
         r = r > part[0] ? r : part[0];
-        if (r) atomicMax(amax_bits + (blockIdx.x % slots) * kAmaxSlotStride, r);
+        if (PACKED) amax_bits[blockIdx.x] = r;
+        else if (r) atomicMax(amax_bits + (blockIdx.x % slots) * kAmaxSlotStride, r);
     }
 }
 
-void launch_amax_batch(const void *const *src, const size_t *n, uint32_t *const *amax_bits, int count, hipStream_t st) {
+static unsigned amax_blocks(size_t n16) {
+    const size_t runs = (n16 + kAmaxBf16Loads * 256 - 1) / (kAmaxBf16Loads * 256);
+    return (unsigned)(runs < kAmaxBlocks ? runs : kAmaxBlocks);
+}
+
+static int launch_amax_batch(const CastArgs *list, int count, const ZeroWords &zero, hipStream_t st) {
     AmaxBatch batch;
     size_t largest = 0;
     double bytes = 0.0;
-    int m = 0;
-    for (int i = 0; i < count && m < 3; ++i) {
-        if (n[i] / 8 == 0) continue;
-        batch.src[m] = (const ssg_u32x4 *)src[i]; batch.n16[m] = n[i] / 8; batch.amax_bits[m] = amax_bits[i];
-        largest = batch.n16[m] > largest ? batch.n16[m] : largest;
-        bytes += 2.0 * (double)n[i];
-        ++m;
+    for (int i = 0; i < 3; ++i) {
+        const CastArgs &c = list[i < count ? i : 0];
+        const size_t n = (size_t)c.rows * (size_t)c.cols;
+        batch.src[i] = (const ssg_u32x4 *)c.src; batch.n16[i] = n / 8; batch.amax_bits[i] = c.range_words;
+        if (i >= count) continue;
+        largest = n / 8 > largest ? n / 8 : largest;
+        bytes += 2.0 * (double)n;
     }
-    if (m == 0) return;
-    for (int i = m; i < 3; ++i) { batch.src[i] = batch.src[0]; batch.n16[i] = 0; batch.amax_bits[i] = batch.amax_bits[0]; }
-    const size_t runs = (largest + kAmaxBf16Loads * 256 - 1) / (kAmaxBf16Loads * 256);
-    const unsigned blocks = (unsigned)(runs < 1024 ? runs : 1024);
+    batch.zero = zero;
+    const unsigned blocks = amax_blocks(largest);
     profile_before(kTagAmax, st, bytes);
-    hipLaunchKernelGGL(amax_bf16_kernel, dim3(blocks, (unsigned)m), dim3(256), 0, st, batch, kAmaxSlots);
+    hipLaunchKernelGGL(amax_bf16_kernel<true>, dim3(blocks, (unsigned)count), dim3(256), 0, st, batch, 0);
     profile_after(st);
+    return (int)blocks;
 }
 
 void launch_amax(const void *src, SrcKind kind, size_t n, uint32_t *amax_bits, int slots, hipStream_t st) {
@@ -198,9 +213,8 @@ void launch_amax(const void *src, SrcKind kind, size_t n, uint32_t *amax_bits, i
     if (kind == SRC_BF16) {
         AmaxBatch batch;
         for (int i = 0; i < 3; ++i) { batch.src[i] = (const ssg_u32x4 *)src; batch.n16[i] = n8; batch.amax_bits[i] = amax_bits; }
-        const size_t runs = (n8 + kAmaxBf16Loads * 256 - 1) / (kAmaxBf16Loads * 256);
-        const unsigned blocks = (unsigned)(runs < 1024 ? runs : 1024);
-        hipLaunchKernelGGL(amax_bf16_kernel, dim3(blocks), dim3(256), 0, st, batch, slots);
+        batch.zero = ZeroWords{};
+        hipLaunchKernelGGL(amax_bf16_kernel<false>, dim3(amax_blocks(n8)), dim3(256), 0, st, batch, slots);
     } else {
         const size_t units = (n8 + 2047) / 2048;
         const size_t cap = slots > 1 ? 2048 : 512;
@@ -244,7 +258,7 @@ struct CastItem {
     Loader ld;
     int64_t rows, cols;
     const float *col_scale, *amax;
-    int amax_slots;
+    int amax_slots, range_count;
     float *amax_out;
     const float *scale_in;
     float *scale_out;
@@ -256,6 +270,7 @@ template <class Loader>
 struct CastBatch {
     CastItem<Loader> item[3];
     int pow2;
+    ZeroWords zero;
 };
 // The work of one workgroup: tile (bx, by) of item `it`.
 template <class Loader, int FMT, bool COLSCALE, bool TRANSPOSED, bool RECORD = false, bool COUNT = false>
@@ -279,11 +294,22 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
     bool tensor_scale = false;
     if (scale_in) { sigma = *scale_in; tensor_scale = true; }
     else if (amax) {
-        // maximum over the slots the producers folded into: lane i of every wave takes slot i
-        // (kAmaxSlots = wave size), then a wave-wide maximum
+        // maximum over the words of the range pass, or over the slots the producers folded into: lane i of every wave
+        // takes slot i (kAmaxSlots = wave size); then a wave-wide maximum
         const uint32_t *ab = reinterpret_cast<const uint32_t *>(amax);
         const int lane = threadIdx.x & 63;
-        uint32_t mbits = lane < amax_slots ? ab[lane * kAmaxSlotStride] : 0u;
+        uint32_t mbits = 0u;
+        if (it.range_count) {
+            // one 16-byte load per thread for all of them, then across the waves: reading all words in every wave cost
+            // 6 us over the casts of a step at T = 4096, d = 4096, f = 11008
+            __shared__ uint32_t wave_range[4];
+            mbits = wave_max_u32(range_word_max(ab, it.range_count, threadIdx.x));
+            if (lane == 0) wave_range[threadIdx.x >> 6] = mbits;
+            __syncthreads();
+            mbits = wave_range[lane & 3];
+        } else if (lane < amax_slots) {
+            mbits = ab[lane * kAmaxSlotStride];
+        }
         mbits = wave_max_u32(mbits);
         const float m = __uint_as_float(mbits);
         sigma = scale_from_amax(m, Fp8Traits<FMT>::fmax, pow2);
@@ -424,6 +450,7 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
 template <class Loader, int FMT, bool COLSCALE, bool TRANSPOSED, bool RECORD = false, bool COUNT = false>
 __global__ void __launch_bounds__(256)
 cast_kernel(const CastBatch<Loader> batch) {
+    if (blockIdx.z == 0) zero_words(batch.zero, (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
     cast_block<Loader, FMT, COLSCALE, TRANSPOSED, RECORD, COUNT>(batch.item[blockIdx.z], batch.pow2, blockIdx.x, blockIdx.y);
 }
 
@@ -439,7 +466,7 @@ cast_h_w3_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3, cons
 
 template <class Loader>
 static CastItem<Loader> cast_item(const Loader &ld, const CastArgs &a) {
-    return CastItem<Loader>{ld, a.rows, a.cols, a.col_scale, a.amax, a.amax_slots, a.amax_out, a.scale_in, a.scale_out,
+    return CastItem<Loader>{ld, a.rows, a.cols, a.col_scale, a.amax, a.amax_slots, a.range_count, a.amax_out, a.scale_in, a.scale_out,
                             a.dst, a.dst_t, a.record, a.counters};
 }
 
@@ -452,7 +479,7 @@ static bool same_cast_form(const CastArgs &a, const CastArgs &b) {
 }
 
 template <class Loader, int FMT, class MakeLoader>
-static void launch_cast_l(const CastArgs *list, int n, MakeLoader make, hipStream_t st) {
+static void launch_cast_l(const CastArgs *list, int n, MakeLoader make, const ZeroWords &zero, hipStream_t st) {
     const CastArgs &a = list[0];
     CastBatch<Loader> batch;
     int64_t rows = 0, cols = 0;
@@ -462,6 +489,7 @@ static void launch_cast_l(const CastArgs *list, int n, MakeLoader make, hipStrea
         if (i < n) { rows = x.rows > rows ? x.rows : rows; cols = x.cols > cols ? x.cols : cols; }
     }
     batch.pow2 = a.pow2;
+    batch.zero = zero;
     dim3 grid((unsigned)((cols + kTile - 1) / kTile), (unsigned)((rows + kTile - 1) / kTile), (unsigned)n);
     const bool cs = a.col_scale != nullptr, tr = a.dst_t != nullptr;
 #define SSG_CAST(...) hipLaunchKernelGGL((cast_kernel<Loader, FMT, __VA_ARGS__>), grid, dim3(256), 0, st, batch)
@@ -485,17 +513,17 @@ static void launch_cast_l(const CastArgs *list, int n, MakeLoader make, hipStrea
 }
 
 template <int FMT>
-static void launch_cast_f(const CastArgs *list, int n, hipStream_t st) {
+static void launch_cast_f(const CastArgs *list, int n, const ZeroWords &zero, hipStream_t st) {
     switch (list[0].kind) {
         case SRC_BF16:
-            launch_cast_l<LoadBf16, FMT>(list, n, [](const CastArgs &x) { return LoadBf16{(const uint16_t *)x.src}; }, st);
+            launch_cast_l<LoadBf16, FMT>(list, n, [](const CastArgs &x) { return LoadBf16{(const uint16_t *)x.src}; }, zero, st);
             break;
         case SRC_F32:
-            launch_cast_l<LoadF32, FMT>(list, n, [](const CastArgs &x) { return LoadF32{(const float *)x.src}; }, st);
+            launch_cast_l<LoadF32, FMT>(list, n, [](const CastArgs &x) { return LoadF32{(const float *)x.src}; }, zero, st);
             break;
         case SRC_SWIGLU:
             launch_cast_l<LoadSwiglu, FMT>(list, n, [](const CastArgs &x) {
-                return LoadSwiglu{(const uint16_t *)x.src, (const uint16_t *)x.src2}; }, st);
+                return LoadSwiglu{(const uint16_t *)x.src, (const uint16_t *)x.src2}; }, zero, st);
             break;
     }
 }
@@ -505,7 +533,7 @@ static double cast_bytes(const CastArgs &a) {
     return ((a.kind == SRC_BF16 ? 2.0 : 4.0) + (a.dst_t ? 2.0 : 1.0)) * (double)a.rows * (double)a.cols;
 }
 
-void launch_cast_batch(const CastArgs *list, int n, hipStream_t st) {
+void launch_cast_batch(const CastArgs *list, int n, const ZeroWords &zero, hipStream_t st) {
     // items that are empty or of another form than the first go on their own
     int m = 0;
     CastArgs same[3];
@@ -519,12 +547,90 @@ void launch_cast_batch(const CastArgs *list, int n, hipStream_t st) {
     for (int i = 0; i < m; ++i) bytes += cast_bytes(same[i]);
     const CastArgs &a = same[0];
     profile_before(a.kind == SRC_SWIGLU ? kTagCastSwiglu : a.col_scale ? kTagCastColscale : kTagCast, st, bytes);
-    if (a.fmt == kE4M3) launch_cast_f<kE4M3>(same, m, st);
-    else launch_cast_f<kE5M2>(same, m, st);
+    if (a.fmt == kE4M3) launch_cast_f<kE4M3>(same, m, zero, st);
+    else launch_cast_f<kE5M2>(same, m, zero, st);
     profile_after(st);
 }
 
-void launch_cast(const CastArgs &a, hipStream_t st) { launch_cast_batch(&a, 1, st); }
+void launch_cast(const CastArgs &a, hipStream_t st) { launch_cast_batch(&a, 1, ZeroWords{}, st); }
+
+// ------------------------------------------------------------------ range and cast of small tensors in one launch
+// A tensor of at most 512 KB is read whole by every workgroup (L2 serves it), which then casts its own 16 KB: no range
+// words go between two launches.  Bound by the two launch latencies it replaces; a workgroup's range sweep of the 512 KB
+// takes as long as the launch it saves, so the line lies there.
+constexpr size_t kSmallElems = (size_t)1 << 18;
+constexpr int kSmallThreads = 1024;
+template <int FMT>
+__global__ void __launch_bounds__(kSmallThreads) quantize_small_kernel(const CastBatch<LoadBf16> batch) {
+    const CastItem<LoadBf16> &it = batch.item[blockIdx.y];
+    if (blockIdx.y == 0) zero_words(batch.zero, blockIdx.x * kSmallThreads + threadIdx.x, gridDim.x * kSmallThreads);
+    const unsigned n16 = (unsigned)(it.rows * it.cols / 8);
+    if (blockIdx.x * kSmallThreads >= n16) return;
+    const ssg_u32x4 *__restrict__ src = reinterpret_cast<const ssg_u32x4 *>(it.ld.p);
+    const unsigned own = blockIdx.x * kSmallThreads + threadIdx.x;
+    const ssg_u32x4 mine = own < n16 ? src[own] : ssg_u32x4{0u, 0u, 0u, 0u};
+    ssg_i16x2 m = {0x7f, 0x7f};
+    for (unsigned base = threadIdx.x; base < n16; base += 8 * kSmallThreads) {
+        ssg_u32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = base + u * kSmallThreads < n16 ? src[base + u * kSmallThreads] : ssg_u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) m = __builtin_elementwise_max(m, biased_abs_pk(v[u][k]));
+    }
+    __shared__ uint32_t part[kSmallThreads / 64];
+    uint32_t bits = wave_max_u32(unbias_max_pk(m));
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = bits;
+    __syncthreads();
+    bits = wave_max_u32(part[threadIdx.x & (kSmallThreads / 64 - 1)]);
+    const float amax = __uint_as_float(bits), sigma = scale_from_amax(amax, Fp8Traits<FMT>::fmax, batch.pow2);
+    if (own == 0) {
+        *it.amax_out = amax; *it.scale_out = sigma;
+        if (it.record) *it.record = bits;
+    }
+    if (own >= n16) return;
+    float v[8];
+    LoadBf16::widen(make_uint4(mine[0], mine[1], mine[2], mine[3]), v);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = __fmul_rn(v[k], sigma);
+    *reinterpret_cast<uint2 *>(it.dst + (size_t)own * 8) = make_uint2(satcast_pk4<FMT>(v[0], v[1], v[2], v[3]), satcast_pk4<FMT>(v[4], v[5], v[6], v[7]));
+}
+
+// Q of up to three bf16 tensors from their own ranges (Section 2).  Returns the number of packed range words each
+// tensor's `range_words` holds afterwards.
+int launch_quantize_batch(CastArgs *list, int n, const ZeroWords &zero, hipStream_t st) {
+    size_t largest = 0;
+    double bytes = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const size_t elems = (size_t)list[i].rows * (size_t)list[i].cols;
+        largest = elems > largest ? elems : largest;
+        bytes += cast_bytes(list[i]);
+    }
+    if (largest <= kSmallElems) {
+        CastBatch<LoadBf16> batch;
+        for (int i = 0; i < 3; ++i) {
+            const CastArgs &a = list[i < n ? i : 0];
+            batch.item[i] = cast_item<LoadBf16>(LoadBf16{(const uint16_t *)a.src}, a);
+            batch.item[i].record = a.range_words;
+        }
+        batch.pow2 = list[0].pow2;
+        batch.zero = zero;
+        const dim3 grid((unsigned)((largest / 8 + kSmallThreads - 1) / kSmallThreads), (unsigned)n);
+        profile_before(kTagCast, st, bytes);
+        if (list[0].fmt == kE4M3) hipLaunchKernelGGL(quantize_small_kernel<kE4M3>, grid, dim3(kSmallThreads), 0, st, batch);
+        else hipLaunchKernelGGL(quantize_small_kernel<kE5M2>, grid, dim3(kSmallThreads), 0, st, batch);
+        profile_after(st);
+        return 1;
+    }
+    const int words = launch_amax_batch(list, n, zero, st);
+    for (int i = 0; i < n; ++i) {
+        list[i].amax = reinterpret_cast<const float *>(list[i].range_words);
+        list[i].range_count = words;
+    }
+    launch_cast_batch(list, n, ZeroWords{}, st);
+    return words;
+}
 
 bool cast_h_w3_ok(const CastArgs &h, const CastArgs &w3) {
     return h.kind == SRC_SWIGLU && w3.kind == SRC_BF16 && h.fmt == kE4M3 && w3.fmt == kE4M3 && h.col_scale && w3.col_scale &&
@@ -831,14 +937,23 @@ void launch_scaling_init(uint32_t *state, hipStream_t st) {
                        kScalingWords);
 }
 
-// One wave per tensor: the range of the call just made (maximum over its slots, which are cleared
-// for the next call) replaces the oldest history entry; the next call's scale is fmax over the
+// One wave per tensor: the range of the call just made (maximum over the packed words of the range pass, or over its
+// slots, which are cleared for the next call) replaces the oldest history entry; the next call's scale is fmax over the
 // largest entry (Section 2, delayed scaling).
 __global__ void __launch_bounds__(64) scaling_update_kernel(uint32_t *state, ScalingUpdate u) {
     const int k = blockIdx.x, lane = threadIdx.x;
     uint32_t *slots = u.slots[k];
-    const uint32_t seen = wave_max_u32(slots[lane * kAmaxSlotStride]);
-    slots[lane * kAmaxSlotStride] = 0u;
+    uint32_t seen = 0u;
+    if (u.range_count[k]) {
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t w = range_word_max(slots, u.range_count[k], q * 64 + lane);
+            seen = seen > w ? seen : w;
+        }
+    } else {
+        seen = slots[lane * kAmaxSlotStride];
+        slots[lane * kAmaxSlotStride] = 0u;
+    }
+    seen = wave_max_u32(seen);
     uint32_t *w = state + (size_t)u.tensor[k] * kScalingStride;
     const uint32_t pos = w[1] % kScalingHistory;
     uint32_t h = lane < kScalingHistory ? w[8 + lane] : 0u;
