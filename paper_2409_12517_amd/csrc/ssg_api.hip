@@ -583,18 +583,19 @@ ssg_status ssg_quantize(const void *src, ssg_dtype src_dtype, int64_t rows, int6
     ssg::CastArgs a;
     a.src = src; a.kind = src_kind(src_dtype); a.rows = rows; a.cols = cols; a.fmt = fmt;
     a.dst = dst; a.dst_t = dst_t; a.pow2 = rnd == SSG_ROUND_POW2;
+    const size_t n = (size_t)(rows * cols);
+    // the range pass leaves its words in dst, which the cast overwrites once the scale is known
+    uint32_t *words = reinterpret_cast<uint32_t *>(dst);
+    a.scale_in = scale_dev;
     if (mode == SSG_SCALE_CURRENT) {
-        ssg::launch_fill_u32(reinterpret_cast<uint32_t *>(amax_dev), 1, 0u, st);
-        ssg::launch_amax(src, a.kind, (size_t)(rows * cols), reinterpret_cast<uint32_t *>(amax_dev), 1, st);
-        a.amax = amax_dev;
-        a.scale_out = scale_dev;
-        if (empty) ssg::launch_fill_u32(reinterpret_cast<uint32_t *>(scale_dev), 1, 0x3f800000u, st);
-    } else {
-        a.scale_in = scale_dev;
-        if (amax_dev && !empty) {
+        if (empty) {
             ssg::launch_fill_u32(reinterpret_cast<uint32_t *>(amax_dev), 1, 0u, st);
-            ssg::launch_amax(src, a.kind, (size_t)(rows * cols), reinterpret_cast<uint32_t *>(amax_dev), 1, st);
+            ssg::launch_fill_u32(reinterpret_cast<uint32_t *>(scale_dev), 1, 0x3f800000u, st);
+        } else {
+            ssg::launch_range_scale(src, a.kind, n, words, fmt, a.pow2, amax_dev, scale_dev, st);
         }
+    } else if (amax_dev && !empty) {
+        ssg::launch_range_scale(src, a.kind, n, words, fmt, 0, amax_dev, nullptr, st);
     }
     ssg::launch_cast(a, st);
     return check_launch("ssg_quantize");
@@ -656,7 +657,10 @@ ssg_status ssg_smooth_swiglu_quantize(const void *U, const void *G, int64_t T, i
     ssg::launch_fill_u32(hmax, 4, 0u, st);
     ssg::launch_col_amax(U, G, ssg::SRC_SWIGLU, T, f, reinterpret_cast<uint32_t *>(camax), st);
     // camax also stands in for the per-channel range of w3 (its product only feeds the sink)
-    ssg::launch_channel_factors(camax, camax, f, smooth, s, sinv, sink, hmax, nullptr, st);
+    ssg::ChannelFactors fac;
+    fac.h_camax = camax; fac.w3_camax = camax; fac.f = f; fac.smooth = smooth; fac.s = s; fac.sinv = sinv;
+    fac.amax_w3s_bits = sink; fac.hmax_bits = hmax;
+    ssg::launch_channel_factors(fac, st);
     ssg::CastArgs a;
     a.src = U; a.src2 = G; a.kind = ssg::SRC_SWIGLU; a.rows = T; a.cols = f; a.fmt = ssg::kE4M3;
     a.col_scale = s; a.dst = h_q; a.dst_t = h_qT;
@@ -783,7 +787,6 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
     // zeroed by the call's first kernel: h's per-channel maxima and (unless cached: then they are left as the earlier call
     // wrote them) W3's, the range of s^-1 * w3 and of h
     uint32_t *part = reinterpret_cast<uint32_t *>(b + L.partials);
-    uint32_t *part_x = part, *part_w1 = part + ssg::kAmaxSlotWords, *part_w2 = part + 2 * ssg::kAmaxSlotWords;
     ssg::ZeroWords zero;
     zero.p[0] = reinterpret_cast<uint32_t *>(h_camax);
     zero.n[0] = (unsigned)((cached ? 0 : (L.w3_camax - L.h_camax) / 4) + (size_t)f);
@@ -803,7 +806,7 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
     // x and (unless cached) W1, W2 go through one range launch and one cast launch together
     ssg::CastArgs casts[3];
     int n_in = 0;
-    auto add_input = [&](const void *src, int64_t rows, int64_t cols, uint32_t *part, int k, float *amax_out,
+    auto add_input = [&](const void *src, int64_t rows, int64_t cols, int k, float *amax_out,
                          float *scale_out, uint8_t *dst) {
         ssg::CastArgs &c = casts[n_in];
         c.kind = ssg::SRC_BF16; c.fmt = ssg::kE4M3; c.pow2 = pow2; c.amax_slots = ssg::kAmaxSlots;
@@ -811,18 +814,25 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
         if (delayed) {
             c.scale_in = state_scale(k); c.record = state_slots(k);
         } else {
-            c.range_words = part; c.amax_out = amax_out;
+            c.range_words = part + (size_t)k * ssg::kAmaxSlotWords; c.amax_out = amax_out;
         }
         ++n_in;
     };
-    add_input(x, T, dm, part_x, 0, sc + S_AMAX_X, sc + S_SX, b + L.x_q);
+    add_input(x, T, dm, 0, sc + S_AMAX_X, sc + S_SX, b + L.x_q);
     if (!cached) {
-        add_input(W1, f, dm, part_w1, 1, sc + S_AMAX_W1, sc + S_SW1, b + L.w1_q);
-        add_input(W2, f, dm, part_w2, 2, sc + S_AMAX_W2, sc + S_SW2, b + L.w2_q);
+        add_input(W1, f, dm, 1, sc + S_AMAX_W1, sc + S_SW1, b + L.w1_q);
+        add_input(W2, f, dm, 2, sc + S_AMAX_W2, sc + S_SW2, b + L.w2_q);
     }
     int range_count = 0;
     if (delayed) ssg::launch_cast_batch(casts, n_in, zero, st);
     else range_count = ssg::launch_quantize_batch(casts, n_in, zero, st);
+    // this call's ranges of x, W1, W2, for the history
+    ssg::ScalingUpdate history;
+    history.state = state; history.pow2 = pow2; history.count = n_in;
+    for (int k = 0; k < n_in; ++k) {
+        history.slots[k] = delayed ? state_slots(k) : part + (size_t)k * ssg::kAmaxSlotWords;
+        history.range_count[k] = range_count; history.tensor[k] = k; history.fmt[k] = ssg::kE4M3;
+    }
     if (!cached) {
         // per-channel range of w3 as a launch of its own (unless it rides in the GEMM below)
         if (!bf16_last && !w3_range_in_gemm)
@@ -837,25 +847,18 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
         // the SwiGLU output stays in bf16 (rounded once from the fp32 product), straight and transposed
         ssg::launch_swiglu_bf16(b + L.U, b + L.G, T, f, b + L.h_b, b + L.h_bT, st);
         ssg::launch_gemm(g2, st);
-        if (state) {
-            ssg::ScalingUpdate u;
-            u.pow2 = pow2;
-            for (int &n : u.range_count) n = range_count;
-            u.slots[0] = part_x; u.tensor[0] = 0; u.fmt[0] = ssg::kE4M3; u.count = 1;
-            if (!cached) {
-                u.slots[1] = part_w1; u.tensor[1] = 1; u.fmt[1] = ssg::kE4M3;
-                u.slots[2] = part_w2; u.tensor[2] = 2; u.fmt[2] = ssg::kE4M3;
-                u.count = 3;
-            }
-            ssg::launch_scaling_update(state, u, st);
-        }
+        if (state) ssg::launch_scaling_update(history, st);
         return check_launch("ssg_mlp_fwd");
     }
 
     // a5: factors s_i, s_i^-1 and the range of s^-1 * w3 (from the per-channel range of w3); plain block:
-    // one scale for all of h, from its own range or as the caller gives it
-    ssg::launch_channel_factors(h_camax, w3_camax, f, desc->smooth, s, sinv, scb + S_AMAX_W3S, scb + S_HMAX,
-                                desc->h_scale_mode == SSG_SCALE_GIVEN ? desc->h_scale : nullptr, st);
+    // one scale for all of h, from its own range or as the caller gives it.  With a history attached this call's ranges
+    // of x, W1, W2 are entered on the side; the scales that writes serve the next call
+    ssg::ChannelFactors fac;
+    fac.h_camax = h_camax; fac.w3_camax = w3_camax; fac.f = f; fac.smooth = desc->smooth; fac.s = s; fac.sinv = sinv;
+    fac.amax_w3s_bits = scb + S_AMAX_W3S; fac.hmax_bits = scb + S_HMAX;
+    fac.h_scale_given = desc->h_scale_mode == SSG_SCALE_GIVEN ? desc->h_scale : nullptr;
+    if (state) fac.update = history;
 
     // a6: h^ = cast(s_i * h), recomputing h from the stored bf16 U, G
     ssg::CastArgs hq;
@@ -869,27 +872,14 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
     wq.col_scale = sinv; wq.amax = sc + S_AMAX_W3S; wq.scale_out = sc + S_SW3;
     wq.dst = b + L.w3_q;
     if (gemm_grouping_enabled()) {
-        ssg::launch_cast_h_w3(hq, wq, st);
+        ssg::launch_cast_h_w3(hq, wq, fac, st);
     } else {
+        ssg::launch_channel_factors(fac, st);
         ssg::launch_cast(hq, st);
         ssg::launch_cast(wq, st);
     }
 
     ssg::launch_gemm(g2, st);
-
-    if (state) {
-        // enter this call's ranges into the history; the scales written here serve the next call
-        ssg::ScalingUpdate u;
-        u.pow2 = pow2;
-        for (int &n : u.range_count) n = range_count;
-        u.slots[0] = delayed ? state_slots(0) : part_x; u.tensor[0] = 0; u.fmt[0] = ssg::kE4M3; u.count = 1;
-        if (!cached) {
-            u.slots[1] = delayed ? state_slots(1) : part_w1; u.tensor[1] = 1; u.fmt[1] = ssg::kE4M3;
-            u.slots[2] = delayed ? state_slots(2) : part_w2; u.tensor[2] = 2; u.fmt[2] = ssg::kE4M3;
-            u.count = 3;
-        }
-        ssg::launch_scaling_update(state, u, st);
-    }
     return check_launch("ssg_mlp_fwd");
 }
 
@@ -1045,29 +1035,29 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
         gc[1].scale_out = wsc + W_SDG; gc[1].dst = wk + Wl.dg_q;
         ssg::launch_cast_batch(gc, 2, ssg::ZeroWords{}, st);
     }
-    if (grouped) {
-        if (dw3_split < dw3_sets) ssg::launch_gemm_group(group_b, 4, dw3_split, st);
-        else ssg::launch_gemm_group(group_b, 3, -1, st);
-    } else if (grouped_b) {
-        ssg::launch_gemm(g3, st);
-        ssg::launch_gemm_group(group_b, 3, -1, st);
-    } else {
-        ssg::launch_gemm(g3, st);
-        ssg::launch_gemm(g4a, st);
-        if (!dx_one) ssg::launch_gemm(g4b, st);
-        ssg::launch_gemm(g5a, st);
-        ssg::launch_gemm(g5b, st);
-    }
+    ssg::ScalingUpdate u;
     if (state) {
-        ssg::ScalingUpdate u;
-        u.pow2 = pow2; u.count = 3;
+        u.state = state; u.pow2 = pow2; u.count = 3;
         u.slots[0] = delayed ? state_dy_slots : part_dy; u.tensor[0] = 3; u.fmt[0] = ssg::kE5M2; u.range_count[0] = dy_range_count;
         u.slots[1] = part_du; u.tensor[1] = 4; u.fmt[1] = ssg::kE5M2;
         u.slots[2] = part_dg; u.tensor[2] = 5; u.fmt[2] = ssg::kE5M2;
         if (bf16_last) {                 // dY is not quantized: no range of it was taken
             u.slots[0] = part_du; u.tensor[0] = 4; u.slots[1] = part_dg; u.tensor[1] = 5; u.count = 2;
         }
-        ssg::launch_scaling_update(state, u, st);
+    }
+    if (grouped) {
+        if (dw3_split < dw3_sets) ssg::launch_gemm_group(group_b, 4, dw3_split, st, u);
+        else ssg::launch_gemm_group(group_b, 3, -1, st, u);
+    } else if (grouped_b) {
+        ssg::launch_gemm(g3, st);
+        ssg::launch_gemm_group(group_b, 3, -1, st, u);
+    } else {
+        ssg::launch_gemm(g3, st);
+        ssg::launch_gemm(g4a, st);
+        if (!dx_one) ssg::launch_gemm(g4b, st);
+        ssg::launch_gemm(g5a, st);
+        ssg::launch_gemm(g5b, st);
+        ssg::launch_scaling_update(u, st);
     }
     return check_launch("ssg_mlp_bwd");
 }

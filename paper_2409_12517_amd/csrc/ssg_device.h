@@ -49,6 +49,11 @@ __device__ __forceinline__ float scale_from_amax(float amax, float fmax, int pow
     return s;
 }
 
+// The per-channel factors of Smooth-SwiGLU (Section 4.4) from the channel's largest |h|: s = fl32(448 / a) and
+// s^-1 = fl32(a / 448), both 1 for an all-zero channel.
+__device__ __forceinline__ float smooth_factor(float a) { return scale_from_amax(a, 448.0f, 0); }
+__device__ __forceinline__ float smooth_factor_inv(float a) { return a > 0.0f ? __fdiv_rn(a, 448.0f) : 1.0f; }
+
 // Two fp32 values -> two FP8 codes in the low 16 bits.  The hardware
 // conversion rounds to nearest even through the subnormal range but turns
 // out-of-range magnitudes into NaN/Inf codes, so the value is clamped to the

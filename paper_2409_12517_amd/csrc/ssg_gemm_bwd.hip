@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "ssg_gemm_tile.h"
+#include "ssg_scaling.h"
 
 namespace ssg {
 
@@ -26,6 +27,7 @@ struct GroupParams {
     GemmParams p[4];
     int sets[4];
     int first[4];
+    int tile_blocks;        // workgroups of all sets
 };
 
 // dH (with the SwiGLU derivative; EPI = EPI_SWIGLU_BWD or EPI_SWIGLU_BWD_Q), then the first part of dW3: both read dY^.
@@ -44,7 +46,7 @@ __global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_group_dh_dw
 
 // dX (sum of two products in one tile: the long tiles, dealt first), then dW1, dW2 and the rest of dW3.
 template <int WB>
-__global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_group_dx_dw_kernel(GroupParams g) {
+__global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_group_dx_dw_kernel(GroupParams g, ScalingUpdate update) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB)];
     int G = set_of<WB>((int)blockIdx.x);
     const int x = (int)(blockIdx.x & 7), q = quarter_of<WB>((int)blockIdx.x);
@@ -56,6 +58,12 @@ __global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_group_dx_dw
     G -= g.sets[0];
     int m = 1;
     if (G >= g.sets[1]) { G -= g.sets[1]; m = 2; if (G >= g.sets[2]) { G -= g.sets[2]; m = 3; } }
+    if (m == 3 && G >= g.sets[3]) {
+        // the workgroups after the last tile: the ranges of dY, dU, dG are complete and nothing here reads the state
+        const int k = (int)blockIdx.x - g.tile_blocks;
+        if (k < update.count && threadIdx.x < 64) scaling_update_wave(update, k, (int)threadIdx.x);
+        return;
+    }
     const GemmParams &p = g.p[m];
     const int vb = (G + g.first[m]) * 8 + x;
     if (vb < p.tiles_m * p.tiles_n) gemm_tile<WB, EPI_STORE, kE5M2, 0, 2>(p, vb, q, smem);
@@ -139,13 +147,13 @@ int gemm_group_split_sets(const GemmArgs &dh, const GemmArgs &dw_split, const Ge
 }
 
 template <int WB>
-static void launch_group(const GroupParams &g, int n, int epilogue, dim3 grid, hipStream_t st) {
-    if (n >= 3) hipLaunchKernelGGL(gemm_group_dx_dw_kernel<WB>, grid, dim3(kThreads), 0, st, g);
+static void launch_group(const GroupParams &g, int n, int epilogue, dim3 grid, const ScalingUpdate &update, hipStream_t st) {
+    if (n >= 3) hipLaunchKernelGGL(gemm_group_dx_dw_kernel<WB>, dim3(grid.x + (unsigned)update.count), dim3(kThreads), 0, st, g, update);
     else if (epilogue == EPI_SWIGLU_BWD) hipLaunchKernelGGL((gemm_group_dh_dw3_kernel<WB, EPI_SWIGLU_BWD>), grid, dim3(kThreads), 0, st, g);
     else hipLaunchKernelGGL((gemm_group_dh_dw3_kernel<WB, EPI_SWIGLU_BWD_Q>), grid, dim3(kThreads), 0, st, g);
 }
 
-bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipStream_t st) {
+bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipStream_t st, const ScalingUpdate &update) {
     if (!gemm_group_ok(list, n)) return false;
     GroupParams g;
     int total = 0;
@@ -180,8 +188,9 @@ bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipSt
     if (total == 0) return true;
     const dim3 grid((unsigned)total * set_workgroups(wb));
     profile_before(n == 2 ? 16 : 17, st, flops);
-    if (wb == 4) launch_group<4>(g, n, list[0]->epilogue, grid, st);
-    else launch_group<2>(g, n, list[0]->epilogue, grid, st);
+    g.tile_blocks = (int)grid.x;
+    if (wb == 4) launch_group<4>(g, n, list[0]->epilogue, grid, update, st);
+    else launch_group<2>(g, n, list[0]->epilogue, grid, update, st);
     profile_after(st);
     return true;
 }

@@ -524,7 +524,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     // ---- epilogue: per-wave LDS patch, one 32 x WN slab (mb) at a time
     // (In the two-product form the loop above is executed twice; the compiler would compute the epilogue's lane
     // arithmetic before it and spill it across.  The empty statement makes the lane id opaque from here on.)
-    if (TWO) asm volatile("" : "+v"(l));
+    if (TWO || (WB == 4 && !kBwd)) asm volatile("" : "+v"(l));
     auto stage_slab = [&](int mb) {
 #pragma unroll
         for (int nb = 0; nb < WB; ++nb)

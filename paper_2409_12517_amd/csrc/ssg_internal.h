@@ -11,6 +11,10 @@ enum SrcKind { SRC_BF16 = 0, SRC_F32 = 1, SRC_SWIGLU = 2 };
 
 // ---- elementwise / reduction passes (ssg_quant.hip) -------------------------
 void launch_fill_u32(uint32_t *p, size_t n, uint32_t value, hipStream_t st);
+// The range of a tensor of n > 0 elements and the scale it gives (scale_out may be null).  scratch: n bytes at least, at
+// most 4 KB of them are written.
+void launch_range_scale(const void *src, SrcKind kind, size_t n, uint32_t *scratch, int fmt, int pow2, float *amax_out,
+                        float *scale_out, hipStream_t st);
 // up to two runs of words that a kernel zeroes on the side for the kernels after it
 struct ZeroWords {
     uint32_t *p[2] = {nullptr, nullptr};
@@ -55,20 +59,37 @@ void launch_cast_batch(const CastArgs *list, int n, const ZeroWords &zero, hipSt
 // given; one format), in one launch for small tensors, else a range and a cast launch.  Returns how many packed words of
 // each range_words hold its range afterwards.
 int launch_quantize_batch(CastArgs *list, int n, const ZeroWords &zero, hipStream_t st);
-// the smooth cast of h (from bf16 U, G) and the fold + cast of w3 in one launch (falls back to two for any other pair)
-void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, hipStream_t st);
-
 // camax_bits[c] = max_r |v[r,c]| as float bits (zeroed by the caller).
 void launch_col_amax(const void *src, const void *src2, SrcKind kind, int64_t rows, int64_t cols,
                      uint32_t *camax_bits, hipStream_t st);
 
+// The ranges of a call, to be entered into the history of delayed scaling
+struct ScalingUpdate {
+    uint32_t *slots[3] = {nullptr, nullptr, nullptr};   // slotted range words of the call just made (cleared afterwards),
+    int range_count[3] = {0, 0, 0};                     // or this many packed words
+    int tensor[3] = {0, 0, 0};
+    int fmt[3] = {0, 0, 0};
+    int count = 0;
+    int pow2 = 0;
+    uint32_t *state = nullptr;
+};
+
 // Per-channel factors from the per-channel maxima (Section 4.4) and the range
 // of s^-1 * w3 for the folded weight.  smooth = 0: one factor for all channels.
-//   hmax_bits: scratch for the plain mode (zeroed by the caller); receives the tensor's range
-//   h_scale_given: plain mode only, optional device scalar: the scale of h as the caller gives it
-void launch_channel_factors(const float *h_camax, const float *w3_camax, int64_t f, int smooth,
-                            float *s, float *sinv, uint32_t *amax_w3s_bits, uint32_t *hmax_bits,
-                            const float *h_scale_given, hipStream_t st);
+struct ChannelFactors {
+    const float *h_camax = nullptr, *w3_camax = nullptr;
+    int64_t f = 0;
+    int smooth = 1;
+    float *s = nullptr, *sinv = nullptr;
+    uint32_t *amax_w3s_bits = nullptr;      // zeroed by the caller
+    uint32_t *hmax_bits = nullptr;          // plain mode: scratch, zeroed by the caller; receives the tensor's range
+    const float *h_scale_given = nullptr;   // plain mode only, optional device scalar: the scale of h as the caller gives it
+    ScalingUpdate update;                   // optional (count > 0): entered into the history by the same launch
+};
+void launch_channel_factors(const ChannelFactors &c, hipStream_t st);
+// the factors, then the smooth cast of h (from bf16 U, G) and the fold + cast of w3 in one launch (two for any other pair);
+// in one launch altogether for few channels
+void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, const ChannelFactors &fac, hipStream_t st);
 
 // amax_bits = max_i fl32(w3_camax[i] * sinv[i]) as float bits (zeroed by the caller).
 void launch_fold_range(const float *w3_camax, const float *sinv, int64_t f, uint32_t *amax_bits, hipStream_t st);
@@ -154,14 +175,15 @@ int gemm_profile_tag(const GemmArgs &a);
 //   { dH (EPI_SWIGLU_BWD or _Q), weight gradient (EPI_STORE, layout 2, A E5M2) }
 //   { input gradient as one launch (part = 3), one to three weight gradients }
 // gemm_group_ok tells whether `list` is one of them with every member valid; launch_gemm_group returns false
-// (nothing launched) otherwise.  Timing tags: 16 and 17.
+// (nothing launched) otherwise.  Timing tags: 16 and 17.  `update` (second group only; count > 0): workgroups at the end
+// of the grid enter these ranges into the history of delayed scaling.
 // split_sets >= 0 splits the LAST member (workgroups come in sets of 8 tiles, gemm_tile_sets of them per GEMM): the
 // two-member group runs its sets [0, split_sets), the other group the rest, so that one weight gradient can be
 // shared out between the two launches; split_sets < 0: every member whole.
 // gemm_group_split_sets picks that split for {dh, dw_split} followed by {second..., rest of dw_split} on `units`
 // compute units, from a replay of the in-order dispatch with per-tile times estimated from K steps and epilogues.
 bool gemm_group_ok(const GemmArgs *const *list, int n);
-bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipStream_t st);
+bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipStream_t st, const ScalingUpdate &update = {});
 int gemm_tile_sets(const GemmArgs &a);
 int gemm_group_split_sets(const GemmArgs &dh, const GemmArgs &dw_split, const GemmArgs *const *second, int n_second, int units);
 
@@ -181,16 +203,8 @@ constexpr int kTagAmax = 40, kTagCast = 41, kTagCastSwiglu = 42, kTagCastColscal
 constexpr int kScalingTensors = 6, kScalingHistory = 16, kScalingStride = 32;
 constexpr size_t kScalingHeaderWords = 256;
 constexpr size_t kScalingWords = kScalingHeaderWords + 4 * kAmaxSlotWords;
-struct ScalingUpdate {
-    uint32_t *slots[3] = {nullptr, nullptr, nullptr};   // slotted range words of the call just made (cleared afterwards),
-    int range_count[3] = {0, 0, 0};                     // or this many packed words
-    int tensor[3] = {0, 0, 0};
-    int fmt[3] = {0, 0, 0};
-    int count = 0;
-    int pow2 = 0;
-};
 void launch_scaling_init(uint32_t *state, hipStream_t st);
-void launch_scaling_update(uint32_t *state, const ScalingUpdate &u, hipStream_t st);
+void launch_scaling_update(const ScalingUpdate &u, hipStream_t st);
 
 // ---- Adam with FP8 moments (ssg_adam.hip) ---------------------------------------
 struct AdamArgs {

@@ -10,6 +10,7 @@
 #include "ssg_col_range.h"
 #include "ssg_device.h"
 #include "ssg_internal.h"
+#include "ssg_scaling.h"
 
 namespace ssg {
 
@@ -83,19 +84,14 @@ struct LoadSwiglu {          // h = u * Swish(g) from stored bf16 U, G
 };
 
 // ------------------------------------------------------------------ amax
-// the largest of words 4t .. 4t+3 of `count` packed range words (the array itself is longer)
-__device__ __forceinline__ uint32_t range_word_max(const uint32_t *words, int count, int t) {
-    if (4 * t >= count) return 0u;
-    const uint4 q = *reinterpret_cast<const uint4 *>(words + 4 * t);
-    uint32_t m = q.x;
-    if (4 * t + 1 < count) m = m > q.y ? m : q.y;
-    if (4 * t + 2 < count) m = m > q.z ? m : q.z;
-    if (4 * t + 3 < count) m = m > q.w ? m : q.w;
-    return m;
+// Into one word from many workgroups: atomics on one address serialise (about 12 ns each), so those that cannot raise the
+// maximum any more look first.
+__device__ __forceinline__ void fold_max(uint32_t *word, uint32_t v) {
+    if (v > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, v);
 }
 
-template <class Loader>
-__global__ void __launch_bounds__(256) amax_kernel(Loader ld, size_t n8, uint32_t *amax_bits, int slots) {
+template <class Loader, bool PACKED>
+__global__ void __launch_bounds__(256) amax_kernel(Loader ld, size_t n8, uint32_t *amax_bits) {
     uint32_t m = 0;
     // work is cut into units of 2048 chunks (32 KB of bf16): 8 independent 16-byte loads per lane,
     // 4 KB apart; workgroup b takes units b, b + gridDim.x, ... (the launch picks gridDim.x so that
@@ -128,7 +124,8 @@ __global__ void __launch_bounds__(256) amax_kernel(Loader ld, size_t n8, uint32_
     if (threadIdx.x == 0) {
         uint32_t r = part[0];
         for (int w = 1; w < 4; ++w) r = r > part[w] ? r : part[w];
-        if (r) atomicMax(amax_bits + (blockIdx.x % slots) * kAmaxSlotStride, r);
+        if (PACKED) amax_bits[blockIdx.x] = r;
+        else fold_max(amax_bits, r);
     }
 }
 
@@ -177,7 +174,8 @@ amax_bf16_kernel(const AmaxBatch batch, int slots) {
         for (int w = 1; w < 4; ++w) r = r > part[w] ? r : part[w];
         r = r > part[0] ? r : part[0];
         if (PACKED) amax_bits[blockIdx.x] = r;
-        else if (r) atomicMax(amax_bits + (blockIdx.x % slots) * kAmaxSlotStride, r);
+        else if (slots > 1) { if (r) atomicMax(amax_bits + (blockIdx.x % slots) * kAmaxSlotStride, r); }
+        else fold_max(amax_bits, r);
     }
 }
 
@@ -206,6 +204,12 @@ static int launch_amax_batch(const CastArgs *list, int count, const ZeroWords &z
     return (int)blocks;
 }
 
+// grid of the fp32 pass: units of 2048 pieces of 8, the same number of them for every workgroup
+static unsigned amax_f32_blocks(size_t n8, size_t cap) {
+    const size_t units = (n8 + 2047) / 2048, per_block = (units + cap - 1) / cap;
+    return (unsigned)((units + per_block - 1) / per_block);
+}
+
 void launch_amax(const void *src, SrcKind kind, size_t n, uint32_t *amax_bits, int slots, hipStream_t st) {
     size_t n8 = n / 8;      // n is a multiple of 16 at every call site (rows, cols multiples of 16)
     if (n8 == 0) return;
@@ -216,13 +220,47 @@ void launch_amax(const void *src, SrcKind kind, size_t n, uint32_t *amax_bits, i
         batch.zero = ZeroWords{};
         hipLaunchKernelGGL(amax_bf16_kernel<false>, dim3(amax_blocks(n8)), dim3(256), 0, st, batch, slots);
     } else {
-        const size_t units = (n8 + 2047) / 2048;
-        const size_t cap = slots > 1 ? 2048 : 512;
-        const size_t per_block = (units + cap - 1) / cap;               // units per workgroup, the same for all
-        unsigned blocks = (unsigned)((units + per_block - 1) / per_block);
-        hipLaunchKernelGGL(amax_kernel<LoadF32>, dim3(blocks), dim3(256), 0, st,
-                           LoadF32{(const float *)src}, n8, amax_bits, slots);
+        // (one word: the fp32 form is used by the public entry points only)
+        hipLaunchKernelGGL((amax_kernel<LoadF32, false>), dim3(amax_f32_blocks(n8, 512)), dim3(256), 0, st,
+                           LoadF32{(const float *)src}, n8, amax_bits);
     }
+    profile_after(st);
+}
+
+// The largest of `count` packed range words, and the scale it gives.
+__global__ void __launch_bounds__(256)
+range_scale_kernel(const uint32_t *__restrict__ words, int count, float fmax, int pow2, float *amax_out, float *scale_out) {
+    __shared__ uint32_t part[4];
+    const uint32_t r = wave_max_u32(range_word_max(words, count, threadIdx.x));
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = r;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t m = part[0];
+        for (int w = 1; w < 4; ++w) m = m > part[w] ? m : part[w];
+        *amax_out = __uint_as_float(m);
+        if (scale_out) *scale_out = scale_from_amax(__uint_as_float(m), fmax, pow2);
+    }
+}
+
+void launch_range_scale(const void *src, SrcKind kind, size_t n, uint32_t *scratch, int fmt, int pow2, float *amax_out,
+                        float *scale_out, hipStream_t st) {
+    const size_t n8 = n / 8;
+    unsigned blocks;
+    profile_before(kTagAmax, st, (kind == SRC_BF16 ? 2.0 : 4.0) * (double)n);
+    if (kind == SRC_BF16) {
+        AmaxBatch batch;
+        for (int i = 0; i < 3; ++i) { batch.src[i] = (const ssg_u32x4 *)src; batch.n16[i] = n8; batch.amax_bits[i] = scratch; }
+        batch.zero = ZeroWords{};
+        blocks = amax_blocks(n8);
+        hipLaunchKernelGGL(amax_bf16_kernel<true>, dim3(blocks), dim3(256), 0, st, batch, 0);
+    } else {
+        blocks = amax_f32_blocks(n8, kAmaxBlocks);
+        hipLaunchKernelGGL((amax_kernel<LoadF32, true>), dim3(blocks), dim3(256), 0, st, LoadF32{(const float *)src}, n8, scratch);
+    }
+    profile_after(st);
+    profile_before(kTagSmall, st, 4.0 * blocks);
+    hipLaunchKernelGGL(range_scale_kernel, dim3(1), dim3(256), 0, st, scratch, (int)blocks,
+                       fmt == kE4M3 ? Fp8Traits<kE4M3>::fmax : Fp8Traits<kE5M2>::fmax, pow2, amax_out, scale_out);
     profile_after(st);
 }
 
@@ -273,8 +311,12 @@ struct CastBatch {
     ZeroWords zero;
 };
 // The work of one workgroup: tile (bx, by) of item `it`.
-template <class Loader, int FMT, bool COLSCALE, bool TRANSPOSED, bool RECORD = false, bool COUNT = false>
-__device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int pow2, const unsigned bx, const unsigned by) {
+// FACT: the per-column factor is formed here from the per-channel maxima of h that col_scale points to: s_i (kFactS) or
+// s_i^-1 (kFactSinv), and the per-tensor scale, if any, is given as `sigma_known`.
+enum { kFactNone = 0, kFactS = 1, kFactSinv = 2 };
+template <class Loader, int FMT, bool COLSCALE, bool TRANSPOSED, bool RECORD = false, bool COUNT = false, int FACT = kFactNone>
+__device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int pow2, const unsigned bx, const unsigned by,
+                                           const float sigma_known = 1.0f) {
     const Loader ld = it.ld;
     const int64_t rows = it.rows, cols = it.cols;
     if ((int64_t)bx * kTile >= cols || (int64_t)by * kTile >= rows) return;
@@ -290,8 +332,8 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
     __shared__ uint32_t tile[TRANSPOSED ? kTile * kTPitchWords : 1];
     uint32_t n_sat = 0, n_flush = 0;
 
-    float sigma = 1.0f;
-    bool tensor_scale = false;
+    float sigma = sigma_known;
+    bool tensor_scale = FACT == kFactSinv;
     if (scale_in) { sigma = *scale_in; tensor_scale = true; }
     else if (amax) {
         // maximum over the words of the range pass, or over the slots the producers folded into: lane i of every wave
@@ -333,6 +375,10 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
         float4 b = *reinterpret_cast<const float4 *>(col_scale + col + 4);
         cs[0] = a.x; cs[1] = a.y; cs[2] = a.z; cs[3] = a.w;
         cs[4] = b.x; cs[5] = b.y; cs[6] = b.z; cs[7] = b.w;
+        if (FACT != kFactNone) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) cs[i] = FACT == kFactS ? smooth_factor(cs[i]) : smooth_factor_inv(cs[i]);
+        }
     }
 
     ssg_i16x2 seen2 = {0x7f, 0x7f};                     // RECORD: largest (|bf16 pattern| + 0x7f) this lane met, per half
@@ -462,6 +508,44 @@ __global__ void __launch_bounds__(256)
 cast_h_w3_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3, const int pow2) {
     if (blockIdx.z == 0) cast_block<LoadSwiglu, kE4M3, true, false, false, COUNT>(h, pow2, blockIdx.x, blockIdx.y);
     else cast_block<LoadBf16, kE4M3, true, false, false, false>(w3, pow2, blockIdx.x, blockIdx.y);
+}
+
+// The same with the channel factors formed on the way (Smooth-SwiGLU): h.col_scale and w3.col_scale are the per-channel
+// maxima of h, f.w3_camax those of W3.  Every workgroup of the second cast takes the maximum of s^-1 * w3's range over all
+// channels itself, which saves the launch of channel_factors_kernel (4.7 us) and costs each of them a read of 8 f bytes.
+struct InlineFactors {
+    const float *h_camax, *w3_camax;
+    int64_t f;
+    float *s, *sinv, *amax_w3s;
+};
+template <bool COUNT>
+__global__ void __launch_bounds__(256)
+cast_h_w3_factors_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3, const int pow2, const InlineFactors fac) {
+    if (blockIdx.z == 0) {
+        const int64_t col = (int64_t)blockIdx.x * kTile + threadIdx.x;
+        if (blockIdx.y == 0 && threadIdx.x < kTile && col < fac.f) {
+            const float a = fac.h_camax[col];
+            fac.s[col] = smooth_factor(a);
+            fac.sinv[col] = smooth_factor_inv(a);
+        }
+        cast_block<LoadSwiglu, kE4M3, true, false, false, COUNT, kFactS>(h, pow2, blockIdx.x, blockIdx.y);
+        return;
+    }
+    if ((int64_t)blockIdx.x * kTile >= w3.cols || (int64_t)blockIdx.y * kTile >= w3.rows) return;
+    uint32_t m = 0;
+    for (int64_t i = threadIdx.x; i < fac.f; i += 256) {
+        const uint32_t b = abs_bits_ignore_nan(__fmul_rn(fac.w3_camax[i], smooth_factor_inv(fac.h_camax[i])));
+        m = m > b ? m : b;
+    }
+    __shared__ uint32_t wave_m[4];
+    m = wave_max_u32(m);
+    if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = wave_max_u32(wave_m[threadIdx.x & 3]);
+    const float amax = __uint_as_float(m);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *fac.amax_w3s = amax;
+    cast_block<LoadBf16, kE4M3, true, false, false, false, kFactSinv>(w3, pow2, blockIdx.x, blockIdx.y,
+                                                                      scale_from_amax(amax, Fp8Traits<kE4M3>::fmax, pow2));
 }
 
 template <class Loader>
@@ -638,18 +722,29 @@ bool cast_h_w3_ok(const CastArgs &h, const CastArgs &w3) {
            w3.cols > 0;
 }
 
-void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, hipStream_t st) {
-    if (!cast_h_w3_ok(h, w3)) {             // not the pair this launch is built for: one after the other
+void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, const ChannelFactors &fac, hipStream_t st) {
+    const bool pair = cast_h_w3_ok(h, w3);
+    // the line: 8 f bytes read by every workgroup of the w3 cast against a launch (f = 688: 64.5 us a step with the launch,
+    // 62.6 without; f = 2736: 126 either way)
+    const bool inline_factors = pair && fac.smooth && fac.update.count == 0 && fac.f <= 1024;
+    if (!inline_factors) launch_channel_factors(fac, st);
+    if (!pair) {                            // not the pair this launch is built for: one after the other
         launch_cast(h, st);
         launch_cast(w3, st);
         return;
     }
-    const CastItem<LoadSwiglu> hi = cast_item<LoadSwiglu>(LoadSwiglu{(const uint16_t *)h.src, (const uint16_t *)h.src2}, h);
-    const CastItem<LoadBf16> wi = cast_item<LoadBf16>(LoadBf16{(const uint16_t *)w3.src}, w3);
+    CastItem<LoadSwiglu> hi = cast_item<LoadSwiglu>(LoadSwiglu{(const uint16_t *)h.src, (const uint16_t *)h.src2}, h);
+    CastItem<LoadBf16> wi = cast_item<LoadBf16>(LoadBf16{(const uint16_t *)w3.src}, w3);
     const int64_t rows = h.rows > w3.rows ? h.rows : w3.rows, cols = h.cols > w3.cols ? h.cols : w3.cols;
     dim3 grid((unsigned)((cols + kTile - 1) / kTile), (unsigned)((rows + kTile - 1) / kTile), 2u);
     profile_before(kTagCastHW3, st, cast_bytes(h) + cast_bytes(w3));
-    if (h.counters) hipLaunchKernelGGL(cast_h_w3_kernel<true>, grid, dim3(256), 0, st, hi, wi, w3.pow2);
+    if (inline_factors) {
+        hi.col_scale = wi.col_scale = fac.h_camax;
+        wi.amax = nullptr;
+        const InlineFactors in{fac.h_camax, fac.w3_camax, fac.f, fac.s, fac.sinv, reinterpret_cast<float *>(fac.amax_w3s_bits)};
+        if (h.counters) hipLaunchKernelGGL(cast_h_w3_factors_kernel<true>, grid, dim3(256), 0, st, hi, wi, w3.pow2, in);
+        else hipLaunchKernelGGL(cast_h_w3_factors_kernel<false>, grid, dim3(256), 0, st, hi, wi, w3.pow2, in);
+    } else if (h.counters) hipLaunchKernelGGL(cast_h_w3_kernel<true>, grid, dim3(256), 0, st, hi, wi, w3.pow2);
     else hipLaunchKernelGGL(cast_h_w3_kernel<false>, grid, dim3(256), 0, st, hi, wi, w3.pow2);
     profile_after(st);
 }
@@ -738,18 +833,25 @@ void launch_col_amax(const void *src, const void *src2, SrcKind kind, int64_t ro
 // Smooth-SwiGLU (Section 4.4): s_i = fl32(448 / a_i), sinv_i = fl32(a_i / 448),
 // both 1 for an all-zero channel.  The range of s^-1 * w3 needs no pass over
 // W3: rounding is monotone, so max_j fl32(|w_ji| * sinv_i) = fl32(max_j |w_ji| * sinv_i).
+// Workgroups after the `blocks` of the factors enter the call's ranges into the history of delayed scaling, a tensor
+// each: they are complete by now and no later kernel of the call reads the state.
 __global__ void __launch_bounds__(256)
 channel_factors_kernel(const float *__restrict__ h_camax, const float *__restrict__ w3_camax, int64_t f,
                        int smooth, const uint32_t *__restrict__ hmax_bits, const float *__restrict__ h_scale_given,
-                       float *__restrict__ s, float *__restrict__ sinv, uint32_t *__restrict__ amax_w3s_bits) {
+                       float *__restrict__ s, float *__restrict__ sinv, uint32_t *__restrict__ amax_w3s_bits,
+                       const unsigned blocks, const ScalingUpdate update) {
+    if (blockIdx.x >= blocks) {
+        if (threadIdx.x < 64) scaling_update_wave(update, (int)(blockIdx.x - blocks), (int)threadIdx.x);
+        return;
+    }
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     uint32_t wbits = 0;
     if (i < f) {
         float si, sv;
         if (smooth) {
             const float a = h_camax[i];
-            si = scale_from_amax(a, 448.0f, 0);
-            sv = a > 0.0f ? __fdiv_rn(a, 448.0f) : 1.0f;
+            si = smooth_factor(a);
+            sv = smooth_factor_inv(a);
         } else {
             // plain block: one scale for the whole tensor, from its own range or as the caller gives it
             si = h_scale_given ? *h_scale_given : scale_from_amax(__uint_as_float(*hmax_bits), 448.0f, 0);
@@ -771,18 +873,16 @@ vec_max_kernel(const float *__restrict__ v, int64_t n, uint32_t *__restrict__ ou
     if ((threadIdx.x & 63) == 0 && b) atomicMax(out_bits, b);
 }
 
-void launch_channel_factors(const float *h_camax, const float *w3_camax, int64_t f, int smooth, float *s,
-                            float *sinv, uint32_t *amax_w3s_bits, uint32_t *hmax_bits, const float *h_scale_given,
-                            hipStream_t st) {
-    const unsigned blocks = (unsigned)((f + 255) / 256);
-    if (!smooth) {
-        profile_before(kTagSmall, st, 4.0 * (double)f);
-        hipLaunchKernelGGL(vec_max_kernel, dim3(blocks), dim3(256), 0, st, h_camax, f, hmax_bits);
+void launch_channel_factors(const ChannelFactors &c, hipStream_t st) {
+    const unsigned blocks = (unsigned)((c.f + 255) / 256);
+    if (!c.smooth) {
+        profile_before(kTagSmall, st, 4.0 * (double)c.f);
+        hipLaunchKernelGGL(vec_max_kernel, dim3(blocks), dim3(256), 0, st, c.h_camax, c.f, c.hmax_bits);
         profile_after(st);
     }
-    profile_before(kTagSmall, st, 16.0 * (double)f);
-    hipLaunchKernelGGL(channel_factors_kernel, dim3(blocks), dim3(256), 0, st, h_camax, w3_camax, f, smooth,
-                       hmax_bits, smooth ? nullptr : h_scale_given, s, sinv, amax_w3s_bits);
+    profile_before(kTagSmall, st, 16.0 * (double)c.f);
+    hipLaunchKernelGGL(channel_factors_kernel, dim3(blocks + (unsigned)c.update.count), dim3(256), 0, st, c.h_camax, c.w3_camax, c.f,
+                       c.smooth, c.hmax_bits, c.smooth ? nullptr : c.h_scale_given, c.s, c.sinv, c.amax_w3s_bits, blocks, c.update);
     profile_after(st);
 }
 
@@ -937,40 +1037,13 @@ void launch_scaling_init(uint32_t *state, hipStream_t st) {
                        kScalingWords);
 }
 
-// One wave per tensor: the range of the call just made (maximum over the packed words of the range pass, or over its
-// slots, which are cleared for the next call) replaces the oldest history entry; the next call's scale is fmax over the
-// largest entry (Section 2, delayed scaling).
-__global__ void __launch_bounds__(64) scaling_update_kernel(uint32_t *state, ScalingUpdate u) {
-    const int k = blockIdx.x, lane = threadIdx.x;
-    uint32_t *slots = u.slots[k];
-    uint32_t seen = 0u;
-    if (u.range_count[k]) {
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t w = range_word_max(slots, u.range_count[k], q * 64 + lane);
-            seen = seen > w ? seen : w;
-        }
-    } else {
-        seen = slots[lane * kAmaxSlotStride];
-        slots[lane * kAmaxSlotStride] = 0u;
-    }
-    seen = wave_max_u32(seen);
-    uint32_t *w = state + (size_t)u.tensor[k] * kScalingStride;
-    const uint32_t pos = w[1] % kScalingHistory;
-    uint32_t h = lane < kScalingHistory ? w[8 + lane] : 0u;
-    if (lane == (int)pos) h = seen;
-    const float largest = __uint_as_float(wave_max_u32(h));
-    const float fmax = u.fmt[k] == kE4M3 ? Fp8Traits<kE4M3>::fmax : Fp8Traits<kE5M2>::fmax;
-    if (lane == 0) {
-        w[8 + pos] = seen;
-        w[1] = (pos + 1) % kScalingHistory;
-        w[2] = seen;
-        w[0] = __float_as_uint(scale_from_amax(largest, fmax, u.pow2));
-    }
+__global__ void __launch_bounds__(64) scaling_update_kernel(ScalingUpdate u) {
+    scaling_update_wave(u, (int)blockIdx.x, (int)threadIdx.x);
 }
-void launch_scaling_update(uint32_t *state, const ScalingUpdate &u, hipStream_t st) {
+void launch_scaling_update(const ScalingUpdate &u, hipStream_t st) {
     if (u.count <= 0) return;
     profile_before(kTagSmall, st, 0.0);
-    hipLaunchKernelGGL(scaling_update_kernel, dim3((unsigned)u.count), dim3(64), 0, st, state, u);
+    hipLaunchKernelGGL(scaling_update_kernel, dim3((unsigned)u.count), dim3(64), 0, st, u);
     profile_after(st);
 }
 

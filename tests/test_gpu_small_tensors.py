@@ -58,3 +58,27 @@ def test_garbage_in_the_buffers_changes_nothing(T, d, f, delayed):
         out.append([t.view(torch.uint8).cpu() for t in (blk.y, blk.dx, blk.dW1, blk.dW2, blk.dW3, state[: 6 * 32 * 4])])
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("rows,cols", [(16, 16), (16, 1040), (1024, 1040), (4096, 2064)])
+@pytest.mark.parametrize("src_dtype", [ssg.SSG_BF16, ssg.SSG_F32])
+def test_quantize_with_its_range_words_in_the_result_buffer(rows, cols, src_dtype):
+    """One to 1024 range words, which the range pass leaves in dst; the largest element first, last and in between, and
+    scales rounded to powers of two; GIVEN with a range asked for."""
+    gen = torch.Generator().manual_seed(rows + cols)
+    base = torch.randn(rows, cols, generator=gen).to(torch.bfloat16 if src_dtype == ssg.SSG_BF16 else torch.float32)
+    for at in ((0, 0), (rows - 1, cols - 1), (rows // 2, 7)):
+        v = base.clone()
+        v[at] = -37.5
+        x = gu.dev(v)
+        q, qt = gu.empty_u8(rows, cols), gu.empty_u8(cols, rows)
+        scale, amax = gu.empty_f32(1), gu.empty_f32(1)
+        for rnd, pow2 in ((ssg.SSG_ROUND_EXACT_DIV, False), (ssg.SSG_ROUND_POW2, True)):
+            ssg.ssg_quantize(x, src_dtype, rows, cols, ssg.SSG_E4M3, ssg.SSG_SCALE_CURRENT, rnd, q, qt, scale, amax)
+            ref_q, ref_s, ref_a = quant.quantize_per_tensor(v.float().numpy(), fp8.E4M3, pow2=pow2)
+            assert gu.scalar(amax) == ref_a == np.float32(37.5) and gu.scalar(scale) == ref_s
+            assert np.array_equal(gu.u8(q), ref_q) and np.array_equal(gu.u8(qt), ref_q.T)
+        amax.zero_()
+        ssg.ssg_quantize(x, src_dtype, rows, cols, ssg.SSG_E4M3, ssg.SSG_SCALE_GIVEN, ssg.SSG_ROUND_EXACT_DIV, q, None, scale, amax)
+        assert gu.scalar(amax) == np.float32(37.5) and gu.scalar(scale) == ref_s
+        assert np.array_equal(gu.u8(q), ref_q)
