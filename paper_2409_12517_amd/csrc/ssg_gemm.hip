@@ -21,9 +21,9 @@ struct ColRangeParams {
 template <int WB>
 __global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_swiglu_col_range_kernel(GemmParams p, ColRangeParams r) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB)];
-    const int tiles = p.tiles_m * p.tiles_n, gemm_blocks = (tiles + 7) / 8 * (WB == 4 ? 8 : 32);
+    const int tiles = p.tiles_m * p.tiles_n, gemm_blocks = p.sets * (WB == 4 ? 8 : 32);
     if ((int)blockIdx.x < gemm_blocks) {
-        const int b = (int)blockIdx.x, vb = set_of<WB>(b) * 8 + (b & 7);
+        const int b = (int)blockIdx.x, vb = (p.first_set + set_of<WB>(b)) * 8 + (b & 7);
         if (vb < tiles) gemm_tile<WB, EPI_SWIGLU, kE4M3, 0, 0>(p, vb, quarter_of<WB>(b), smem);
     } else {
         const int b = (int)blockIdx.x - gemm_blocks;
@@ -94,6 +94,16 @@ static int64_t tile_count(const GemmArgs &a, int WB) {
     return ((a.M + edge - 1) / edge) * ((a.N + cols - 1) / cols);
 }
 
+// Estimated time of `tiles` small tiles of one GEMM, each of `cost` microseconds when two share a compute unit.
+static double small_tile_time(int64_t tiles, double cost) {
+    // a tile that has its compute unit to itself is bound by the latency of its loads: 0.44 per K step with a ring of
+    // nine, 0.58 when all compute units are at it; beyond two rounds the tiles drift out of step and the rounds blur
+    if (tiles <= kComputeUnits) return 5.5 + (cost - 5.5) * (tiles <= 160 ? 0.46 : 0.6);
+    if (tiles <= 2 * kComputeUnits) return cost * (0.65 + 0.35 * (double)(tiles - kComputeUnits) / kComputeUnits);
+    const double blurred = std::max(cost, cost * (double)tiles / (2.0 * kComputeUnits));
+    return tiles <= 3 * kComputeUnits ? std::max(blurred, 1.65 * cost) : blurred;
+}
+
 // Estimated time of the GEMMs of `list` in one grid.
 static double grid_time(const GemmArgs *const *list, int n, int WB) {
     double sum = 0.0, longest = 0.0;
@@ -105,15 +115,8 @@ static double grid_time(const GemmArgs *const *list, int n, int WB) {
         sum += cost * (double)t;
         longest = std::max(longest, cost);
     }
-    if (WB == 2) {
-        // a tile that has its compute unit to itself is bound by the latency of its loads: 0.44 per K step with a ring of
-        // nine, 0.58 when all compute units are at it; beyond two rounds the tiles drift out of step and the rounds blur
-        if (tiles <= kComputeUnits) return 5.5 + (longest - 5.5) * (tiles <= 160 ? 0.46 : 0.6);
-        const double blurred = std::max(longest, sum / (2.0 * kComputeUnits));
-        if (n != 1 || tiles > 3 * kComputeUnits) return blurred;
-        if (tiles > 2 * kComputeUnits) return std::max(blurred, 1.65 * longest);
-        return longest * (0.65 + 0.35 * (double)(tiles - kComputeUnits) / kComputeUnits);
-    }
+    if (WB == 2) return n == 1 ? small_tile_time(tiles, longest) : tiles <= kComputeUnits ? small_tile_time(tiles, longest)
+                                                                 : std::max(longest, sum / (2.0 * kComputeUnits));
     // one tile per compute unit: a single GEMM runs in whole rounds, a group's last round is filled by its other members
     const double rounds = (double)((tiles + kComputeUnits - 1) / kComputeUnits);
     return n == 1 ? rounds * longest : std::max(longest, sum / kComputeUnits);
@@ -125,6 +128,22 @@ int gemm_wave_blocks(const GemmArgs *const *list, int n) {
         if (list[i]->part == 3 && !sum_in_large_tile_ok(list[i]->K)) return 2;
     }
     return grid_time(list, n, 2) < grid_time(list, n, 4) ? 2 : 4;
+}
+
+// Sets of large tiles that make whole rounds of the chip when the rest is worth a launch of small tiles of its own (5 us):
+// a last round of large tiles that fills a third of the chip takes as long as a full one.  0: the GEMM stays whole.
+// (gate/up of the inference form at T = 4096, d = 4096, f = 11008, 5.4 rounds: 303 us whole, 288 as 5 rounds and 384 small
+// tiles; at T = 1024, 1.3 rounds: 104 and 99.)  The range pass over w3 in the grid hides in a last round of large tiles
+// but not beside small ones, where its 90 MB take 21 us (T = 4096: 346 us whole, 353 in two; T = 2048, d = 2048, f = 5504,
+// 22 MB, a step: 305 us with all small tiles, 298 in two).
+static int full_round_sets(const GemmArgs &a, int wb, double whole) {
+    if (a.a_fmt == kBF16) return 0;
+    const double range = a.tail_src ? 2.0 * (double)(a.tail_rows * a.tail_cols) / 4.2e6 : 0.0;
+    if (wb == 2) whole += range;
+    const int64_t tiles = tile_count(a, 4), rounds = tiles / kComputeUnits, rest = tiles - rounds * kComputeUnits;
+    if (rounds == 0 || rest == 0) return 0;
+    const double split = (double)rounds * gemm_tile_cost(a, 4) + 5.0 + small_tile_time(4 * rest, gemm_tile_cost(a, 2)) + range;
+    return split < 0.97 * whole ? (int)(rounds * kComputeUnits / 8) : 0;
 }
 
 // The input gradient of a hidden width that is no multiple of 128: in one launch of small tiles together with the
@@ -155,9 +174,14 @@ static void launch_fmt(const GemmParams &p, int a_fmt, unsigned blocks, hipStrea
 }
 
 template <int WB, int UNITS>
-static void launch_gemm_wb(const GemmArgs &a, hipStream_t st) {
-    const GemmParams p = make_gemm_params(a);
-    const unsigned blocks = (unsigned)sets_of(p) * set_workgroups(WB);
+static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream_t st) {
+    GemmParams p = make_gemm_params(a);
+    const int tiles = p.tiles_m * p.tiles_n, hi = std::min((first_set + sets) * 8, tiles);
+    p.first_set = first_set;
+    p.sets = sets;
+    const unsigned blocks = (unsigned)sets * set_workgroups(WB);
+    const bool tail = a.tail_src && hi == tiles;          // the range pass over w3 rides in the last launch of the GEMM
+    profile_before(gemm_profile_tag(a), st, gemm_flops(a) * (double)(hi - first_set * 8) / (double)tiles);
     switch (a.epilogue) {
         case EPI_STORE:
             if (a.a_fmt == kBF16) hipLaunchKernelGGL((gemm_kernel<4, EPI_STORE, kBF16, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
@@ -166,7 +190,7 @@ static void launch_gemm_wb(const GemmArgs &a, hipStream_t st) {
             else launch_fmt<WB, UNITS, EPI_STORE, 0>(p, a.a_fmt, blocks, st);
             break;
         case EPI_SWIGLU:
-            if (a.tail_src) {
+            if (tail) {
                 ColRangeParams r{static_cast<const uint16_t *>(a.tail_src), a.tail_rows, a.tail_cols, a.tail_camax_bits,
                                  col_range_blocks_x(a.tail_cols)};
                 const unsigned extra = (unsigned)(r.blocks_x * col_range_blocks_y(a.tail_rows));
@@ -179,22 +203,29 @@ static void launch_gemm_wb(const GemmArgs &a, hipStream_t st) {
             hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU_Q, kE4M3, 0, 0, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
             break;
     }
+    profile_after(st);
 }
 
 bool launch_gemm(const GemmArgs &a, hipStream_t st) {
     if (!gemm_args_ok(a)) return false;
     if (a.part != 0 || a.epilogue == EPI_SWIGLU_BWD || a.epilogue == EPI_SWIGLU_BWD_Q) return launch_gemm_bwd(a, st);
-    profile_before(gemm_profile_tag(a), st, gemm_flops(a));
     const GemmArgs *one = &a;
-    const int wb = gemm_wave_blocks(&one, 1);
-    if (gemm_skinny_time(a) < grid_time(&one, 1, wb)) launch_gemm_skinny(a, st);
-    else if (wb == 4) launch_gemm_wb<4, 5>(a, st);
+    const int wb = gemm_wave_blocks(&one, 1), all = sets_of(make_gemm_params(a));
+    const double whole = grid_time(&one, 1, wb);
+    if (gemm_skinny_time(a) < whole) {
+        profile_before(gemm_profile_tag(a), st, gemm_flops(a));
+        launch_gemm_skinny(a, st);
+        profile_after(st);
+        return true;
+    }
+    const int full = full_round_sets(a, wb, whole);
+    if (full > 0) launch_gemm_wb<4, 5>(a, 0, full, st);
     // one small tile to a compute unit, so up to 8 large tiles on an XCD of 32: the longer ring, which leaves no room
     // for a second workgroup (M = 528, N = 2048, K = 4096, 80 tiles: 27 us with five units, 21 with nine; 65 large tiles
     // give one XCD a second round: 28 and 34)
-    else if (tile_count(a, 4) <= kComputeUnits / 4) launch_gemm_wb<2, 9>(a, st);
-    else launch_gemm_wb<2, 5>(a, st);
-    profile_after(st);
+    if (wb == 4 && full == 0) launch_gemm_wb<4, 5>(a, 0, all, st);
+    else if (tile_count(a, 4) - 8 * full <= kComputeUnits / 4) launch_gemm_wb<2, 9>(a, full, all - full, st);
+    else launch_gemm_wb<2, 5>(a, full, all - full, st);
     return true;
 }
 

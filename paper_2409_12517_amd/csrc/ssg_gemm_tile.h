@@ -60,6 +60,7 @@ struct GemmParams {
     uint32_t *camax_bits, *amax_bits, *amax_bits2;
     int c_f32;
     int tiles_m, tiles_n;       // in tiles of 256 x 256, also where the small tiles compute
+    int first_set, sets;        // single launches: the sets of 8 large tiles this launch computes
     float *tmp;          // fp32 [M, N] scratch for the two-launch form of a sum of two products (may be null)
     const float *add;    // gemm_kernel<.., ADD>: fp32 [M, N] added before the store
     const float *q_scale, *q_scale2;        // EPI_SWIGLU_BWD_Q: scales of dU, dG
@@ -782,7 +783,7 @@ inline unsigned set_workgroups(int WB) { return WB == 4 ? 8u : 32u; }
 template <int WB, int EPI, int AFMT, int PART = 0, int LAY = 0, int UNITS = 5>
 __global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB, UNITS)];
-    const int b = (int)blockIdx.x, vb = set_of<WB>(b) * 8 + (b & 7);
+    const int b = (int)blockIdx.x, vb = (p.first_set + set_of<WB>(b)) * 8 + (b & 7);
     if (vb < p.tiles_m * p.tiles_n) gemm_tile<WB, EPI, AFMT, PART, LAY, UNITS>(p, vb, quarter_of<WB>(b), smem);
 }
 
@@ -816,6 +817,8 @@ inline GemmParams make_gemm_params(const GemmArgs &a) {
     p.tiles_m = (int)((a.M + edge - 1) / edge);
     const int n_per_tile = (a.epilogue == EPI_SWIGLU || a.epilogue == EPI_SWIGLU_Q) ? edge / 2 : edge;
     p.tiles_n = (int)((a.N + n_per_tile - 1) / n_per_tile);
+    p.first_set = 0;
+    p.sets = sets_of(p);
     return p;
 }
 

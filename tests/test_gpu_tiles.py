@@ -17,8 +17,8 @@ import test_gpu_mlp as tm  # noqa: E402
 
 SMALL = [(128, 128, 128), (16, 144, 272), (144, 112, 16), (272, 128, 400), (112, 400, 256)]
 # 256 tiles of 256 x 256, one for every compute unit: the large tile, with a ragged last K step (1168 = 9 * 128 + 16),
-# a short last row and column of tiles
-LARGE = [(4048, 4080, 1168)]
+# a short last row and column of tiles; and 272 of them, one whole round and the rest in small tiles
+LARGE = [(4048, 4080, 1168), (4080, 4336, 1040)]
 
 
 @pytest.mark.parametrize("M,N,K", SMALL + LARGE)
@@ -121,3 +121,9 @@ def test_few_rows_of_the_inference_form(T_inf):
     product next to zero, 2^-9 apart in code, now and then crosses more than one step when its sum rounds otherwise.)"""
     inp = synth.make_inputs(64, 272, 2512, seed=59)
     ti.check(ti.Infer(inp, T_inf=T_inf, seed_inf=8), tm._np_inputs(inp))
+
+
+def test_inference_form_in_whole_rounds_and_a_rest():
+    """9 x 33 tiles of 256 rows by 128 channels: 256 of them in large tiles, the other 41 in small ones."""
+    inp = synth.make_inputs(64, 272, 4112, seed=61)
+    ti.check(ti.Infer(inp, T_inf=2064, seed_inf=9), tm._np_inputs(inp))
