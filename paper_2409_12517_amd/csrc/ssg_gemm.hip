@@ -104,12 +104,12 @@ static double small_tile_time(int64_t tiles, double cost) {
     return tiles <= 3 * kComputeUnits ? std::max(blurred, 1.65 * cost) : blurred;
 }
 
-// Estimated time of the GEMMs of `list` in one grid.
-static double grid_time(const GemmArgs *const *list, int n, int WB) {
+// Estimated time of the GEMMs of `list` in one grid; of the last one, the share `last` of its tiles.
+static double grid_time(const GemmArgs *const *list, int n, int WB, double last = 1.0) {
     double sum = 0.0, longest = 0.0;
     int64_t tiles = 0;
     for (int i = 0; i < n; ++i) {
-        const int64_t t = tile_count(*list[i], WB);
+        const int64_t t = (int64_t)((double)tile_count(*list[i], WB) * (i == n - 1 ? last : 1.0));
         const double cost = gemm_tile_cost(*list[i], WB);
         tiles += t;
         sum += cost * (double)t;
@@ -119,15 +119,18 @@ static double grid_time(const GemmArgs *const *list, int n, int WB) {
                                                                  : std::max(longest, sum / (2.0 * kComputeUnits));
     // one tile per compute unit: a single GEMM runs in whole rounds, a group's last round is filled by its other members
     const double rounds = (double)((tiles + kComputeUnits - 1) / kComputeUnits);
-    return n == 1 ? rounds * longest : std::max(longest, sum / kComputeUnits);
+    if (n == 1) return rounds * longest;
+    // where a few long tiles decide (dX of a short batch: 64 tiles of 172 K steps), the members beside them slow them
+    // down (T = 1024, d = 4096, f = 11008: 305 us for 258 estimated; the step 605 us, 574 with small tiles)
+    return std::max(1.15 * longest, sum / kComputeUnits);
 }
 
-int gemm_wave_blocks(const GemmArgs *const *list, int n) {
+int gemm_wave_blocks(const GemmArgs *const *list, int n, double last) {
     for (int i = 0; i < n; ++i) {
         if (list[i]->a_fmt == kBF16 || list[i]->part == 1 || list[i]->part == 2) return 4;      // not built in the small tile
         if (list[i]->part == 3 && !sum_in_large_tile_ok(list[i]->K)) return 2;
     }
-    return grid_time(list, n, 2) < grid_time(list, n, 4) ? 2 : 4;
+    return grid_time(list, n, 2, last) < grid_time(list, n, 4, last) ? 2 : 4;
 }
 
 // Sets of large tiles that make whole rounds of the chip when the rest is worth a launch of small tiles of its own (5 us):

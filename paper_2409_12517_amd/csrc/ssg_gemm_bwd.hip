@@ -158,7 +158,6 @@ bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipSt
     GroupParams g;
     int total = 0;
     double flops = 0.0;
-    const int wb = gemm_wave_blocks(list, n);
     for (int i = 0; i < 4; ++i) {
         g.p[i] = make_gemm_params(*list[i < n ? i : 0]);
         g.sets[i] = i < n ? sets_of(g.p[i]) : 0;
@@ -171,6 +170,7 @@ bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipSt
         if (n == 2) g.sets[1] = cut;
         else { g.first[n - 1] = cut; g.sets[n - 1] = all - cut; }
     }
+    const int wb = gemm_wave_blocks(list, n, (double)g.sets[n - 1] / (double)sets_of(g.p[n - 1]));
     // The fp32 weight gradients of the second launch go out through non-temporal stores: nothing reads them before
     // the optimizer, and kept out of the caches they leave in place what the passes after this launch read (measured
     // at the Llama2-7B shape: -10 us per step, in the launches that follow, not in this one).  In the first launch,

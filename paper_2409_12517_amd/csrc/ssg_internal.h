@@ -166,7 +166,8 @@ void launch_gemm_skinny(const GemmArgs &a, hipStream_t st);
 bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st);       // the backward forms (called by launch_gemm)
 constexpr int kComputeUnits = 256;
 // Tile of a launch that runs these GEMMs in one grid: 32 x 32 blocks per wave and direction, 4 (256 x 256 tiles) or 2 (128 x 128)
-int gemm_wave_blocks(const GemmArgs *const *list, int n);
+// (of the last one: the share `last` of its tiles)
+int gemm_wave_blocks(const GemmArgs *const *list, int n, double last = 1.0);
 double gemm_tile_cost(const GemmArgs &a, int WB);               // estimated microseconds of one tile
 // whether the input gradient runs as part = 3 (in one grid with weight gradients like `dw`) or as parts 1 and 2
 bool gemm_sum_in_one_launch(const GemmArgs &dx, const GemmArgs &dw);
