@@ -27,14 +27,15 @@ if ROOT not in sys.path:
 
 PEAK_FP8_TFLOPS = 5000.0          # MI355X dense FP8 MFMA peak (published: 5.0 PFLOP/s)
 METRIC = "FP8 Smooth-SwiGLU MLP fwd+bwd TFLOP/s (7B shape), % of FP8 MFMA peak"
-# tag of ssg_profile_read -> kernel symbol as rocprofv3 prints it.  gemm_kernel<epilogue, A format, part, layout>:
+# tag of ssg_profile_read -> kernel symbol as rocprofv3 prints it, at the headline shape, which runs in the large tile.
+# gemm_kernel<blocks per wave (4 = 256 x 256 tile, 2 = 128 x 128), epilogue, A format, part, layout, ring units>:
 # epilogue 0 = store, 1 = SwiGLU forward, 2 = SwiGLU backward; part 3 = a sum of two products in one launch;
 # layout 0 = both operands K-contiguous, 1 = B K-major, 2 = A and B K-major.  The backward GEMMs run as two grouped
 # launches; the single-launch tags appear only when the grouping is switched off (SSG_GEMM_GROUPING=0).
-TAG_NAMES = {0: "gemm_kernel<0, 0, 0, 0>", 2: "gemm_kernel<1, 0, 0, 0>", 18: "gemm_swiglu_col_range_kernel",
-             16: "gemm_group_dh_dw3_kernel<2>",
-             17: "gemm_group_dx_dw_kernel", 5: "gemm_kernel<2, 1, 0, 1>", 1: "gemm_kernel<0, 1, 0, 2>",
-             11: "gemm_kernel<0, 1, 3, 1>", 9: "gemm_kernel<0, 1, 1, 1>", 10: "gemm_kernel<0, 1, 2, 1>"}
+TAG_NAMES = {0: "gemm_kernel<4, 0, 0, 0, 0, 5>", 2: "gemm_kernel<4, 1, 0, 0, 0, 5>", 18: "gemm_swiglu_col_range_kernel<4>",
+             16: "gemm_group_dh_dw3_kernel<4, 2>",
+             17: "gemm_group_dx_dw_kernel<4>", 5: "gemm_kernel<4, 2, 1, 0, 1, 5>", 1: "gemm_kernel<4, 0, 1, 0, 2, 5>",
+             11: "gemm_kernel<4, 0, 1, 3, 1, 5>", 9: "gemm_kernel<4, 0, 1, 1, 1, 5>", 10: "gemm_kernel<4, 0, 1, 2, 1, 5>"}
 TAG_ROLES = {0: "y = h^ w3~^T", 2: "U, G + SwiGLU + channel maxima",
              18: "U, G + SwiGLU + channel maxima, with the per-channel range of W3 in the grid's last round", 16: "dH + SwiGLU backward, then the first part of dW3 (one grid)",
              17: "dX (both products), then dW1, dW2 and the rest of dW3 (one grid)", 5: "dH + SwiGLU backward", 1: "dW3, dW1, dW2",
@@ -47,7 +48,7 @@ ELEMENTWISE = {40: ("amax_bf16_kernel", "per-tensor range of x, W1, W2, dY"),
                43: ("cast_kernel<LoadBf16, 0, true, ...>", "w3~ = Q(s^-1 w3)"),
                47: ("cast_h_w3_kernel", "h^ = cast(s_i h) from bf16 U, G and w3~ = Q(s^-1 w3), one launch"),
                44: ("col_amax_bf16_kernel", "per-channel range of W3"),
-               45: ("reset / fill / channel_factors kernels", "bookkeeping")}
+               45: ("fill / channel_factors kernels", "bookkeeping")}
 PEAK_HBM_GBS = 8000.0             # MI355X HBM3E (published: 8 TB/s)
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "bench_7b_hbm_traffic.txt")
 
@@ -236,11 +237,12 @@ def summarize_profiles(src: str) -> int:
         return hits[0] if hits else None
 
     shape = "Llama2-7B MLP shape, fwd+bwd, T=4096 d=4096 f=11008"
-    legend = ("gemm_kernel<epilogue, A format, part, layout>: epilogue 0 = store, 1 = SwiGLU forward (U, G, channel maxima), 2 = SwiGLU "
+    legend = ("gemm_kernel<blocks per wave, epilogue, A format, part, layout, ring units>: 4 blocks per wave = 256 x 256 tile, "
+              "2 = 128 x 128; gemm_skinny_kernel = few rows; epilogue 0 = store, 1 = SwiGLU forward (U, G, channel maxima), 2 = SwiGLU "
               "backward, 3 = SwiGLU + E4M3 cast (inference form), 4 = SwiGLU backward + E5M2 cast (delayed scaling); A format 0 = E4M3, "
               "1 = E5M2; part 3 = a sum of two products in one launch; layout 0 = both operands K-contiguous, 1 = B K-major, 2 = A and B "
               "K-major.  gemm_group_dh_dw3_kernel = dH then the first part of dW3 in one grid; gemm_group_dx_dw_kernel = dX, then dW1, dW2 and "
-              "the rest of dW3 in one grid; gemm_swiglu_col_range_kernel = gemm_kernel<1, 0, 0, 0> with the per-channel range pass over W3 "
+              "the rest of dW3 in one grid; gemm_swiglu_col_range_kernel = the gate/up GEMM with the per-channel range pass over W3 "
               "as extra workgroups of the same grid; cast_h_w3_kernel = the casts of h and w3 in one launch.")
     # 1. per-kernel durations
     stats = find("stats", "kernel_stats.csv")

@@ -138,15 +138,18 @@ int gemm_wave_blocks(const GemmArgs *const *list, int n, double last) {
 // (gate/up of the inference form at T = 4096, d = 4096, f = 11008, 5.4 rounds: 303 us whole, 288 as 5 rounds and 384 small
 // tiles; at T = 1024, 1.3 rounds: 104 and 99.)  The range pass over w3 in the grid hides in a last round of large tiles
 // but not beside small ones, where its 90 MB take 21 us (T = 4096: 346 us whole, 353 in two; T = 2048, d = 2048, f = 5504,
-// 22 MB, a step: 305 us with all small tiles, 298 in two).
+// 22 MB, a step: 305 us with all small tiles, 298 in two).  Small tiles fold the channel maxima of U, G's product with
+// twice the atomics, 64 to a channel at T = 4096, about 6 ns a row where few channels are at it (without the range pass:
+// T = 4096 342 us whole, 355 in two).
 static int full_round_sets(const GemmArgs &a, int wb, double whole) {
     if (a.a_fmt == kBF16) return 0;
     const double range = a.tail_src ? 2.0 * (double)(a.tail_rows * a.tail_cols) / 4.2e6 : 0.0;
-    if (wb == 2) whole += range;
+    const double extra = range + (a.epilogue == EPI_SWIGLU ? 6e-3 * (double)a.M : 0.0);
+    if (wb == 2) whole += extra;
     const int64_t tiles = tile_count(a, 4), rounds = tiles / kComputeUnits, rest = tiles - rounds * kComputeUnits;
     if (rounds == 0 || rest == 0) return 0;
-    const double split = (double)rounds * gemm_tile_cost(a, 4) + 5.0 + small_tile_time(4 * rest, gemm_tile_cost(a, 2)) + range;
-    return split < 0.97 * whole ? (int)(rounds * kComputeUnits / 8) : 0;
+    const double split = (double)rounds * gemm_tile_cost(a, 4) + 5.0 + small_tile_time(4 * rest, gemm_tile_cost(a, 2)) + extra;
+    return split < 0.98 * whole ? (int)(rounds * kComputeUnits / 8) : 0;
 }
 
 // The input gradient of a hidden width that is no multiple of 128: in one launch of small tiles together with the
