@@ -225,7 +225,7 @@ typedef struct {
  * its two grouped GEMM launches on a GPU with `compute_units` compute units: workgroups come in sets of 8 output
  * tiles; *dw3_sets_total receives the number of sets of dW3, *dw3_sets_first how many of them run in the first
  * launch (beside dH), the rest running in the second (beside dX, dW1, dW2).  The choice minimises the predicted
- * time of the two launches; it changes no result.  Host pointers; nothing is launched and no GPU is needed (the
+ * time of the two launches in tiles of 256 x 256; it changes no result.  Host pointers; nothing is launched and no GPU is needed (the
  * call ssg_mlp_bwd makes uses the compute unit count of the current device).  *dw3_sets_first = *dw3_sets_total
  * where the grouped launches are not used (w3_layer_bf16 = 1, shapes whose input gradient takes two launches). */
 ssg_status ssg_mlp_bwd_plan(const ssg_mlp_desc *desc, int32_t compute_units, int32_t *dw3_sets_first,
@@ -326,7 +326,7 @@ ssg_status ssg_adam_view_state(int64_t n, int32_t step, const void *state, ssg_a
  * Tags.  GEMMs (bytes = 0: priced in flops by the caller): 2 * epilogue + a_fmt with epilogue 0 = plain store
  * (y: tag 0; a weight gradient: tag 1), 1 = fused SwiGLU forward (U, G, channel maxima: tag 2), 2 = fused SwiGLU
  * backward (dH: tag 5), 3 = fused SwiGLU product + E4M3 cast of the inference form (tag 6); 11 = the input
- * gradient, both products in one launch (9 and 10: its two launches on shapes where that form is not built);
+ * gradient, both products in one launch (9 and 10: its two launches where those are estimated faster);
  * 16 = grouped launch {dH, dW3}; 17 = grouped launch {dX, dW1, dW2}; 18 = tag 2 with the per-column range pass over
  * W3 riding in the same grid; bf16 operands (w3_layer_bf16 = 1): 20 = plain
  * store (y, dW3), 21 = dH with the fused SwiGLU backward.

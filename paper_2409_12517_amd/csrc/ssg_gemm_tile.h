@@ -206,7 +206,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     constexpr int kChunks = BM / 16;                   // 16-byte chunks of a K-major row
     constexpr bool ADD = PART == 2;
     constexpr bool TWO = PART == 3;
-    constexpr bool kTwoWhole = TWO && WB == 4;         // no general loop body there (see gemm_sum_in_one_launch_ok)
+    constexpr bool kTwoWhole = TWO && WB == 4;         // no general loop body there (see sum_in_large_tile_ok)
     static_assert(!TWO || EPI == EPI_STORE, "a sum of two products ends in the plain store epilogue");
     constexpr bool AKM = LAY == 2, BKM = LAY >= 1;
     constexpr bool kBwd = EPI == EPI_SWIGLU_BWD || EPI == EPI_SWIGLU_BWD_Q;     // dH -> dU, dG through the SwiGLU derivative
