@@ -127,3 +127,23 @@ def test_inference_form_in_whole_rounds_and_a_rest():
     """9 x 33 tiles of 256 rows by 128 channels: 256 of them in large tiles, the other 41 in small ones."""
     inp = synth.make_inputs(64, 272, 4112, seed=61)
     ti.check(ti.Infer(inp, T_inf=2064, seed_inf=9), tm._np_inputs(inp))
+
+
+def test_large_tile_sum_of_two_products_over_a_ragged_last_column():
+    """dX in one launch of large tiles (16 x 16 of them, K = 8192 twice) whose last row and column of tiles are cut, with
+    dW1, dW2 beside it: every element against the contraction of the stored codes in binary64 on the device."""
+    T, d, f = 4080, 3984, 8192
+    blk = tm.Block(synth.make_inputs(T, d, f, seed=17), y_dtype=ssg.SSG_F32)
+    blk.fwd()
+    blk.bwd()
+    sc, wsc = blk.sv("scales", (16,), torch.float32).double(), blk.wv("scales", (8,), torch.float32).double()
+
+    def dec(t, dtype):
+        return t.view(dtype).double()
+
+    duq, dgq = (dec(blk.wv(n, (T, f), torch.uint8), torch.float8_e5m2) for n in ("du_q", "dg_q"))
+    w1, w2 = (dec(blk.sv(n, (f, d), torch.uint8), torch.float8_e4m3fn) for n in ("w1_q", "w2_q"))
+    xq = dec(blk.sv("x_q", (T, d), torch.uint8), torch.float8_e4m3fn)
+    for name, got, ref in (("dX", blk.dx, duq @ w1 / (wsc[1] * sc[1]) + dgq @ w2 / (wsc[2] * sc[2])),
+                           ("dW1", blk.dW1, duq.t() @ xq / (wsc[1] * sc[0])), ("dW2", blk.dW2, dgq.t() @ xq / (wsc[2] * sc[0]))):
+        assert float((got.double() - ref).abs().max()) <= 2e-3 * float(ref.abs().max()), name
