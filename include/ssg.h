@@ -106,6 +106,19 @@ ssg_status ssg_gemm_fp8_layout(const uint8_t *A, ssg_fp8_format a_fmt, int a_kma
                                ssg_fp8_format b_fmt, int b_kmajor, int64_t M, int64_t N, int64_t K,
                                const float *sa_dev, const float *sb_dev, void *C, ssg_dtype c_dtype, void *stream);
 
+/* Which kernel a GEMM of the block, of the inference form or of ssg_gemm_fp8_layout runs in, for tests and reports: the
+ * decision the call itself makes.  Host logic on an MI355X with 256 compute units; nothing is launched and no GPU is
+ * needed. */
+typedef struct {
+    int32_t tile;            /* edge of the output tiles: 256 or 128; 0: the kernel for few rows */
+    int32_t ring;            /* operand tiles in LDS; few rows: K steps of 128 bytes in a wave's ring */
+    int32_t whole_sets;      /* > 0 (tile = 128): the first whole_sets * 8 tiles of 256 x 256 run as such, in a launch before */
+    int32_t rows, cols;      /* few rows: rows and columns of the result per workgroup (else 0) */
+    int32_t launches;        /* GEMM launches */
+} ssg_gemm_plan;
+ssg_status ssg_gemm_fp8_plan(ssg_fp8_format a_fmt, int a_kmajor, int b_kmajor, int64_t M, int64_t N, int64_t K,
+                             ssg_dtype c_dtype, ssg_gemm_plan *out);
+
 /* SwiGLU product of Section 4.1 from stored bf16 U, G [T,f], in fp32:
  * h = u * (g * (1 / (1 + exp(-g)))).  Debug / test entry: this is the h the
  * fused kernels quantize.  h out [T,f] float. */
@@ -230,6 +243,16 @@ typedef struct {
  * where the grouped launches are not used (w3_layer_bf16 = 1, shapes whose input gradient takes two launches). */
 ssg_status ssg_mlp_bwd_plan(const ssg_mlp_desc *desc, int32_t compute_units, int32_t *dw3_sets_first,
                             int32_t *dw3_sets_total);
+/* The same for the GEMMs of ssg_mlp_fwd, ssg_mlp_bwd and ssg_infer_fwd. */
+enum {
+    SSG_PLAN_GATE_UP = 0,        /* U, G */
+    SSG_PLAN_Y = 1,
+    SSG_PLAN_BWD_FIRST = 2,      /* dH and the first part of dW3 (in one grid: launches = 1) */
+    SSG_PLAN_BWD_SECOND = 3,     /* dX, dW1, dW2 and the rest of dW3 (in one grid: launches = 1; dX in two launches: 4 in all) */
+    SSG_PLAN_INFER_GATE_UP = 4,  /* h^ of the inference form */
+    SSG_PLAN_INFER_Y = 5
+};
+ssg_status ssg_mlp_gemm_plan(const ssg_mlp_desc *desc, int which, ssg_gemm_plan *out);
 ssg_status ssg_mlp_view_saved(const ssg_mlp_desc *desc, const void *saved, ssg_mlp_saved_view *out);
 ssg_status ssg_mlp_view_workspace(const ssg_mlp_desc *desc, const void *workspace, ssg_mlp_workspace_view *out);
 

@@ -30,9 +30,9 @@ SSG_SCALE_CURRENT, SSG_SCALE_GIVEN, SSG_SCALE_DELAYED = 0, 1, 2
 SSG_ROUND_EXACT_DIV, SSG_ROUND_POW2 = 0, 1
 
 EXPORTS = [
-    "ssg_last_error", "ssg_version", "ssg_amax", "ssg_quantize", "ssg_gemm_fp8", "ssg_gemm_fp8_layout", "ssg_swiglu",
+    "ssg_last_error", "ssg_version", "ssg_amax", "ssg_quantize", "ssg_gemm_fp8", "ssg_gemm_fp8_layout", "ssg_gemm_fp8_plan", "ssg_swiglu",
     "ssg_smooth_swiglu_quantize", "ssg_fold_w3", "ssg_mlp_saved_bytes", "ssg_mlp_workspace_bytes",
-    "ssg_mlp_fwd", "ssg_mlp_bwd", "ssg_mlp_bwd_plan", "ssg_mlp_view_saved", "ssg_mlp_view_workspace",
+    "ssg_mlp_fwd", "ssg_mlp_bwd", "ssg_mlp_bwd_plan", "ssg_mlp_gemm_plan", "ssg_mlp_view_saved", "ssg_mlp_view_workspace",
     "ssg_mlp_scaling_state_bytes", "ssg_mlp_scaling_init",
     "ssg_infer_prepared_bytes", "ssg_infer_workspace_bytes", "ssg_infer_prepare", "ssg_infer_fwd", "ssg_infer_view",
     "ssg_infer_noalloc_max_bytes", "ssg_infer_fwd_noalloc",
@@ -47,6 +47,13 @@ class ssg_mlp_desc(Structure):
                 ("h_scale_mode", c_int32), ("keep_bf16_grads", c_int32), ("w3_layer_bf16", c_int32), ("reserved", c_int32 * 3),
                 ("scaling_state", c_void_p), ("h_scale", c_void_p),
                 ("h_counters", c_void_p)]
+
+
+class ssg_gemm_plan(Structure):
+    _fields_ = [(n, c_int32) for n in ("tile", "ring", "whole_sets", "rows", "cols", "launches")]
+
+
+SSG_PLAN_GATE_UP, SSG_PLAN_Y, SSG_PLAN_BWD_FIRST, SSG_PLAN_BWD_SECOND, SSG_PLAN_INFER_GATE_UP, SSG_PLAN_INFER_Y = range(6)
 
 
 class ssg_infer_view_t(Structure):
@@ -81,6 +88,8 @@ _lib.ssg_gemm_fp8.argtypes = [c_void_p, c_int, c_void_p, c_int, c_int64, c_int64
                               c_void_p, c_int, c_void_p]
 _lib.ssg_gemm_fp8_layout.argtypes = [c_void_p, c_int, c_int, c_void_p, c_int, c_int, c_int64, c_int64, c_int64, c_void_p,
                                      c_void_p, c_void_p, c_int, c_void_p]
+_lib.ssg_gemm_fp8_plan.argtypes = [c_int, c_int, c_int, c_int64, c_int64, c_int64, c_int, POINTER(ssg_gemm_plan)]
+_lib.ssg_mlp_gemm_plan.argtypes = [POINTER(ssg_mlp_desc), c_int, POINTER(ssg_gemm_plan)]
 _lib.ssg_swiglu.argtypes = [c_void_p, c_void_p, c_int64, c_int64, c_void_p, c_void_p]
 _lib.ssg_smooth_swiglu_quantize.argtypes = [c_void_p, c_void_p, c_int64, c_int64, c_int, c_void_p, c_void_p,
                                             c_void_p, c_void_p, c_void_p, c_void_p]
@@ -235,6 +244,18 @@ def ssg_mlp_bwd_plan(desc, compute_units: int):
     first, total = ctypes.c_int32(), ctypes.c_int32()
     _check(_lib.ssg_mlp_bwd_plan(ctypes.byref(desc), int(compute_units), ctypes.byref(first), ctypes.byref(total)))
     return first.value, total.value
+
+
+def ssg_gemm_fp8_plan(a_fmt, a_kmajor, b_kmajor, M, N, K, c_dtype) -> ssg_gemm_plan:
+    p = ssg_gemm_plan()
+    _check(_lib.ssg_gemm_fp8_plan(a_fmt, a_kmajor, b_kmajor, M, N, K, c_dtype, ctypes.byref(p)))
+    return p
+
+
+def ssg_mlp_gemm_plan(desc, which: int) -> ssg_gemm_plan:
+    p = ssg_gemm_plan()
+    _check(_lib.ssg_mlp_gemm_plan(ctypes.byref(desc), which, ctypes.byref(p)))
+    return p
 
 
 def ssg_mlp_view_saved(desc, saved) -> ssg_mlp_saved_view:

@@ -61,6 +61,21 @@ void backward_gemm_shapes(const ssg_mlp_desc &desc, BackwardGemms &b) {
     }
 }
 
+// Those of the forward and of the inference form.  (tail_src only says that the range pass over W3 rides along.)
+void forward_gemm_shapes(const ssg_mlp_desc &desc, ssg::GemmArgs &gate_up, ssg::GemmArgs &y) {
+    gate_up.epilogue = ssg::EPI_SWIGLU; gate_up.a_fmt = ssg::kE4M3; gate_up.M = desc.T; gate_up.N = desc.f; gate_up.K = desc.d;
+    y.epilogue = ssg::EPI_STORE; y.a_fmt = desc.w3_layer_bf16 ? ssg::kBF16 : ssg::kE4M3;
+    y.M = desc.T; y.N = desc.d; y.K = desc.f;
+    y.c_f32 = desc.y_dtype == SSG_F32;
+}
+void infer_gemm_shapes(const ssg_mlp_desc &desc, ssg::GemmArgs &gate_up, ssg::GemmArgs &y) {
+    forward_gemm_shapes(desc, gate_up, y);
+    gate_up.epilogue = ssg::EPI_SWIGLU_Q;
+}
+// the per-channel range of w3 (needed for the range of s^-1 * w3, constant between weight updates) rides in the
+// gate/up GEMM's grid, where it fills the last, partly occupied round of tiles
+bool w3_range_rides_along(const ssg_mlp_desc &desc) { return !desc.weights_cached && !desc.w3_layer_bf16 && gemm_grouping_enabled(); }
+
 // Split of dW3 between the two grouped launches of the backward (see gemm_group_split_sets), remembered for the last
 // few problem shapes: the replay costs a few milliseconds of host time.
 int dw3_split_sets(const ssg::GemmArgs &dh, const ssg::GemmArgs &dw3, const ssg::GemmArgs *const *second) {
@@ -385,14 +400,12 @@ ssg_status infer_forward(const char *who, const ssg_mlp_desc *desc, const void *
     float *wsc = reinterpret_cast<float *>(wk + Wl.scalars);
     uint32_t *slots = reinterpret_cast<uint32_t *>(wk + Wl.slots);
     // both inner products, the SwiGLU product and its cast in one kernel: h^ = cast((s_i u_i) Swish(g_i))
-    ssg::GemmArgs g;
-    g.epilogue = ssg::EPI_SWIGLU_Q; g.a_fmt = ssg::kE4M3; g.M = T; g.N = f; g.K = dm;
+    // y = h^ w3~^T / sigma_w3
+    ssg::GemmArgs g, g2;
+    infer_gemm_shapes(*desc, g, g2);
     g.A = wk + Wl.x_q; g.B = pb + P.w1_q; g.B2 = pb + P.w2_q; g.sa = wsc + 0; g.sb = psc + 0; g.sb2 = psc + 1;
     g.C = wk + Wl.h_q;
-    // y = h^ w3~^T / sigma_w3
-    ssg::GemmArgs g2;
-    g2.epilogue = ssg::EPI_STORE; g2.a_fmt = ssg::kE4M3; g2.M = T; g2.N = dm; g2.K = f;
-    g2.A = wk + Wl.h_q; g2.B = pb + P.w3_q; g2.sb = psc + 2; g2.C = y; g2.c_f32 = desc->y_dtype == SSG_F32;
+    g2.A = wk + Wl.h_q; g2.B = pb + P.w3_q; g2.sb = psc + 2; g2.C = y;
     if (!ssg::gemm_args_ok(g) || !ssg::gemm_args_ok(g2)) return fail(SSG_ERR_ARG, "%s: internal GEMM arguments", who);
     ssg_status rc = check_entry(who);
     if (rc != SSG_OK) return rc;
@@ -626,6 +639,41 @@ ssg_status ssg_gemm_fp8_layout(const uint8_t *A, ssg_fp8_format a_fmt, int a_kma
     return check_launch("ssg_gemm_fp8");
 }
 
+namespace {
+// The launch decision for one GEMM (launch_gemm's own) or, n > 1, for a group in one grid.
+ssg_gemm_plan describe(const ssg::GemmArgs &a) {
+    ssg_gemm_plan out{};
+    if (a.part != 0 || a.epilogue == ssg::EPI_SWIGLU_BWD || a.epilogue == ssg::EPI_SWIGLU_BWD_Q) {
+        const ssg::GemmArgs *one = &a;
+        out.tile = 64 * ssg::gemm_wave_blocks(&one, 1); out.ring = 5; out.launches = 1;
+        return out;
+    }
+    const ssg::GemmPlan p = ssg::gemm_plan(a);
+    out.tile = 64 * p.wave_blocks; out.ring = p.units; out.whole_sets = p.whole_sets; out.launches = p.whole_sets > 0 ? 2 : 1;
+    if (p.wave_blocks == 0) {
+        int rows, cols, steps;
+        ssg::gemm_skinny_extent(a, p.form, &rows, &cols, &steps);
+        out.rows = rows; out.cols = cols; out.ring = steps;
+    }
+    return out;
+}
+}  // namespace
+
+ssg_status ssg_gemm_fp8_plan(ssg_fp8_format a_fmt, int a_kmajor, int b_kmajor, int64_t M, int64_t N, int64_t K,
+                             ssg_dtype c_dtype, ssg_gemm_plan *out) {
+    if (!out) return fail(SSG_ERR_ARG, "ssg_gemm_fp8_plan: out is NULL");
+    if (!fmt_ok(a_fmt) || !dtype_ok(c_dtype)) return fail(SSG_ERR_ARG, "ssg_gemm_fp8_plan: bad format or dtype");
+    if ((a_kmajor != 0 && a_kmajor != 1) || (b_kmajor != 0 && b_kmajor != 1) || (a_kmajor && !b_kmajor))
+        return fail(SSG_ERR_ARG, "ssg_gemm_fp8_plan: bad layout");
+    if (!extent_ok(M) || !extent_ok(N) || !extent_ok(K) || M * K >= kMaxElems || N * K >= kMaxElems || M * N >= kMaxElems)
+        return fail(SSG_ERR_SHAPE, "ssg_gemm_fp8_plan: M=%lld N=%lld K=%lld", (long long)M, (long long)N, (long long)K);
+    ssg::GemmArgs g;
+    g.epilogue = ssg::EPI_STORE; g.a_fmt = a_fmt; g.M = M; g.N = N; g.K = K; g.layout = a_kmajor ? 2 : (b_kmajor ? 1 : 0);
+    g.c_f32 = c_dtype == SSG_F32;
+    *out = describe(g);
+    return SSG_OK;
+}
+
 ssg_status ssg_gemm_fp8(const uint8_t *A, ssg_fp8_format a_fmt, const uint8_t *B, ssg_fp8_format b_fmt, int64_t M,
                         int64_t N, int64_t K, const float *sa_dev, const float *sb_dev, void *C,
                         ssg_dtype c_dtype, void *stream) {
@@ -758,26 +806,22 @@ ssg_status ssg_mlp_fwd(const ssg_mlp_desc *desc, const void *x, const void *W1, 
 
     // every GEMM argument set is built and checked before the first launch
     // a3 + a4 + first half of a5: both inner products of Eq. 2, bf16 U and G, per-channel max |h|
-    ssg::GemmArgs g;
-    g.epilogue = ssg::EPI_SWIGLU; g.a_fmt = ssg::kE4M3; g.M = T; g.N = f; g.K = dm;
+    // a8: last linear layer.  Smooth: only the scale of w3~ is left; plain: s_i = sigma_h for all i
+    ssg::GemmArgs g, g2;
+    forward_gemm_shapes(*desc, g, g2);
     g.A = b + L.x_q; g.B = b + L.w1_q; g.B2 = b + L.w2_q;
     g.sa = sc + S_SX; g.sb = sc + S_SW1; g.sb2 = sc + S_SW2;
     g.C = b + L.U; g.C2 = b + L.G; g.camax_bits = reinterpret_cast<uint32_t *>(h_camax);
-    // a8: last linear layer.  Smooth: only the scale of w3~ is left; plain: s_i = sigma_h for all i
-    ssg::GemmArgs g2;
-    g2.epilogue = ssg::EPI_STORE; g2.a_fmt = ssg::kE4M3; g2.M = T; g2.N = dm; g2.K = f;
     g2.A = b + L.h_q; g2.B = b + L.w3_q;
     g2.sa = desc->smooth ? nullptr : s; g2.sb = sc + S_SW3;
-    g2.C = y; g2.c_f32 = desc->y_dtype == SSG_F32;
+    g2.C = y;
     const bool bf16_last = desc->w3_layer_bf16 != 0;
     if (bf16_last) {
         // Section 4.3: the last linear layer on bf16 operands: y = h_b W3^T, no scales
-        g2.a_fmt = ssg::kBF16; g2.A = b + L.h_b; g2.B = static_cast<const uint8_t *>(W3); g2.sa = nullptr; g2.sb = nullptr;
+        g2.A = b + L.h_b; g2.B = static_cast<const uint8_t *>(W3); g2.sa = nullptr; g2.sb = nullptr;
     }
     const bool cached = desc->weights_cached != 0;
-    // the per-channel range of w3 (needed for the range of s^-1 * w3, constant between weight updates) rides in the
-    // gate/up GEMM's grid, where it fills the last, partly occupied round of tiles
-    const bool w3_range_in_gemm = !cached && !bf16_last && gemm_grouping_enabled();
+    const bool w3_range_in_gemm = w3_range_rides_along(*desc);
     if (w3_range_in_gemm) {
         g.tail_src = W3; g.tail_rows = dm; g.tail_cols = f; g.tail_camax_bits = reinterpret_cast<uint32_t *>(w3_camax);
     }
@@ -899,6 +943,38 @@ ssg_status ssg_mlp_bwd_plan(const ssg_mlp_desc *desc, int32_t compute_units, int
     if (gemm_grouping_enabled() && !desc->w3_layer_bf16 && bg.dx.part == 3) {
         const ssg::GemmArgs *second[3] = {&bg.dx, &bg.dw1, &bg.dw2};
         *dw3_sets_first = ssg::gemm_group_split_sets(bg.dh, bg.dw3, second, 3, compute_units);
+    }
+    return SSG_OK;
+}
+
+ssg_status ssg_mlp_gemm_plan(const ssg_mlp_desc *desc, int which, ssg_gemm_plan *out) {
+    const bool infer = which == SSG_PLAN_INFER_GATE_UP || which == SSG_PLAN_INFER_Y;
+    ssg_status rc = infer ? check_infer_desc(desc, "ssg_mlp_gemm_plan") : check_desc(desc, "ssg_mlp_gemm_plan");
+    if (rc != SSG_OK) return rc;
+    if (!out) return fail(SSG_ERR_ARG, "ssg_mlp_gemm_plan: out is NULL");
+    if (which < SSG_PLAN_GATE_UP || which > SSG_PLAN_INFER_Y) return fail(SSG_ERR_ARG, "ssg_mlp_gemm_plan: which = %d", which);
+    if (infer || which == SSG_PLAN_GATE_UP || which == SSG_PLAN_Y) {
+        ssg::GemmArgs g, g2;
+        if (infer) infer_gemm_shapes(*desc, g, g2);
+        else forward_gemm_shapes(*desc, g, g2);
+        if (!infer && w3_range_rides_along(*desc)) { g.tail_src = desc; g.tail_rows = desc->d; g.tail_cols = desc->f; }
+        *out = describe(which == SSG_PLAN_GATE_UP || which == SSG_PLAN_INFER_GATE_UP ? g : g2);
+        return SSG_OK;
+    }
+    BackwardGemms bg;
+    backward_gemm_shapes(*desc, bg);
+    const bool grouped_b = gemm_grouping_enabled() && bg.dx.part == 3, grouped = grouped_b && !desc->w3_layer_bf16;
+    const ssg::GemmArgs *group_a[2] = {&bg.dh, &bg.dw3}, *group_b[4] = {&bg.dx, &bg.dw1, &bg.dw2, &bg.dw3};
+    const int all = ssg::gemm_tile_sets(bg.dw3);
+    const int split = grouped ? ssg::gemm_group_split_sets(bg.dh, bg.dw3, group_b, 3, ssg::kComputeUnits) : all;
+    if (which == SSG_PLAN_BWD_FIRST) {
+        *out = describe(bg.dh);
+        if (grouped) out->tile = 64 * ssg::gemm_group_wave_blocks(group_a, 2, split);
+        else out->launches = 2;
+    } else {
+        *out = describe(bg.dx);
+        if (grouped_b) out->tile = 64 * (split < all ? ssg::gemm_group_wave_blocks(group_b, 4, split) : ssg::gemm_group_wave_blocks(group_b, 3, -1));
+        else out->launches = bg.dx.part == 3 ? 3 : 4;
     }
     return SSG_OK;
 }

@@ -212,26 +212,36 @@ static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream
     profile_after(st);
 }
 
-bool launch_gemm(const GemmArgs &a, hipStream_t st) {
-    if (!gemm_args_ok(a)) return false;
-    if (a.part != 0 || a.epilogue == EPI_SWIGLU_BWD || a.epilogue == EPI_SWIGLU_BWD_Q) return launch_gemm_bwd(a, st);
+GemmPlan gemm_plan(const GemmArgs &a) {
     const GemmArgs *one = &a;
-    const int wb = gemm_wave_blocks(&one, 1), all = sets_of(make_gemm_params(a));
-    const double whole = grid_time(&one, 1, wb);
-    if (gemm_skinny_time(a) < whole) {
-        profile_before(gemm_profile_tag(a), st, gemm_flops(a));
-        launch_gemm_skinny(a, st);
-        profile_after(st);
-        return true;
-    }
-    const int full = full_round_sets(a, wb, whole);
-    if (full > 0) launch_gemm_wb<4, 5>(a, 0, full, st);
+    GemmPlan p;
+    p.wave_blocks = gemm_wave_blocks(&one, 1);
+    const double whole = grid_time(&one, 1, p.wave_blocks);
+    if (gemm_skinny_time(a, &p.form) < whole) { p.wave_blocks = 0; return p; }
+    p.whole_sets = full_round_sets(a, p.wave_blocks, whole);
+    if (p.whole_sets > 0) p.wave_blocks = 2;
     // one small tile to a compute unit, so up to 8 large tiles on an XCD of 32: the longer ring, which leaves no room
     // for a second workgroup (M = 528, N = 2048, K = 4096, 80 tiles: 27 us with five units, 21 with nine; 65 large tiles
     // give one XCD a second round: 28 and 34)
-    if (wb == 4 && full == 0) launch_gemm_wb<4, 5>(a, 0, all, st);
-    else if (tile_count(a, 4) - 8 * full <= kComputeUnits / 4) launch_gemm_wb<2, 9>(a, full, all - full, st);
-    else launch_gemm_wb<2, 5>(a, full, all - full, st);
+    if (p.wave_blocks == 2 && tile_count(a, 4) - 8 * p.whole_sets <= kComputeUnits / 4) p.units = 9;
+    return p;
+}
+
+bool launch_gemm(const GemmArgs &a, hipStream_t st) {
+    if (!gemm_args_ok(a)) return false;
+    if (a.part != 0 || a.epilogue == EPI_SWIGLU_BWD || a.epilogue == EPI_SWIGLU_BWD_Q) return launch_gemm_bwd(a, st);
+    const GemmPlan plan = gemm_plan(a);
+    if (plan.wave_blocks == 0) {
+        profile_before(gemm_profile_tag(a), st, gemm_flops(a));
+        launch_gemm_skinny(a, plan.form, st);
+        profile_after(st);
+        return true;
+    }
+    const int full = plan.whole_sets, rest = sets_of(make_gemm_params(a)) - full;
+    if (full > 0) launch_gemm_wb<4, 5>(a, 0, full, st);
+    if (plan.wave_blocks == 4) launch_gemm_wb<4, 5>(a, 0, rest, st);
+    else if (plan.units == 9) launch_gemm_wb<2, 9>(a, full, rest, st);
+    else launch_gemm_wb<2, 5>(a, full, rest, st);
     return true;
 }
 

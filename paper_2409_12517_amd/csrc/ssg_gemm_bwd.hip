@@ -153,6 +153,17 @@ static void launch_group(const GroupParams &g, int n, int epilogue, dim3 grid, c
     else hipLaunchKernelGGL((gemm_group_dh_dw3_kernel<WB, EPI_SWIGLU_BWD_Q>), grid, dim3(kThreads), 0, st, g);
 }
 
+// The split member is the last one of either group: the first launch runs its sets [0, split), the second the rest.
+static int last_member_sets(int n, int split_sets, int all) {
+    const int cut = split_sets < all ? split_sets : all;
+    return split_sets < 0 || n == 3 ? all : n == 2 ? cut : all - cut;
+}
+
+int gemm_group_wave_blocks(const GemmArgs *const *list, int n, int split_sets) {
+    const int all = gemm_tile_sets(*list[n - 1]);
+    return gemm_wave_blocks(list, n, (double)last_member_sets(n, split_sets, all) / (double)all);
+}
+
 bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipStream_t st, const ScalingUpdate &update) {
     if (!gemm_group_ok(list, n)) return false;
     GroupParams g;
@@ -163,14 +174,10 @@ bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipSt
         g.sets[i] = i < n ? sets_of(g.p[i]) : 0;
         g.first[i] = 0;
     }
-    // the split member is the last one of either group: the first launch runs its sets [0, split), the second the rest
-    if (split_sets >= 0 && (n == 2 || n == 4)) {
-        const int all = g.sets[n - 1];
-        const int cut = split_sets < all ? split_sets : all;
-        if (n == 2) g.sets[1] = cut;
-        else { g.first[n - 1] = cut; g.sets[n - 1] = all - cut; }
-    }
-    const int wb = gemm_wave_blocks(list, n, (double)g.sets[n - 1] / (double)sets_of(g.p[n - 1]));
+    const int all = g.sets[n - 1];
+    g.sets[n - 1] = last_member_sets(n, split_sets, all);
+    if (n == 4) g.first[3] = all - g.sets[3];
+    const int wb = gemm_group_wave_blocks(list, n, split_sets);
     // The fp32 weight gradients of the second launch go out through non-temporal stores: nothing reads them before
     // the optimizer, and kept out of the caches they leave in place what the passes after this launch read (measured
     // at the Llama2-7B shape: -10 us per step, in the launches that follow, not in this one).  In the first launch,

@@ -153,19 +153,26 @@ static void launch_form(const GemmParams &p, hipStream_t st) {
     hipLaunchKernelGGL((gemm_skinny_kernel<EPI, AFMT, MB, NB, KW, STEPS>), dim3(mblocks * nsets * 8), dim3(64 * KW), 0, st, p);
 }
 
-// The forms of the plain store: blocks of A and of B per workgroup.  Larger ones fetch fewer bytes per product, smaller
-// ones leave fewer compute units idle.
-static constexpr struct { int mb, nb; } kStoreForms[] = {{1, 1}, {1, 2}, {2, 2}, {4, 2}, {4, 4}, {6, 4}};
+// The forms: blocks of A and of B per workgroup, waves, steps of a wave's ring.  Of the plain store (the first six):
+// larger ones fetch fewer bytes per product, smaller ones leave fewer compute units idle.  The last two are the SwiGLU form's.
+constexpr int kStoreForms = 6;
+static constexpr struct { int mb, nb, waves, steps; } kForms[] = {{1, 1, 4, 5}, {1, 2, 4, 3}, {2, 2, 4, 2}, {4, 2, 4, 3},
+                                                                  {4, 4, 4, 2}, {6, 4, 4, 2}, {1, 2, 4, 3}, {4, 4, 2, 2}};
+
+template <int EPI, int AFMT, int I>
+static void launch_indexed(const GemmParams &p, hipStream_t st) {
+    launch_form<EPI, AFMT, kForms[I].mb, kForms[I].nb, kForms[I].waves, kForms[I].steps>(p, st);
+}
 
 template <int AFMT>
 static void launch_store(const GemmParams &p, int form, hipStream_t st) {
     switch (form) {
-        case 0: launch_form<EPI_STORE, AFMT, 1, 1, 4, 5>(p, st); break;
-        case 1: launch_form<EPI_STORE, AFMT, 1, 2, 4, 3>(p, st); break;
-        case 2: launch_form<EPI_STORE, AFMT, 2, 2, 4, 2>(p, st); break;
-        case 3: launch_form<EPI_STORE, AFMT, 4, 2, 4, 3>(p, st); break;
-        case 4: launch_form<EPI_STORE, AFMT, 4, 4, 4, 2>(p, st); break;
-        default: launch_form<EPI_STORE, AFMT, 6, 4, 4, 2>(p, st); break;
+        case 0: launch_indexed<EPI_STORE, AFMT, 0>(p, st); break;
+        case 1: launch_indexed<EPI_STORE, AFMT, 1>(p, st); break;
+        case 2: launch_indexed<EPI_STORE, AFMT, 2>(p, st); break;
+        case 3: launch_indexed<EPI_STORE, AFMT, 3>(p, st); break;
+        case 4: launch_indexed<EPI_STORE, AFMT, 4>(p, st); break;
+        default: launch_indexed<EPI_STORE, AFMT, 5>(p, st); break;
     }
 }
 
@@ -176,7 +183,7 @@ static void launch_store(const GemmParams &p, int form, hipStream_t st) {
 // {6,4} 32 / 33; the 128 x 128 tile with its longer ring takes 42 to 57 for all of them.)  More workgroups than compute
 // units pay the 4 each round, and a third more per byte (1040 x 2736 x 4096, two rounds of {6,4}: 35 / 39; tile: 22).
 static double form_time(const GemmArgs &a, int form) {
-    const int64_t m = 16 * kStoreForms[form].mb, n = 16 * kStoreForms[form].nb;
+    const int64_t m = 16 * kForms[form].mb, n = 16 * kForms[form].nb;
     const int64_t groups = ((a.M + m - 1) / m) * ((a.N + n - 1) / n), rounds = (groups + kComputeUnits - 1) / kComputeUnits;
     const double fetch = (double)((m + n) * a.K) / 70e3, hbm = (double)(a.N * a.K) / 4.2e6;
     const double busy = rounds == 1 ? fetch : (double)rounds * (1.35 * fetch + 4.0) - 4.0;
@@ -187,28 +194,35 @@ static double form_time(const GemmArgs &a, int form) {
 // form: up to 128 rows (gate/up of the inference form against the 128 x 128 tile, us, d = 4096, f = 11008: T = 16 22
 // against 36, T = 64 27 against 40, T = 128 44 against 48, T = 208 53 against 43; d = 2048, f = 5504: T = 128 15 against
 // 18, T = 272 24 against 22).
-double gemm_skinny_time(const GemmArgs &a) {
+double gemm_skinny_time(const GemmArgs &a, int *form) {
     const double never = 1e30;
+    *form = 0;
     if (a.layout != 0 || a.part != 0 || a.a_fmt == kBF16 || a.col_scale) return never;
-    if (a.epilogue == EPI_SWIGLU_Q) return a.M <= 128 ? 0.0 : never;
+    if (a.epilogue == EPI_SWIGLU_Q) {
+        *form = a.M <= 16 ? kStoreForms : kStoreForms + 1;
+        return a.M <= 128 ? 0.0 : never;
+    }
     if (a.epilogue != EPI_STORE) return never;
-    double best = never;
-    for (int i = 0; i < (int)(sizeof(kStoreForms) / sizeof(kStoreForms[0])); ++i) best = std::min(best, form_time(a, i));
+    double best = form_time(a, 0);
+    for (int i = 1; i < kStoreForms; ++i) {
+        const double t = form_time(a, i);
+        if (t < best) { best = t; *form = i; }
+    }
     return best;
 }
 
-void launch_gemm_skinny(const GemmArgs &a, hipStream_t st) {
+void launch_gemm_skinny(const GemmArgs &a, int form, hipStream_t st) {
     const GemmParams p = make_gemm_params(a);
-    if (a.epilogue == EPI_SWIGLU_Q) {
-        if (p.M <= 16) launch_form<EPI_SWIGLU_Q, kE4M3, 1, 2, 4, 3>(p, st);
-        else launch_form<EPI_SWIGLU_Q, kE4M3, 4, 4, 2, 2>(p, st);
-        return;
-    }
-    int form = 0;
-    for (int i = 1; i < (int)(sizeof(kStoreForms) / sizeof(kStoreForms[0])); ++i)
-        if (form_time(a, i) < form_time(a, form)) form = i;
-    if (a.a_fmt == kE4M3) launch_store<kE4M3>(p, form, st);
+    if (form == kStoreForms) launch_indexed<EPI_SWIGLU_Q, kE4M3, kStoreForms>(p, st);
+    else if (form > kStoreForms) launch_indexed<EPI_SWIGLU_Q, kE4M3, kStoreForms + 1>(p, st);
+    else if (a.a_fmt == kE4M3) launch_store<kE4M3>(p, form, st);
     else launch_store<kE5M2>(p, form, st);
+}
+
+void gemm_skinny_extent(const GemmArgs &a, int form, int *rows, int *cols, int *steps) {
+    *rows = 16 * kForms[form].mb;
+    *cols = 16 * kForms[form].nb / (a.epilogue == EPI_SWIGLU_Q ? 2 : 1);
+    *steps = kForms[form].steps;
 }
 
 }  // namespace ssg

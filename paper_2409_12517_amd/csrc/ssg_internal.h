@@ -160,9 +160,20 @@ struct GemmArgs {
 bool gemm_args_ok(const GemmArgs &a);
 // false (nothing launched): gemm_args_ok(a) is false
 bool launch_gemm(const GemmArgs &a, hipStream_t st);
-// few rows (ssg_gemm_skinny.hip): estimated microseconds, 1e30 for an argument set it is not built for
-double gemm_skinny_time(const GemmArgs &a);
-void launch_gemm_skinny(const GemmArgs &a, hipStream_t st);
+// How launch_gemm runs a GEMM other than the backward forms; shapes, formats and options decide, no pointer but
+// tail_src and col_scale (null or not) is looked at
+struct GemmPlan {
+    int wave_blocks = 4;        // 4: tiles of 256 x 256, 2: tiles of 128 x 128, 0: few rows
+    int units = 5;              // operand tiles of the ring
+    int whole_sets = 0;         // > 0: so many sets of 8 large tiles in a launch before that of the small ones
+    int form = 0;               // few rows: which of its forms
+};
+GemmPlan gemm_plan(const GemmArgs &a);
+// few rows (ssg_gemm_skinny.hip): estimated microseconds of the best form, 1e30 for an argument set it is not built for
+double gemm_skinny_time(const GemmArgs &a, int *form);
+void launch_gemm_skinny(const GemmArgs &a, int form, hipStream_t st);
+// rows and columns of the result per workgroup, steps of 128 bytes of K in a wave's ring
+void gemm_skinny_extent(const GemmArgs &a, int form, int *rows, int *cols, int *steps);
 bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st);       // the backward forms (called by launch_gemm)
 constexpr int kComputeUnits = 256;
 // Tile of a launch that runs these GEMMs in one grid: 32 x 32 blocks per wave and direction, 4 (256 x 256 tiles) or 2 (128 x 128)
@@ -185,6 +196,7 @@ int gemm_profile_tag(const GemmArgs &a);
 // compute units, from a replay of the in-order dispatch with per-tile times estimated from K steps and epilogues.
 bool gemm_group_ok(const GemmArgs *const *list, int n);
 bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipStream_t st, const ScalingUpdate &update = {});
+int gemm_group_wave_blocks(const GemmArgs *const *list, int n, int split_sets);      // the tile it runs in
 int gemm_tile_sets(const GemmArgs &a);
 int gemm_group_split_sets(const GemmArgs &dh, const GemmArgs &dw_split, const GemmArgs *const *second, int n_second, int units);
 

@@ -1,0 +1,63 @@
+"""CPU checks of the host rule that picks the kernel of each GEMM (ssg_gemm_fp8_plan, ssg_mlp_gemm_plan)."""
+import random
+
+import pytest
+
+import paper_2409_12517_amd as ssg
+
+
+def _log(rng, lo, hi):
+    return max(16, int(round(lo * (hi / lo) ** rng.random() / 16)) * 16)
+
+
+def _gemm(M, N, K, layout=0, c=ssg.SSG_BF16):
+    return ssg.ssg_gemm_fp8_plan(ssg.SSG_E5M2 if layout else ssg.SSG_E4M3, int(layout == 2), int(layout >= 1), M, N, K, c)
+
+
+def _check_form(p, M, N):
+    tiles = -(-M // 256) * -(-N // 256)
+    assert p.tile in (0, 128, 256) and p.launches == (2 if p.whole_sets else 1)
+    if p.tile == 0:
+        assert p.rows in (16, 32, 64, 96) and p.cols in (16, 32, 64) and 2 <= p.ring <= 5 and p.whole_sets == 0
+    else:
+        assert p.rows == p.cols == 0 and p.ring in (5, 9) and (p.ring == 5 or p.tile == 128)
+    # whole rounds of 256 large tiles (32 sets of 8) and something left for the small ones
+    assert p.whole_sets % 32 == 0 and (p.whole_sets == 0 or (p.tile == 128 and p.whole_sets * 8 < tiles))
+
+
+def test_plans_are_well_formed():
+    rng = random.Random(5)
+    for _ in range(400):
+        M, N, K, layout = _log(rng, 16, 8192), _log(rng, 16, 28672), _log(rng, 16, 28672), rng.randrange(3)
+        p = _gemm(M, N, K, layout, rng.randrange(2))
+        _check_form(p, M, N)
+        assert layout == 0 or p.tile != 0                 # the few-rows kernel takes K-contiguous operands
+    for _ in range(200):
+        T, d = _log(rng, 16, 8192), _log(rng, 256, 8192)
+        f = int(round(d * rng.uniform(1, 4) / 16)) * 16
+        desc = ssg.make_desc(T, d, f, weights_cached=rng.randrange(2))
+        _check_form(ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_GATE_UP), T, 2 * f)
+        _check_form(ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_INFER_GATE_UP), T, 2 * f)
+        _check_form(ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_Y), T, d)
+        _check_form(ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_INFER_Y), T, d)
+        first, second = (ssg.ssg_mlp_gemm_plan(desc, w) for w in (ssg.SSG_PLAN_BWD_FIRST, ssg.SSG_PLAN_BWD_SECOND))
+        assert (first.launches, second.launches) in ((1, 1), (2, 4)) and first.tile in (128, 256) and second.tile in (128, 256)
+
+
+def test_the_bf16_last_layer_runs_in_large_tiles_on_its_own():
+    desc = ssg.make_desc(272, 256, 768, smooth=0, w3_layer_bf16=1)
+    for which in (ssg.SSG_PLAN_Y, ssg.SSG_PLAN_BWD_FIRST):
+        assert ssg.ssg_mlp_gemm_plan(desc, which).tile == 256
+    assert ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_BWD_FIRST).launches == 2
+
+
+def test_plan_queries_validate_their_arguments():
+    for bad in (dict(a_kmajor=1, b_kmajor=0), dict(M=24), dict(K=0), dict(a_fmt=7), dict(M=1 << 20, N=1 << 20)):
+        kw = dict(a_fmt=ssg.SSG_E4M3, a_kmajor=0, b_kmajor=0, M=256, N=256, K=256, c_dtype=ssg.SSG_F32)
+        kw.update(bad)
+        with pytest.raises(ssg.SsgError):
+            ssg.ssg_gemm_fp8_plan(**kw)
+    with pytest.raises(ssg.SsgError):
+        ssg.ssg_mlp_gemm_plan(ssg.make_desc(256, 256, 688), 6)
+    with pytest.raises(ssg.SsgError):
+        ssg.ssg_mlp_gemm_plan(ssg.make_desc(256, 256, 688, smooth=0), ssg.SSG_PLAN_INFER_Y)   # the folded form is smooth
