@@ -492,7 +492,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             // half of the register file and spill.)
             asm volatile("" : "+v"(l));      // as at the epilogue: keep this block's lane arithmetic inside the block
             const double s1 = (double)*p.sa * (double)*p.sb, s2 = (double)*p.sa_ph2 * (double)*p.sb_ph2;
-            const float rho = (float)(swapped ? s1 / s2 : s2 / s1);
+            // the ratio as a normal number times an exact power of two: far below 2^-126 it still meets accumulators of 2^28
+            const double ratio = swapped ? s1 / s2 : s2 / s1;
+            const float post = ratio < 0x1p-100 ? 0x1p-96f : 1.0f, rho = (float)(ratio / (double)post);
 #pragma unroll
             for (int mb = 0; mb < WB; ++mb) {
 #pragma unroll
@@ -506,7 +508,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                     const int e = (q * 64 + l) * 4;
                     float4 *at = reinterpret_cast<float4 *>(stg + e / WN * kPitch + e % WN);
                     float4 v = *at;
-                    v.x *= rho; v.y *= rho; v.z *= rho; v.w *= rho;
+                    v.x = v.x * rho * post; v.y = v.y * rho * post; v.z = v.z * rho * post; v.w = v.w * rho * post;
                     *at = v;
                     __builtin_amdgcn_sched_barrier(0);
                 }

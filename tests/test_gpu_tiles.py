@@ -81,6 +81,35 @@ def test_input_gradient_with_scales_far_apart(f, du_exp, dg_exp):
     gu.assert_close_gemm(gu.f32(blk.dx), ref, False, f"dX {f} {du_exp} {dg_exp}")
 
 
+@pytest.mark.parametrize("f", [688, 768])
+@pytest.mark.parametrize("du_exp,dg_exp", [(115, -37), (-37, 115)])
+def test_input_gradient_where_one_gradient_flushes_to_zero(f, du_exp, dg_exp):
+    """Given scales 2^152 apart: the codes of one gradient are all zero, those of the other saturate, and dX (about 2^-98)
+    is the product of the latter alone.  The change of units between the two products, 2^-152 or so, is no binary32 number,
+    the product of an accumulator (2^28) with it is one."""
+    T, d = 272, 256
+    inp = synth.make_inputs(T, d, f, seed=5)
+    blk = tm.Block(inp, y_dtype=ssg.SSG_F32)
+    state = torch.empty(ssg.ssg_mlp_scaling_state_bytes(), dtype=torch.uint8, device=gu.DEV)
+    ssg.ssg_mlp_scaling_init(state)
+    blk.desc.scaling_state = state.data_ptr()
+    blk.fwd()
+    blk.bwd()                                    # current scaling: fills the history
+    blk.desc.scale_mode = ssg.SSG_SCALE_DELAYED
+    words = state[: 6 * 32 * 4].view(torch.float32)
+    words[4 * 32], words[5 * 32] = 2.0 ** du_exp, 2.0 ** dg_exp
+    blk.fwd()
+    blk.bwd()
+    sc, wsc = gu.f32(blk.sv("scales", (16,), torch.float32)).astype(np.float64), gu.f32(blk.wv("scales", (8,), torch.float32)).astype(np.float64)
+    grad, weight, i, j = ("du_q", "w1_q", 1, 1) if du_exp > 0 else ("dg_q", "w2_q", 2, 2)
+    other = "dg_q" if du_exp > 0 else "du_q"
+    assert not (gu.u8(blk.wv(other, (T, f), torch.uint8)) & 0x7F).any()
+    ref = (fp8.decode(gu.u8(blk.wv(grad, (T, f), torch.uint8)), fp8.E5M2).astype(np.float64) @
+           fp8.decode(gu.u8(blk.sv(weight, (f, d), torch.uint8)), fp8.E4M3).astype(np.float64)) / (wsc[i] * sc[j])
+    # binary32 sums of 688 or 768 products: 2e-3 of the largest element, as for every contraction here
+    assert 2.0 ** -126 < np.abs(ref).max() and np.abs(gu.f32(blk.dx) - ref).max() <= 2e-3 * np.abs(ref).max()
+
+
 # The few-rows kernel: rows per workgroup 16, 16, 32, 64, 64, 96 with 16, 32, 32, 32, 64, 64 columns (the form each
 # shape is given by its size); ragged K, a last workgroup with part of its columns, rows beyond the last one; K shorter
 # than one step for each wave; 4096 rows by 1024 columns take the 128 x 128 tile with the long ring (K ragged and whole)
