@@ -182,9 +182,11 @@ static void launch_store(const GemmParams &p, int form, hipStream_t st) {
 // {1,1} 16 / 14, T = 32 {1,2} 17 / 16, T = 64 {2,2} 17 / 19, T = 128 {4,2} 22 / 24, T = 208 {4,4} 27 / 26, T = 272
 // {6,4} 32 / 33; the 128 x 128 tile with its longer ring takes 42 to 57 for all of them.)  More workgroups than compute
 // units pay the 4 each round, and a third more per byte (1040 x 2736 x 4096, two rounds of {6,4}: 35 / 39; tile: 22).
+// Rounds are counted on the XCD that has most: all row blocks of one column block go to the same, so 128 columns in blocks
+// of 64 are the work of two XCDs (6400 x 128 x 256: 17.6 us in {4,4}, 7.2 in 128 x 128 tiles).
 static double form_time(const GemmArgs &a, int form) {
     const int64_t m = 16 * kForms[form].mb, n = 16 * kForms[form].nb;
-    const int64_t groups = ((a.M + m - 1) / m) * ((a.N + n - 1) / n), rounds = (groups + kComputeUnits - 1) / kComputeUnits;
+    const int64_t groups = ((a.M + m - 1) / m) * (((a.N + n - 1) / n + 7) / 8), rounds = (groups + kComputeUnits / 8 - 1) / (kComputeUnits / 8);
     const double fetch = (double)((m + n) * a.K) / 70e3, hbm = (double)(a.N * a.K) / 4.2e6;
     const double busy = rounds == 1 ? fetch : (double)rounds * (1.35 * fetch + 4.0) - 4.0;
     return 4.0 + std::max(busy, hbm) + 0.25 * std::min(busy, hbm);

@@ -61,3 +61,17 @@ def test_plan_queries_validate_their_arguments():
         ssg.ssg_mlp_gemm_plan(ssg.make_desc(256, 256, 688), 6)
     with pytest.raises(ssg.SsgError):
         ssg.ssg_mlp_gemm_plan(ssg.make_desc(256, 256, 688, smooth=0), ssg.SSG_PLAN_INFER_Y)   # the folded form is smooth
+
+
+@pytest.mark.parametrize("M,N,K", [(4864, 128, 80), (5536, 128, 2544), (6400, 128, 256), (7072, 112, 6560)])
+def test_few_column_blocks_do_not_take_the_few_rows_kernel(M, N, K):
+    """It gives all row blocks of a column block to one XCD: with one or two column blocks most of the chip is idle
+    (measured 1.08 to 1.28 times the 256 x 256 tiles and about twice the 128 x 128 ones)."""
+    assert _gemm(M, N, K).tile == 128
+
+
+@pytest.mark.parametrize("M,N,K,rows,cols", [(16, 4096, 11008, 16, 16), (32, 4096, 11008, 16, 32), (64, 4096, 11008, 32, 32),
+                                             (128, 4096, 11008, 64, 32), (208, 4096, 11008, 64, 64), (272, 4096, 11008, 96, 64)])
+def test_few_rows_take_the_form_that_fills_the_chip_once(M, N, K, rows, cols):
+    p = _gemm(M, N, K)
+    assert (p.tile, p.rows, p.cols) == (0, rows, cols)
