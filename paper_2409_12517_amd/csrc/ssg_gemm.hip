@@ -70,23 +70,27 @@ static bool sum_in_large_tile_ok(int64_t K) { return K % BK == 0 && K >= 2 * BK;
 // about 90 % busy where it fills the chip (y at T = 4096, d = 4096, f = 11008: 133 us against 168); the small one has
 // four times the workgroups, two to a compute unit, whose epilogues run under each other's main loops (y at T = 2048,
 // d = 2048, f = 5504, 64 large tiles for 256 compute units: 53 us against 30).  Which wins is a matter of how many
-// tiles there are, so the time of a launch is estimated for both and the smaller one taken: over a range of training
-// steps, inference calls and contractions the choice stays within 3 % of the better of the two, and within 6 % for
-// every one of them.
+// tiles there are, of how their rows lie to the cache lines and of what comes from HBM, so the time of a launch is
+// estimated for both and the smaller one taken.  Over 3405 contractions (16 to 8192 rows, up to 28672 columns and K) and
+// 842 calls of the forward and inference forms the choice takes 2.2 % longer on average than the best route measured; 25
+// are more than 3 % slower than large tiles alone, the worst 1.24 times (896 x 8448 x 25424, B [K,N], A [K,M]).
 
-// Microseconds of one tile with all compute units busy, from time stamps (large tile: 1.33 per K step, 1.45 in the
-// long tiles of the one-launch sum, which all run at once; 2.5 before the first step; the epilogue: 33 with the SwiGLU
+// Microseconds of one tile of a group with all compute units busy, from time stamps (large tile: 1.33 per K step, 1.45 in
+// the long tiles of the one-launch sum, which all run at once; 2.5 before the first step; the epilogue: 33 with the SwiGLU
 // derivative, 42 when it also casts, 10 for U, G or an fp32 store, 6 for bf16).  Small tile, two on a compute unit:
 // 0.96 per K step, 3.5 before and after, a quarter of the large tile's epilogue.
-double gemm_tile_cost(const GemmArgs &a, int WB) {
+static double k_steps(const GemmArgs &a) {
     const int64_t kbytes = a.a_fmt == kBF16 ? 2 * a.K : a.K;
-    const double ksteps = (double)((kbytes + BK - 1) / BK) * (a.part == 3 ? 2.0 : 1.0);
-    double epilogue = a.c_f32 ? 10.0 : 6.0;
-    if (is_dual(a)) epilogue = 10.0;
-    if (a.epilogue == EPI_SWIGLU_BWD) epilogue = 33.0;
-    if (a.epilogue == EPI_SWIGLU_BWD_Q) epilogue = 42.0;
-    if (WB == 2) return 3.5 + 0.96 * ksteps + 0.25 * epilogue;
-    return 2.5 + (a.part == 3 ? 1.45 : 1.33) * ksteps + epilogue;
+    return (double)((kbytes + BK - 1) / BK) * (a.part == 3 ? 2.0 : 1.0);
+}
+static double epilogue_cost(const GemmArgs &a) {
+    if (a.epilogue == EPI_SWIGLU_BWD) return 33.0;
+    if (a.epilogue == EPI_SWIGLU_BWD_Q) return 42.0;
+    return is_dual(a) || a.c_f32 ? 10.0 : 6.0;
+}
+double gemm_tile_cost(const GemmArgs &a, int WB) {
+    if (WB == 2) return 3.5 + 0.96 * k_steps(a) + 0.25 * epilogue_cost(a);
+    return 2.5 + (a.part == 3 ? 1.45 : 1.33) * k_steps(a) + epilogue_cost(a);
 }
 
 static int64_t tile_count(const GemmArgs &a, int WB) {
@@ -97,11 +101,54 @@ static int64_t tile_count(const GemmArgs &a, int WB) {
 // Estimated time of `tiles` small tiles of one GEMM, each of `cost` microseconds when two share a compute unit.
 static double small_tile_time(int64_t tiles, double cost) {
     // a tile that has its compute unit to itself is bound by the latency of its loads: 0.44 per K step with a ring of
-    // nine, 0.58 when all compute units are at it; beyond two rounds the tiles drift out of step and the rounds blur
+    // nine, 0.58 when all compute units are at it.  With 257 to 512 of them the units that hold two decide, and these slow
+    // each other down the more of them there are.  Beyond two rounds the tiles drift out of step and the rounds blur
     if (tiles <= kComputeUnits) return 5.5 + (cost - 5.5) * (tiles <= 160 ? 0.46 : 0.6);
     if (tiles <= 2 * kComputeUnits) return cost * (0.65 + 0.35 * (double)(tiles - kComputeUnits) / kComputeUnits);
     const double blurred = std::max(cost, cost * (double)tiles / (2.0 * kComputeUnits));
     return tiles <= 3 * kComputeUnits ? std::max(blurred, 1.65 * cost) : blurred;
+}
+
+// Operand bytes that have to come from memory once, and how many of the two operands have rows that do not start on
+// 128-byte lines, so that a small tile's 128-byte pieces of them span two lines each.
+static double operand_bytes(const GemmArgs &a) {
+    return (double)(a.M + (is_dual(a) ? 2 : 1) * a.N) * (double)a.K * (a.a_fmt == kBF16 ? 2.0 : 1.0) * (a.part == 3 ? 2.0 : 1.0);
+}
+static int split_line_operands(const GemmArgs &a) {
+    return ((a.layout == 2 ? a.M : a.K) % 128 != 0) + ((a.layout >= 1 ? a.N : a.K) % 128 != 0);
+}
+constexpr double kHbmBytesPerUs = 4.2e6;         // what a launch of these kernels draws from HBM
+
+// Estimated microseconds of `tiles` of the tiles of one GEMM in a launch of its own.
+// Large tiles: 1.26 per K step in a round that fills the chip.  A last round that does not draws less power and runs at a
+// higher clock: 0.86 per K step with few tiles, 1.06 with half of the chip, and a cheaper epilogue (2064 x 11008 x 11008,
+// 1.5 rounds: 211 to 221 us in large tiles, 251 to 286 in small ones).
+static double large_launch_time(const GemmArgs &a, int64_t tiles) {
+    const int64_t full = tiles / kComputeUnits, rest = tiles - full * kComputeUnits;
+    const double ks = k_steps(a), epilogue = 1.4 * epilogue_cost(a), share = (double)rest / kComputeUnits;
+    double t = (double)full * (2.5 + 1.26 * ks + epilogue);
+    if (rest) t += 2.5 + (0.86 + 0.4 * share) * ks + epilogue * (0.57 + 0.43 * share) * std::min(1.0, (double)a.M / tile_edge(4));
+    return 4.0 + std::max(t, operand_bytes(a) / kHbmBytesPerUs * ((double)tiles / (double)tile_count(a, 4)));
+}
+// Small tiles: a fifth more per K step for each operand that splits lines (256 to 2000 tiles: 0.95, 1.17, 1.33 per step of
+// a full chip with none, one, both), and half as much again for its bytes.  Where compute units hold two, a quarter of the
+// smaller of the two times does not hide behind the larger.  In the training forward they fold the channel maxima of U,
+// G's product with twice the atomics, 64 to a channel at T = 4096, and slow down the range pass over w3 beside them, which
+// a last round of large tiles hides (gate/up at T = 4096, d = 768, f = 2048: 39 us large, 53 small; 32 and 46 without the
+// pass).
+static double small_launch_time(const GemmArgs &a, int64_t tiles) {
+    const int split = split_line_operands(a);
+    const double cost = 3.0 + 0.96 * k_steps(a) * (1.0 + 0.2 * split) + 0.25 * epilogue_cost(a);
+    const double share = (double)tiles / (double)tile_count(a, 2), run = small_tile_time(tiles, cost);
+    const double hbm = std::min(1.0, share) * operand_bytes(a) / kHbmBytesPerUs * (1.0 + 0.5 * split);
+    const double range = a.tail_src ? 2.0 * (double)(a.tail_rows * a.tail_cols) / kHbmBytesPerUs : 0.0;
+    double t = std::max(run, hbm) + (tiles > kComputeUnits ? 0.25 * std::min(run, hbm) : 0.0);
+    if (a.epilogue == EPI_SWIGLU && tiles == tile_count(a, 2)) t += 4.5e-3 * (double)a.M + 0.5 * range;
+    else if (a.epilogue == EPI_SWIGLU) t += (0.6e-3 + 3e-3 * share) * (double)a.M + 0.25 * range;     // the rest of a split
+    return t;
+}
+static double launch_time(const GemmArgs &a, int WB) {
+    return WB == 2 ? small_launch_time(a, tile_count(a, 2)) : large_launch_time(a, tile_count(a, 4));
 }
 
 // Estimated time of the GEMMs of `list` in one grid; of the last one, the share `last` of its tiles.
@@ -115,11 +162,8 @@ static double grid_time(const GemmArgs *const *list, int n, int WB, double last 
         sum += cost * (double)t;
         longest = std::max(longest, cost);
     }
-    if (WB == 2) return n == 1 ? small_tile_time(tiles, longest) : tiles <= kComputeUnits ? small_tile_time(tiles, longest)
-                                                                 : std::max(longest, sum / (2.0 * kComputeUnits));
-    // one tile per compute unit: a single GEMM runs in whole rounds, a group's last round is filled by its other members
-    const double rounds = (double)((tiles + kComputeUnits - 1) / kComputeUnits);
-    if (n == 1) return rounds * longest;
+    if (WB == 2) return tiles <= kComputeUnits ? small_tile_time(tiles, longest) : std::max(longest, sum / (2.0 * kComputeUnits));
+    // one tile per compute unit: the last round of one member is filled by the others
     // where a few long tiles decide (dX of a short batch: 64 tiles of 172 K steps), the members beside them slow them
     // down (T = 1024, d = 4096, f = 11008: 305 us for 258 estimated; the step 605 us, 574 with small tiles)
     return std::max(1.15 * longest, sum / kComputeUnits);
@@ -130,25 +174,20 @@ int gemm_wave_blocks(const GemmArgs *const *list, int n, double last) {
         if (list[i]->a_fmt == kBF16 || list[i]->part == 1 || list[i]->part == 2) return 4;      // not built in the small tile
         if (list[i]->part == 3 && !sum_in_large_tile_ok(list[i]->K)) return 2;
     }
+    if (n == 1) return launch_time(*list[0], 2) < 0.98 * launch_time(*list[0], 4) ? 2 : 4;
     return grid_time(list, n, 2, last) < grid_time(list, n, 4, last) ? 2 : 4;
 }
 
 // Sets of large tiles that make whole rounds of the chip when the rest is worth a launch of small tiles of its own (5 us):
-// a last round of large tiles that fills a third of the chip takes as long as a full one.  0: the GEMM stays whole.
+// a last round of large tiles that fills a third of the chip takes longer than its share.  0: the GEMM stays whole.
 // (gate/up of the inference form at T = 4096, d = 4096, f = 11008, 5.4 rounds: 303 us whole, 288 as 5 rounds and 384 small
-// tiles; at T = 1024, 1.3 rounds: 104 and 99.)  The range pass over w3 in the grid hides in a last round of large tiles
-// but not beside small ones, where its 90 MB take 21 us (T = 4096: 346 us whole, 353 in two; T = 2048, d = 2048, f = 5504,
-// 22 MB, a step: 305 us with all small tiles, 298 in two).  Small tiles fold the channel maxima of U, G's product with
-// twice the atomics, 64 to a channel at T = 4096, about 6 ns a row where few channels are at it (without the range pass:
-// T = 4096 342 us whole, 355 in two).
-static int full_round_sets(const GemmArgs &a, int wb, double whole) {
+// tiles.  The training forward at d = 3072, f = 8208, W1, W2 cached: T = 2048, 2.03 rounds, 261 us whole, 247 in two;
+// T = 2064, 2.3 rounds, 264 and 256; T = 1552, 1.8 rounds, 216 and 232.)
+static int full_round_sets(const GemmArgs &a, double whole) {
     if (a.a_fmt == kBF16) return 0;
-    const double range = a.tail_src ? 2.0 * (double)(a.tail_rows * a.tail_cols) / 4.2e6 : 0.0;
-    const double extra = range + (a.epilogue == EPI_SWIGLU ? 6e-3 * (double)a.M : 0.0);
-    if (wb == 2) whole += extra;
     const int64_t tiles = tile_count(a, 4), rounds = tiles / kComputeUnits, rest = tiles - rounds * kComputeUnits;
     if (rounds == 0 || rest == 0) return 0;
-    const double split = (double)rounds * gemm_tile_cost(a, 4) + 5.0 + small_tile_time(4 * rest, gemm_tile_cost(a, 2)) + extra;
+    const double split = large_launch_time(a, rounds * kComputeUnits) + 5.0 + small_launch_time(a, 4 * rest);
     return split < 0.98 * whole ? (int)(rounds * kComputeUnits / 8) : 0;
 }
 
@@ -159,8 +198,9 @@ bool gemm_sum_in_one_launch(const GemmArgs &dx, const GemmArgs &dw) {
     if (sum_in_large_tile_ok(dx.K)) return true;
     GemmArgs sum = dx, half = dx;
     sum.part = 3; half.part = 1; half.c_f32 = 1;
-    const GemmArgs *one[3] = {&sum, &dw, &dw}, *halves = &half, *single = &dw;
-    const double separate = 2.0 * grid_time(&halves, 1, 4) + 2.0 * std::min(grid_time(&single, 1, 4), grid_time(&single, 1, 2));
+    const GemmArgs *one[3] = {&sum, &dw, &dw};
+    auto rounds = [](const GemmArgs &a) { return gemm_tile_cost(a, 4) * (double)((tile_count(a, 4) + kComputeUnits - 1) / kComputeUnits); };
+    const double separate = 2.0 * rounds(half) + 2.0 * std::min(rounds(dw), small_tile_time(tile_count(dw, 2), gemm_tile_cost(dw, 2)));
     return grid_time(one, 3, 2) < separate;
 }
 
@@ -216,9 +256,9 @@ GemmPlan gemm_plan(const GemmArgs &a) {
     const GemmArgs *one = &a;
     GemmPlan p;
     p.wave_blocks = gemm_wave_blocks(&one, 1);
-    const double whole = grid_time(&one, 1, p.wave_blocks);
+    const double whole = launch_time(a, p.wave_blocks);
     if (gemm_skinny_time(a, &p.form) < whole) { p.wave_blocks = 0; return p; }
-    p.whole_sets = full_round_sets(a, p.wave_blocks, whole);
+    p.whole_sets = full_round_sets(a, whole);
     if (p.whole_sets > 0) p.wave_blocks = 2;
     // one small tile to a compute unit, so up to 8 large tiles on an XCD of 32: the longer ring, which leaves no room
     // for a second workgroup (M = 528, N = 2048, K = 4096, 80 tiles: 27 us with five units, 21 with nine; 65 large tiles

@@ -75,3 +75,21 @@ def test_few_column_blocks_do_not_take_the_few_rows_kernel(M, N, K):
 def test_few_rows_take_the_form_that_fills_the_chip_once(M, N, K, rows, cols):
     p = _gemm(M, N, K)
     assert (p.tile, p.rows, p.cols) == (0, rows, cols)
+
+
+@pytest.mark.parametrize("M,N,K,layout", [(2064, 11008, 11008, 0), (2064, 11008, 11008, 1), (2064, 11008, 11008, 2), (2064, 11008, 4112, 0),
+                                          (2064, 11008, 4112, 2), (896, 8448, 25424, 0), (896, 8448, 25424, 1), (1664, 4848, 25648, 0),
+                                          (3728, 2144, 22432, 0), (5680, 1328, 10768, 2), (304, 17120, 24192, 1), (592, 11392, 16640, 2),
+                                          (4096, 4096, 11008, 0)])
+def test_large_tiles_where_small_ones_were_measured_slower(M, N, K, layout):
+    """One and a half rounds or half a round of large tiles, long K, rows that split cache lines: 1.1 to 1.55 times the
+    time in 128 x 128 tiles."""
+    p = _gemm(M, N, K, layout)
+    assert p.tile == 256 and p.launches == 1
+
+
+@pytest.mark.parametrize("M,N,K,layout", [(1040, 2736, 4112, 0), (384, 15104, 3584, 0), (896, 6528, 4224, 2), (464, 10224, 7424, 0),
+                                          (1408, 3088, 7808, 0), (2048, 2048, 5504, 0), (1024, 1024, 2736, 1)])
+def test_small_tiles_where_large_ones_were_measured_slower(M, N, K, layout):
+    """0.64 to 0.8 of the time in 256 x 256 tiles, or less."""
+    assert _gemm(M, N, K, layout).tile == 128
