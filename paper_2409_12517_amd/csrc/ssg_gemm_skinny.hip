@@ -192,17 +192,28 @@ static double form_time(const GemmArgs &a, int form) {
     return 4.0 + std::max(busy, hbm) + 0.25 * std::min(busy, hbm);
 }
 
-// K-contiguous FP8 operands, the plain store without a per-column factor or the inference form's SwiGLU.  The SwiGLU
-// form: up to 128 rows (gate/up of the inference form against the 128 x 128 tile, us, d = 4096, f = 11008: T = 16 22
-// against 36, T = 64 27 against 40, T = 128 44 against 48, T = 208 53 against 43; d = 2048, f = 5504: T = 128 15 against
-// 18, T = 272 24 against 22).
+// The SwiGLU form: up to 128 rows (gate/up of the inference form against the 128 x 128 tile, us, d = 4096, f = 11008: T = 16
+// 22 against 36, T = 64 27 against 40, T = 128 44 against 48, T = 208 53 against 43; d = 2048, f = 5504: T = 128 15 against
+// 18, T = 272 24 against 22), and so many workgroups that each compute unit runs at most 4.5 of them one after the other
+// (against large tiles: d = 4864, f = 17760, 140 on an XCD, T = 96 49 and 52; d = 2048, f = 28672, 224, 38 and 33;
+// d = 7680, f = 24592, 194, 126 and 99).  Rows that do not start on 128-byte lines cost both its waves two lines per piece:
+// less of them by what a compute unit fetches (d = 4656, f = 11680, T = 80: 70 and 81; d = 7120, f = 19216, T = 64: 119 and
+// 101; d = 7760, f = 24752, T = 96: 170 and 116).
+static bool swiglu_form_ok(const GemmArgs &a) {
+    if (a.M <= 16) return true;
+    const int64_t rows = 16 * kForms[kStoreForms + 1].mb, cols = 8 * kForms[kStoreForms + 1].nb;
+    const int64_t on_xcd = ((a.M + rows - 1) / rows) * (((a.N + cols - 1) / cols + 7) / 8);
+    return a.M <= 128 && on_xcd <= 9 * kComputeUnits / 16 && (a.K % 128 == 0 || on_xcd * a.K <= 450000);
+}
+
+// K-contiguous FP8 operands, the plain store without a per-column factor or the inference form's SwiGLU.
 double gemm_skinny_time(const GemmArgs &a, int *form) {
     const double never = 1e30;
     *form = 0;
     if (a.layout != 0 || a.part != 0 || a.a_fmt == kBF16 || a.col_scale) return never;
     if (a.epilogue == EPI_SWIGLU_Q) {
         *form = a.M <= 16 ? kStoreForms : kStoreForms + 1;
-        return a.M <= 128 ? 0.0 : never;
+        return swiglu_form_ok(a) ? 0.0 : never;
     }
     if (a.epilogue != EPI_STORE) return never;
     double best = form_time(a, 0);

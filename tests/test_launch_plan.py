@@ -93,3 +93,16 @@ def test_large_tiles_where_small_ones_were_measured_slower(M, N, K, layout):
 def test_small_tiles_where_large_ones_were_measured_slower(M, N, K, layout):
     """0.64 to 0.8 of the time in 256 x 256 tiles, or less."""
     assert _gemm(M, N, K, layout).tile == 128
+
+
+@pytest.mark.parametrize("T,d,f", [(96, 7680, 24592), (128, 8192, 28672), (80, 2048, 28672), (96, 7760, 24752), (64, 7120, 19216)])
+def test_wide_weights_do_not_take_the_few_rows_form_of_the_inference_form(T, d, f):
+    """1.14 to 1.6 times the time of gate/up in large tiles."""
+    assert ssg.ssg_mlp_gemm_plan(ssg.make_desc(T, d, f), ssg.SSG_PLAN_INFER_GATE_UP).tile == 256
+
+
+@pytest.mark.parametrize("T,d,f,rows", [(16, 4096, 11008, 16), (16, 8192, 28672, 16), (32, 7680, 24592, 64), (64, 4096, 11008, 64),
+                                        (96, 4864, 17760, 64), (128, 2048, 5504, 64), (80, 4656, 11680, 64), (128, 272, 2512, 64)])
+def test_short_batches_take_the_few_rows_form_of_the_inference_form(T, d, f, rows):
+    p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T, d, f), ssg.SSG_PLAN_INFER_GATE_UP)
+    assert (p.tile, p.rows) == (0, rows)
