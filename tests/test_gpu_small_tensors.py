@@ -82,3 +82,22 @@ def test_quantize_with_its_range_words_in_the_result_buffer(rows, cols, src_dtyp
         ssg.ssg_quantize(x, src_dtype, rows, cols, ssg.SSG_E4M3, ssg.SSG_SCALE_GIVEN, ssg.SSG_ROUND_EXACT_DIV, q, None, scale, amax)
         assert gu.scalar(amax) == np.float32(37.5) and gu.scalar(scale) == ref_s
         assert np.array_equal(gu.u8(q), ref_q)
+
+
+@pytest.mark.parametrize("n,src_dtype", [(16, ssg.SSG_BF16), (1 << 25, ssg.SSG_BF16), ((1 << 25) + 16, ssg.SSG_BF16),
+                                         (16, ssg.SSG_F32), (1 << 23, ssg.SSG_F32), ((1 << 23) + 16, ssg.SSG_F32)])
+def test_range_on_both_sides_of_looking_before_the_atomic(n, src_dtype):
+    """Up to 2^25 bf16 elements (four runs for each of 1024 workgroups), 2^23 fp32 ones (one unit for each of 512): every
+    workgroup's maximum goes to the word; above, only those that can raise it.  The largest element first, last, in the
+    middle; NaN beside it; all zeros."""
+    dt = torch.bfloat16 if src_dtype == ssg.SSG_BF16 else torch.float32
+    x = torch.randn(n, device=gu.DEV).to(dt)
+    amax = gu.empty_f32(1)
+    for at in (0, n - 1, n // 2):
+        v = x.clone()
+        v[at] = -37.5
+        v[(at + 5) % n] = float("nan")
+        ssg.ssg_amax(v, src_dtype, n, amax)
+        assert gu.scalar(amax) == np.float32(37.5), at
+    ssg.ssg_amax(torch.zeros(n, device=gu.DEV, dtype=dt), src_dtype, n, amax)
+    assert gu.scalar(amax) == 0.0
