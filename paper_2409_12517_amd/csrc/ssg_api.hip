@@ -79,7 +79,8 @@ bool w3_range_rides_along(const ssg_mlp_desc &desc) { return !desc.weights_cache
 // Split of dW3 between the two grouped launches of the backward (see gemm_group_split_sets), remembered for the last
 // few problem shapes: the replay costs a few milliseconds of host time.
 int dw3_split_sets(const ssg::GemmArgs &dh, const ssg::GemmArgs &dw3, const ssg::GemmArgs *const *second) {
-    struct Entry { int64_t M, N, K; int epilogue, c_f32, device, split; };
+    // (what the replay depends on: the three extents, dH's form, the output types of dW and of dX, the device)
+    struct Entry { int64_t M, N, K; int epilogue, c_f32, dx_f32, device, split; };
     static std::mutex mu;
     static Entry cache[8];
     static int used = 0, next = 0;
@@ -88,13 +89,14 @@ int dw3_split_sets(const ssg::GemmArgs &dh, const ssg::GemmArgs &dw3, const ssg:
     std::lock_guard<std::mutex> lock(mu);
     for (int i = 0; i < used; ++i) {
         const Entry &e = cache[i];
-        if (e.M == dh.M && e.N == dh.N && e.K == dh.K && e.epilogue == dh.epilogue && e.c_f32 == dw3.c_f32 && e.device == device)
+        if (e.M == dh.M && e.N == dh.N && e.K == dh.K && e.epilogue == dh.epilogue && e.c_f32 == dw3.c_f32 &&
+            e.dx_f32 == second[0]->c_f32 && e.device == device)
             return e.split;
     }
     int units = 0;
     if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) units = 0;
     const int split = ssg::gemm_group_split_sets(dh, dw3, second, 3, units);
-    cache[next] = Entry{dh.M, dh.N, dh.K, dh.epilogue, dw3.c_f32, device, split};
+    cache[next] = Entry{dh.M, dh.N, dh.K, dh.epilogue, dw3.c_f32, second[0]->c_f32, device, split};
     next = (next + 1) % 8;
     used = used < 8 ? used + 1 : 8;
     return split;

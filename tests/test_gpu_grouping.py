@@ -61,3 +61,34 @@ def test_single_launches_give_the_same_bits_as_grouped_launches(tmp_path):
         # bit patterns, so that -0.0 / NaN payloads count too
         assert torch.equal(a.view(torch.uint8) if a.dtype != torch.uint8 else a,
                            b.view(torch.uint8) if b.dtype != torch.uint8 else b), k
+
+
+@pytest.mark.parametrize("order", [(ssg.SSG_BF16, ssg.SSG_F32), (ssg.SSG_F32, ssg.SSG_BF16)])
+def test_dw3_is_shared_out_as_planned_for_each_output_type(order):
+    """The split depends on the time of dX's epilogue, so on y_dtype: 66 of 75 sets in the first launch with bf16 dX, 32
+    with fp32.  What the first launch really ran is read from its recorded flops, dH's and dW3's share of its own."""
+    T, d, f = (1408, 3712, 10208) if order[0] == ssg.SSG_BF16 else (1520, 3392, 10208)      # a shape of its own per order
+    gen = torch.Generator(device=gu.DEV).manual_seed(3)
+    x, dy = (torch.randn(T, d, device=gu.DEV, generator=gen).to(torch.bfloat16) for _ in range(2))
+    W = [torch.randn(s, device=gu.DEV, generator=gen).mul_(0.02).to(torch.bfloat16) for s in ((f, d), (f, d), (d, f))]
+    dW = [torch.empty(f * d, device=gu.DEV) for _ in range(3)]
+    y, dx = torch.empty(T, d, device=gu.DEV), torch.empty(T, d, device=gu.DEV)
+    plans = {}
+    ssg.ssg_profile_select(16)
+    ssg.ssg_profile_enable(4)
+    try:
+        for y_dtype in order:
+            desc = ssg.make_desc(T, d, f, y_dtype=y_dtype)
+            saved, work = gu.empty_u8(ssg.ssg_mlp_saved_bytes(desc)), gu.empty_u8(ssg.ssg_mlp_workspace_bytes(desc))
+            first, total = plans[y_dtype] = ssg.ssg_mlp_bwd_plan(desc, torch.cuda.get_device_properties(0).multi_processor_count)
+            ssg.ssg_mlp_fwd(desc, x, *W, y, saved)
+            ssg.ssg_mlp_bwd(desc, dy, saved, dx, *dW, work)
+            _, tags, flops = ssg.ssg_profile_read(4, with_bytes=True)
+            assert tags == [16]
+            tiles = -(-d // 256) * -(-f // 256)
+            share = flops[0] / (2.0 * T * d * f) - 1.0
+            assert abs(share - min(8 * first, tiles) / tiles) < 1e-9, (y_dtype, first, total, share)
+    finally:
+        ssg.ssg_profile_enable(0)
+        ssg.ssg_profile_select(-1)
+    assert plans[order[0]] != plans[order[1]], "the shapes were chosen so that the output type matters"
