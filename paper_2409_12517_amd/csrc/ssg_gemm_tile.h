@@ -174,7 +174,7 @@ __device__ __forceinline__ void map_tile(const GemmParams &p, int vblock, int &t
 // then every wave holds both halves of step k in registers, so the barrier both retires step k's ring
 // slots and publishes step k+1 (each wave first waits for its own DMA share).
 constexpr int kThreads = 256;
-constexpr int waves_per_simd(int WB) { return WB == 4 ? 1 : 2; }
+constexpr int waves_per_simd(int WB, int UNITS = 5) { return WB == 4 || UNITS > 5 ? 1 : 2; }     // what registers and LDS leave room for
 
 template <int N> __device__ __forceinline__ void wait_dma() {       // at most N direct-to-LDS loads still in flight
     static_assert(N == 4 || N == 8 || N == 16 || N == 20 || N == 24, "whole units of 4 or 8 loads");
@@ -783,7 +783,7 @@ inline unsigned set_workgroups(int WB) { return WB == 4 ? 8u : 32u; }
 
 // One GEMM per launch.
 template <int WB, int EPI, int AFMT, int PART = 0, int LAY = 0, int UNITS = 5>
-__global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_kernel(GemmParams p) {
+__global__ void __launch_bounds__(kThreads, waves_per_simd(WB, UNITS)) gemm_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB, UNITS)];
     const int b = (int)blockIdx.x, vb = (p.first_set + set_of<WB>(b)) * 8 + (b & 7);
     if (vb < p.tiles_m * p.tiles_n) gemm_tile<WB, EPI, AFMT, PART, LAY, UNITS>(p, vb, quarter_of<WB>(b), smem);
