@@ -16,8 +16,9 @@ import test_gpu_infer as ti  # noqa: E402
 import test_gpu_mlp as tm  # noqa: E402
 
 SMALL = [(128, 128, 128), (16, 144, 272), (144, 112, 16), (272, 128, 400), (112, 400, 256)]
-# 256 tiles of 256 x 256, one for every compute unit: the large tile, with a ragged last K step (1168 = 9 * 128 + 16),
-# a short last row and column of tiles; and 272 of them, one whole round and the rest in small tiles
+# 256 tiles of 256 x 256, one for every compute unit, with a ragged last K step (1168 = 9 * 128 + 16), a short last row and
+# column of tiles; and 272 of them.  (Sizes around the tiles' edges; which kernel a shape takes is asserted in
+# test_gpu_paths.py, with every route.)
 LARGE = [(4048, 4080, 1168), (4080, 4336, 1040)]
 
 
@@ -40,8 +41,7 @@ def test_contraction_at_tile_edges(M, N, K, layout):
 
 @pytest.mark.parametrize("T,d,f", [(144, 272, 400), (400, 144, 1168), (3856, 784, 4096)])
 def test_block_at_tile_edges(T, d, f):
-    """Odd extents in every direction; the last shape runs U, G in the large tile (16 x 32 tiles of 256 x 128 channels)
-    over a ragged K, and everything else in the small one."""
+    """Odd extents in every direction; the last shape has 16 x 32 tiles of 256 x 128 channels in U, G, over a ragged K."""
     inp = synth.make_inputs(T, d, f, seed=T + d + f)
     npi = tm._np_inputs(inp)
     blk = tm.Block(inp)
@@ -110,9 +110,8 @@ def test_input_gradient_where_one_gradient_flushes_to_zero(f, du_exp, dg_exp):
     assert 2.0 ** -126 < np.abs(ref).max() and np.abs(gu.f32(blk.dx) - ref).max() <= 2e-3 * np.abs(ref).max()
 
 
-# The few-rows kernel: rows per workgroup 16, 16, 32, 64, 64, 96 with 16, 32, 32, 32, 64, 64 columns (the form each
-# shape is given by its size); ragged K, a last workgroup with part of its columns, rows beyond the last one; K shorter
-# than one step for each wave; 4096 rows by 1024 columns take the 128 x 128 tile with the long ring (K ragged and whole)
+# Few rows with ragged K and a last workgroup with part of its columns, rows beyond the last one; K shorter than one step
+# for each wave; and 4096 rows by 1024 columns (K ragged and whole), in small tiles
 @pytest.mark.parametrize("M,N,K", [(16, 4112, 1040), (48, 2032, 1168), (64, 4080, 784), (112, 4080, 656), (176, 4080, 912),
                                    (272, 4000, 1168), (32, 48, 16), (16, 16, 272), (4096, 1040, 400), (4096, 1024, 512)])
 @pytest.mark.parametrize("a_fmt,c_dtype", [(ssg.SSG_E4M3, ssg.SSG_F32), (ssg.SSG_E5M2, ssg.SSG_BF16)])
@@ -153,7 +152,7 @@ def test_few_rows_of_the_inference_form(T_inf):
 
 
 def test_inference_form_in_whole_rounds_and_a_rest():
-    """9 x 33 tiles of 256 rows by 128 channels: 256 of them in large tiles, the other 41 in small ones."""
+    """9 x 33 tiles of 256 rows by 128 channels, 41 more than one round of large ones."""
     inp = synth.make_inputs(64, 272, 4112, seed=61)
     ti.check(ti.Infer(inp, T_inf=2064, seed_inf=9), tm._np_inputs(inp))
 
