@@ -10,8 +10,9 @@ namespace ssg {
 
 // The gate/up GEMM with an independent streaming pass in its grid.  1376 tiles on 256 compute units are 5.4
 // rounds: during the last one 160 units would idle.  The workgroups after the last tile take the per-channel range
-// of w3 (Section 4.4; it depends on no result of this GEMM and is needed only after it), so that pass costs no time
-// of its own.  A workgroup of this kernel owns a whole compute unit (registers, LDS), hence 16 loads in flight per lane.
+// of w3 (Section 4.4; it depends on no result of this GEMM and is needed only after it), so that pass costs little time
+// of its own.  A workgroup of this kernel owns a whole compute unit (registers, LDS) with large tiles and shares it with one
+// other with small ones, hence 16 loads in flight per lane.
 struct ColRangeParams {
     const uint16_t *src;
     int64_t rows, cols;
@@ -100,8 +101,9 @@ static int64_t tile_count(const GemmArgs &a, int WB) {
 
 // Estimated time of `tiles` small tiles of one GEMM, each of `cost` microseconds when two share a compute unit.
 static double small_tile_time(int64_t tiles, double cost) {
-    // a tile that has its compute unit to itself is bound by the latency of its loads: 0.44 per K step with a ring of
-    // nine, 0.58 when all compute units are at it.  With 257 to 512 of them the units that hold two decide, and these slow
+    // a tile that has its compute unit to itself is bound by the latency of its loads: taken as 0.44 per K step, 0.58 when
+    // all compute units are at it (long K, up to 160 tiles: 0.41 with a ring of five, as in the groups, 0.30 with one of
+    // nine; 0.47 and 0.41 up to 256; up to twice that where rows split cache lines).  With 257 to 512 of them the units that hold two decide, and these slow
     // each other down the more of them there are.  Beyond two rounds the tiles drift out of step and the rounds blur
     if (tiles <= kComputeUnits) return 5.5 + (cost - 5.5) * (tiles <= 160 ? 0.46 : 0.6);
     if (tiles <= 2 * kComputeUnits) return cost * (0.65 + 0.35 * (double)(tiles - kComputeUnits) / kComputeUnits);

@@ -16,13 +16,14 @@
 //           at 128 B); main loop about 60 % MFMA, but one workgroup's prologue and epilogue run under the other's main
 //           loop, and four times the tiles fill the chip where the large ones leave most of it idle.
 // Operand tiles are streamed global -> LDS with 16-byte direct-to-LDS loads (no staging registers) into a ring of five
-// 32 KB (16 KB) tiles.  A row of a tile is 128 bytes; the eight 16-byte chunks of a row are stored XOR-permuted by the
+// 32 KB (16 KB) tiles, or nine of 16 KB where a small tile has its compute unit to itself.  A row of a tile is 128 bytes; the eight 16-byte chunks of a row are stored XOR-permuted by the
 // row index so that the lanes that read the same logical chunk of different rows spread over all banks.
 //
 // Epilogues:
 //   STORE       C = acc / (sa*sb) [* col_scale[n]] [+ addend], bf16 or fp32.  A sum of two
-//               products (the input gradient) runs as two launches: the first leaves its
-//               scaled product as fp32 scratch, the second adds it before rounding.
+//               products (the input gradient) runs in one tile (PART = 3), or as two launches:
+//               the first leaves its scaled product as fp32 scratch, the second adds it before
+//               rounding (PART = 1, 2).
 //   SWIGLU      B tile = 128 (64) rows of W1 and the same rows of W2, so a wave
 //               holds u and g of the same (t,i): stores bf16 U, G and folds
 //               max_t |u * Swish(g)| into the per-channel maxima (Section 4.4).

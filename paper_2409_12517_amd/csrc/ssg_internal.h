@@ -175,7 +175,7 @@ void launch_gemm_skinny(const GemmArgs &a, int form, hipStream_t st);
 // rows and columns of the result per workgroup, steps of 128 bytes of K in a wave's ring
 void gemm_skinny_extent(const GemmArgs &a, int form, int *rows, int *cols, int *steps);
 bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st);       // the backward forms (called by launch_gemm)
-constexpr int kComputeUnits = 256;
+constexpr int kComputeUnits = 256;      // of an MI355X; the estimates of a launch's time are in its rounds
 // Tile of a launch that runs these GEMMs in one grid: 32 x 32 blocks per wave and direction, 4 (256 x 256 tiles) or 2 (128 x 128)
 // (of the last one: the share `last` of its tiles)
 int gemm_wave_blocks(const GemmArgs *const *list, int n, double last = 1.0);
