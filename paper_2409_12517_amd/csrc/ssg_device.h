@@ -142,8 +142,9 @@ __device__ __forceinline__ float sigmoid_fast_f32(float g) {
 }
 __device__ __forceinline__ void swiglu_grad_f32(float u, float g, float dh, float &du, float &dg) {
     const float sg = sigmoid_fast_f32(g);
-    du = dh * (g * sg);
-    dg = (dh * u) * (sg * (1.0f + g * (1.0f - sg)));
+    const float sw = g * sg;
+    du = dh * sw;
+    dg = (dh * u) * __fmaf_rn(sw, 1.0f - sg, sg);
 }
 
 // |x| of a non-NaN float as an unsigned integer orders like the float; NaN -> 0.

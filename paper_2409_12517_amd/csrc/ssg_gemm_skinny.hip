@@ -119,7 +119,8 @@ __global__ void __launch_bounds__(64 * KW) gemm_skinny_kernel(GemmParams p) {
                 part[(w * (16 * MB) + mb * 16 + (l >> 4) * 4 + i) * kPitch + nb * 16 + (l & 15)] = acc[mb][nb][i];
     __syncthreads();
 
-    const Dequant dq = inv_scale_product(p.sa, p.sb), dq2 = kDual ? inv_scale_product(p.sa, p.sb2) : dq;
+    const float s_a = p.sa ? *p.sa : 1.0f, s_b = p.sb ? *p.sb : 1.0f, s_b2 = kDual && p.sb2 ? *p.sb2 : 1.0f;
+    const Dequant dq = inv_scale_product(s_a, s_b), dq2 = kDual ? inv_scale_product(s_a, s_b2) : dq;
     // a thread finishes two neighbouring columns
     for (int e = threadIdx.x; e < 16 * MB * (8 * NCOL); e += 64 * KW) {
         const int row = e / (8 * NCOL), c = e % (8 * NCOL) * 2;

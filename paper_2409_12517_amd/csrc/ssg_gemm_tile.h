@@ -111,15 +111,18 @@ __device__ __forceinline__ void dma16_s(const uint8_t *base_uniform, uint32_t la
 // MFMA instructions at half the duration each, and K in bytes is twice the element count.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+// The weight's fragment goes first: of a 32 x 32 block a lane then holds row l & 31, and its registers 4q .. 4q+3 are the four
+// neighbouring columns 8q + 4 (l >> 5) .. + 3, which leave in one 16-byte (fp32) or 8-byte (bf16) access to LDS.  (With the
+// operands the other way round a lane holds one column, and every register is an access of its own.)
 template <int AFMT>
 __device__ __forceinline__ v16f mfma(const v8i &a, const v8i &b, const v16f &c) {
     if constexpr (AFMT == kBF16) {
         const v4i a_lo = {a[0], a[1], a[2], a[3]}, a_hi = {a[4], a[5], a[6], a[7]};
         const v4i b_lo = {b[0], b[1], b[2], b[3]}, b_hi = {b[4], b[5], b[6], b[7]};
-        const v16f t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a_lo), __builtin_bit_cast(v8bf, b_lo), c, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a_hi), __builtin_bit_cast(v8bf, b_hi), t, 0, 0, 0);
+        const v16f t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, b_lo), __builtin_bit_cast(v8bf, a_lo), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, b_hi), __builtin_bit_cast(v8bf, a_hi), t, 0, 0, 0);
     } else {
-        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, AFMT, 0, 0, 0, 0, 0);
+        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b, a, c, kE4M3, AFMT, 0, 0, 0, 0);
     }
 }
 
@@ -128,11 +131,8 @@ __device__ __forceinline__ v16f mfma(const v8i &a, const v8i &b, const v16f &c) 
 // subnormals, so it is formed in binary64 and handed out as a normal binary32 factor `a` (rounded once) times
 // an exact power of two `post`, which is 1 except in those extreme cases.
 struct Dequant { float a, post; };
-__device__ __forceinline__ Dequant inv_scale_product(const float *sa, const float *sb) {
-    double p = 1.0;
-    if (sa) p = (double)*sa;
-    if (sb) p *= (double)*sb;
-    const double r = 1.0 / p;
+__device__ __forceinline__ Dequant inv_scale_product(float sa, float sb) {
+    const double r = 1.0 / ((double)sa * (double)sb);
     Dequant d;
     d.post = 1.0f;
     if (r < 0x1p-100) d.post = 0x1p-96f;
@@ -140,6 +140,11 @@ __device__ __forceinline__ Dequant inv_scale_product(const float *sa, const floa
     d.a = (float)(r / (double)d.post);
     return d;
 }
+
+// Rows and columns of a tile beyond the matrix (both are multiples of 16, as are the tile's) repeat the matrix's last 16: their
+// results are copies of results inside, are stored over these, equal, and change no maximum, so that no access of the
+// epilogues needs a mask.
+template <class T> __device__ __forceinline__ T clamp16(T at, T extent) { return at < extent ? at : extent - 16 + (at & 15); }
 
 // Large tile number -> its place.  Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its
 // own L2, so give every XCD a contiguous range of a tile order in which any 32 consecutive tiles
@@ -217,6 +222,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int l = tid & 63;            // (not const: see the note at the epilogue)
     const int wm = w >> 1, wn = w & 1;
+    // the scales are read before anything else, so that nothing waits for them at the end
+    const float s_a = p.sa ? *p.sa : 1.0f, s_b = p.sb ? *p.sb : 1.0f, s_b2 = kDual && p.sb2 ? *p.sb2 : 1.0f;
+    const float s_a_ph2 = TWO ? *p.sa_ph2 : 1.0f, s_b_ph2 = TWO ? *p.sb_ph2 : 1.0f;
     int tile_m, tile_n;
     map_tile(p, vblock, tile_m, tile_n);
     constexpr int kTileN = kDual ? BN / 2 : BN;
@@ -253,26 +261,25 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         const int ck = ((j & 1) ? chunk_odd : chunk_even) * 16;
         const int kr = kmaj_row(j);
         const int ckm = kmaj_chunk(kr, l % kChunks) * 16;               // K-major: the chunk this lane fetches
-        // rows (K-major: columns) beyond the matrix are clamped to its last ones: they only feed results that are
-        // not stored
+        // rows (K-major: columns) beyond the matrix are those of its last 16 again
         if (AKM) {
             int64_t gm = m0 + ckm;
-            gm = gm < p.M ? gm : p.M - 16;
+            gm = clamp16(gm, p.M);
             a_lane[j] = (uint32_t)((int64_t)kr * p.M + gm);
         } else {
             int64_t gm = m0 + row;
-            gm = gm < p.M ? gm : p.M - 1;
+            gm = clamp16(gm, p.M);
             a_lane[j] = (uint32_t)(gm * p.K) + ck;
         }
         if (BKM) {
             int64_t gn = n0 + ckm;
-            gn = gn < p.N ? gn : p.N - 16;
+            gn = clamp16(gn, p.N);
             b_lane[j] = (uint32_t)((int64_t)kr * p.N + gn);
         } else {
             int64_t gn;
             if (kDual) gn = n0 + (row & (BN / 2 - 1));
             else gn = n0 + row;
-            gn = gn < p.N ? gn : p.N - 1;
+            gn = clamp16(gn, p.N);
             b_lane[j] = (uint32_t)(gn * p.K) + ck;
         }
     }
@@ -320,15 +327,14 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     const int nk = (int)((p.K + BK - 1) / BK);
     // the staging patch of the epilogue (one 32-row slab of a wave's accumulators at a time), also used where a
     // sum of two products changes the units of its accumulators
-    constexpr int kPitch = WN + 8;                       // floats; 4 rows apart lands on the other 32 banks
+    constexpr int kPitch = WN + 4;                       // floats; neighbouring rows are one 16-byte bank group apart
     float *stg = reinterpret_cast<float *>(smem) + w * (32 * kPitch);
-    // where accumulator register i of column block nb of a slab lies in the patch
-    auto stg_at = [&](int nb, int i) { return ((i >> 2) * 8 + (l >> 5) * 4 + (i & 3)) * kPitch + nb * 32 + (l & 31); };
+    // where accumulator registers 4q .. 4q+3 of column block nb of a slab lie in the patch
+    auto stg_at = [&](int nb, int q) { return reinterpret_cast<float4 *>(stg + (l & 31) * kPitch + (l >> 5) * 4 + nb * 32 + q * 8); };
     // a sum of two products starts with the one whose scales are larger: its accumulators change units by a factor of
     // at most 1, so that they cannot overflow however far apart the scales are
     bool swapped = false;
-    if (TWO) swapped = __builtin_amdgcn_readfirstlane((double)*p.sa_ph2 * (double)*p.sb_ph2 > (double)*p.sa * (double)*p.sb) != 0;
-    const float *sa_last = TWO && !swapped ? p.sa_ph2 : p.sa, *sb_last = TWO && !swapped ? p.sb_ph2 : p.sb;
+    if (TWO) swapped = __builtin_amdgcn_readfirstlane((double)s_a_ph2 * (double)s_b_ph2 > (double)s_a * (double)s_b) != 0;
 #pragma nounroll
     for (int phase = 0; phase < (TWO ? 2 : 1); ++phase) {
         const bool second = TWO && (phase == 1) != swapped;
@@ -492,7 +498,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             // back.  (Multiplying them in registers makes this compiler shuffle all 256 of them through the other
             // half of the register file and spill.)
             asm volatile("" : "+v"(l));      // as at the epilogue: keep this block's lane arithmetic inside the block
-            const double s1 = (double)*p.sa * (double)*p.sb, s2 = (double)*p.sa_ph2 * (double)*p.sb_ph2;
+            const double s1 = (double)s_a * (double)s_b, s2 = (double)s_a_ph2 * (double)s_b_ph2;
             // the ratio as a normal number times an exact power of two: far below 2^-126 it still meets accumulators of 2^28
             const double ratio = swapped ? s1 / s2 : s2 / s1;
             const float post = ratio < 0x1p-100 ? 0x1p-96f : 1.0f, rho = (float)(ratio / (double)post);
@@ -501,8 +507,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 #pragma unroll
                 for (int nb = 0; nb < WB; ++nb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        stg[stg_at(nb, i)] = acc[mb][nb][i];
+                    for (int q = 0; q < 4; ++q)
+                        *stg_at(nb, q) = make_float4(acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int q = 0; q < 4 * WB; ++q) {
@@ -516,8 +522,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 #pragma unroll
                 for (int nb = 0; nb < WB; ++nb) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        acc[mb][nb][i] = stg[stg_at(nb, i)];
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 v = *stg_at(nb, q);
+                        acc[mb][nb][4 * q] = v.x; acc[mb][nb][4 * q + 1] = v.y; acc[mb][nb][4 * q + 2] = v.z; acc[mb][nb][4 * q + 3] = v.w;
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -525,21 +533,41 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         }
     }
 
-    // ---- epilogue: per-wave LDS patch, one 32 x WN slab (mb) at a time
-    // (In the two-product form the loop above is executed twice; the compiler would compute the epilogue's lane
-    // arithmetic before it and spill it across.  The empty statement makes the lane id opaque from here on.)
-    if (TWO || (WB == 4 && !kBwd)) asm volatile("" : "+v"(l));
-    auto stage_slab = [&](int mb) {
+    // ---- epilogue: a slab of 32 rows of the wave's tile at a time.  In the large tile nothing runs beside it, so it is bound
+    // by its own instructions and their latencies: 16-byte accesses to the patch, all reads of a slab before their use, no
+    // mask on any access (see clamp16), and one copy of the code for all slabs, in a loop (straight-line code for four would
+    // be fetched once per tile and run once; dH's was 80 KB and is 15).  A slab of an fp32 weight gradient takes 1.4 us
+    // (5504 x 2048 x 1024 and larger, time stamps), with one register per access and a masked store after every read 3.1; of
+    // bf16 y 0.95 (1.7); dH's tile 52 us altogether (73); 11008 x 4096 x 1024 in fp32 61 us (79).
+    // (The empty statement makes the lane id opaque from here on: the compiler would compute the epilogue's lane arithmetic
+    // before the main loop and spill it across.)
+    asm volatile("" : "+v"(l));
+    constexpr int kSlabN = kDual ? WN / 2 : WN;          // columns of the result in a wave's tile
+    const int64_t wrow0 = m0 + wm * WN, wcol0 = n0 + wn * kSlabN;
+    const int rows_left = wcol0 < p.N && wrow0 < p.M ? (int)(p.M - wrow0 < WN ? p.M - wrow0 : WN) : 0;
+    const int cols_left = (int)(p.N - wcol0 < kSlabN ? p.N - wcol0 : kSlabN);
+    auto stage_slab = [&](int slab) {
 #pragma unroll
-        for (int nb = 0; nb < WB; ++nb)
+        for (int mb = 0; mb < WB; ++mb) {
+            if (slab != mb) continue;
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-                stg[stg_at(nb, i)] = acc[mb][nb][i];
+            for (int nb = 0; nb < WB; ++nb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *stg_at(nb, q) = make_float4(acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]);
+            asm volatile("; slab %0" :: "n"(mb));        // (else the compiler makes one block of them, indexing registers in memory)
+        }
     };
-    auto load8 = [&](int r, int c, float (&v)[8]) {
-        const float4 a = *reinterpret_cast<const float4 *>(stg + r * kPitch + c);
-        const float4 b = *reinterpret_cast<const float4 *>(stg + r * kPitch + c + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    // (The sum of two products runs its slabs unrolled: in a loop the compiler spills its accumulators.)
+    auto for_slabs = [&](auto &&work) {
+        if constexpr (TWO) {
+#pragma unroll
+            for (int mb = 0; mb < WB; ++mb)
+                if (32 * mb < rows_left) work(32 * mb);
+        } else {
+#pragma nounroll
+            for (int row = 0; row < rows_left; row += 32) work(row);
+        }
     };
     auto pack_bf16x8 = [&](const float (&v)[8]) {
         uint32_t q[4];
@@ -557,142 +585,158 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     };
 
     if (EPI == EPI_STORE || kBwd) {
-        // lane -> (row of the slab in kPasses passes of kRows rows, 8 columns c8 of the wave's WN)
-        constexpr int kLanes = WN / 8, kRows = 64 / kLanes, kPasses = 32 / kRows;
-        const int c8 = (l % kLanes) * 8;
-        const int64_t col = n0 + wn * WN + c8;
-        const bool col_ok = col < p.N;
-        const Dequant dq = inv_scale_product(sa_last, sb_last);
+        const Dequant dq = TWO && !swapped ? inv_scale_product(s_a_ph2, s_b_ph2) : inv_scale_product(s_a, s_b);
         const float alpha = dq.a;
         const bool post = dq.post != 1.0f;               // wave-uniform, false except for extreme scales
-        float f[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) f[k] = alpha;
-        if (p.col_scale && col_ok) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) f[k] = __fmul_rn(alpha, p.col_scale[col + k]);
-        }
         // running |.| maxima of the stored dU, dG as floats: rounding to bf16 is monotone, so the
         // maximum of the rounded values is the rounded maximum (taken once, at the end); fmaxf drops NaN
         float du_maxf = 0.0f, dg_maxf = 0.0f;
-        float q_su = 1.0f, q_sg = 1.0f;
-        if (EPI == EPI_SWIGLU_BWD_Q) {
-            q_su = *p.q_scale; q_sg = *p.q_scale2;
-            if (vblock == 0 && sub == 0 && tid == 0) { *p.q_scale_out = q_su; *p.q_scale_out2 = q_sg; }
-        }
-        uint4 ru[2][kPasses], rg[2][kPasses];
-        auto fetch_ug = [&](int mb) {                  // the slab's stored U, G (or addend)
-            if (!kBwd && !ADD) return;
+        if (EPI == EPI_STORE && !ADD && p.c_f32) {
+            // fp32 output: one 16-byte store per lane and pass, consecutive lanes on consecutive 16 bytes, so
+            // every store instruction writes whole 512-byte (WB = 2: 256-byte) row segments
+            constexpr int kLanes = WN / 4, kRows = 64 / kLanes, kPasses = 32 / kRows;
+            typedef float f32x4 __attribute__((ext_vector_type(4)));
+            const int lr = l / kLanes, lc = (l % kLanes) * 4, c = clamp16(lc, cols_left);
+            float f[4] = {alpha, alpha, alpha, alpha};
+            if (p.col_scale && rows_left > 0) {
 #pragma unroll
-            for (int pass = 0; pass < kPasses; ++pass) {
-                const int64_t row = m0 + wm * WN + mb * 32 + pass * kRows + l / kLanes;
-                if (col_ok && row < p.M) {
-                    const size_t at = (size_t)row * (size_t)p.N + (size_t)col;
-                    if (ADD) {
-                        ru[mb & 1][pass] = *reinterpret_cast<const uint4 *>(p.add + at);
-                        rg[mb & 1][pass] = *reinterpret_cast<const uint4 *>(p.add + at + 4);
-                    } else {
-                        ru[mb & 1][pass] = *reinterpret_cast<const uint4 *>(p.U + at);
-                        rg[mb & 1][pass] = *reinterpret_cast<const uint4 *>(p.G + at);
-                    }
-                }
+                for (int k = 0; k < 4; ++k) f[k] = __fmul_rn(alpha, p.col_scale[wcol0 + c + k]);
             }
-        };
-        fetch_ug(0);
+            float *out = reinterpret_cast<float *>(p.C) + (size_t)wrow0 * (size_t)p.N + (size_t)wcol0;
+            for_slabs([&](const int row) {
+                stage_slab(row >> 5);
+                f32x4 v[kPasses];
 #pragma unroll
-        for (int mb = 0; mb < WB; ++mb) {
-            if (mb + 1 < WB) fetch_ug(mb + 1);          // one slab ahead: the loads fly while this slab is worked
-            stage_slab(mb);
-            if (EPI == EPI_STORE && !ADD && p.c_f32) {
-                // fp32 output: one 16-byte store per lane and pass, consecutive lanes on consecutive 16 bytes, so
-                // every store instruction writes whole 512-byte (WB = 2: 256-byte) row segments
-                constexpr int kLanes4 = WN / 4, kRows4 = 64 / kLanes4;
-                const int c4 = (l % kLanes4) * 4;
-                const int64_t col4 = n0 + wn * WN + c4;
-                float f4[4] = {alpha, alpha, alpha, alpha};
-                if (p.col_scale && col4 < p.N) {
+                for (int pass = 0; pass < kPasses; ++pass) v[pass] = *reinterpret_cast<const f32x4 *>(stg + (pass * kRows + lr) * kPitch + lc);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) f4[k] = __fmul_rn(alpha, p.col_scale[col4 + k]);
-                }
+                for (int pass = 0; pass < kPasses; ++pass)
 #pragma unroll
-                for (int pass = 0; pass < 32 / kRows4; ++pass) {
-                    const int r = pass * kRows4 + l / kLanes4;
-                    const int64_t row = m0 + wm * WN + mb * 32 + r;
-                    const float4 a = *reinterpret_cast<const float4 *>(stg + r * kPitch + c4);
-                    if (col4 >= p.N || row >= p.M) continue;
-                    float *out = reinterpret_cast<float *>(p.C) + (size_t)row * (size_t)p.N + (size_t)col4;
-                    float4 o = make_float4(__fmul_rn(a.x, f4[0]), __fmul_rn(a.y, f4[1]), __fmul_rn(a.z, f4[2]), __fmul_rn(a.w, f4[3]));
-                    if (post) o = make_float4(o.x * dq.post, o.y * dq.post, o.z * dq.post, o.w * dq.post);
-                    if (p.nt_store) {
-                        typedef float f32x4 __attribute__((ext_vector_type(4)));
-                        __builtin_nontemporal_store(f32x4{o.x, o.y, o.z, o.w}, reinterpret_cast<f32x4 *>(out));
-                    } else {
-                        *reinterpret_cast<float4 *>(out) = o;
-                    }
-                }
-                continue;
-            }
-#pragma unroll
-            for (int pass = 0; pass < kPasses; ++pass) {
-                const int r = pass * kRows + l / kLanes;
-                const int64_t row = m0 + wm * WN + mb * 32 + r;
-                float v[8];
-                load8(r, c8, v);
-                if (!col_ok || row >= p.M) continue;
-                const size_t at = (size_t)row * (size_t)p.N + (size_t)col;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) v[k] = __fmul_rn(v[k], f[k]);
+                    for (int k = 0; k < 4; ++k) v[pass][k] = __fmul_rn(v[pass][k], f[k]);
                 if (post) {
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) v[k] *= dq.post;
+                    for (int pass = 0; pass < kPasses; ++pass) v[pass] *= dq.post;
                 }
-                if (ADD) {
-                    const uint4 a0 = ru[mb & 1][pass], a1 = rg[mb & 1][pass];
-                    const uint32_t aw[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+                f32x4 *at[kPasses];
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) v[k] = __fadd_rn(v[k], __uint_as_float(aw[k]));
-                }
-                if (EPI == EPI_STORE) {
-                    if (p.c_f32) {
-                        float *out = reinterpret_cast<float *>(p.C) + at;
-                        *reinterpret_cast<float4 *>(out) = make_float4(v[0], v[1], v[2], v[3]);
-                        *reinterpret_cast<float4 *>(out + 4) = make_float4(v[4], v[5], v[6], v[7]);
-                    } else {
-                        *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C) + at) = pack_bf16x8(v);
-                    }
+                for (int pass = 0; pass < kPasses; ++pass)
+                    at[pass] = reinterpret_cast<f32x4 *>(out + (size_t)(uint32_t)clamp16(row + pass * kRows + lr, rows_left) * (size_t)p.N + c);
+                if (p.nt_store) {
+#pragma unroll
+                    for (int pass = 0; pass < kPasses; ++pass) __builtin_nontemporal_store(v[pass], at[pass]);
                 } else {
-                    float u[8], g[8], du[8], dg[8];
-                    unpack_bf16x8(ru[mb & 1][pass], u);
-                    unpack_bf16x8(rg[mb & 1][pass], g);
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        swiglu_grad_f32(u[k], g[k], v[k], du[k], dg[k]);
-                        du_maxf = fmaxf(du_maxf, fabsf(du[k]));
-                        dg_maxf = fmaxf(dg_maxf, fabsf(dg[k]));
+                    for (int pass = 0; pass < kPasses; ++pass) *at[pass] = v[pass];
+                }
+            });
+        } else {
+            // a lane has eight columns of a row, the slab takes kPasses passes of kRows rows
+            constexpr int kLanes = WN / 8, kRows = 64 / kLanes, kPasses = 32 / kRows, kBatch = kPasses < 4 ? kPasses : 4;
+            const int lr = l / kLanes, lc = (l % kLanes) * 8, c = clamp16(lc, cols_left);
+            const size_t base = (size_t)wrow0 * (size_t)p.N + (size_t)wcol0;
+            auto at = [&](int row) { return base + (size_t)(uint32_t)clamp16(row + lr, rows_left) * (size_t)p.N + c; };
+            // the stored U, G (or the addend) of the slab that comes next: read while this one is worked, as its registers
+            // become free
+            uint4 ru[kPasses], rg[kPasses];
+            auto fetch = [&](int pass, int row) {
+                if (ADD) {
+                    ru[pass] = *reinterpret_cast<const uint4 *>(p.add + at(row));
+                    rg[pass] = *reinterpret_cast<const uint4 *>(p.add + at(row) + 4);
+                } else if (kBwd) {
+                    ru[pass] = *reinterpret_cast<const uint4 *>(p.U + at(row));
+                    rg[pass] = *reinterpret_cast<const uint4 *>(p.G + at(row));
+                }
+            };
+            if (rows_left > 0) {
+#pragma unroll
+                for (int pass = 0; pass < kPasses; ++pass) fetch(pass, pass * kRows);
+            }
+            float f[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) f[k] = alpha;
+            if (p.col_scale && rows_left > 0) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) f[k] = __fmul_rn(alpha, p.col_scale[wcol0 + c + k]);
+            }
+            float q_su = 1.0f, q_sg = 1.0f;
+            if (EPI == EPI_SWIGLU_BWD_Q) {
+                q_su = *p.q_scale; q_sg = *p.q_scale2;
+                if (vblock == 0 && sub == 0 && tid == 0) { *p.q_scale_out = q_su; *p.q_scale_out2 = q_sg; }
+            }
+            for_slabs([&](const int row) {
+                stage_slab(row >> 5);
+                const int next = row + 32 < rows_left ? row + 32 : row;      // (the last slab's are read again, for nothing)
+#pragma unroll
+                for (int first = 0; first < kPasses; first += kBatch) {
+                    if (kBwd) __builtin_amdgcn_sched_barrier(0);             // (the compiler would read all of the slab, and spill)
+                    float v[kBatch][8];
+#pragma unroll
+                    for (int b = 0; b < kBatch; ++b) {
+                        const float *src = stg + ((first + b) * kRows + lr) * kPitch + lc;
+                        const float4 lo = *reinterpret_cast<const float4 *>(src), hi = *reinterpret_cast<const float4 *>(src + 4);
+                        const float q[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) v[b][k] = __fmul_rn(q[k], f[k]);
                     }
-                    const uint4 qu = pack_bf16x8(du), qg = pack_bf16x8(dg);
-                    if (EPI == EPI_SWIGLU_BWD_Q) {
-                        // delayed scaling: the scales are known beforehand, so the bf16 values (formed only to
-                        // round as the stored-tensor path does) go straight to E5M2 codes
-                        unpack_bf16x8(qu, du);
-                        unpack_bf16x8(qg, dg);
+                    if (post) {
+#pragma unroll
+                        for (int b = 0; b < kBatch; ++b)
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) v[b][k] *= dq.post;
+                    }
+#pragma unroll
+                    for (int b = 0; b < kBatch; ++b) {
+                        const int pass = first + b;
+                        const size_t o = at(row + pass * kRows);
+                        if (EPI == EPI_STORE) {
+                            if (ADD) {
+                                const uint32_t aw[8] = {ru[pass].x, ru[pass].y, ru[pass].z, ru[pass].w, rg[pass].x, rg[pass].y, rg[pass].z, rg[pass].w};
+#pragma unroll
+                                for (int k = 0; k < 8; ++k) v[b][k] = __fadd_rn(v[b][k], __uint_as_float(aw[k]));
+                                fetch(pass, next + pass * kRows);
+                            }
+                            if (ADD && p.c_f32) {
+                                float *out = reinterpret_cast<float *>(p.C) + o;
+                                *reinterpret_cast<float4 *>(out) = make_float4(v[b][0], v[b][1], v[b][2], v[b][3]);
+                                *reinterpret_cast<float4 *>(out + 4) = make_float4(v[b][4], v[b][5], v[b][6], v[b][7]);
+                            } else {
+                                *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C) + o) = pack_bf16x8(v[b]);
+                            }
+                            continue;
+                        }
+                        float u[8], g[8], du[8], dg[8];
+                        unpack_bf16x8(ru[pass], u);
+                        unpack_bf16x8(rg[pass], g);
+                        fetch(pass, next + pass * kRows);
 #pragma unroll
                         for (int k = 0; k < 8; ++k) {
-                            du[k] = __fmul_rn(du[k], q_su);
-                            dg[k] = __fmul_rn(dg[k], q_sg);
+                            swiglu_grad_f32(u[k], g[k], v[b][k], du[k], dg[k]);
+                            du_maxf = fmaxf(du_maxf, fabsf(du[k]));
+                            dg_maxf = fmaxf(dg_maxf, fabsf(dg[k]));
                         }
-                        *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C) + at) = satcast_pk8<kE5M2>(du);
-                        *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C2) + at) = satcast_pk8<kE5M2>(dg);
-                        if (p.keep_u) {
-                            *reinterpret_cast<uint4 *>(p.keep_u + at) = qu;
-                            *reinterpret_cast<uint4 *>(p.keep_g + at) = qg;
+                        const uint4 qu = pack_bf16x8(du), qg = pack_bf16x8(dg);
+                        if (EPI == EPI_SWIGLU_BWD_Q) {
+                            // delayed scaling: the scales are known beforehand, so the bf16 values (formed only to
+                            // round as the stored-tensor path does) go straight to E5M2 codes
+                            unpack_bf16x8(qu, du);
+                            unpack_bf16x8(qg, dg);
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) {
+                                du[k] = __fmul_rn(du[k], q_su);
+                                dg[k] = __fmul_rn(dg[k], q_sg);
+                            }
+                            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C) + o) = satcast_pk8<kE5M2>(du);
+                            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C2) + o) = satcast_pk8<kE5M2>(dg);
+                            if (p.keep_u) {
+                                *reinterpret_cast<uint4 *>(p.keep_u + o) = qu;
+                                *reinterpret_cast<uint4 *>(p.keep_g + o) = qg;
+                            }
+                        } else {
+                            *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C) + o) = qu;
+                            *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C2) + o) = qg;
                         }
-                    } else {
-                        *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C) + at) = qu;
-                        *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C2) + at) = qg;
                     }
                 }
-            }
+            });
         }
         // bf16 bits of the rounded maxima (an infinite maximum, 0x7f80, is kept; NaN never enters)
         uint32_t du_max = pack_bf16x2(du_maxf, 0.0f) & 0x7fffu, dg_max = pack_bf16x2(dg_maxf, 0.0f) & 0x7fffu;
@@ -710,68 +754,109 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                 if (m) atomicMax(dst + ((vblock * (16 / (WB * WB)) + sub) % kAmaxSlots) * kAmaxSlotStride, m << 16);
             }
         }
-    } else {   // EPI_SWIGLU, EPI_SWIGLU_Q: the slab's first WN / 2 columns are u, the others g of the same channels
+    } else {   // EPI_SWIGLU, EPI_SWIGLU_Q: the first half of the column blocks are u, the others g of the same channels
         constexpr int kLanes = WN / 16, kRows = 64 / kLanes, kPasses = 32 / kRows;
-        const int c8 = (l % kLanes) * 8;
-        const int64_t col = n0 + wn * (WN / 2) + c8;
-        const bool col_ok = col < p.N;
-        const Dequant dq_u = inv_scale_product(p.sa, p.sb), dq_g = inv_scale_product(p.sa, p.sb2);
+        const int lr = l / kLanes, lc = (l % kLanes) * 8, c = clamp16(lc, cols_left);
+        const Dequant dq_u = inv_scale_product(s_a, s_b), dq_g = inv_scale_product(s_a, s_b2);
         const float alpha_u = dq_u.a, alpha_g = dq_g.a;
         const bool post = dq_u.post != 1.0f || dq_g.post != 1.0f;
-        float hmaxf[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // fmaxf drops NaN
+        // A lane holds u and g of the same elements, so the product is formed in registers; the patch only turns what is
+        // stored (U and G side by side, or the codes) into whole pieces of rows.
+        constexpr int NBU = WB / 2;                              // column blocks of u
+        constexpr bool kCodes = EPI == EPI_SWIGLU_Q;
+        constexpr int kRowBytes = kCodes ? WN / 2 + 8 : 2 * WN + 16;
+        uint8_t *patch = smem + w * (32 * kRowBytes);
+        const size_t base = (size_t)wrow0 * (size_t)p.N + (size_t)wcol0;
+        float hmaxf[NBU][16];                                    // fmaxf drops NaN
 #pragma unroll
-        for (int mb = 0; mb < WB; ++mb) {
-            stage_slab(mb);
+        for (int nb = 0; nb < NBU; ++nb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) hmaxf[nb][i] = 0.0f;
+#pragma nounroll
+        for (int row = 0; row < rows_left; row += 32) {
+            float t[WB][16];
+#pragma unroll
+            for (int mb = 0; mb < WB; ++mb) {
+                if (row != 32 * mb) continue;
+#pragma unroll
+                for (int nb = 0; nb < WB; ++nb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) t[nb][i] = __fmul_rn(acc[mb][nb][i], nb < NBU ? alpha_u : alpha_g);
+            }
+            if (post) {
+#pragma unroll
+                for (int nb = 0; nb < WB; ++nb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) t[nb][i] *= nb < NBU ? dq_u.post : dq_g.post;
+            }
+#pragma unroll
+            for (int nb = 0; nb < NBU; ++nb)
+#pragma unroll
+                for (int q = 0; q < 4; q += 2) {                 // eight columns: two groups of four
+                    float u[8], g[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) { u[k] = t[nb][4 * q + k]; g[k] = t[nb + NBU][4 * q + k]; }
+                    if (kCodes) {
+                        // inference: the factor s_i is already inside u (folded into w1), so the product is cast as
+                        // it stands; nothing else is stored
+                        float h[8];
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) h[k] = swiglu_f32(u[k], g[k]);
+                        const uint2 code = satcast_pk8<kE4M3>(h);
+                        uint8_t *at = patch + (l & 31) * kRowBytes + (l >> 5) * 4 + nb * 32 + q * 8;
+                        *reinterpret_cast<uint32_t *>(at) = code.x;
+                        *reinterpret_cast<uint32_t *>(at + 8) = code.y;
+                        continue;
+                    }
+                    const uint4 qu = pack_bf16x8(u), qg = pack_bf16x8(g);
+                    uint8_t *at = patch + (l & 31) * kRowBytes + (l >> 5) * 8 + nb * 64 + q * 16;
+                    *reinterpret_cast<uint2 *>(at) = make_uint2(qu.x, qu.y);
+                    *reinterpret_cast<uint2 *>(at + 16) = make_uint2(qu.z, qu.w);
+                    *reinterpret_cast<uint2 *>(at + WN) = make_uint2(qg.x, qg.y);
+                    *reinterpret_cast<uint2 *>(at + WN + 16) = make_uint2(qg.z, qg.w);
+                    unpack_bf16x8(qu, u);
+                    unpack_bf16x8(qg, g);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) hmaxf[nb][4 * q + k] = fmaxf(hmaxf[nb][4 * q + k], fabsf(swiglu_f32(u[k], g[k])));
+                }
 #pragma unroll
             for (int pass = 0; pass < kPasses; ++pass) {
-                const int r = pass * kRows + l / kLanes;
-                const int64_t row = m0 + wm * WN + mb * 32 + r;
-                float u[8], g[8];
-                load8(r, c8, u);
-                load8(r, WN / 2 + c8, g);
-                if (!col_ok || row >= p.M) continue;
-                const size_t at = (size_t)row * (size_t)p.N + (size_t)col;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    u[k] = __fmul_rn(u[k], alpha_u);
-                    g[k] = __fmul_rn(g[k], alpha_g);
+                const uint8_t *src = patch + (pass * kRows + lr) * kRowBytes;
+                const size_t o = base + (size_t)(uint32_t)clamp16(row + pass * kRows + lr, rows_left) * (size_t)p.N + c;
+                if (kCodes) {
+                    *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C) + o) = *reinterpret_cast<const uint2 *>(src + lc);
+                } else {
+                    *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C) + o) = *reinterpret_cast<const uint4 *>(src + 2 * lc);
+                    *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C2) + o) = *reinterpret_cast<const uint4 *>(src + WN + 2 * lc);
                 }
-                if (post) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) { u[k] *= dq_u.post; g[k] *= dq_g.post; }
-                }
-                if (EPI == EPI_SWIGLU_Q) {
-                    // inference: the factor s_i is already inside u (folded into w1), so the product is cast as
-                    // it stands; nothing else is stored
-                    float h[8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) h[k] = swiglu_f32(u[k], g[k]);
-                    *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C) + at) = satcast_pk8<kE4M3>(h);
-                    continue;
-                }
-                const uint4 qu = pack_bf16x8(u), qg = pack_bf16x8(g);
-                *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C) + at) = qu;
-                *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.C2) + at) = qg;
-                unpack_bf16x8(qu, u);
-                unpack_bf16x8(qg, g);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) hmaxf[k] = fmaxf(hmaxf[k], fabsf(swiglu_f32(u[k], g[k])));
             }
         }
-        uint32_t hmax[8];                                // non-negative floats order like their bit patterns
+        if (EPI == EPI_SWIGLU) {
+            // The 32 lanes of a half wave hold 16 NBU channels each, over a row each.  At every step a lane keeps half of its
+            // channels and gives the other half to its partner, so that in the end each has the maximum of one channel:
+            // one atomic instruction for all of them.  (Non-negative floats order like their bit patterns.)
+            uint32_t m[16 * NBU];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) hmax[k] = __float_as_uint(hmaxf[k]);
+            for (int nb = 0; nb < NBU; ++nb)
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
+                for (int i = 0; i < 16; ++i) m[16 * nb + i] = __float_as_uint(hmaxf[nb][i]);
 #pragma unroll
-            for (int off = kLanes; off < 64; off <<= 1) {
-                const uint32_t o = (uint32_t)__shfl_xor((int)hmax[k], off, 64);
-                hmax[k] = hmax[k] > o ? hmax[k] : o;
+            for (int half = 8 * NBU; half > 0; half >>= 1) {
+                const bool upper = (l & half) != 0;
+#pragma unroll
+                for (int i = 0; i < half; ++i) {
+                    const uint32_t keep = upper ? m[half + i] : m[i], give = upper ? m[i] : m[half + i];
+                    const uint32_t got = (uint32_t)__shfl_xor((int)give, half, 64);
+                    m[i] = keep > got ? keep : got;
+                }
             }
-        if (EPI == EPI_SWIGLU && l < kLanes && col_ok) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (hmax[k]) atomicMax(&p.camax_bits[col + k], hmax[k]);
+            if (NBU == 1) {
+                const uint32_t o = (uint32_t)__shfl_xor((int)m[0], 16, 64);
+                m[0] = m[0] > o ? m[0] : o;
+            }
+            const int i = l & 15, nb = (l >> 4) & (NBU - 1);
+            const int64_t channel = n0 + wn * (WN / 2) + nb * 32 + (i >> 2) * 8 + (l >> 5) * 4 + (i & 3);
+            if (channel < p.N && m[0] && (NBU == 2 || (l & 16) == 0)) atomicMax(&p.camax_bits[channel], m[0]);
         }
     }
 }
