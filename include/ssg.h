@@ -113,7 +113,8 @@ typedef struct {
     int32_t tile;            /* edge of the output tiles: 256 or 128; 0: the kernel for few rows */
     int32_t ring;            /* operand tiles in LDS; few rows: K steps of 128 bytes in a wave's ring */
     int32_t whole_sets;      /* > 0 (tile = 128): the first whole_sets * 8 tiles of 256 x 256 run as such, in a launch before */
-    int32_t rows, cols;      /* few rows: rows and columns of the result per workgroup (else 0) */
+    int32_t rows, cols;      /* few rows: rows and columns of the result per workgroup (else 0; SSG_PLAN_BWD_SECOND: rows = 2
+                              * where the two products of dX run in tiles of their own) */
     int32_t launches;        /* GEMM launches */
 } ssg_gemm_plan;
 ssg_status ssg_gemm_fp8_plan(ssg_fp8_format a_fmt, int a_kmajor, int b_kmajor, int64_t M, int64_t N, int64_t K,

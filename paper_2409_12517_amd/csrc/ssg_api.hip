@@ -52,8 +52,8 @@ void backward_gemm_shapes(const ssg_mlp_desc &desc, BackwardGemms &b) {
     b.dw1.epilogue = ssg::EPI_STORE; b.dw1.a_fmt = ssg::kE5M2; b.dw1.M = f; b.dw1.N = dm; b.dw1.K = T; b.dw1.layout = 2;
     b.dw1.c_f32 = dw_f32;
     b.dw2 = b.dw1;
-    b.dx.part = ssg::gemm_sum_in_one_launch(b.dx, b.dw1) ? 3 : 1;
-    b.dx.c_f32 = b.dx.part == 3 ? desc.y_dtype == SSG_F32 : 1;
+    b.dx.part = ssg::gemm_sum_form(b.dx, b.dw1);
+    b.dx.c_f32 = b.dx.part >= 3 ? desc.y_dtype == SSG_F32 : 1;
     if (desc.w3_layer_bf16) {
         // Section 4.3: dH = dY W3 and dW3 = dY^T h_b on bf16 operands, every operand with its contraction index contiguous
         b.dh.epilogue = ssg::EPI_SWIGLU_BWD; b.dh.a_fmt = ssg::kBF16; b.dh.layout = 0;
@@ -183,11 +183,17 @@ WorkLayout work_layout(const ssg_mlp_desc &d) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align256(bytes); return at; };
     L.scalars = take(W_COUNT * 4);
-    L.partials = take(3 * ssg::kAmaxSlotWords * 4);     // range words of dY, slotted running maxima of dU, dG
+    // the input gradient: its fp32 first product; where both have tiles of their own, their results and the words in which
+    // they meet
+    BackwardGemms bg;
+    backward_gemm_shapes(d, bg);
+    const bool halves = bg.dx.part == 4;
+    // range words of dY, slotted running maxima of dU, dG
+    L.partials = take((3 * ssg::kAmaxSlotWords + (halves ? ssg::gemm_arrival_words(T, dm) : 0)) * 4);
     L.dy_q = take(T * dm);
     L.dU = take(T * f * 2); L.dG = take(T * f * 2);
     L.du_q = take(T * f); L.dg_q = take(T * f);
-    L.dx_tmp = take(T * dm * 4);                        // fp32 first product of the input gradient
+    L.dx_tmp = take(halves ? 2 * ssg::gemm_partial_floats(T, dm) * 4 : T * dm * 4);
     L.dyT = take(d.w3_layer_bf16 ? T * dm * 2 : 0);     // bf16 dY transposed (last layer left in bf16)
     L.total = o;
     return L;
@@ -942,7 +948,7 @@ ssg_status ssg_mlp_bwd_plan(const ssg_mlp_desc *desc, int32_t compute_units, int
     *dw3_sets_total = all;
     *dw3_sets_first = all;
     // the split exists only where both grouped launches are built: FP8 operands, the input gradient in one launch
-    if (gemm_grouping_enabled() && !desc->w3_layer_bf16 && bg.dx.part == 3) {
+    if (gemm_grouping_enabled() && !desc->w3_layer_bf16 && bg.dx.part >= 3) {
         const ssg::GemmArgs *second[3] = {&bg.dx, &bg.dw1, &bg.dw2};
         *dw3_sets_first = ssg::gemm_group_split_sets(bg.dh, bg.dw3, second, 3, compute_units);
     }
@@ -965,7 +971,7 @@ ssg_status ssg_mlp_gemm_plan(const ssg_mlp_desc *desc, int which, ssg_gemm_plan 
     }
     BackwardGemms bg;
     backward_gemm_shapes(*desc, bg);
-    const bool grouped_b = gemm_grouping_enabled() && bg.dx.part == 3, grouped = grouped_b && !desc->w3_layer_bf16;
+    const bool grouped_b = gemm_grouping_enabled() && bg.dx.part >= 3, grouped = grouped_b && !desc->w3_layer_bf16;
     const ssg::GemmArgs *group_a[2] = {&bg.dh, &bg.dw3}, *group_b[4] = {&bg.dx, &bg.dw1, &bg.dw2, &bg.dw3};
     const int all = ssg::gemm_tile_sets(bg.dw3);
     const int split = grouped ? ssg::gemm_group_split_sets(bg.dh, bg.dw3, group_b, 3, ssg::kComputeUnits) : all;
@@ -975,8 +981,9 @@ ssg_status ssg_mlp_gemm_plan(const ssg_mlp_desc *desc, int which, ssg_gemm_plan 
         else out->launches = 2;
     } else {
         *out = describe(bg.dx);
+        out->rows = bg.dx.part == 4 ? 2 : 0;
         if (grouped_b) out->tile = 64 * (split < all ? ssg::gemm_group_wave_blocks(group_b, 4, split) : ssg::gemm_group_wave_blocks(group_b, 3, -1));
-        else out->launches = bg.dx.part == 3 ? 3 : 4;
+        else out->launches = bg.dx.part >= 3 ? 3 : 4;
     }
     return SSG_OK;
 }
@@ -1038,7 +1045,7 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
     // launches, the first product through fp32 scratch
     float *dx_tmp = reinterpret_cast<float *>(wk + Wl.dx_tmp);
     ssg::GemmArgs &g4a = bg.dx;
-    const bool dx_one = g4a.part == 3;
+    const bool dx_one = g4a.part >= 3;
     g4a.A = wk + Wl.du_q; g4a.B = sv + L.w1_q; g4a.sa = wsc + W_SDU; g4a.sb = sc + S_SW1; g4a.C = dx_tmp;
     ssg::GemmArgs g4b = g4a;
     g4b.part = 2;
@@ -1046,6 +1053,7 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
     g4b.C = dx; g4b.c_f32 = desc->y_dtype == SSG_F32;
     if (dx_one) {
         g4a.C = dx;
+        if (g4a.part == 4) { g4a.partials = dx_tmp; g4a.arrivals = wpart + 3 * ssg::kAmaxSlotWords; }
         g4a.A_ph2 = g4b.A; g4a.B_ph2 = g4b.B; g4a.sa_ph2 = g4b.sa; g4a.sb_ph2 = g4b.sb;
     }
     // a14: dW1, dW2
@@ -1076,7 +1084,7 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
     // zeroed by the call's first kernel: the slots of dU's and dG's ranges, and the scalars that nothing writes under
     // delayed scaling (under current scaling every scalar of the view is written)
     ssg::ZeroWords zero;
-    zero.p[0] = part_du; zero.n[0] = 2 * ssg::kAmaxSlotWords;
+    zero.p[0] = part_du; zero.n[0] = (unsigned)(2 * ssg::kAmaxSlotWords + (g4a.part == 4 ? ssg::gemm_arrival_words(T, dm) : 0));
     static_assert(W_AMAX_DU == W_AMAX_DY + 1 && W_AMAX_DG == W_AMAX_DY + 2, "one run of words");
     zero.p[1] = wscb + W_AMAX_DY; zero.n[1] = delayed ? 3 : 0;
     int dy_range_count = 0;

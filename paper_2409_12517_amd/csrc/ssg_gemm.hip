@@ -53,11 +53,12 @@ bool gemm_args_ok(const GemmArgs &a) {
     // the backward forms are built for the block's own use: gradient operand E5M2, weight operand K-major
     if (bwd && a.a_fmt != kBF16 && (a.layout != 1 || a.a_fmt != kE5M2)) return false;
     if (a.epilogue == EPI_SWIGLU_BWD_Q && (!a.q_scale || !a.q_scale2 || !a.q_scale_out || !a.q_scale_out2)) return false;
-    if (a.part < 0 || a.part > 3) return false;
+    if (a.part < 0 || a.part > 4) return false;
     if (a.part != 0 && (a.layout != 1 || a.a_fmt != kE5M2)) return false;
     if ((a.part == 2) != (a.add != nullptr)) return false;
     if (a.part == 1 && !a.c_f32) return false;
-    if ((a.part == 3) != (a.A_ph2 != nullptr) || (a.part == 3 && (!a.B_ph2 || !a.sa || !a.sb || !a.sa_ph2 || !a.sb_ph2))) return false;
+    if (a.part == 4 && (!a.partials || !a.arrivals)) return false;
+    if ((a.part >= 3) != (a.A_ph2 != nullptr) || (a.part >= 3 && (!a.B_ph2 || !a.sa || !a.sb || !a.sa_ph2 || !a.sb_ph2))) return false;
     if ((a.keep_u != nullptr) != (a.keep_g != nullptr) || (a.keep_u && a.epilogue != EPI_SWIGLU_BWD_Q)) return false;
     if (bwd && (!a.U || !a.G || !a.C2 || !a.amax_bits || !a.amax_bits2)) return false;
     return true;
@@ -96,7 +97,7 @@ double gemm_tile_cost(const GemmArgs &a, int WB) {
 
 static int64_t tile_count(const GemmArgs &a, int WB) {
     const int64_t edge = tile_edge(WB), cols = is_dual(a) ? edge / 2 : edge;
-    return ((a.M + edge - 1) / edge) * ((a.N + cols - 1) / cols);
+    return ((a.M + edge - 1) / edge) * ((a.N + cols - 1) / cols) * (a.part == 4 ? 2 : 1);
 }
 
 // Estimated time of `tiles` small tiles of one GEMM, each of `cost` microseconds when two share a compute unit.
@@ -114,7 +115,7 @@ static double small_tile_time(int64_t tiles, double cost) {
 // Operand bytes that have to come from memory once, and how many of the two operands have rows that do not start on
 // 128-byte lines, so that a small tile's 128-byte pieces of them span two lines each.
 static double operand_bytes(const GemmArgs &a) {
-    return (double)(a.M + (is_dual(a) ? 2 : 1) * a.N) * (double)a.K * (a.a_fmt == kBF16 ? 2.0 : 1.0) * (a.part == 3 ? 2.0 : 1.0);
+    return (double)(a.M + (is_dual(a) ? 2 : 1) * a.N) * (double)a.K * (a.a_fmt == kBF16 ? 2.0 : 1.0) * (a.part >= 3 ? 2.0 : 1.0);
 }
 static int split_line_operands(const GemmArgs &a) {
     return ((a.layout == 2 ? a.M : a.K) % 128 != 0) + ((a.layout >= 1 ? a.N : a.K) % 128 != 0);
@@ -171,7 +172,30 @@ static double grid_time(const GemmArgs *const *list, int n, int WB, double last 
     return std::max(1.15 * longest, sum / kComputeUnits);
 }
 
+// Estimated microseconds of the second backward group, dX in form `part` and two weight gradients, in either tile.  dX's tiles
+// are dealt first; where there are few of them they decide, else the work does.  Large tile: 1.36 per K step; a long tile
+// beside many short ones that write takes up to 1.35 times as long.  Small tile: 0.93 per K step where two share a compute
+// unit, 0.44 for one that has it to itself, which dX's are once the weight gradients have ended, if they end early; a tenth more for each operand
+// that splits lines; fp32 gradients leave at 3.6 MB/us.
+static double dx_group_time(GemmArgs dx, const GemmArgs &dw, int part, int WB) {
+    dx.part = part;
+    const double kx = k_steps(dx), kw = k_steps(dw), nx = (double)tile_count(dx, WB), nw = 2.0 * (double)tile_count(dw, WB);
+    if (WB == 4) {
+        const double cx = 2.5 + 1.36 * kx + (part == 4 ? 8.0 : 5.0), cw = 2.5 + 1.36 * kw + (dw.c_f32 ? 7.5 : 5.0);
+        return 4.0 + std::max(1.35 * cx, (nx * cx + nw * cw) / kComputeUnits + 0.4 * cw);
+    }
+    const double slots = 2.0 * kComputeUnits, split = 1.0 + 0.1 * split_line_operands(dx), shared = 0.93 * split, alone = 0.44 * split;
+    const double end_x = 3.5 + (part == 4 ? 3.0 : 2.0), cx = end_x + shared * kx, cw = 6.0 + shared * kw;
+    const double beside = std::max(nw * cw / slots, 2.0 * (double)(dw.M * dw.N) * (dw.c_f32 ? 4.0 : 2.0) / 3.6e6);
+    const double contended = beside > 0.5 * shared * kx ? kx : std::min(kx, beside / shared);      // (steps beside another tile)
+    return 6.0 + std::max(end_x + shared * contended + alone * (kx - contended), nx * cx / slots + beside + (nx + nw > slots ? 0.5 * cw : 0.0));
+}
+
 int gemm_wave_blocks(const GemmArgs *const *list, int n, double last) {
+    if (list[0]->part == 4) {
+        const GemmArgs &dw = *list[n > 1 ? 1 : 0];       // (alone: the tile does not change its bits; taken as with weight gradients of its own size)
+        return dx_group_time(*list[0], dw, 4, 2) < dx_group_time(*list[0], dw, 4, 4) ? 2 : 4;
+    }
     for (int i = 0; i < n; ++i) {
         if (list[i]->a_fmt == kBF16 || list[i]->part == 1 || list[i]->part == 2) return 4;      // not built in the small tile
         if (list[i]->part == 3 && !sum_in_large_tile_ok(list[i]->K)) return 2;
@@ -196,20 +220,47 @@ static int full_round_sets(const GemmArgs &a, double whole) {
 // The input gradient of a hidden width that is no multiple of 128: in one launch of small tiles together with the
 // weight gradients, or as two launches of large tiles through fp32 scratch and the weight gradients each on its own
 // (T = 4096, d = 4096, f = 11024, the whole step: 1982 us against 1870; T = 2048, d = 3072, f = 8208: 745 against 884).
-bool gemm_sum_in_one_launch(const GemmArgs &dx, const GemmArgs &dw) {
-    if (sum_in_large_tile_ok(dx.K)) return true;
+size_t gemm_arrival_words(int64_t M, int64_t N) {
+    return (size_t)(4 * ((M + tile_edge(4) - 1) / tile_edge(4)) * ((N + tile_edge(4) - 1) / tile_edge(4)));
+}
+static int sum_form_unsplit(const GemmArgs &dx, const GemmArgs &dw, double *separate_time) {
+    *separate_time = 0.0;
+    if (sum_in_large_tile_ok(dx.K)) return 3;
     GemmArgs sum = dx, half = dx;
     sum.part = 3; half.part = 1; half.c_f32 = 1;
     const GemmArgs *one[3] = {&sum, &dw, &dw};
     auto rounds = [](const GemmArgs &a) { return gemm_tile_cost(a, 4) * (double)((tile_count(a, 4) + kComputeUnits - 1) / kComputeUnits); };
     const double separate = 2.0 * rounds(half) + 2.0 * std::min(rounds(dw), small_tile_time(tile_count(dw, 2), gemm_tile_cost(dw, 2)));
-    return grid_time(one, 3, 2) < separate;
+    *separate_time = separate;
+    return grid_time(one, 3, 2) < separate ? 3 : 1;
+}
+
+// Each product of dX in tiles of its own, which meet where the second of them is done: for short batches, whose few tiles of
+// both products (172 K steps at d = 4096, f = 11008) are still running when the weight gradients have long ended.  Up to 96
+// large tiles, twice that as halves; beyond, the tiles of dX fill the chip by themselves and the products' way through memory
+// (the one, 256 KB per large tile, out and in) only costs (2048 x 4096, f = 11008, 128 tiles: 339 us either way; 4096 x 4096:
+// 559 whole, 590 in halves).  Measured, dX, dW1 and dW2 in one launch, whole and in halves: T = 1024, d = 4096, f = 11008 302
+// and 212 us (large tiles); 512 225 and 167, 128 200 and 142 (small); 2048, 3072, 8192 225 and 204; 1040, 1024, 2736 34 and
+// 28; 256, 1024, 2736 32 and 23.  Not where the estimates are close: 2048, 2048, 5504 112 and 113, 2048, 1024, 2736 39 and 46.
+int gemm_sum_form(const GemmArgs &dx, const GemmArgs &dw) {
+    double separate;
+    const int whole = sum_form_unsplit(dx, dw, &separate);
+    GemmArgs sum = dx;
+    sum.part = 0;
+    if (tile_count(sum, 4) > 3 * kComputeUnits / 8) return whole;
+    double unsplit = separate;
+    if (whole == 3) {
+        sum.part = 3;
+        const GemmArgs *list[3] = {&sum, &dw, &dw};
+        unsplit = dx_group_time(sum, dw, 3, gemm_wave_blocks(list, 3));
+    }
+    return dx_group_time(sum, dw, 4, 2) < 0.95 * unsplit || dx_group_time(sum, dw, 4, 4) < 0.82 * unsplit ? 4 : whole;
 }
 
 int gemm_profile_tag(const GemmArgs &a) {
     // 2 * epilogue + A format; the halves of a sum of two products run as two launches get 9 and 10, the sum in
     // one launch 11; the gate/up GEMM with the column range pass in its grid 18
-    if (a.part) return 8 + a.part;
+    if (a.part) return 8 + (a.part == 4 ? 3 : a.part);
     if (a.tail_src) return 18;
     if (a.a_fmt == kBF16) return a.epilogue == EPI_STORE ? 20 : 21;
     return 2 * (a.epilogue == EPI_SWIGLU_BWD_Q ? (int)EPI_SWIGLU_BWD : a.epilogue) + a.a_fmt;

@@ -23,10 +23,11 @@ namespace ssg {
 // Workgroups are dealt in sets of 8 large tiles (see set_of: one per XCD, so that vblock % 8 stays the XCD inside each
 // GEMM and map_tile's per-XCD patches survive); member i runs sets [first[i], first[i] + sets[i]) of its GEMM -- a GEMM
 // may be split between two launches at a set boundary.
+// (second group: dX is member 0, or, where its products have tiles of their own, members 0 and 1; dW1, dW2, dW3 are 2 to 4)
 struct GroupParams {
-    GemmParams p[4];
-    int sets[4];
-    int first[4];
+    GemmParams p[5];
+    int sets[5];
+    int first[5];
     int tile_blocks;        // workgroups of all sets
 };
 
@@ -44,21 +45,24 @@ __global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_group_dh_dw
     }
 }
 
-// dX (sum of two products in one tile: the long tiles, dealt first), then dW1, dW2 and the rest of dW3.
-template <int WB>
+// dX (PART = 3: the sum of two products in one tile; 4: the products in tiles of their own.  The long tiles, dealt first),
+// then dW1, dW2 and the rest of dW3.
+template <int WB, int PART>
 __global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_group_dx_dw_kernel(GroupParams g, ScalingUpdate update) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB)];
     int G = set_of<WB>((int)blockIdx.x);
     const int x = (int)(blockIdx.x & 7), q = quarter_of<WB>((int)blockIdx.x);
-    if (G < g.sets[0]) {
-        const int vb = G * 8 + x;
-        if (vb < g.p[0].tiles_m * g.p[0].tiles_n) gemm_tile<WB, EPI_STORE, kE5M2, 3, 1>(g.p[0], vb, q, smem);
+    const int dx_sets = g.sets[0] + (PART == 4 ? g.sets[1] : 0);
+    if (G < dx_sets) {
+        const int half = PART == 4 && G >= g.sets[0] ? 1 : 0;
+        const int vb = (G - half * g.sets[0]) * 8 + x;
+        if (vb < g.p[0].tiles_m * g.p[0].tiles_n) gemm_tile<WB, EPI_STORE, kE5M2, PART, 1>(g.p[half], vb, q, smem);
         return;
     }
-    G -= g.sets[0];
-    int m = 1;
-    if (G >= g.sets[1]) { G -= g.sets[1]; m = 2; if (G >= g.sets[2]) { G -= g.sets[2]; m = 3; } }
-    if (m == 3 && G >= g.sets[3]) {
+    G -= dx_sets;
+    int m = 2;
+    if (G >= g.sets[2]) { G -= g.sets[2]; m = 3; if (G >= g.sets[3]) { G -= g.sets[3]; m = 4; } }
+    if (m == 4 && G >= g.sets[4]) {
         // the workgroups after the last tile: the ranges of dY, dU, dG are complete and nothing here reads the state
         const int k = (int)blockIdx.x - g.tile_blocks;
         if (k < update.count && threadIdx.x < 64) scaling_update_wave(update, k, (int)threadIdx.x);
@@ -83,7 +87,7 @@ bool gemm_group_ok(const GemmArgs *const *list, int n) {
     }
     for (int i = 1; i < n; ++i)
         if (!is_wgrad(*list[i])) return false;
-    return list[0]->epilogue == EPI_STORE && list[0]->part == 3;
+    return list[0]->epilogue == EPI_STORE && list[0]->part >= 3;
 }
 
 // ---- where to split a weight gradient between the two grouped launches of the backward ------------------------
@@ -113,12 +117,17 @@ int gemm_group_split_sets(const GemmArgs &dh, const GemmArgs &dw_split, const Ge
     const GemmParams ph = make_gemm_params(dh), pw = make_gemm_params(dw_split);
     const int tiles_w = pw.tiles_m * pw.tiles_n;
     double cost_b[4]; int tiles_b[4];
+    // (where dX runs in halves, its tiles are short and the stores weigh more: 7.5 fp32, 4.5 bf16, 8 where the halves meet)
+    const bool halves = second[0]->part == 4;
+    auto cost_of = [&](const GemmArgs &a) {
+        return gemm_tile_cost(a, 4) + (!halves ? 0.0 : (a.c_f32 ? -2.5 : -1.5) + (a.part == 4 ? 8.0 : 0.0));
+    };
     for (int i = 0; i < n_second; ++i) {
         const GemmParams p = make_gemm_params(*second[i]);
-        cost_b[i] = gemm_tile_cost(*second[i], 4); tiles_b[i] = p.tiles_m * p.tiles_n;
+        cost_b[i] = cost_of(*second[i]); tiles_b[i] = p.tiles_m * p.tiles_n * (second[i]->part == 4 ? 2 : 1);
     }
-    cost_b[n_second] = gemm_tile_cost(dw_split, 4);
-    const double cost_a[2] = {gemm_tile_cost(dh, 4), gemm_tile_cost(dw_split, 4)};
+    cost_b[n_second] = cost_of(dw_split);
+    const double cost_a[2] = {gemm_tile_cost(dh, 4), cost_of(dw_split)};
     std::vector<double> heap;
     // the predicted time is a step function of the split.  Of the longest run of equally good splits take a point a
     // quarter of the run below its upper end: measured, the second launch behaves like a fluid (its tiles have
@@ -147,10 +156,24 @@ int gemm_group_split_sets(const GemmArgs &dh, const GemmArgs &dw_split, const Ge
 }
 
 template <int WB>
-static void launch_group(const GroupParams &g, int n, int epilogue, dim3 grid, const ScalingUpdate &update, hipStream_t st) {
-    if (n >= 3) hipLaunchKernelGGL(gemm_group_dx_dw_kernel<WB>, dim3(grid.x + (unsigned)update.count), dim3(kThreads), 0, st, g, update);
+static void launch_group_wb(const GroupParams &g, int part, int epilogue, dim3 grid, const ScalingUpdate &update, hipStream_t st) {
+    const dim3 with_update(grid.x + (unsigned)update.count);
+    if (part == 4) hipLaunchKernelGGL((gemm_group_dx_dw_kernel<WB, 4>), with_update, dim3(kThreads), 0, st, g, update);
+    else if (part == 3) hipLaunchKernelGGL((gemm_group_dx_dw_kernel<WB, 3>), with_update, dim3(kThreads), 0, st, g, update);
     else if (epilogue == EPI_SWIGLU_BWD) hipLaunchKernelGGL((gemm_group_dh_dw3_kernel<WB, EPI_SWIGLU_BWD>), grid, dim3(kThreads), 0, st, g);
     else hipLaunchKernelGGL((gemm_group_dh_dw3_kernel<WB, EPI_SWIGLU_BWD_Q>), grid, dim3(kThreads), 0, st, g);
+}
+static bool launch_group(GroupParams &g, int wb, int part, int epilogue, int tag, double flops, const ScalingUpdate &update, hipStream_t st) {
+    int sets = 0;
+    for (int m = 0; m < 5; ++m) sets += g.sets[m];
+    if (sets == 0) return true;
+    const dim3 grid((unsigned)sets * set_workgroups(wb));
+    g.tile_blocks = (int)grid.x;
+    profile_before(tag, st, flops);
+    if (wb == 4) launch_group_wb<4>(g, part, epilogue, grid, update, st);
+    else launch_group_wb<2>(g, part, epilogue, grid, update, st);
+    profile_after(st);
+    return true;
 }
 
 // The split member is the last one of either group: the first launch runs its sets [0, split), the second the rest.
@@ -164,42 +187,36 @@ int gemm_group_wave_blocks(const GemmArgs *const *list, int n, int split_sets) {
     return gemm_wave_blocks(list, n, (double)last_member_sets(n, split_sets, all) / (double)all);
 }
 
+// The member that list[i] is (the second group keeps member 1 for the second product of dX).
+static int member_of(int part, int i) { return part && i > 0 ? i + 1 : i; }
+
 bool launch_gemm_group(const GemmArgs *const *list, int n, int split_sets, hipStream_t st, const ScalingUpdate &update) {
     if (!gemm_group_ok(list, n)) return false;
+    const int part = list[0]->part;
     GroupParams g;
-    int total = 0;
     double flops = 0.0;
-    for (int i = 0; i < 4; ++i) {
-        g.p[i] = make_gemm_params(*list[i < n ? i : 0]);
-        g.sets[i] = i < n ? sets_of(g.p[i]) : 0;
-        g.first[i] = 0;
+    for (int m = 0; m < 5; ++m) { g.p[m] = make_gemm_params(*list[0]); g.sets[m] = 0; g.first[m] = 0; }
+    for (int i = 0; i < n; ++i) {
+        const int m = member_of(part, i);
+        g.p[m] = make_gemm_params(*list[i]);
+        g.sets[m] = sets_of(g.p[m]);
     }
-    const int all = g.sets[n - 1];
-    g.sets[n - 1] = last_member_sets(n, split_sets, all);
-    if (n == 4) g.first[3] = all - g.sets[3];
-    const int wb = gemm_group_wave_blocks(list, n, split_sets);
+    const int last = member_of(part, n - 1), all = g.sets[last];
+    g.sets[last] = last_member_sets(n, split_sets, all);
+    if (n == 4) g.first[last] = all - g.sets[last];
     // The fp32 weight gradients of the second launch go out through non-temporal stores: nothing reads them before
     // the optimizer, and kept out of the caches they leave in place what the passes after this launch read (measured
     // at the Llama2-7B shape: -10 us per step, in the launches that follow, not in this one).  In the first launch,
     // beside dH's epilogue traffic, the same stores cost 3-7 us: left as they are.
-    if (n >= 3)
-        for (int i = 1; i < n; ++i) g.p[i].nt_store = 1;
+    for (int m = 2; m < 5; ++m) g.p[m].nt_store = part != 0;
     for (int i = 0; i < n; ++i) {
         // flops of the tiles this launch runs (a last set may be partly beyond the GEMM's tile count)
-        const int tiles = g.p[i].tiles_m * g.p[i].tiles_n;
-        int hi = (g.first[i] + g.sets[i]) * 8, lo = g.first[i] * 8;
-        hi = hi < tiles ? hi : tiles; lo = lo < tiles ? lo : tiles;
+        const int m = member_of(part, i), tiles = g.p[m].tiles_m * g.p[m].tiles_n;
+        const int hi = std::min((g.first[m] + g.sets[m]) * 8, tiles), lo = std::min(g.first[m] * 8, tiles);
         flops += gemm_flops(*list[i]) * (double)(hi - lo) / (double)tiles;
-        total += g.sets[i];
     }
-    if (total == 0) return true;
-    const dim3 grid((unsigned)total * set_workgroups(wb));
-    profile_before(n == 2 ? 16 : 17, st, flops);
-    g.tile_blocks = (int)grid.x;
-    if (wb == 4) launch_group<4>(g, n, list[0]->epilogue, grid, update, st);
-    else launch_group<2>(g, n, list[0]->epilogue, grid, update, st);
-    profile_after(st);
-    return true;
+    if (part == 4) { g.p[1] = make_gemm_params(*list[0], 1); g.sets[1] = g.sets[0]; }
+    return launch_group(g, gemm_group_wave_blocks(list, n, split_sets), part, list[0]->epilogue, n == 2 ? 16 : 17, flops, update, st);
 }
 
 // The backward forms launched on their own (a.part != 0, or one of the SwiGLU-backward epilogues); the
@@ -217,6 +234,11 @@ bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st) {
     const GemmParams p = make_gemm_params(a);
     const dim3 grid((unsigned)sets_of(p) * set_workgroups(4));
     const GemmArgs *one = &a;
+    if (a.part == 4) {                                   // the second group without its weight gradients
+        GroupParams g;
+        for (int m = 0; m < 5; ++m) { g.p[m] = make_gemm_params(a, m == 1); g.sets[m] = m < 2 ? sets_of(p) : 0; g.first[m] = 0; }
+        return launch_group(g, gemm_wave_blocks(&one, 1), 4, a.epilogue, gemm_profile_tag(a), gemm_flops(a), {}, st);
+    }
     profile_before(gemm_profile_tag(a), st, gemm_flops(a));
     if (a.epilogue == EPI_SWIGLU_BWD && a.a_fmt == kBF16)
         hipLaunchKernelGGL((gemm_kernel<4, EPI_SWIGLU_BWD, kBF16, 0, 0>), grid, dim3(kThreads), 0, st, p);

@@ -70,6 +70,11 @@ struct GemmParams {
     // PART = 3 (a sum of two products in one tile): operands and scales of the second product, same shapes
     const uint8_t *A_ph2, *B_ph2;
     const float *sa_ph2, *sb_ph2;
+    // PART = 4 (one product of such a sum): where this product leaves its scaled result if it is done first, where the other
+    // one did (fp32, a tile after the other), and a word per tile, zero at the start, that counts those done
+    float *mine;
+    const float *other;
+    uint32_t *arrivals;
     int nt_store;        // EPI_STORE, fp32 output: 1 = non-temporal stores (the output is not read again soon)
 };
 
@@ -182,6 +187,12 @@ __device__ __forceinline__ void map_tile(const GemmParams &p, int vblock, int &t
 constexpr int kThreads = 256;
 constexpr int waves_per_simd(int WB, int UNITS = 5) { return WB == 4 || UNITS > 5 ? 1 : 2; }     // what registers and LDS leave room for
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes that a workgroup on another XCD reads, or wrote, while the kernel runs: past this XCD's own L2 (sc1).
+constexpr int kThrough = 16;
+constexpr int kBufferWord3 = 0x00020000;              // of a raw buffer's descriptor: 32-bit data
+
 template <int N> __device__ __forceinline__ void wait_dma() {       // at most N direct-to-LDS loads still in flight
     static_assert(N == 4 || N == 8 || N == 16 || N == 20 || N == 24, "whole units of 4 or 8 loads");
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -201,6 +212,7 @@ template <int N> __device__ __forceinline__ void wait_dma() {       // at most N
 // 1 = B "K-major" (stored [K,N], N contiguous); 2 = both K-major (A stored [K,M]).  A K-major tile is streamed
 // into LDS as 128 rows of K x 256 (128) bytes and its MFMA fragments are read with the transposing LDS load, so the
 // backward contractions read the forward's quantized tensors as they are: no transposed copies exist.
+// PART = 4: one product of such a sum, the tiles of the other being elsewhere in the grid; the later of the two adds.
 // PART = 3: the sum of two products in one tile -- the K loop runs twice, over (A, B) and then over (A_ph2, B_ph2)
 // of the same shapes (or the other way round), and the accumulators are rescaled by the ratio of the two dequantization
 // factors in between, so that one epilogue with the last factor finishes both.
@@ -210,7 +222,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     constexpr int NI = 2 * WB;                         // DMA instructions of 1 KB per wave and unit; fragment reads per half step
     constexpr int kUnits = UNITS, AHEAD = (UNITS - 1) / 2;   // operand tiles are issued AHEAD K steps before their use
     constexpr int kChunks = BM / 16;                   // 16-byte chunks of a K-major row
-    constexpr bool ADD = PART == 2;
+    constexpr bool HALF = PART == 4, ADD = PART == 2;
     constexpr bool TWO = PART == 3;
     constexpr bool kTwoWhole = TWO && WB == 4;         // no general loop body there (see sum_in_large_tile_ok)
     static_assert(!TWO || EPI == EPI_STORE, "a sum of two products ends in the plain store epilogue");
@@ -537,8 +549,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     // by its own instructions and their latencies: 16-byte accesses to the patch, all reads of a slab before their use, no
     // mask on any access (see clamp16), and one copy of the code for all slabs, in a loop (straight-line code for four would
     // be fetched once per tile and run once; dH's was 80 KB and is 15).  A slab of an fp32 weight gradient takes 1.4 us
-    // (5504 x 2048 x 1024 and larger, time stamps), with one register per access and a masked store after every read 3.1; of
-    // bf16 y 0.95 (1.7); dH's tile 52 us altogether (73); 11008 x 4096 x 1024 in fp32 61 us (79).
+    // (11008 x 4096 x 1024, time stamps), with one register per access and a masked store after every read 3.1; that
+    // contraction 61 us (79).  dH's epilogue at T = 4096, d = 4096, f = 11008 takes 23.5 us (33): every compute unit is in it
+    // at once, 134 MB of U, G, dU, dG at 5.7 TB/s.
     // (The empty statement makes the lane id opaque from here on: the compiler would compute the epilogue's lane arithmetic
     // before the main loop and spill it across.)
     asm volatile("" : "+v"(l));
@@ -546,7 +559,47 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     const int64_t wrow0 = m0 + wm * WN, wcol0 = n0 + wn * kSlabN;
     const int rows_left = wcol0 < p.N && wrow0 < p.M ? (int)(p.M - wrow0 < WN ? p.M - wrow0 : WN) : 0;
     const int cols_left = (int)(p.N - wcol0 < kSlabN ? p.N - wcol0 : kSlabN);
+    const Dequant dq = TWO && !swapped ? inv_scale_product(s_a_ph2, s_b_ph2) : inv_scale_product(s_a, s_b);
+    const uint32_t tile = (uint32_t)(vblock * (16 / (WB * WB)) + sub);
+    f32x4 theirs[HALF ? WB : 1][4];                      // HALF: the other product's registers of the slab that comes next
+    auto fetch_theirs = [&](int slab) {
+        if constexpr (HALF) {
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.other) + (size_t)tile * (BM * BN), 0, BM * BN * 4, kBufferWord3);
+#pragma unroll
+            for (int nb = 0; nb < WB; ++nb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    theirs[nb][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, tid * 16, ((slab * WB + nb) * 4 + q) * (kThreads * 16), kThrough));
+        }
+    };
+    // the slab's accumulators, each times a factor, in ordinary registers (one block of code for each slab, which the
+    // compiler must not make one that indexes them)
+    auto scaled_slab = [&](int slab, float (&t)[WB][16], float first, float second) {
+#pragma unroll
+        for (int mb = 0; mb < WB; ++mb) {
+            if (slab != mb) continue;
+#pragma unroll
+            for (int nb = 0; nb < WB; ++nb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) t[nb][i] = __fmul_rn(acc[mb][nb][i], nb < WB / 2 ? first : second);
+        }
+    };
     auto stage_slab = [&](int slab) {
+        if constexpr (HALF) {
+            float t[WB][16];
+            scaled_slab(slab, t, dq.a, dq.a);
+#pragma unroll
+            for (int nb = 0; nb < WB; ++nb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float v[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[k] = __fadd_rn(t[nb][4 * q + k] * dq.post, theirs[nb][q][k]);
+                    *stg_at(nb, q) = make_float4(v[0], v[1], v[2], v[3]);
+                }
+            if (32 * (slab + 1) < rows_left) fetch_theirs(slab + 1);
+            return;
+        }
 #pragma unroll
         for (int mb = 0; mb < WB; ++mb) {
             if (slab != mb) continue;
@@ -585,17 +638,49 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     };
 
     if (EPI == EPI_STORE || kBwd) {
-        const Dequant dq = TWO && !swapped ? inv_scale_product(s_a_ph2, s_b_ph2) : inv_scale_product(s_a, s_b);
-        const float alpha = dq.a;
-        const bool post = dq.post != 1.0f;               // wave-uniform, false except for extreme scales
+        const float alpha = HALF ? 1.0f : dq.a;          // (HALF: the scales enter where the two products meet)
+        const bool post = !HALF && dq.post != 1.0f;      // wave-uniform, false except for extreme scales
         // running |.| maxima of the stored dU, dG as floats: rounding to bf16 is monotone, so the
         // maximum of the rounded values is the rounded maximum (taken once, at the end); fmaxf drops NaN
         float du_maxf = 0.0f, dg_maxf = 0.0f;
+        if constexpr (HALF) {
+            // The product that is done first leaves its result, each lane its own registers (whole 1 KB pieces per wave, whatever
+            // the tile's edges), the other adds it to its own.  Either may be the first: the sum of two numbers is the same in
+            // either order.  Neither waits for the other.
+            uint32_t *const arrivals = p.arrivals + tile, *const shared_word = reinterpret_cast<uint32_t *>(smem + 4 * 32 * kPitch * 4);
+            if (tid == 0) *shared_word = __hip_atomic_load(arrivals, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            bool last = __builtin_amdgcn_readfirstlane(*shared_word) != 0u;
+            if (!last) {
+                const __amdgpu_buffer_rsrc_t mine = __builtin_amdgcn_make_buffer_rsrc(p.mine + (size_t)tile * (BM * BN), 0, BM * BN * 4, kBufferWord3);
+                for_slabs([&](const int row) {
+                    float t[WB][16];
+                    scaled_slab(row >> 5, t, dq.a, dq.a);
+#pragma unroll
+                    for (int nb = 0; nb < WB; ++nb)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            f32x4 v;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) v[k] = t[nb][4 * q + k] * dq.post;
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), mine, tid * 16,
+                                                                   (((row >> 5) * WB + nb) * 4 + q) * (kThreads * 16), kThrough);
+                        }
+                });
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's part is where the others see it
+                __syncthreads();
+                if (tid == 0) *shared_word = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __syncthreads();
+                last = __builtin_amdgcn_readfirstlane(*shared_word) != 0u;      // the other one came in between
+                if (!last) return;
+            }
+            asm volatile("" ::: "memory");
+            if (rows_left > 0) fetch_theirs(0);
+        }
         if (EPI == EPI_STORE && !ADD && p.c_f32) {
             // fp32 output: one 16-byte store per lane and pass, consecutive lanes on consecutive 16 bytes, so
             // every store instruction writes whole 512-byte (WB = 2: 256-byte) row segments
             constexpr int kLanes = WN / 4, kRows = 64 / kLanes, kPasses = 32 / kRows;
-            typedef float f32x4 __attribute__((ext_vector_type(4)));
             const int lr = l / kLanes, lc = (l % kLanes) * 4, c = clamp16(lc, cols_left);
             float f[4] = {alpha, alpha, alpha, alpha};
             if (p.col_scale && rows_left > 0) {
@@ -775,14 +860,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 #pragma nounroll
         for (int row = 0; row < rows_left; row += 32) {
             float t[WB][16];
-#pragma unroll
-            for (int mb = 0; mb < WB; ++mb) {
-                if (row != 32 * mb) continue;
-#pragma unroll
-                for (int nb = 0; nb < WB; ++nb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) t[nb][i] = __fmul_rn(acc[mb][nb][i], nb < NBU ? alpha_u : alpha_g);
-            }
+            scaled_slab(row >> 5, t, alpha_u, alpha_g);
             if (post) {
 #pragma unroll
                 for (int nb = 0; nb < WB; ++nb)
@@ -879,13 +957,14 @@ __global__ void __launch_bounds__(kThreads, waves_per_simd(WB, UNITS)) gemm_kern
 // of the one-launch sum)
 inline double gemm_flops(const GemmArgs &a) {
     const bool dual = a.epilogue == EPI_SWIGLU || a.epilogue == EPI_SWIGLU_Q;
-    return 2.0 * (double)a.M * (double)a.N * (double)a.K * (dual ? 2.0 : 1.0) * (a.part == 3 ? 2.0 : 1.0);
+    return 2.0 * (double)a.M * (double)a.N * (double)a.K * (dual ? 2.0 : 1.0) * (a.part >= 3 ? 2.0 : 1.0);
 }
 
 inline int sets_of(const GemmParams &p) { return (p.tiles_m * p.tiles_n + 7) / 8; }
 
 // Host side: the kernel's parameter block from the launch interface's argument set.
-inline GemmParams make_gemm_params(const GemmArgs &a) {
+// (part = 4: of its first or second product)
+inline GemmParams make_gemm_params(const GemmArgs &a, int half = 0) {
     GemmParams p;
     p.A = a.A; p.B = a.B; p.B2 = a.B2;
     p.M = a.M; p.N = a.N;
@@ -900,6 +979,14 @@ inline GemmParams make_gemm_params(const GemmArgs &a) {
     p.q_scale = a.q_scale; p.q_scale2 = a.q_scale2; p.q_scale_out = a.q_scale_out; p.q_scale_out2 = a.q_scale_out2;
     p.keep_u = (uint16_t *)a.keep_u; p.keep_g = (uint16_t *)a.keep_g;
     p.A_ph2 = a.A_ph2; p.B_ph2 = a.B_ph2; p.sa_ph2 = a.sa_ph2; p.sb_ph2 = a.sb_ph2;
+    p.mine = nullptr; p.other = nullptr; p.arrivals = a.arrivals;
+    if (a.part == 4) {
+        if (half == 1) { p.A = a.A_ph2; p.B = a.B_ph2; p.sa = a.sa_ph2; p.sb = a.sb_ph2; }
+        if (a.partials) {
+            p.mine = a.partials + (half == 1 ? gemm_partial_floats(a.M, a.N) : 0);
+            p.other = a.partials + (half == 1 ? 0 : gemm_partial_floats(a.M, a.N));
+        }
+    }
     p.nt_store = 0;
     constexpr int edge = tile_edge(4);
     p.tiles_m = (int)((a.M + edge - 1) / edge);

@@ -130,11 +130,15 @@ struct GemmArgs {
     //   part = 2: `add` (that scratch) is added to this product, scaled, before rounding into C
     //   part = 3: the whole sum in one launch: C = A B^T / (sa sb) + A_ph2 B_ph2^T / (sa_ph2 sb_ph2), the second pair of
     //             operands of the same shapes, formats and layout; all four scale pointers are required
+    //   part = 4: as 3, but each product in tiles of its own, twice as many of half the length; `partials` (twice
+    //             gemm_partial_floats) and `arrivals` (a word per tile, zeroed by the caller, gemm_arrival_words of them) are scratch
     // (parts are built for the input gradient: A E5M2, layout 1)
     int part = 0;
     const float *add = nullptr;
     const uint8_t *A_ph2 = nullptr, *B_ph2 = nullptr;
     const float *sa_ph2 = nullptr, *sb_ph2 = nullptr;
+    float *partials = nullptr;
+    uint32_t *arrivals = nullptr;
     // dequantization: alpha = 1 / (sa * sb); null pointer = 1
     const float *sa = nullptr, *sb = nullptr, *sb2 = nullptr;   // sb2: scale of B2
     const float *col_scale = nullptr;   // optional [N] factor (EPI_STORE, EPI_SWIGLU_BWD)
@@ -180,12 +184,15 @@ constexpr int kComputeUnits = 256;      // of an MI355X; the estimates of a laun
 // (of the last one: the share `last` of its tiles)
 int gemm_wave_blocks(const GemmArgs *const *list, int n, double last = 1.0);
 double gemm_tile_cost(const GemmArgs &a, int WB);               // estimated microseconds of one tile
-// whether the input gradient runs as part = 3 (in one grid with weight gradients like `dw`) or as parts 1 and 2
-bool gemm_sum_in_one_launch(const GemmArgs &dx, const GemmArgs &dw);
+// how the input gradient is best run: as part = 3 or 4 (in one grid with weight gradients like `dw`), or as parts 1 and 2 (1)
+int gemm_sum_form(const GemmArgs &dx, const GemmArgs &dw);
+// part = 4: a word for every 128 x 128 tile, and 64 KB
+size_t gemm_arrival_words(int64_t M, int64_t N);
+inline size_t gemm_partial_floats(int64_t M, int64_t N) { return gemm_arrival_words(M, N) * (128 * 128); }
 int gemm_profile_tag(const GemmArgs &a);
 // Several independent GEMMs in one grid, the workgroups of one following those of the other.  Built groups:
 //   { dH (EPI_SWIGLU_BWD or _Q), weight gradient (EPI_STORE, layout 2, A E5M2) }
-//   { input gradient as one launch (part = 3), one to three weight gradients }
+//   { input gradient as one launch (part = 3 or 4), one to three weight gradients }
 // gemm_group_ok tells whether `list` is one of them with every member valid; launch_gemm_group returns false
 // (nothing launched) otherwise.  Timing tags: 16 and 17.  `update` (second group only; count > 0): workgroups at the end
 // of the grid enter these ranges into the history of delayed scaling.
