@@ -1,12 +1,17 @@
 // Adam step with the first moment stored in E4M3 and the second in E5M2 (Section 5).
 //
-// Two HBM-bound passes over a flat parameter tensor, 16 elements per lane per trip (16-byte
-// accesses for the codes as well as for the gradient and the weights):
+// Two HBM-bound passes over a flat parameter tensor:
 //   pass 1  new moments from the stored codes and the gradient, their ranges (max|m|, max v)
 //           into 64 slotted atomics each;
 //   pass 2  the same moments again (bit-identical: same inputs, same operations), the
 //           bias-corrected update of the fp32 master weights (optionally a bf16 copy), and the
 //           moments re-encoded with the per-tensor scales fmax / range.
+// A lane takes four neighbouring elements at a time, 16 bytes of an fp32 gradient or of the weights and 4 of each code, so that
+// the lanes of a wave lie side by side in every access (with 16 elements per lane a wave's load of the gradient touched 64
+// pieces of 64 bytes).  Gradient and weights are read and the weights written past the caches, which leaves these to the codes:
+// 45 M weights, fp32 gradient, bf16 copy: 80 + 140 us before, 83 + 138 with the narrow accesses alone, 70 + 140 with the
+// gradient's reads non-temporal, 52 + 134 with the weights' reads and writes too (codes non-temporal as well: 48 + 154, the
+// update pass then finds none of them); 16 M 26 + 56 and 22 + 54.
 // Every arithmetic step is a single rounded fp32 operation in a fixed order (the build disables
 // contraction and uses correctly rounded division and square root), so codes, scales and
 // weights can be compared bit for bit with a binary32 reference.
@@ -35,87 +40,73 @@ constexpr int kAdamScaleM = 0, kAdamScaleV = 1, kAdamAmaxM = 2, kAdamAmaxV = 3; 
 constexpr int kAdamSlotsM = 64;                                                  // + parity * 2 * kAmaxSlotWords
 constexpr int kAdamThreads = 256;
 
+typedef float ssg_f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int ssg_u32x2 __attribute__((ext_vector_type(2)));
+// A lane takes four neighbouring elements at a time: 16 bytes of an fp32 gradient or of the weights, 4 bytes of each code, so
+// that the lanes of a wave lie side by side in every access.
 template <bool GRAD_BF16>
-__device__ __forceinline__ void load_grad8(const void *grad, size_t i, float (&g)[8]) {
+__device__ __forceinline__ void load_grad4(const void *grad, size_t i, float (&g)[4]) {
     if (GRAD_BF16) {
-        const uint4 q = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(grad) + i);
-        const uint32_t w4[4] = {q.x, q.y, q.z, q.w};
+        const ssg_u32x2 q = __builtin_nontemporal_load(reinterpret_cast<const ssg_u32x2 *>(reinterpret_cast<const uint16_t *>(grad) + i));
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            g[2 * k] = __uint_as_float(w4[k] << 16);
-            g[2 * k + 1] = __uint_as_float(w4[k] & 0xffff0000u);
+        for (int k = 0; k < 2; ++k) {
+            g[2 * k] = __uint_as_float(q[k] << 16);
+            g[2 * k + 1] = __uint_as_float(q[k] & 0xffff0000u);
         }
     } else {
-        const float4 a = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(grad) + i);
-        const float4 b = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(grad) + i + 4);
-        g[0] = a.x; g[1] = a.y; g[2] = a.z; g[3] = a.w; g[4] = b.x; g[5] = b.y; g[6] = b.z; g[7] = b.w;
-    }
-}
-
-// 8 * HALVES codes as words: one 8- or 16-byte access
-template <int HALVES>
-__device__ __forceinline__ void load_codes(const uint8_t *src, uint32_t (&q)[2 * HALVES]) {
-    if (HALVES == 1) {
-        const uint2 t = *reinterpret_cast<const uint2 *>(src);
-        q[0] = t.x; q[1] = t.y;
-    } else {
-        const uint4 t = *reinterpret_cast<const uint4 *>(src);
-        q[0] = t.x; q[1] = t.y; q[2 * (HALVES - 1)] = t.z; q[2 * (HALVES - 1) + 1] = t.w;
-    }
-}
-template <int HALVES>
-__device__ __forceinline__ void store_codes(uint8_t *dst, const uint32_t (&q)[2 * HALVES]) {
-    if (HALVES == 1) *reinterpret_cast<uint2 *>(dst) = make_uint2(q[0], q[1]);
-    else *reinterpret_cast<uint4 *>(dst) = make_uint4(q[0], q[1], q[2 * (HALVES - 1)], q[2 * (HALVES - 1) + 1]);
-}
-
-// eight stored moments from two words of codes, as fp32: decode(code) * (1 / scale)
-__device__ __forceinline__ void decode_moments8(uint32_t m0, uint32_t m1, uint32_t v0, uint32_t v1, float inv_sm,
-                                                float inv_sv, float (&m)[8], float (&v)[8]) {
-    const uint32_t mw[2] = {m0, m1}, vw[2] = {v0, v1};
+        const ssg_f32x4 q = __builtin_nontemporal_load(reinterpret_cast<const ssg_f32x4 *>(reinterpret_cast<const float *>(grad) + i));
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        m[4 * h + 0] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw[h], 0), inv_sm);
-        m[4 * h + 1] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw[h], 1), inv_sm);
-        m[4 * h + 2] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw[h], 2), inv_sm);
-        m[4 * h + 3] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw[h], 3), inv_sm);
-        v[4 * h + 0] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw[h], 0), inv_sv);
-        v[4 * h + 1] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw[h], 1), inv_sv);
-        v[4 * h + 2] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw[h], 2), inv_sv);
-        v[4 * h + 3] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw[h], 3), inv_sv);
+        for (int k = 0; k < 4; ++k) g[k] = q[k];
     }
+}
+
+// four stored moments from a word of codes each, as fp32: decode(code) * (1 / scale)
+__device__ __forceinline__ void decode_moments4(uint32_t mw, uint32_t vw, float inv_sm, float inv_sv, float (&m)[4], float (&v)[4]) {
+    m[0] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw, 0), inv_sm);
+    m[1] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw, 1), inv_sm);
+    m[2] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw, 2), inv_sm);
+    m[3] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw, 3), inv_sm);
+    v[0] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw, 0), inv_sv);
+    v[1] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw, 1), inv_sv);
+    v[2] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw, 2), inv_sv);
+    v[3] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw, 3), inv_sv);
 }
 
 // exponential moving averages of the gradient and of its square
-__device__ __forceinline__ void new_moments8(const AdamParams &p, const float (&g)[8], float (&m)[8], float (&v)[8]) {
+__device__ __forceinline__ void new_moments4(const AdamParams &p, const float (&g)[4], float (&m)[4], float (&v)[4]) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < 4; ++k) {
         m[k] = __fadd_rn(__fmul_rn(p.b1, m[k]), __fmul_rn(p.omb1, g[k]));
         v[k] = __fadd_rn(__fmul_rn(p.b2, v[k]), __fmul_rn(__fmul_rn(p.omb2, g[k]), g[k]));
     }
 }
 
-template <bool GRAD_BF16, int HALVES>
+// CHUNKS groups of four per lane and trip, a workgroup's 1024 elements apart
+template <bool GRAD_BF16, int CHUNKS>
 __global__ void __launch_bounds__(kAdamThreads) adam_range_kernel(AdamParams p) {
     const uint32_t *old = p.scalars + 8 * (p.parity ^ 1);
     const float inv_sm = __fdiv_rn(1.0f, __uint_as_float(old[kAdamScaleM])), inv_sv = __fdiv_rn(1.0f, __uint_as_float(old[kAdamScaleV]));
     uint32_t mmax = 0, vmax = 0;
-    constexpr int kPer = 8 * HALVES;
-    const size_t stride = (size_t)gridDim.x * kAdamThreads * kPer;
-    for (size_t i = ((size_t)blockIdx.x * kAdamThreads + threadIdx.x) * kPer; i < (size_t)p.n; i += stride) {
-        uint32_t mq[2 * HALVES], vq[2 * HALVES];
-        load_codes<HALVES>(p.m_q + i, mq);
-        load_codes<HALVES>(p.v_q + i, vq);
-        float g[HALVES][8];
+    constexpr int kChunk = 4 * kAdamThreads;
+    const size_t stride = (size_t)gridDim.x * kChunk * CHUNKS;
+    for (size_t i = (size_t)blockIdx.x * kChunk * CHUNKS + 4 * threadIdx.x; i < (size_t)p.n; i += stride) {
+        float g[CHUNKS][4];
+        uint32_t mq[CHUNKS], vq[CHUNKS];
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) load_grad8<GRAD_BF16>(p.grad, i + 8 * h, g[h]);
+        for (int c = 0; c < CHUNKS; ++c) {
+            const size_t j = i + (size_t)c * kChunk;
+            const size_t at = j < (size_t)p.n ? j : i;           // (a group beyond the end: this lane's first one again)
+            load_grad4<GRAD_BF16>(p.grad, at, g[c]);
+            mq[c] = *reinterpret_cast<const uint32_t *>(p.m_q + at);
+            vq[c] = *reinterpret_cast<const uint32_t *>(p.v_q + at);
+        }
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) {
-            float m[8], v[8];
-            decode_moments8(mq[2 * h], mq[2 * h + 1], vq[2 * h], vq[2 * h + 1], inv_sm, inv_sv, m, v);
-            new_moments8(p, g[h], m, v);
+        for (int c = 0; c < CHUNKS; ++c) {
+            float m[4], v[4];
+            decode_moments4(mq[c], vq[c], inv_sm, inv_sv, m, v);
+            new_moments4(p, g[c], m, v);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < 4; ++k) {
                 const uint32_t a = abs_bits_ignore_nan(m[k]), b = abs_bits_ignore_nan(v[k]);
                 mmax = mmax > a ? mmax : a;
                 vmax = vmax > b ? vmax : b;
@@ -137,7 +128,7 @@ __global__ void __launch_bounds__(kAdamThreads) adam_range_kernel(AdamParams p) 
     }
 }
 
-template <bool GRAD_BF16, int HALVES>
+template <bool GRAD_BF16, int CHUNKS>
 __global__ void __launch_bounds__(kAdamThreads) adam_update_kernel(AdamParams p) {
     const uint32_t *old = p.scalars + 8 * (p.parity ^ 1);
     const float inv_sm = __fdiv_rn(1.0f, __uint_as_float(old[kAdamScaleM])), inv_sv = __fdiv_rn(1.0f, __uint_as_float(old[kAdamScaleV]));
@@ -160,54 +151,44 @@ __global__ void __launch_bounds__(kAdamThreads) adam_update_kernel(AdamParams p)
         if (threadIdx.x < 2 * kAmaxSlots)
             next[(threadIdx.x >> 6) * kAmaxSlotWords + (threadIdx.x & 63) * kAmaxSlotStride] = 0u;
     }
-    constexpr int kPer = 8 * HALVES;
-    const size_t stride = (size_t)gridDim.x * kAdamThreads * kPer;
-    for (size_t i = ((size_t)blockIdx.x * kAdamThreads + threadIdx.x) * kPer; i < (size_t)p.n; i += stride) {
-        uint32_t mq[2 * HALVES], vq[2 * HALVES];
-        load_codes<HALVES>(p.m_q + i, mq);
-        load_codes<HALVES>(p.v_q + i, vq);
-        float g[HALVES][8];
-        float4 wv[2 * HALVES];
+    constexpr int kChunk = 4 * kAdamThreads;
+    const size_t stride = (size_t)gridDim.x * kChunk * CHUNKS;
+    for (size_t i = (size_t)blockIdx.x * kChunk * CHUNKS + 4 * threadIdx.x; i < (size_t)p.n; i += stride) {
+        float g[CHUNKS][4];
+        uint32_t mq[CHUNKS], vq[CHUNKS];
+        ssg_f32x4 w[CHUNKS];
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) load_grad8<GRAD_BF16>(p.grad, i + 8 * h, g[h]);
+        for (int c = 0; c < CHUNKS; ++c) {
+            const size_t j = i + (size_t)c * kChunk;
+            const size_t at = j < (size_t)p.n ? j : i;
+            load_grad4<GRAD_BF16>(p.grad, at, g[c]);
+            mq[c] = *reinterpret_cast<const uint32_t *>(p.m_q + at);
+            vq[c] = *reinterpret_cast<const uint32_t *>(p.v_q + at);
+            w[c] = __builtin_nontemporal_load(reinterpret_cast<const ssg_f32x4 *>(p.w + at));
+        }
 #pragma unroll
-        for (int q = 0; q < 2 * HALVES; ++q) wv[q] = *reinterpret_cast<const float4 *>(p.w + i + 4 * q);
-        uint32_t mo[2 * HALVES], vo[2 * HALVES];
+        for (int c = 0; c < CHUNKS; ++c) {
+            const size_t j = i + (size_t)c * kChunk;
+            if (c > 0 && j >= (size_t)p.n) break;
+            float m[4], v[4];
+            decode_moments4(mq[c], vq[c], inv_sm, inv_sv, m, v);
+            new_moments4(p, g[c], m, v);
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) {
-            float m[8], v[8];
-            float w[8] = {wv[2 * h].x, wv[2 * h].y, wv[2 * h].z, wv[2 * h].w,
-                          wv[2 * h + 1].x, wv[2 * h + 1].y, wv[2 * h + 1].z, wv[2 * h + 1].w};
-            decode_moments8(mq[2 * h], mq[2 * h + 1], vq[2 * h], vq[2 * h + 1], inv_sm, inv_sv, m, v);
-            new_moments8(p, g[h], m, v);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < 4; ++k) {
                 // bias-corrected step, decoupled decay
                 const float mhat = __fmul_rn(m[k], p.c1);
                 const float vhat = __fmul_rn(v[k], p.c2);
                 const float denom = __fadd_rn(sqrtf(vhat), p.eps);   // sqrtf, not __fsqrt_rn: only the former is correctly rounded here
                 float upd = __fdiv_rn(mhat, denom);
-                upd = __fadd_rn(upd, __fmul_rn(p.wd, w[k]));
-                w[k] = __fsub_rn(w[k], __fmul_rn(p.lr, upd));
+                upd = __fadd_rn(upd, __fmul_rn(p.wd, w[c][k]));
+                w[c][k] = __fsub_rn(w[c][k], __fmul_rn(p.lr, upd));
             }
-            wv[2 * h] = make_float4(w[0], w[1], w[2], w[3]);
-            wv[2 * h + 1] = make_float4(w[4], w[5], w[6], w[7]);
-            mo[2 * h] = satcast_pk4<kE4M3>(__fmul_rn(m[0], sm), __fmul_rn(m[1], sm), __fmul_rn(m[2], sm), __fmul_rn(m[3], sm));
-            mo[2 * h + 1] = satcast_pk4<kE4M3>(__fmul_rn(m[4], sm), __fmul_rn(m[5], sm), __fmul_rn(m[6], sm), __fmul_rn(m[7], sm));
-            vo[2 * h] = satcast_pk4<kE5M2>(__fmul_rn(v[0], sv), __fmul_rn(v[1], sv), __fmul_rn(v[2], sv), __fmul_rn(v[3], sv));
-            vo[2 * h + 1] = satcast_pk4<kE5M2>(__fmul_rn(v[4], sv), __fmul_rn(v[5], sv), __fmul_rn(v[6], sv), __fmul_rn(v[7], sv));
+            __builtin_nontemporal_store(w[c], reinterpret_cast<ssg_f32x4 *>(p.w + j));
+            if (p.w_bf16)
+                *reinterpret_cast<ssg_u32x2 *>(p.w_bf16 + j) = ssg_u32x2{pack_bf16x2(w[c][0], w[c][1]), pack_bf16x2(w[c][2], w[c][3])};
+            *reinterpret_cast<uint32_t *>(p.m_q + j) = satcast_pk4<kE4M3>(__fmul_rn(m[0], sm), __fmul_rn(m[1], sm), __fmul_rn(m[2], sm), __fmul_rn(m[3], sm));
+            *reinterpret_cast<uint32_t *>(p.v_q + j) = satcast_pk4<kE5M2>(__fmul_rn(v[0], sv), __fmul_rn(v[1], sv), __fmul_rn(v[2], sv), __fmul_rn(v[3], sv));
         }
-#pragma unroll
-        for (int q = 0; q < 2 * HALVES; ++q) *reinterpret_cast<float4 *>(p.w + i + 4 * q) = wv[q];
-        if (p.w_bf16) {
-#pragma unroll
-            for (int h = 0; h < HALVES; ++h)
-                *reinterpret_cast<uint4 *>(p.w_bf16 + i + 8 * h) =
-                    make_uint4(pack_bf16x2(wv[2 * h].x, wv[2 * h].y), pack_bf16x2(wv[2 * h].z, wv[2 * h].w),
-                               pack_bf16x2(wv[2 * h + 1].x, wv[2 * h + 1].y), pack_bf16x2(wv[2 * h + 1].z, wv[2 * h + 1].w));
-        }
-        store_codes<HALVES>(p.m_q + i, mo);
-        store_codes<HALVES>(p.v_q + i, vo);
     }
 }
 
@@ -233,24 +214,22 @@ void launch_adam_step(const AdamArgs &a, hipStream_t st) {
     p.grad = a.grad; p.w = a.w; p.w_bf16 = (uint16_t *)a.w_bf16; p.m_q = a.m_q; p.v_q = a.v_q; p.scalars = a.scalars;
     p.n = a.n; p.b1 = a.beta1; p.b2 = a.beta2; p.omb1 = a.one_minus_beta1; p.omb2 = a.one_minus_beta2;
     p.c1 = a.c1; p.c2 = a.c2; p.lr = a.lr; p.eps = a.eps; p.wd = a.weight_decay; p.parity = a.step & 1; p.pow2 = a.pow2;
-    // range pass: 16 elements per lane (16-byte code loads); update pass: 8 per lane measured faster
-    constexpr int kRangeHalves = 2, kUpdateHalves = 1;
-    // measured at 45 M elements: the read-only range pass is fastest with one trip per lane (57 us against 67
-    // with 4096 looping workgroups), the update pass with 2048 looping workgroups (141 us against 160)
-    auto grid = [&](int per_lane, size_t cap) {
-        const size_t groups = ((size_t)a.n / per_lane + kAdamThreads - 1) / kAdamThreads;
+    // 16 elements per lane in the range pass, one trip; 8 in the update pass, 2048 looping workgroups
+    constexpr int kRangeChunks = 4, kUpdateChunks = 2;
+    auto grid = [&](int chunks, size_t cap) {
+        const size_t per = (size_t)4 * kAdamThreads * chunks, groups = ((size_t)a.n + per - 1) / per;
         return (unsigned)(groups < cap ? groups : cap);
     };
-    const unsigned grid_r = grid(8 * kRangeHalves, (size_t)1 << 20), grid_u = grid(8 * kUpdateHalves, 2048);
+    const unsigned grid_r = grid(kRangeChunks, (size_t)1 << 20), grid_u = grid(kUpdateChunks, 2048);
     // timing records (when enabled): tag 32 = range pass, 33 = update pass
     const double gbytes = a.grad_bf16 ? 2.0 : 4.0;       // algorithmic bytes per element: gradient + two codes; update: + w in/out, bf16 copy, codes out
     profile_before(32, st, (gbytes + 2.0) * (double)a.n);
-    if (a.grad_bf16) hipLaunchKernelGGL((adam_range_kernel<true, kRangeHalves>), dim3(grid_r), dim3(kAdamThreads), 0, st, p);
-    else hipLaunchKernelGGL((adam_range_kernel<false, kRangeHalves>), dim3(grid_r), dim3(kAdamThreads), 0, st, p);
+    if (a.grad_bf16) hipLaunchKernelGGL((adam_range_kernel<true, kRangeChunks>), dim3(grid_r), dim3(kAdamThreads), 0, st, p);
+    else hipLaunchKernelGGL((adam_range_kernel<false, kRangeChunks>), dim3(grid_r), dim3(kAdamThreads), 0, st, p);
     profile_after(st);
     profile_before(33, st, (gbytes + 2.0 + 4.0 + 4.0 + (a.w_bf16 ? 2.0 : 0.0) + 2.0) * (double)a.n);
-    if (a.grad_bf16) hipLaunchKernelGGL((adam_update_kernel<true, kUpdateHalves>), dim3(grid_u), dim3(kAdamThreads), 0, st, p);
-    else hipLaunchKernelGGL((adam_update_kernel<false, kUpdateHalves>), dim3(grid_u), dim3(kAdamThreads), 0, st, p);
+    if (a.grad_bf16) hipLaunchKernelGGL((adam_update_kernel<true, kUpdateChunks>), dim3(grid_u), dim3(kAdamThreads), 0, st, p);
+    else hipLaunchKernelGGL((adam_update_kernel<false, kUpdateChunks>), dim3(grid_u), dim3(kAdamThreads), 0, st, p);
     profile_after(st);
 }
 
