@@ -236,25 +236,27 @@ static int sum_form_unsplit(const GemmArgs &dx, const GemmArgs &dw, double *sepa
 }
 
 // Each product of dX in tiles of its own, which meet where the second of them is done: for short batches, whose few tiles of
-// both products (172 K steps at d = 4096, f = 11008) are still running when the weight gradients have long ended.  Up to 96
+// both products (172 K steps at d = 4096, f = 11008) are still running when the weight gradients have long ended.  Up to 80
 // large tiles, twice that as halves; beyond, the tiles of dX fill the chip by themselves and the products' way through memory
-// (the one, 256 KB per large tile, out and in) only costs (2048 x 4096, f = 11008, 128 tiles: 339 us either way; 4096 x 4096:
-// 559 whole, 590 in halves).  Measured, dX, dW1 and dW2 in one launch, whole and in halves: T = 1024, d = 4096, f = 11008 302
-// and 212 us (large tiles); 512 225 and 167, 128 200 and 142 (small); 2048, 3072, 8192 225 and 204; 1040, 1024, 2736 34 and
-// 28; 256, 1024, 2736 32 and 23.  Not where the estimates are close: 2048, 2048, 5504 112 and 113, 2048, 1024, 2736 39 and 46.
+// (the one, 256 KB per large tile, out and in) only costs (2048, 3072, 8192, 96 tiles: 210 us whole, 219 in halves; 2048, 4096,
+// 11008 339 either way; 4096, 4096, 11008 559 and 590), and only where a tile of both products is the longer one (3584, 640,
+// 1680: 34 and 38).  Measured, dX, dW1 and dW2 in one launch, whole and in halves: T = 1024, d = 4096, f = 11008 299 and
+// 221 us (large tiles); 1536, 3072, 9216 230 and 187; 512, 4096, 11008 200 and 163; 640, 2928, 9952 147 and 131; 256, 2048, 5504
+// 55 and 37; 1040, 1024, 2736 32 and 25; 2048, 512, 1360 19 and 16.  Not where large tiles are estimated close: 3072, 1536, 4096
+// 92 and 104, though 2048, 2048, 5504 121 and 103.
 int gemm_sum_form(const GemmArgs &dx, const GemmArgs &dw) {
     double separate;
     const int whole = sum_form_unsplit(dx, dw, &separate);
     GemmArgs sum = dx;
     sum.part = 0;
-    if (tile_count(sum, 4) > 3 * kComputeUnits / 8) return whole;
+    if (tile_count(sum, 4) > 5 * kComputeUnits / 16 || 2.0 * k_steps(sum) <= k_steps(dw)) return whole;
     double unsplit = separate;
     if (whole == 3) {
         sum.part = 3;
         const GemmArgs *list[3] = {&sum, &dw, &dw};
         unsplit = dx_group_time(sum, dw, 3, gemm_wave_blocks(list, 3));
     }
-    return dx_group_time(sum, dw, 4, 2) < 0.95 * unsplit || dx_group_time(sum, dw, 4, 4) < 0.82 * unsplit ? 4 : whole;
+    return dx_group_time(sum, dw, 4, 2) < unsplit || dx_group_time(sum, dw, 4, 4) < 0.82 * unsplit ? 4 : whole;
 }
 
 int gemm_profile_tag(const GemmArgs &a) {

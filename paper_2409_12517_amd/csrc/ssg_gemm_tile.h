@@ -706,8 +706,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                 for (int pass = 0; pass < kPasses; ++pass)
                     at[pass] = reinterpret_cast<f32x4 *>(out + (size_t)(uint32_t)clamp16(row + pass * kRows + lr, rows_left) * (size_t)p.N + c);
                 if (p.nt_store) {
+                    // (the empty statements keep the compiler from making one of the two branches, which loses the hint)
+                    asm volatile("; past the caches" ::: "memory");
 #pragma unroll
                     for (int pass = 0; pass < kPasses; ++pass) __builtin_nontemporal_store(v[pass], at[pass]);
+                    asm volatile("; past the caches" ::: "memory");
                 } else {
 #pragma unroll
                     for (int pass = 0; pass < kPasses; ++pass) *at[pass] = v[pass];
