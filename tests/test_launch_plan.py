@@ -106,3 +106,12 @@ def test_wide_weights_do_not_take_the_few_rows_form_of_the_inference_form(T, d, 
 def test_short_batches_take_the_few_rows_form_of_the_inference_form(T, d, f, rows):
     p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T, d, f), ssg.SSG_PLAN_INFER_GATE_UP)
     assert (p.tile, p.rows) == (0, rows)
+
+
+@pytest.mark.parametrize("T,d,f,halves", [(1024, 4096, 11008, True), (640, 2928, 9952, True), (256, 2048, 5504, True), (2048, 512, 1360, True),
+                                          (3584, 640, 1680, False), (4096, 1024, 2816, False), (2048, 3072, 8192, False),
+                                          (4096, 4096, 11008, False)])
+def test_dx_runs_in_halves_where_its_few_long_tiles_decide(T, d, f, halves):
+    """In halves 0.68 to 0.9 of the time; whole 0.89 to 0.97 of it: tiles no longer than a weight gradient's, or too many."""
+    p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T, d, f), ssg.SSG_PLAN_BWD_SECOND)
+    assert (p.rows == 2) == halves
