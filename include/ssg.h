@@ -110,7 +110,8 @@ ssg_status ssg_gemm_fp8_layout(const uint8_t *A, ssg_fp8_format a_fmt, int a_kma
  * decision the call itself makes.  Host logic on an MI355X with 256 compute units; nothing is launched and no GPU is
  * needed. */
 typedef struct {
-    int32_t tile;            /* edge of the output tiles: 256 or 128; 0: the kernel for few rows */
+    int32_t tile;            /* edge of the output tiles: 256 or 128; 0: the kernel for few rows (the inference form's gate/up may
+                              * run a last 16 rows that way in the grid of its 128 x 128 tiles: 128) */
     int32_t ring;            /* operand tiles in LDS; few rows: K steps of 128 bytes in a wave's ring */
     int32_t whole_sets;      /* > 0 (tile = 128): the first whole_sets * 8 tiles of 256 x 256 run as such, in a launch before */
     int32_t rows, cols;      /* few rows: rows and columns of the result per workgroup (else 0; SSG_PLAN_BWD_SECOND: rows = 2

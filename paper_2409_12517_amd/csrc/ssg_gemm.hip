@@ -307,12 +307,30 @@ static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream
     profile_after(st);
 }
 
+// Gate/up of the inference form: 16 rows (the least there can be) beyond whole large tiles go to the few-rows form in the same
+// grid where the others are one round of small tiles, two to most compute units, whose free slots few-rows workgroups fit.
+// With fewer tiles each has its compute unit to itself, and such neighbours slow it down (T = 144, d = 4096, f = 11008: 27.4 us in
+// two rows of small tiles, 33.7 this way); with more than a round they wait like any other (T = 272, d = 8192, f = 28672: 193 in
+// large tiles, 230); an odd row of small tiles leaves half of the last large ones empty and the XCDs uneven (T = 400, d = 3072,
+// f = 8192: 26 and 34).  Within the line, us without and with: T = 272, d = 4096, f = 11008 46 and 34; 272, 4096, 14336 50 and 45;
+// 272, 8192, 14336 98 and 94; 272, 3120, 10032 44 and 37; 272, 1024, 8400 17.1 and 14.0; 528, 2048, 5504 25 and 20; 528, 3072,
+// 8192 40 and 35; 784, 1536, 4096 17.4 and 17.1; 1040, 1024, 2736 14.6 and 14.3; 2064, 512, 2000 16.7 and 14.5.
+static int few_last_rows(const GemmArgs &a) {
+    const int rest = (int)(a.M % tile_edge(4));
+    if (a.epilogue != EPI_SWIGLU_Q || rest == 0 || rest > 16 || a.M < tile_edge(4)) return 0;
+    GemmArgs main = a;
+    main.M -= rest;
+    const int64_t tiles = tile_count(main, 2);
+    return tiles > kComputeUnits && tiles <= 2 * kComputeUnits ? rest : 0;
+}
+
 GemmPlan gemm_plan(const GemmArgs &a) {
     const GemmArgs *one = &a;
     GemmPlan p;
     p.wave_blocks = gemm_wave_blocks(&one, 1);
     const double whole = launch_time(a, p.wave_blocks);
     if (gemm_skinny_time(a, &p.form) < whole) { p.wave_blocks = 0; return p; }
+    if (const int rest = few_last_rows(a)) { p.wave_blocks = 2; p.rest_rows = rest; return p; }
     p.whole_sets = full_round_sets(a, whole);
     if (p.whole_sets > 0) p.wave_blocks = 2;
     // one small tile to a compute unit, so up to 8 large tiles on an XCD of 32: the longer ring, which leaves no room
@@ -329,6 +347,12 @@ bool launch_gemm(const GemmArgs &a, hipStream_t st) {
     if (plan.wave_blocks == 0) {
         profile_before(gemm_profile_tag(a), st, gemm_flops(a));
         launch_gemm_skinny(a, plan.form, st);
+        profile_after(st);
+        return true;
+    }
+    if (plan.rest_rows > 0) {
+        profile_before(gemm_profile_tag(a), st, gemm_flops(a));
+        launch_gemm_rest(a, plan.rest_rows, st);
         profile_after(st);
         return true;
     }

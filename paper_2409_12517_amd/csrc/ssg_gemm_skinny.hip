@@ -23,18 +23,18 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int kBlockBytes = 16 * BK;          // 16 rows of one K step: two DMA instructions
 constexpr int skinny_smem(int MB, int NB, int KW, int STEPS) { return KW * STEPS * (MB + NB) * kBlockBytes; }
 
+// The work of workgroup `block`.
 template <int EPI, int AFMT, int MB, int NB, int KW, int STEPS>
-__global__ void __launch_bounds__(64 * KW) gemm_skinny_kernel(GemmParams p) {
+__device__ __forceinline__ void gemm_skinny_block(const GemmParams &p, const unsigned block, uint8_t *smem) {
     constexpr bool kDual = EPI == EPI_SWIGLU_Q;
     constexpr int NCOL = kDual ? NB / 2 : NB;                          // 16-column blocks of the result
     constexpr int kStepBytes = (MB + NB) * kBlockBytes, kPitch = 16 * NB + 1;
     static_assert(KW * MB * 16 * kPitch * 4 <= skinny_smem(MB, NB, KW, STEPS), "the partial sums reuse the rings");
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[skinny_smem(MB, NB, KW, STEPS)];
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // the row blocks that share 16 * NB rows of B run on the same XCD one after the other: B comes into its L2 once
-    const int mblocks = (int)((p.M + 16 * MB - 1) / (16 * MB)), idx = (int)(blockIdx.x >> 3);
+    const int mblocks = (int)((p.M + 16 * MB - 1) / (16 * MB)), idx = (int)(block >> 3);
     const int64_t m0 = (int64_t)(idx % mblocks) * (16 * MB);
-    const int64_t n0 = ((int64_t)(idx / mblocks) * 8 + (blockIdx.x & 7)) * (16 * NCOL);
+    const int64_t n0 = ((int64_t)(idx / mblocks) * 8 + (block & 7)) * (16 * NCOL);
     if (n0 >= p.N) return;
     const int ksteps = (int)((p.K + BK - 1) / BK), per = (ksteps + KW - 1) / KW;
     const int s0 = w * per, n = (s0 + per < ksteps ? per : ksteps - s0);      // this wave's steps; may be 0 or less
@@ -148,6 +148,29 @@ __global__ void __launch_bounds__(64 * KW) gemm_skinny_kernel(GemmParams p) {
 }
 
 template <int EPI, int AFMT, int MB, int NB, int KW, int STEPS>
+__global__ void __launch_bounds__(64 * KW) gemm_skinny_kernel(GemmParams p) {
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[skinny_smem(MB, NB, KW, STEPS)];
+    gemm_skinny_block<EPI, AFMT, MB, NB, KW, STEPS>(p, blockIdx.x, smem);
+}
+
+// Gate/up of the inference form for a batch whose last row of 128 x 128 tiles would hold at most 16 rows: these run in the
+// few-rows form, in the same grid, in the slots that the tiles leave idle (their LDS fits beside a tile's).  Bound by the
+// tiles, two on a compute unit; a row of 128-row tiles for 16 rows costs a half more (T = 272: 46 us in large tiles, the second
+// row 1/16 full, 34 this way).
+__global__ void __launch_bounds__(kThreads, 2) gemm_swiglu_q_rest_kernel(GemmParams p, GemmParams rest, int tile_blocks) {
+    constexpr int kBytes = std::max(smem_bytes(2), skinny_smem(1, 2, 4, 3));
+    static_assert(2 * kBytes <= 163840, "two workgroups on a compute unit");
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[kBytes];
+    const int b = (int)blockIdx.x;
+    if (b >= tile_blocks) {
+        gemm_skinny_block<EPI_SWIGLU_Q, kE4M3, 1, 2, 4, 3>(rest, (unsigned)(b - tile_blocks), smem);
+        return;
+    }
+    const int vb = set_of<2>(b) * 8 + (b & 7);
+    if (vb < p.tiles_m * p.tiles_n) gemm_tile<2, EPI_SWIGLU_Q, kE4M3, 0, 0>(p, vb, quarter_of<2>(b), smem);
+}
+
+template <int EPI, int AFMT, int MB, int NB, int KW, int STEPS>
 static void launch_form(const GemmParams &p, hipStream_t st) {
     constexpr int cols = 16 * (EPI == EPI_SWIGLU_Q ? NB / 2 : NB);
     const unsigned mblocks = (unsigned)((p.M + 16 * MB - 1) / (16 * MB)), nsets = (unsigned)((p.N + 8 * cols - 1) / (8 * cols));
@@ -231,6 +254,17 @@ void launch_gemm_skinny(const GemmArgs &a, int form, hipStream_t st) {
     else if (form > kStoreForms) launch_indexed<EPI_SWIGLU_Q, kE4M3, kStoreForms + 1>(p, st);
     else if (a.a_fmt == kE4M3) launch_store<kE4M3>(p, form, st);
     else launch_store<kE5M2>(p, form, st);
+}
+
+void launch_gemm_rest(const GemmArgs &a, int rows, hipStream_t st) {
+    GemmArgs main = a, rest = a;
+    main.M = a.M - rows;
+    rest.M = rows;
+    rest.A = a.A + (size_t)main.M * (size_t)a.K;
+    rest.C = static_cast<uint8_t *>(a.C) + (size_t)main.M * (size_t)a.N;
+    const GemmParams p = make_gemm_params(main), q = make_gemm_params(rest);
+    const unsigned blocks = (unsigned)sets_of(p) * set_workgroups(2), more = (unsigned)((a.N + 127) / 128) * 8u;
+    hipLaunchKernelGGL(gemm_swiglu_q_rest_kernel, dim3(blocks + more), dim3(kThreads), 0, st, p, q, (int)blocks);
 }
 
 void gemm_skinny_extent(const GemmArgs &a, int form, int *rows, int *cols, int *steps) {

@@ -171,11 +171,14 @@ struct GemmPlan {
     int units = 5;              // operand tiles of the ring
     int whole_sets = 0;         // > 0: so many sets of 8 large tiles in a launch before that of the small ones
     int form = 0;               // few rows: which of its forms
+    int rest_rows = 0;          // > 0: the batch's last rows, in the few-rows form in the grid of the small tiles
 };
 GemmPlan gemm_plan(const GemmArgs &a);
 // few rows (ssg_gemm_skinny.hip): estimated microseconds of the best form, 1e30 for an argument set it is not built for
 double gemm_skinny_time(const GemmArgs &a, int *form);
 void launch_gemm_skinny(const GemmArgs &a, int form, hipStream_t st);
+// gate/up of the inference form, the last `rows` rows of the batch in the few-rows form
+void launch_gemm_rest(const GemmArgs &a, int rows, hipStream_t st);
 // rows and columns of the result per workgroup, steps of 128 bytes of K in a wave's ring
 void gemm_skinny_extent(const GemmArgs &a, int form, int *rows, int *cols, int *steps);
 bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st);       // the backward forms (called by launch_gemm)

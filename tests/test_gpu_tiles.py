@@ -151,6 +151,16 @@ def test_few_rows_of_the_inference_form(T_inf):
     ti.check(ti.Infer(inp, T_inf=T_inf, seed_inf=8), tm._np_inputs(inp))
 
 
+@pytest.mark.parametrize("T_inf,d,f", [(2064, 272, 1040), (1040, 400, 4096)])
+def test_inference_form_with_its_last_rows_in_the_few_rows_form(T_inf, d, f):
+    """16 rows beyond 16 and 8 rows of small tiles, 272 and the 512 tiles up to which the route goes; K with a last step of 16
+    bytes, a last column of tiles and a last set of few-rows workgroups that are cut."""
+    p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T_inf, d, f), ssg.SSG_PLAN_INFER_GATE_UP)
+    assert (p.tile, p.ring, p.whole_sets, p.launches) == (128, 5, 0, 1)
+    inp = synth.make_inputs(64, d, f, seed=67)
+    ti.check(ti.Infer(inp, T_inf=T_inf, seed_inf=10), tm._np_inputs(inp))
+
+
 def test_inference_form_in_whole_rounds_and_a_rest():
     """9 x 33 tiles of 256 rows by 128 channels, 41 more than one round of large ones."""
     inp = synth.make_inputs(64, 272, 4112, seed=61)
