@@ -34,7 +34,7 @@ METRIC = "FP8 Smooth-SwiGLU MLP fwd+bwd TFLOP/s (7B shape), % of FP8 MFMA peak"
 # launches; the single-launch tags appear only when the grouping is switched off (SSG_GEMM_GROUPING=0).
 TAG_NAMES = {0: "gemm_kernel<4, 0, 0, 0, 0, 5>", 2: "gemm_kernel<4, 1, 0, 0, 0, 5>", 18: "gemm_swiglu_col_range_kernel<4>",
              16: "gemm_group_dh_dw3_kernel<4, 2>",
-             17: "gemm_group_dx_dw_kernel<4>", 5: "gemm_kernel<4, 2, 1, 0, 1, 5>", 1: "gemm_kernel<4, 0, 1, 0, 2, 5>",
+             17: "gemm_group_dx_dw_kernel<4, 3>", 5: "gemm_kernel<4, 2, 1, 0, 1, 5>", 1: "gemm_kernel<4, 0, 1, 0, 2, 5>",
              11: "gemm_kernel<4, 0, 1, 3, 1, 5>", 9: "gemm_kernel<4, 0, 1, 1, 1, 5>", 10: "gemm_kernel<4, 0, 1, 2, 1, 5>"}
 TAG_ROLES = {0: "y = h^ w3~^T", 2: "U, G + SwiGLU + channel maxima",
              18: "U, G + SwiGLU + channel maxima, with the per-channel range of W3 in the grid's last round", 16: "dH + SwiGLU backward, then the first part of dW3 (one grid)",
@@ -102,7 +102,7 @@ def cpu_baseline(T_sample: int, cfg):
             "seconds": dt}
 
 
-ADAM_KERNELS = {32: "adam_range_kernel<false, 2>", 33: "adam_update_kernel<false, 1>"}
+ADAM_KERNELS = {32: "adam_range_kernel<false, 4>", 33: "adam_update_kernel<false, 2>"}
 # algorithmic bytes per element: range pass reads g (4) + two codes; update pass reads g, two codes and w (4),
 # writes w (4), the bf16 copy (2) and two codes
 ADAM_BYTES = {32: 6.0, 33: 18.0}
