@@ -199,8 +199,9 @@ size_t ssg_mlp_scaling_state_bytes(void);
 ssg_status ssg_mlp_scaling_init(void *scaling_state, void *stream);
 
 /* Sizes of the two caller-allocated device buffers.  `saved` carries what the
- * backward pass needs (quantized operands, bf16 U and G, the factors); `workspace` is scratch of the backward pass.  0 on a bad
- * descriptor. */
+ * backward pass needs (quantized operands, bf16 U and G, the factors); `workspace` is scratch of the backward pass.  Both follow
+ * from T, d, f and w3_layer_bf16 alone and never fall as T grows: buffers made for the longest batch serve every shorter one.
+ * 0 on a bad descriptor. */
 size_t ssg_mlp_saved_bytes(const ssg_mlp_desc *desc);
 size_t ssg_mlp_workspace_bytes(const ssg_mlp_desc *desc);
 

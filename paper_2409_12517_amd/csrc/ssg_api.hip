@@ -3,6 +3,7 @@
 // method runs in the kernels of ssg_quant.hip / ssg_gemm.hip.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -183,17 +184,14 @@ WorkLayout work_layout(const ssg_mlp_desc &d) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align256(bytes); return at; };
     L.scalars = take(W_COUNT * 4);
-    // the input gradient: its fp32 first product; where both have tiles of their own, their results and the words in which
-    // they meet
-    BackwardGemms bg;
-    backward_gemm_shapes(d, bg);
-    const bool halves = bg.dx.part == 4;
-    // range words of dY, slotted running maxima of dU, dG
-    L.partials = take((3 * ssg::kAmaxSlotWords + (halves ? ssg::gemm_arrival_words(T, dm) : 0)) * 4);
+    // range words of dY, slotted running maxima of dU, dG, the words in which the two products of the input gradient meet
+    L.partials = take((3 * ssg::kAmaxSlotWords + ssg::kHalvesWords) * 4);
     L.dy_q = take(T * dm);
     L.dU = take(T * f * 2); L.dG = take(T * f * 2);
     L.du_q = take(T * f); L.dg_q = take(T * f);
-    L.dx_tmp = take(halves ? 2 * ssg::gemm_partial_floats(T, dm) * 4 : T * dm * 4);
+    // the input gradient: its fp32 first product, or the results of both where each has tiles of its own.  Room for either,
+    // whichever this T and these types run in: a workspace made for the longest batch holds every shorter one
+    L.dx_tmp = take(std::max(T * dm, ssg::gemm_halves_floats(d.T, d.d)) * 4);
     L.dyT = take(d.w3_layer_bf16 ? T * dm * 2 : 0);     // bf16 dY transposed (last layer left in bf16)
     L.total = o;
     return L;

@@ -249,7 +249,7 @@ int gemm_sum_form(const GemmArgs &dx, const GemmArgs &dw) {
     const int whole = sum_form_unsplit(dx, dw, &separate);
     GemmArgs sum = dx;
     sum.part = 0;
-    if (tile_count(sum, 4) > 5 * kComputeUnits / 16 || 2.0 * k_steps(sum) <= k_steps(dw)) return whole;
+    if (tile_count(sum, 4) > kHalvesTiles || 2.0 * k_steps(sum) <= k_steps(dw)) return whole;
     double unsplit = separate;
     if (whole == 3) {
         sum.part = 3;

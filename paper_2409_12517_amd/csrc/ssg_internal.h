@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace ssg {
 
 enum SrcKind { SRC_BF16 = 0, SRC_F32 = 1, SRC_SWIGLU = 2 };
@@ -189,9 +191,17 @@ int gemm_wave_blocks(const GemmArgs *const *list, int n, double last = 1.0);
 double gemm_tile_cost(const GemmArgs &a, int WB);               // estimated microseconds of one tile
 // how the input gradient is best run: as part = 3 or 4 (in one grid with weight gradients like `dw`), or as parts 1 and 2 (1)
 int gemm_sum_form(const GemmArgs &dx, const GemmArgs &dw);
-// part = 4: a word for every 128 x 128 tile, and 64 KB
+// part = 4: so many tiles of 256 x 256 at most (see gemm_sum_form); a word for every 128 x 128 tile, and 64 KB
+constexpr int kHalvesTiles = 80;
 size_t gemm_arrival_words(int64_t M, int64_t N);
 inline size_t gemm_partial_floats(int64_t M, int64_t N) { return gemm_arrival_words(M, N) * (128 * 128); }
+// The scratch of every part = 4 of N columns and at most M rows, floats of `partials` and words of `arrivals`: what a buffer
+// holds that is sized before the form is chosen.  Neither falls as M grows.
+inline size_t gemm_halves_floats(int64_t M, int64_t N) {
+    const int64_t cols = (N + 255) / 256, rows = std::min((M + 255) / 256, kHalvesTiles / cols);
+    return rows > 0 ? 2 * gemm_partial_floats(256 * rows, N) : 0;
+}
+constexpr size_t kHalvesWords = 4 * kHalvesTiles;
 int gemm_profile_tag(const GemmArgs &a);
 // Several independent GEMMs in one grid, the workgroups of one following those of the other.  Built groups:
 //   { dH (EPI_SWIGLU_BWD or _Q), weight gradient (EPI_STORE, layout 2, A E5M2) }

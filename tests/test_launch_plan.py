@@ -115,3 +115,20 @@ def test_dx_runs_in_halves_where_its_few_long_tiles_decide(T, d, f, halves):
     """In halves 0.68 to 0.9 of the time; whole 0.89 to 0.97 of it: tiles no longer than a weight gradient's, or too many."""
     p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T, d, f), ssg.SSG_PLAN_BWD_SECOND)
     assert (p.rows == 2) == halves
+
+
+@pytest.mark.parametrize("d,f", [(16, 784), (512, 1360), (2048, 5504), (4096, 11008), (4096, 11024), (20512, 1024)])
+def test_buffers_made_for_the_longest_batch_serve_every_shorter_one(d, f):
+    """Neither size falls as T grows, whichever form dX takes at that T, nor depends on the output types."""
+    for extra in ({}, dict(smooth=0, w3_layer_bf16=1)):
+        last = (0, 0)
+        for T in range(16, 4096 + 1, 16):
+            sizes = set()
+            for y in (ssg.SSG_BF16, ssg.SSG_F32):
+                for dw in (ssg.SSG_BF16, ssg.SSG_F32):
+                    desc = ssg.make_desc(T, d, f, y_dtype=y, dw_dtype=dw, **extra)
+                    sizes.add((ssg.ssg_mlp_saved_bytes(desc), ssg.ssg_mlp_workspace_bytes(desc)))
+            assert len(sizes) == 1, (T, sizes)
+            now = sizes.pop()
+            assert now[0] >= last[0] and now[1] >= last[1], (T, last, now)
+            last = now
