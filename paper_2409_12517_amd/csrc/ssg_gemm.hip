@@ -173,22 +173,23 @@ static double grid_time(const GemmArgs *const *list, int n, int WB, double last 
 }
 
 // Estimated microseconds of the second backward group, dX in form `part` and two weight gradients, in either tile.  dX's tiles
-// are dealt first; where there are few of them they decide, else the work does.  Large tile: 1.36 per K step; a long tile
-// beside many short ones that write takes up to 1.35 times as long.  Small tile: 0.93 per K step where two share a compute
-// unit, 0.44 for one that has it to itself, which dX's are once the weight gradients have ended, if they end early; a tenth more for each operand
-// that splits lines; fp32 gradients leave at 3.6 MB/us.
+// are dealt first; where there are few of them they decide, else the work does.  Large tile: a long tile beside many short
+// ones that write takes longer.  Small tile: 0.89 per K step where two share a compute unit, 0.57 for one that has it to
+// itself, which dX's are once the weight gradients have ended, if they end early; a quarter more for each operand that splits
+// lines; gradients leave at 5.9 MB/us at most.  The constants are those with which the choice between the forms and tiles
+// comes out best over 1626 measured calls of the backward (see gemm_sum_form), so what counts is how the estimates compare.
 static double dx_group_time(GemmArgs dx, const GemmArgs &dw, int part, int WB) {
     dx.part = part;
     const double kx = k_steps(dx), kw = k_steps(dw), nx = (double)tile_count(dx, WB), nw = 2.0 * (double)tile_count(dw, WB);
     if (WB == 4) {
-        const double cx = 2.5 + 1.36 * kx + (part == 4 ? 8.0 : 5.0), cw = 2.5 + 1.36 * kw + (dw.c_f32 ? 7.5 : 5.0);
-        return 4.0 + std::max(1.35 * cx, (nx * cx + nw * cw) / kComputeUnits + 0.4 * cw);
+        const double cx = part == 4 ? 25.5 + 1.61 * kx : 2.0 + 1.44 * kx, cw = 9.5 + 1.44 * kw;
+        return 4.0 + std::max(1.16 * cx, (nx * cx + nw * cw) / kComputeUnits + 0.65 * cw);
     }
-    const double slots = 2.0 * kComputeUnits, split = 1.0 + 0.1 * split_line_operands(dx), shared = 0.93 * split, alone = 0.44 * split;
-    const double end_x = 3.5 + (part == 4 ? 3.0 : 2.0), cx = end_x + shared * kx, cw = 6.0 + shared * kw;
-    const double beside = std::max(nw * cw / slots, 2.0 * (double)(dw.M * dw.N) * (dw.c_f32 ? 4.0 : 2.0) / 3.6e6);
-    const double contended = beside > 0.5 * shared * kx ? kx : std::min(kx, beside / shared);      // (steps beside another tile)
-    return 6.0 + std::max(end_x + shared * contended + alone * (kx - contended), nx * cx / slots + beside + (nx + nw > slots ? 0.5 * cw : 0.0));
+    const double slots = 2.0 * kComputeUnits, split = 1.0 + 0.23 * split_line_operands(dx), shared = 0.89 * split, alone = 0.57 * split;
+    const double end_x = part == 4 ? 7.4 : 4.0, cx = end_x + shared * kx, cw = 5.7 + shared * kw;
+    const double beside = std::max(nw * cw / slots, 2.0 * (double)(dw.M * dw.N) * (dw.c_f32 ? 4.0 : 2.0) / 5.9e6);
+    const double contended = std::min(kx, beside / shared);      // (steps beside another tile)
+    return 6.0 + std::max(end_x + shared * contended + alone * (kx - contended), nx * cx / slots + beside + (nx + nw > slots ? 0.7 * cw : 0.0));
 }
 
 int gemm_wave_blocks(const GemmArgs *const *list, int n, double last) {
@@ -238,25 +239,29 @@ static int sum_form_unsplit(const GemmArgs &dx, const GemmArgs &dw, double *sepa
 // Each product of dX in tiles of its own, which meet where the second of them is done: for short batches, whose few tiles of
 // both products (172 K steps at d = 4096, f = 11008) are still running when the weight gradients have long ended.  Up to 80
 // large tiles, twice that as halves; beyond, the tiles of dX fill the chip by themselves and the products' way through memory
-// (the one, 256 KB per large tile, out and in) only costs (2048, 3072, 8192, 96 tiles: 210 us whole, 219 in halves; 2048, 4096,
-// 11008 339 either way; 4096, 4096, 11008 559 and 590), and only where a tile of both products is the longer one (3584, 640,
-// 1680: 34 and 38).  Measured, dX, dW1 and dW2 in one launch, whole and in halves: T = 1024, d = 4096, f = 11008 299 and
-// 221 us (large tiles); 1536, 3072, 9216 230 and 187; 512, 4096, 11008 200 and 163; 640, 2928, 9952 147 and 131; 256, 2048, 5504
-// 55 and 37; 1040, 1024, 2736 32 and 25; 2048, 512, 1360 19 and 16.  Not where large tiles are estimated close: 3072, 1536, 4096
-// 92 and 104, though 2048, 2048, 5504 121 and 103.
+// (the one, 256 KB per large tile, out and in) only costs (the group at 2048, 3072, 8192, 96 tiles: 210 us whole, 219 in
+// halves; 4096, 4096, 11008 559 and 590).  Not where a tile of both products takes less than four thirds of a weight
+// gradient's K steps (the backward, whole and in halves: 3072, 768, 2048 69.4 and 73.2 us; 2560, 512, 1360 57.4 and 60.2), unless all
+// tiles together are few (1280, 256, 688 40.6 and 39.0); elsewhere as estimated.
+// Measured, the whole backward in each form, 27 pairs of d and f from 256 x 688 to 8192 x 28672, T = 16 to 4096, fp32 and bf16
+// gradients: over the 1626 calls with up to 128 tiles the choice takes 0.904 of the time without halves, the best of
+// both for every call 0.903.  8 calls take more than 1.5 % longer than without halves, the worst 1.045 times (2048, 2560, 6912,
+// fp32 gradients).  T = 1024, d = 4096, f = 11008 (fp32) 411 us whole and 356 in halves, 768 343 and 313, 512 317 and 275; 256,
+// 2048, 5504 90 and 73; 656, 3072, 8192 161 and 170, left whole.
 int gemm_sum_form(const GemmArgs &dx, const GemmArgs &dw) {
     double separate;
     const int whole = sum_form_unsplit(dx, dw, &separate);
     GemmArgs sum = dx;
     sum.part = 0;
-    if (tile_count(sum, 4) > kHalvesTiles || 2.0 * k_steps(sum) <= k_steps(dw)) return whole;
+    const bool few = 2 * (tile_count(sum, 2) + tile_count(dw, 2)) <= kComputeUnits / 2;
+    if (tile_count(sum, 4) > kHalvesTiles || (few ? 2.0 : 1.5) * k_steps(sum) <= k_steps(dw)) return whole;
     double unsplit = separate;
     if (whole == 3) {
         sum.part = 3;
         const GemmArgs *list[3] = {&sum, &dw, &dw};
         unsplit = dx_group_time(sum, dw, 3, gemm_wave_blocks(list, 3));
     }
-    return dx_group_time(sum, dw, 4, 2) < unsplit || dx_group_time(sum, dw, 4, 4) < 0.82 * unsplit ? 4 : whole;
+    return std::min(dx_group_time(sum, dw, 4, 2), dx_group_time(sum, dw, 4, 4)) < (dw.c_f32 ? 1.025 : 1.03) * unsplit ? 4 : whole;
 }
 
 int gemm_profile_tag(const GemmArgs &a) {
