@@ -110,12 +110,10 @@ ssg_status ssg_gemm_fp8_layout(const uint8_t *A, ssg_fp8_format a_fmt, int a_kma
  * decision the call itself makes.  Host logic on an MI355X with 256 compute units; nothing is launched and no GPU is
  * needed. */
 typedef struct {
-    int32_t tile;            /* edge of the output tiles: 256 or 128; 0: the kernel for few rows (the inference form's gate/up may
-                              * run a last 16 rows that way in the grid of its 128 x 128 tiles: 128) */
+    int32_t tile;            /* edge of the output tiles: 256 or 128; 0: the kernel for few rows */
     int32_t ring;            /* operand tiles in LDS; few rows: K steps of 128 bytes in a wave's ring */
     int32_t whole_sets;      /* > 0 (tile = 128): the first whole_sets * 8 tiles of 256 x 256 run as such, in a launch before */
-    int32_t rows, cols;      /* few rows: rows and columns of the result per workgroup (else 0; SSG_PLAN_BWD_SECOND: rows = 2
-                              * where the two products of dX run in tiles of their own) */
+    int32_t rows, cols;      /* few rows: rows and columns of the result per workgroup (else 0) */
     int32_t launches;        /* GEMM launches */
 } ssg_gemm_plan;
 ssg_status ssg_gemm_fp8_plan(ssg_fp8_format a_fmt, int a_kmajor, int b_kmajor, int64_t M, int64_t N, int64_t K,
@@ -256,6 +254,21 @@ enum {
     SSG_PLAN_INFER_Y = 5
 };
 ssg_status ssg_mlp_gemm_plan(const ssg_mlp_desc *desc, int which, ssg_gemm_plan *out);
+/* What the plan leaves open: the form in which ssg_mlp_bwd sums the two products of dX (SSG_PLAN_BWD_SECOND), and how many of
+ * the batch's last rows the gate/up GEMM of ssg_infer_fwd hands to the kernel for few rows in the grid of the other rows'
+ * tiles (SSG_PLAN_INFER_GATE_UP).  0 in the fields that `which` does not concern. */
+enum {
+    SSG_DX_TWO_LAUNCHES = 1,     /* one product after the other, the first through scratch */
+    SSG_DX_ONE_TILE = 2,         /* both products in the accumulators of one tile */
+    SSG_DX_HALVES = 3            /* each product in tiles of its own; the later one adds */
+};
+typedef struct {
+    int32_t dx_form;
+    int32_t few_rows;            /* rows that run so (0: none) */
+    int32_t few_rows_block;      /* of them, per workgroup */
+    int32_t reserved;
+} ssg_gemm_route;
+ssg_status ssg_mlp_gemm_route(const ssg_mlp_desc *desc, int which, ssg_gemm_route *out);
 ssg_status ssg_mlp_view_saved(const ssg_mlp_desc *desc, const void *saved, ssg_mlp_saved_view *out);
 ssg_status ssg_mlp_view_workspace(const ssg_mlp_desc *desc, const void *workspace, ssg_mlp_workspace_view *out);
 

@@ -32,7 +32,7 @@ SSG_ROUND_EXACT_DIV, SSG_ROUND_POW2 = 0, 1
 EXPORTS = [
     "ssg_last_error", "ssg_version", "ssg_amax", "ssg_quantize", "ssg_gemm_fp8", "ssg_gemm_fp8_layout", "ssg_gemm_fp8_plan", "ssg_swiglu",
     "ssg_smooth_swiglu_quantize", "ssg_fold_w3", "ssg_mlp_saved_bytes", "ssg_mlp_workspace_bytes",
-    "ssg_mlp_fwd", "ssg_mlp_bwd", "ssg_mlp_bwd_plan", "ssg_mlp_gemm_plan", "ssg_mlp_view_saved", "ssg_mlp_view_workspace",
+    "ssg_mlp_fwd", "ssg_mlp_bwd", "ssg_mlp_bwd_plan", "ssg_mlp_gemm_plan", "ssg_mlp_gemm_route", "ssg_mlp_view_saved", "ssg_mlp_view_workspace",
     "ssg_mlp_scaling_state_bytes", "ssg_mlp_scaling_init",
     "ssg_infer_prepared_bytes", "ssg_infer_workspace_bytes", "ssg_infer_prepare", "ssg_infer_fwd", "ssg_infer_view",
     "ssg_infer_noalloc_max_bytes", "ssg_infer_fwd_noalloc",
@@ -53,6 +53,11 @@ class ssg_gemm_plan(Structure):
     _fields_ = [(n, c_int32) for n in ("tile", "ring", "whole_sets", "rows", "cols", "launches")]
 
 
+class ssg_gemm_route(Structure):
+    _fields_ = [(n, c_int32) for n in ("dx_form", "few_rows", "few_rows_block", "reserved")]
+
+
+SSG_DX_TWO_LAUNCHES, SSG_DX_ONE_TILE, SSG_DX_HALVES = 1, 2, 3
 SSG_PLAN_GATE_UP, SSG_PLAN_Y, SSG_PLAN_BWD_FIRST, SSG_PLAN_BWD_SECOND, SSG_PLAN_INFER_GATE_UP, SSG_PLAN_INFER_Y = range(6)
 
 
@@ -90,6 +95,7 @@ _lib.ssg_gemm_fp8_layout.argtypes = [c_void_p, c_int, c_int, c_void_p, c_int, c_
                                      c_void_p, c_void_p, c_int, c_void_p]
 _lib.ssg_gemm_fp8_plan.argtypes = [c_int, c_int, c_int, c_int64, c_int64, c_int64, c_int, POINTER(ssg_gemm_plan)]
 _lib.ssg_mlp_gemm_plan.argtypes = [POINTER(ssg_mlp_desc), c_int, POINTER(ssg_gemm_plan)]
+_lib.ssg_mlp_gemm_route.argtypes = [POINTER(ssg_mlp_desc), c_int, POINTER(ssg_gemm_route)]
 _lib.ssg_swiglu.argtypes = [c_void_p, c_void_p, c_int64, c_int64, c_void_p, c_void_p]
 _lib.ssg_smooth_swiglu_quantize.argtypes = [c_void_p, c_void_p, c_int64, c_int64, c_int, c_void_p, c_void_p,
                                             c_void_p, c_void_p, c_void_p, c_void_p]
@@ -256,6 +262,12 @@ def ssg_mlp_gemm_plan(desc, which: int) -> ssg_gemm_plan:
     p = ssg_gemm_plan()
     _check(_lib.ssg_mlp_gemm_plan(ctypes.byref(desc), which, ctypes.byref(p)))
     return p
+
+
+def ssg_mlp_gemm_route(desc, which: int) -> ssg_gemm_route:
+    r = ssg_gemm_route()
+    _check(_lib.ssg_mlp_gemm_route(ctypes.byref(desc), which, ctypes.byref(r)))
+    return r
 
 
 def ssg_mlp_view_saved(desc, saved) -> ssg_mlp_saved_view:

@@ -979,9 +979,29 @@ ssg_status ssg_mlp_gemm_plan(const ssg_mlp_desc *desc, int which, ssg_gemm_plan 
         else out->launches = 2;
     } else {
         *out = describe(bg.dx);
-        out->rows = bg.dx.part == 4 ? 2 : 0;
         if (grouped_b) out->tile = 64 * (split < all ? ssg::gemm_group_wave_blocks(group_b, 4, split) : ssg::gemm_group_wave_blocks(group_b, 3, -1));
         else out->launches = bg.dx.part >= 3 ? 3 : 4;
+    }
+    return SSG_OK;
+}
+
+ssg_status ssg_mlp_gemm_route(const ssg_mlp_desc *desc, int which, ssg_gemm_route *out) {
+    const bool infer = which == SSG_PLAN_INFER_GATE_UP || which == SSG_PLAN_INFER_Y;
+    ssg_status rc = infer ? check_infer_desc(desc, "ssg_mlp_gemm_route") : check_desc(desc, "ssg_mlp_gemm_route");
+    if (rc != SSG_OK) return rc;
+    if (!out) return fail(SSG_ERR_ARG, "ssg_mlp_gemm_route: out is NULL");
+    if (which < SSG_PLAN_GATE_UP || which > SSG_PLAN_INFER_Y) return fail(SSG_ERR_ARG, "ssg_mlp_gemm_route: which = %d", which);
+    *out = ssg_gemm_route{};
+    if (which == SSG_PLAN_INFER_GATE_UP) {
+        ssg::GemmArgs g, g2;
+        infer_gemm_shapes(*desc, g, g2);
+        const ssg::GemmPlan p = ssg::gemm_plan(g);
+        out->few_rows = p.rest_rows;
+        out->few_rows_block = p.rest_rows > 0 ? 16 : 0;
+    } else if (which == SSG_PLAN_BWD_SECOND) {
+        BackwardGemms bg;
+        backward_gemm_shapes(*desc, bg);
+        out->dx_form = bg.dx.part == 4 ? SSG_DX_HALVES : bg.dx.part == 3 ? SSG_DX_ONE_TILE : SSG_DX_TWO_LAUNCHES;
     }
     return SSG_OK;
 }

@@ -33,7 +33,8 @@ def test_dx_in_halves(T, d, f, tile, mode):
     blk.bwd()                                             # current scaling: fills the history
     blk.desc = ssg.make_desc(T, d, f, y_dtype=ssg.SSG_F32, scale_mode=mode, **kw)
     p = ssg.ssg_mlp_gemm_plan(blk.desc, ssg.SSG_PLAN_BWD_SECOND)
-    assert (p.tile, p.rows, p.launches) == (tile, 2, 1)
+    assert (p.tile, p.launches) == (tile, 1)
+    assert ssg.ssg_mlp_gemm_route(blk.desc, ssg.SSG_PLAN_BWD_SECOND).dx_form == ssg.SSG_DX_HALVES
     blk.fwd()
     first = None
     for _ in range(4):
@@ -54,7 +55,7 @@ def test_dx_in_halves_in_bf16_and_on_its_own(tmp_path):
     same bits."""
     for shape in ((272, 304, 1040), (1168, 3088, 2064)):
         desc = ssg.make_desc(*shape)
-        assert ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_BWD_SECOND).rows == 2
+        assert ssg.ssg_mlp_gemm_route(desc, ssg.SSG_PLAN_BWD_SECOND).dx_form == ssg.SSG_DX_HALVES
         blk = tm.Block(synth.make_inputs(*shape, seed=tgr.SEED), y_dtype=ssg.SSG_F32)
         blk.fwd()
         blk.bwd()

@@ -157,6 +157,7 @@ def test_inference_form_with_its_last_rows_in_the_few_rows_form(T_inf, d, f):
     bytes, a last column of tiles and a last set of few-rows workgroups that are cut."""
     p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T_inf, d, f), ssg.SSG_PLAN_INFER_GATE_UP)
     assert (p.tile, p.ring, p.whole_sets, p.launches) == (128, 5, 0, 1)
+    assert ssg.ssg_mlp_gemm_route(ssg.make_desc(T_inf, d, f), ssg.SSG_PLAN_INFER_GATE_UP).few_rows == 16
     inp = synth.make_inputs(64, d, f, seed=67)
     ti.check(ti.Infer(inp, T_inf=T_inf, seed_inf=10), tm._np_inputs(inp))
 

@@ -113,8 +113,8 @@ def test_short_batches_take_the_few_rows_form_of_the_inference_form(T, d, f, row
                                           (4096, 4096, 11008, False)])
 def test_dx_runs_in_halves_where_its_few_long_tiles_decide(T, d, f, halves):
     """In halves 0.68 to 0.9 of the time; whole 0.89 to 0.97 of it: tiles no longer than a weight gradient's, or too many."""
-    p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T, d, f), ssg.SSG_PLAN_BWD_SECOND)
-    assert (p.rows == 2) == halves
+    r = ssg.ssg_mlp_gemm_route(ssg.make_desc(T, d, f), ssg.SSG_PLAN_BWD_SECOND)
+    assert (r.dx_form == ssg.SSG_DX_HALVES) == halves
 
 
 @pytest.mark.parametrize("T,d,f,dw,halves", [
@@ -125,8 +125,25 @@ def test_dx_runs_in_halves_where_its_few_long_tiles_decide(T, d, f, halves):
 def test_dx_stays_whole_where_halves_measured_slower(T, d, f, dw, halves):
     """The backward measured in both forms: in the first seven it takes 1.03 to 1.09 times as long in halves, in the others
     0.86 to 0.96 of the time."""
-    p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T, d, f, dw_dtype=dw), ssg.SSG_PLAN_BWD_SECOND)
-    assert (p.rows == 2) == halves
+    r = ssg.ssg_mlp_gemm_route(ssg.make_desc(T, d, f, dw_dtype=dw), ssg.SSG_PLAN_BWD_SECOND)
+    assert (r.dx_form == ssg.SSG_DX_HALVES) == halves
+
+
+def test_the_plan_counts_rows_and_the_route_names_forms():
+    """rows and cols of a plan are a workgroup's of the few-rows kernel and nothing else; what they do not tell has a query of
+    its own, and the fields of another GEMM stay 0."""
+    for T, d, f, form in ((1024, 4096, 11008, ssg.SSG_DX_HALVES), (4096, 4096, 11008, ssg.SSG_DX_ONE_TILE),
+                          (1408, 3712, 10208, ssg.SSG_DX_ONE_TILE), (5280, 3072, 2272, ssg.SSG_DX_TWO_LAUNCHES)):
+        desc = ssg.make_desc(T, d, f)
+        p, r = ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_BWD_SECOND), ssg.ssg_mlp_gemm_route(desc, ssg.SSG_PLAN_BWD_SECOND)
+        assert (p.rows, p.cols, r.dx_form, r.few_rows, r.few_rows_block) == (0, 0, form, 0, 0)
+    for T, rest in ((272, 16), (256, 0), (16, 0)):
+        desc = ssg.make_desc(T, 4096, 11008)
+        r = ssg.ssg_mlp_gemm_route(desc, ssg.SSG_PLAN_INFER_GATE_UP)
+        assert (r.dx_form, r.few_rows, r.few_rows_block) == (0, rest, min(rest, 16))
+        assert ssg.ssg_mlp_gemm_route(desc, ssg.SSG_PLAN_Y).few_rows == 0
+    with pytest.raises(ssg.SsgError):
+        ssg.ssg_mlp_gemm_route(ssg.make_desc(250, 256, 688), ssg.SSG_PLAN_Y)
 
 
 @pytest.mark.parametrize("d,f", [(16, 784), (512, 1360), (2048, 5504), (4096, 11008), (4096, 11024), (20512, 1024)])
