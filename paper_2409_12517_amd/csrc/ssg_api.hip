@@ -997,7 +997,7 @@ ssg_status ssg_mlp_gemm_route(const ssg_mlp_desc *desc, int which, ssg_gemm_rout
         infer_gemm_shapes(*desc, g, g2);
         const ssg::GemmPlan p = ssg::gemm_plan(g);
         out->few_rows = p.rest_rows;
-        out->few_rows_block = p.rest_rows > 0 ? 16 : 0;
+        out->few_rows_block = p.rest_rows > 0 ? ssg::few_last_block(p.rest_rows) : 0;
     } else if (which == SSG_PLAN_BWD_SECOND) {
         BackwardGemms bg;
         backward_gemm_shapes(*desc, bg);

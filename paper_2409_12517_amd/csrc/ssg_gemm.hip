@@ -312,21 +312,45 @@ static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream
     profile_after(st);
 }
 
-// Gate/up of the inference form: 16 rows (the least there can be) beyond whole large tiles go to the few-rows form in the same
-// grid where the others are one round of small tiles, two to most compute units, whose free slots few-rows workgroups fit.
-// With fewer tiles each has its compute unit to itself, and such neighbours slow it down (T = 144, d = 4096, f = 11008: 27.4 us in
-// two rows of small tiles, 33.7 this way); with more than a round they wait like any other (T = 272, d = 8192, f = 28672: 193 in
-// large tiles, 230); an odd row of small tiles leaves half of the last large ones empty and the XCDs uneven (T = 400, d = 3072,
-// f = 8192: 26 and 34).  Within the line, us without and with: T = 272, d = 4096, f = 11008 46 and 34; 272, 4096, 14336 50 and 45;
-// 272, 8192, 14336 98 and 94; 272, 3120, 10032 44 and 37; 272, 1024, 8400 17.1 and 14.0; 528, 2048, 5504 25 and 20; 528, 3072,
-// 8192 40 and 35; 784, 1536, 4096 17.4 and 17.1; 1040, 1024, 2736 14.6 and 14.3; 2064, 512, 2000 16.7 and 14.5.
+// Gate/up of the inference form: up to 64 rows beyond whole large tiles, which would fill another row of tiles to a quarter at
+// most, go to the few-rows form in the grid of the others' small tiles, whose free slots its workgroups fit, where that is
+// estimated shorter.  With at most one tile to a compute unit such neighbours only slow the tiles down (T = 144, d = 4096, f = 11008:
+// 27.4 us in two rows of small tiles, 33.7 this way); a batch that takes whole rounds of large tiles and a rest keeps them.
+// Estimates (microseconds without the launch; K steps of 128): small tiles 7 and 0.62 per step up to 256, 1.2 of two that share a
+// compute unit; large ones 15 and 0.76 to 1.16 per step of a round, the fuller the more; a few-rows workgroup (16 rows; 32 where
+// there are more) takes 0.2 + 0.07 per step (0.7 + 0.12) of one of 512 slots.  Their constants are those with which the choice comes
+// out best over 424 measured calls, so what counts is how they compare.
+// Measured, gate/up alone, 23 pairs of d and f from 256 x 1024 to 8192 x 28672, T = 256 to 2048 and 16, 32, 48 or 64 more: 0.982 of
+// the time without over all, 0.962 were each call's better one known, and 4 calls more than 1.5 % slower, the worst by 0.4 us (784,
+// 400, 4096 15.2 and 15.7).  16, 32, 48 and 64 rows more, in tiles and this way: T = 256, d = 4096, f = 11008 45 and 36, 45 and 39, 44 and
+// 44, 44 and 45; 512, 4096, 11008 65 and 59, 66 and 59, 68 and 63, 68 and 64 (the last two stay in tiles); 1024, 1024, 4096 21 and 18, 20,
+// 21, 20; 512, 2048, 5504 27 and 21, 27 and 21, 28 and 23 (these last stay).  Where they stay because it is longer: 256 and 16, 8192, 28672
+// 184 and 225; 768 and 32, 2048, 5504 30 and 33; 256 and 64, 4096, 14336 50 and 56.
 static int few_last_rows(const GemmArgs &a) {
+    constexpr int kMost = 64;
     const int rest = (int)(a.M % tile_edge(4));
-    if (a.epilogue != EPI_SWIGLU_Q || rest == 0 || rest > 16 || a.M < tile_edge(4)) return 0;
+    if (a.epilogue != EPI_SWIGLU_Q || rest == 0 || rest > kMost || a.M < tile_edge(4)) return 0;
     GemmArgs main = a;
     main.M -= rest;
     const int64_t tiles = tile_count(main, 2);
-    return tiles > kComputeUnits && tiles <= 2 * kComputeUnits ? rest : 0;
+    if (tiles <= kComputeUnits || tiles > 4 * kComputeUnits) return 0;
+    const double ks = k_steps(a), slots = 2.0 * kComputeUnits, split = a.K % 128 != 0 ? 1.8 : 1.0;
+    auto small = [&](int64_t n) {
+        const double two = 1.2, one = 0.62, over = (double)(n - kComputeUnits) / kComputeUnits;
+        const double step = n <= kComputeUnits ? one : n <= 2 * kComputeUnits ? one + (two - one) * over : std::max(two * (double)n / slots, 1.3 * two);
+        return 7.0 + step * split * ks;
+    };
+    auto large = [&](int64_t n) {
+        const int64_t full = n / kComputeUnits, last = n - full * kComputeUnits;
+        return 15.0 + 0.76 * ks * (1.52 * (double)full + (last ? 1.0 + 0.52 * (double)last / kComputeUnits : 0.0));
+    };
+    const int block = few_last_block(rest);
+    const double groups = (double)((rest + block - 1) / block) * (double)((a.N + 15) / 16);
+    const double few = (block == 16 ? 0.2 + 0.07 * ks : 0.7 + 0.12 * ks) * split;
+    const double with = std::max(small(tiles), 7.0 + (1.2 * split * ks * (double)tiles + few * groups) / slots);
+    const GemmArgs *one = &a;
+    const double without = gemm_wave_blocks(&one, 1) == 2 ? small(tile_count(a, 2)) : large(tile_count(a, 4));
+    return with < 0.98 * without ? rest : 0;
 }
 
 GemmPlan gemm_plan(const GemmArgs &a) {
@@ -335,8 +359,9 @@ GemmPlan gemm_plan(const GemmArgs &a) {
     p.wave_blocks = gemm_wave_blocks(&one, 1);
     const double whole = launch_time(a, p.wave_blocks);
     if (gemm_skinny_time(a, &p.form) < whole) { p.wave_blocks = 0; return p; }
-    if (const int rest = few_last_rows(a)) { p.wave_blocks = 2; p.rest_rows = rest; return p; }
     p.whole_sets = full_round_sets(a, whole);
+    if (p.whole_sets == 0) p.rest_rows = few_last_rows(a);
+    if (p.rest_rows > 0) { p.wave_blocks = 2; return p; }
     if (p.whole_sets > 0) p.wave_blocks = 2;
     // one small tile to a compute unit, so up to 8 large tiles on an XCD of 32: the longer ring, which leaves no room
     // for a second workgroup (M = 528, N = 2048, K = 4096, 80 tiles: 27 us with five units, 21 with nine; 65 large tiles

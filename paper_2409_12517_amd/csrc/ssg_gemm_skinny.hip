@@ -153,17 +153,18 @@ __global__ void __launch_bounds__(64 * KW) gemm_skinny_kernel(GemmParams p) {
     gemm_skinny_block<EPI, AFMT, MB, NB, KW, STEPS>(p, blockIdx.x, smem);
 }
 
-// Gate/up of the inference form for a batch whose last row of 128 x 128 tiles would hold at most 16 rows: these run in the
-// few-rows form, in the same grid, in the slots that the tiles leave idle (their LDS fits beside a tile's).  Bound by the
-// tiles, two on a compute unit; a row of 128-row tiles for 16 rows costs a half more (T = 272: 46 us in large tiles, the second
-// row 1/16 full, 34 this way).
+// Gate/up of the inference form for a batch that ends a few rows after whole tiles: these run in the few-rows form, 16 * MB rows
+// to a workgroup, in the same grid, in the slots that the tiles leave idle (their LDS fits beside a tile's).  Bound by the tiles,
+// two on a compute unit; a row of 128-row tiles for 16 rows costs a half more (T = 272, d = 4096, f = 11008: 44 us in large tiles, the
+// second row 1/16 full, 36 this way).  32 rows to a workgroup read the weights half as often as 16 (T = 288: 41 and 38; 320: 52 and 44).
+template <int MB, int STEPS>
 __global__ void __launch_bounds__(kThreads, 2) gemm_swiglu_q_rest_kernel(GemmParams p, GemmParams rest, int tile_blocks) {
-    constexpr int kBytes = std::max(smem_bytes(2), skinny_smem(1, 2, 4, 3));
+    constexpr int kBytes = std::max(smem_bytes(2), skinny_smem(MB, 2, 4, STEPS));
     static_assert(2 * kBytes <= 163840, "two workgroups on a compute unit");
     __shared__ __attribute__((aligned(1024))) uint8_t smem[kBytes];
     const int b = (int)blockIdx.x;
     if (b >= tile_blocks) {
-        gemm_skinny_block<EPI_SWIGLU_Q, kE4M3, 1, 2, 4, 3>(rest, (unsigned)(b - tile_blocks), smem);
+        gemm_skinny_block<EPI_SWIGLU_Q, kE4M3, MB, 2, 4, STEPS>(rest, (unsigned)(b - tile_blocks), smem);
         return;
     }
     const int vb = set_of<2>(b) * 8 + (b & 7);
@@ -263,8 +264,11 @@ void launch_gemm_rest(const GemmArgs &a, int rows, hipStream_t st) {
     rest.A = a.A + (size_t)main.M * (size_t)a.K;
     rest.C = static_cast<uint8_t *>(a.C) + (size_t)main.M * (size_t)a.N;
     const GemmParams p = make_gemm_params(main), q = make_gemm_params(rest);
-    const unsigned blocks = (unsigned)sets_of(p) * set_workgroups(2), more = (unsigned)((a.N + 127) / 128) * 8u;
-    hipLaunchKernelGGL(gemm_swiglu_q_rest_kernel, dim3(blocks + more), dim3(kThreads), 0, st, p, q, (int)blocks);
+    // (column blocks in sets of 8, one to an XCD, the row blocks of one after the other)
+    const int block = few_last_block(rows);
+    const unsigned blocks = (unsigned)sets_of(p) * set_workgroups(2), more = (unsigned)((a.N + 127) / 128 * ((rows + block - 1) / block)) * 8u;
+    if (block == 16) hipLaunchKernelGGL((gemm_swiglu_q_rest_kernel<1, 3>), dim3(blocks + more), dim3(kThreads), 0, st, p, q, (int)blocks);
+    else hipLaunchKernelGGL((gemm_swiglu_q_rest_kernel<2, 2>), dim3(blocks + more), dim3(kThreads), 0, st, p, q, (int)blocks);
 }
 
 void gemm_skinny_extent(const GemmArgs &a, int form, int *rows, int *cols, int *steps) {

@@ -179,7 +179,8 @@ GemmPlan gemm_plan(const GemmArgs &a);
 // few rows (ssg_gemm_skinny.hip): estimated microseconds of the best form, 1e30 for an argument set it is not built for
 double gemm_skinny_time(const GemmArgs &a, int *form);
 void launch_gemm_skinny(const GemmArgs &a, int form, hipStream_t st);
-// gate/up of the inference form, the last `rows` rows of the batch in the few-rows form
+// gate/up of the inference form, the last `rows` rows of the batch in the few-rows form, `few_last_block` to a workgroup
+inline int few_last_block(int rows) { return rows <= 16 ? 16 : 32; }
 void launch_gemm_rest(const GemmArgs &a, int rows, hipStream_t st);
 // rows and columns of the result per workgroup, steps of 128 bytes of K in a wave's ring
 void gemm_skinny_extent(const GemmArgs &a, int form, int *rows, int *cols, int *steps);

@@ -151,13 +151,16 @@ def test_few_rows_of_the_inference_form(T_inf):
     ti.check(ti.Infer(inp, T_inf=T_inf, seed_inf=8), tm._np_inputs(inp))
 
 
-@pytest.mark.parametrize("T_inf,d,f", [(2064, 272, 1040), (1040, 400, 4096)])
-def test_inference_form_with_its_last_rows_in_the_few_rows_form(T_inf, d, f):
-    """16 rows beyond 16 and 8 rows of small tiles, 272 and the 512 tiles up to which the route goes; K with a last step of 16
-    bytes, a last column of tiles and a last set of few-rows workgroups that are cut."""
-    p = ssg.ssg_mlp_gemm_plan(ssg.make_desc(T_inf, d, f), ssg.SSG_PLAN_INFER_GATE_UP)
+@pytest.mark.parametrize("T_inf,d,f,rows", [(2064, 272, 1040, 0), (1040, 400, 4096, 16), (528, 528, 4112, 16), (544, 1040, 4112, 32),
+                                            (1584, 400, 2576, 48), (1088, 400, 4096, 64)])
+def test_inference_form_with_its_last_rows_in_the_few_rows_form(T_inf, d, f, rows):
+    """16 to 64 rows beyond whole large tiles, 260 to 512 small tiles for the others; one and two row blocks of 16 and of 32 rows,
+    the last one half full; K with a last step of 16 bytes, a last column of tiles and a last set of few-rows workgroups that
+    are cut.  And a batch of such a remainder that stays in tiles."""
+    desc = ssg.make_desc(T_inf, d, f)
+    p, r = ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_INFER_GATE_UP), ssg.ssg_mlp_gemm_route(desc, ssg.SSG_PLAN_INFER_GATE_UP)
     assert (p.tile, p.ring, p.whole_sets, p.launches) == (128, 5, 0, 1)
-    assert ssg.ssg_mlp_gemm_route(ssg.make_desc(T_inf, d, f), ssg.SSG_PLAN_INFER_GATE_UP).few_rows == 16
+    assert (r.few_rows, r.few_rows_block) == (rows, 0 if rows == 0 else 16 if rows == 16 else 32)
     inp = synth.make_inputs(64, d, f, seed=67)
     ti.check(ti.Infer(inp, T_inf=T_inf, seed_inf=10), tm._np_inputs(inp))
 
