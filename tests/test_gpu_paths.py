@@ -174,15 +174,18 @@ def _check_backward(blk, delayed):
     _close(blk.dW3, dyq.t() @ hq * sinv / wsc[0], "dW3")
 
 
-# Tiles of the first and second backward launch, and launches of the second: both groups in either tile, a different one
-# each; dX in two launches through its scratch, with dH and dW3 launched singly
-BACKWARD = [(3296, 2064, 3584, 0, 256, 256, 1), (1952, 4096, 1024, 0, 128, 256, 1), (2960, 2064, 3840, 0, 256, 128, 1),
-            (1040, 784, 2736, 0, 128, 128, 1), (5280, 3072, 2272, 0, 128, 256, 4),
-            (1952, 3088, 5376, 2, 256, 256, 1), (2960, 2064, 5632, 2, 256, 128, 1), (1952, 4096, 1024, 2, 128, 256, 1), (1040, 784, 2736, 2, 128, 128, 1)]
+# Tiles of the first and second backward launch, launches of the second, and dX's form: both groups in either tile, a different
+# one each; both products of dX in one tile over whole and ragged K, and in halves; dX in two launches through its scratch,
+# with dH and dW3 launched singly
+ONE, HALVES, TWO = ssg.SSG_DX_ONE_TILE, ssg.SSG_DX_HALVES, ssg.SSG_DX_TWO_LAUNCHES
+BACKWARD = [(3296, 2064, 3584, 0, 256, 256, 1, ONE), (1952, 4096, 1024, 0, 128, 256, 1, ONE), (2960, 2064, 3840, 0, 256, 128, 1, ONE),
+            (1040, 784, 2736, 0, 128, 128, 1, HALVES), (5280, 3072, 2272, 0, 128, 256, 4, TWO), (3584, 640, 1680, 0, 128, 128, 1, ONE),
+            (1952, 3088, 5376, 2, 256, 256, 1, ONE), (2960, 2064, 5632, 2, 256, 128, 1, ONE), (1952, 4096, 1024, 2, 128, 256, 1, ONE),
+            (1040, 784, 2736, 2, 128, 128, 1, HALVES), (3584, 640, 1680, 2, 128, 128, 1, ONE)]
 
 
-@pytest.mark.parametrize("T,d,f,mode,first,second,launches", BACKWARD)
-def test_backward_on_each_route(T, d, f, mode, first, second, launches):
+@pytest.mark.parametrize("T,d,f,mode,first,second,launches,form", BACKWARD)
+def test_backward_on_each_route(T, d, f, mode, first, second, launches, form):
     state = torch.empty(ssg.ssg_mlp_scaling_state_bytes(), dtype=torch.uint8, device=gu.DEV)
     ssg.ssg_mlp_scaling_init(state)
     kw = dict(scaling_state=state, keep_bf16_grads=int(mode == ssg.SSG_SCALE_DELAYED))
@@ -193,6 +196,7 @@ def test_backward_on_each_route(T, d, f, mode, first, second, launches):
         blk.desc = ssg.make_desc(T, d, f, y_dtype=ssg.SSG_F32, scale_mode=mode, **kw)
     p, q = (ssg.ssg_mlp_gemm_plan(blk.desc, w) for w in (ssg.SSG_PLAN_BWD_FIRST, ssg.SSG_PLAN_BWD_SECOND))
     assert (p.tile, q.tile, q.launches) == (first, second, launches)
+    assert ssg.ssg_mlp_gemm_route(blk.desc, ssg.SSG_PLAN_BWD_SECOND).dx_form == form
     for t in (blk.dx, blk.dW1, blk.dW2, blk.dW3):
         t.fill_(float("nan"))
     blk.work.fill_(0x7F)

@@ -51,12 +51,22 @@ def test_block_at_tile_edges(T, d, f):
     tm.check_backward(blk, npi, ref_fw, g)
 
 
-@pytest.mark.parametrize("f", [688, 768])
+# Either form of the sum in either tile: both products in one tile, which changes the units of its accumulators between
+# them (small tiles over whole and ragged K, large ones over whole K, which is all that they take), and in halves
+SUMS = [(272, 256, 688, ssg.SSG_DX_HALVES, 128), (272, 256, 768, ssg.SSG_DX_HALVES, 128), (1552, 2064, 2064, ssg.SSG_DX_HALVES, 256),
+        (1040, 272, 272, ssg.SSG_DX_ONE_TILE, 128), (528, 256, 256, ssg.SSG_DX_ONE_TILE, 128), (2064, 4096, 1024, ssg.SSG_DX_ONE_TILE, 256)]
+
+
+def _assert_sum_form(desc, form, tile):
+    p, r = ssg.ssg_mlp_gemm_plan(desc, ssg.SSG_PLAN_BWD_SECOND), ssg.ssg_mlp_gemm_route(desc, ssg.SSG_PLAN_BWD_SECOND)
+    assert (r.dx_form, p.tile, p.launches) == (form, tile, 1)
+
+
+@pytest.mark.parametrize("T,d,f,form,tile", SUMS)
 @pytest.mark.parametrize("du_exp,dg_exp", [(0, 90), (90, 0), (-60, 60)])
-def test_input_gradient_with_scales_far_apart(f, du_exp, dg_exp):
+def test_input_gradient_with_scales_far_apart(T, d, f, form, tile, du_exp, dg_exp):
     """dX sums two products whose scales may be any two binary32 numbers (here given as delayed scales, 2^90 or 2^120
     apart): the result is the sum of both, whichever is the larger, and finite."""
-    T, d = 272, 256
     inp = synth.make_inputs(T, d, f, seed=5)
     blk = tm.Block(inp, y_dtype=ssg.SSG_F32)
     state = torch.empty(ssg.ssg_mlp_scaling_state_bytes(), dtype=torch.uint8, device=gu.DEV)
@@ -65,6 +75,7 @@ def test_input_gradient_with_scales_far_apart(f, du_exp, dg_exp):
     blk.fwd()
     blk.bwd()                                    # current scaling: fills the history
     blk.desc.scale_mode = ssg.SSG_SCALE_DELAYED
+    _assert_sum_form(blk.desc, form, tile)
     words = state[: 6 * 32 * 4].view(torch.float32)
     words[4 * 32] *= 2.0 ** du_exp
     words[5 * 32] *= 2.0 ** dg_exp
@@ -78,16 +89,15 @@ def test_input_gradient_with_scales_far_apart(f, du_exp, dg_exp):
     ref = (dec(blk.wv("du_q", (T, f), torch.uint8), fp8.E5M2) @ dec(blk.sv("w1_q", (f, d), torch.uint8), fp8.E4M3) / (wsc[1] * sc[1]) +
            dec(blk.wv("dg_q", (T, f), torch.uint8), fp8.E5M2) @ dec(blk.sv("w2_q", (f, d), torch.uint8), fp8.E4M3) / (wsc[2] * sc[2]))
     assert np.isfinite(gu.f32(blk.dx)).all() and np.abs(ref).max() > 0
-    gu.assert_close_gemm(gu.f32(blk.dx), ref, False, f"dX {f} {du_exp} {dg_exp}")
+    gu.assert_close_gemm(gu.f32(blk.dx), ref, False, f"dX {T} {d} {f} {du_exp} {dg_exp}")
 
 
-@pytest.mark.parametrize("f", [688, 768])
+@pytest.mark.parametrize("T,d,f,form,tile", SUMS)
 @pytest.mark.parametrize("du_exp,dg_exp", [(115, -37), (-37, 115)])
-def test_input_gradient_where_one_gradient_flushes_to_zero(f, du_exp, dg_exp):
+def test_input_gradient_where_one_gradient_flushes_to_zero(T, d, f, form, tile, du_exp, dg_exp):
     """Given scales 2^152 apart: the codes of one gradient are all zero, those of the other saturate, and dX (about 2^-98)
     is the product of the latter alone.  The change of units between the two products, 2^-152 or so, is no binary32 number,
     the product of an accumulator (2^28) with it is one."""
-    T, d = 272, 256
     inp = synth.make_inputs(T, d, f, seed=5)
     blk = tm.Block(inp, y_dtype=ssg.SSG_F32)
     state = torch.empty(ssg.ssg_mlp_scaling_state_bytes(), dtype=torch.uint8, device=gu.DEV)
@@ -96,6 +106,7 @@ def test_input_gradient_where_one_gradient_flushes_to_zero(f, du_exp, dg_exp):
     blk.fwd()
     blk.bwd()                                    # current scaling: fills the history
     blk.desc.scale_mode = ssg.SSG_SCALE_DELAYED
+    _assert_sum_form(blk.desc, form, tile)
     words = state[: 6 * 32 * 4].view(torch.float32)
     words[4 * 32], words[5 * 32] = 2.0 ** du_exp, 2.0 ** dg_exp
     blk.fwd()
@@ -106,7 +117,7 @@ def test_input_gradient_where_one_gradient_flushes_to_zero(f, du_exp, dg_exp):
     assert not (gu.u8(blk.wv(other, (T, f), torch.uint8)) & 0x7F).any()
     ref = (fp8.decode(gu.u8(blk.wv(grad, (T, f), torch.uint8)), fp8.E5M2).astype(np.float64) @
            fp8.decode(gu.u8(blk.sv(weight, (f, d), torch.uint8)), fp8.E4M3).astype(np.float64)) / (wsc[i] * sc[j])
-    # binary32 sums of 688 or 768 products: 2e-3 of the largest element, as for every contraction here
+    # binary32 sums of 256 to 2064 products: 2e-3 of the largest element, as for every contraction here
     assert 2.0 ** -126 < np.abs(ref).max() and np.abs(gu.f32(blk.dx) - ref).max() <= 2e-3 * np.abs(ref).max()
 
 
