@@ -1059,8 +1059,8 @@ ssg_status ssg_mlp_bwd(const ssg_mlp_desc *desc, const void *dy, const void *sav
     ssg::GemmArgs &g3 = bg.dw3;
     g3.A = wk + Wl.dy_q; g3.B = sv + L.h_q; g3.sa = wsc + W_SDY; g3.sb = desc->smooth ? nullptr : s;
     g3.col_scale = desc->smooth ? sinv : nullptr; g3.C = dW3;
-    // a13: dX.  One launch that runs both products into the same accumulators, or (gemm_sum_in_one_launch) two
-    // launches, the first product through fp32 scratch
+    // a13: dX, in the form that gemm_sum_form names: both products into the same accumulators (part 3), each in tiles of its
+    // own that meet (4), either in one launch; or two launches, the first product through fp32 scratch (1, 2)
     float *dx_tmp = reinterpret_cast<float *>(wk + Wl.dx_tmp);
     ssg::GemmArgs &g4a = bg.dx;
     const bool dx_one = g4a.part >= 3;

@@ -69,18 +69,22 @@ static bool sum_in_large_tile_ok(int64_t K) { return K % BK == 0 && K >= 2 * BK;
 
 // ---- which tile computes a launch --------------------------------------------------------------------------------
 // The 256 x 256 tile reads half as many operand bytes per product as the 128 x 128 one and keeps the matrix cores
-// about 90 % busy where it fills the chip (y at T = 4096, d = 4096, f = 11008: 133 us against 168); the small one has
+// about 90 % busy where it fills the chip (y at T = 4096, d = 4096, f = 11008: 123 us against 150); the small one has
 // four times the workgroups, two to a compute unit, whose epilogues run under each other's main loops (y at T = 2048,
-// d = 2048, f = 5504, 64 large tiles for 256 compute units: 53 us against 30).  Which wins is a matter of how many
+// d = 2048, f = 5504, 64 large tiles for 256 compute units: 50 us against 25).  Which wins is a matter of how many
 // tiles there are, of how their rows lie to the cache lines and of what comes from HBM, so the time of a launch is
-// estimated for both and the smaller one taken.  Over 3405 contractions (16 to 8192 rows, up to 28672 columns and K) and
-// 842 calls of the forward and inference forms the choice takes 2.2 % longer on average than the best route measured; 25
-// are more than 3 % slower than large tiles alone, the worst 1.24 times (896 x 8448 x 25424, B [K,N], A [K,M]).
+// estimated for both and the smaller one taken.  Over 1499 contractions (16 to 8192 rows, up to 28672 columns and K) the
+// choice takes 1.8 % longer on average than the best route measured (large tiles, small ones, whole rounds and a rest, few
+// rows); 17 are more than 3 % slower than large tiles alone, the worst 1.15 times (5504 x 2384 x 1056, both K-major).  Over 964
+// GEMMs of the forward and inference forms 1.2 %, 7 and 1.20 times (y at T = 1152, d = 7168, f = 18560).
 
 // Microseconds of one tile of a group with all compute units busy, from time stamps (large tile: 1.33 per K step, 1.45 in
 // the long tiles of the one-launch sum, which all run at once; 2.5 before the first step; the epilogue: 33 with the SwiGLU
 // derivative, 42 when it also casts, 10 for U, G or an fp32 store, 6 for bf16).  Small tile, two on a compute unit:
 // 0.96 per K step, 3.5 before and after, a quarter of the large tile's epilogue.
+// (The epilogues are priced as they were when the lines between the tiles were set; measured now: 23.5 with the derivative, 5.6 for
+// an fp32 store.  The constants of all estimates below belong together with these, and the figures above are of the choice that
+// they make with the present kernels.)
 static double k_steps(const GemmArgs &a) {
     const int64_t kbytes = a.a_fmt == kBF16 ? 2 * a.K : a.K;
     return (double)((kbytes + BK - 1) / BK) * (a.part == 3 ? 2.0 : 1.0);
@@ -125,7 +129,7 @@ constexpr double kHbmBytesPerUs = 4.2e6;         // what a launch of these kerne
 // Estimated microseconds of `tiles` of the tiles of one GEMM in a launch of its own.
 // Large tiles: 1.26 per K step in a round that fills the chip.  A last round that does not draws less power and runs at a
 // higher clock: 0.86 per K step with few tiles, 1.06 with half of the chip, and a cheaper epilogue (2064 x 11008 x 11008,
-// 1.5 rounds: 211 to 221 us in large tiles, 251 to 286 in small ones).
+// 1.5 rounds: 207 to 226 us in large tiles, 247 to 292 in small ones).
 static double large_launch_time(const GemmArgs &a, int64_t tiles) {
     const int64_t full = tiles / kComputeUnits, rest = tiles - full * kComputeUnits;
     const double ks = k_steps(a), epilogue = 1.4 * epilogue_cost(a), share = (double)rest / kComputeUnits;
@@ -135,10 +139,10 @@ static double large_launch_time(const GemmArgs &a, int64_t tiles) {
 }
 // Small tiles: a fifth more per K step for each operand that splits lines (256 to 2000 tiles: 0.95, 1.17, 1.33 per step of
 // a full chip with none, one, both), and half as much again for its bytes.  Where compute units hold two, a quarter of the
-// smaller of the two times does not hide behind the larger.  In the training forward they fold the channel maxima of U,
-// G's product with twice the atomics, 64 to a channel at T = 4096, and slow down the range pass over w3 beside them, which
-// a last round of large tiles hides (gate/up at T = 4096, d = 768, f = 2048: 39 us large, 53 small; 32 and 46 without the
-// pass).
+// smaller of the two times does not hide behind the larger.  In the training forward small tiles pay for more atomics on the
+// channel maxima of U, G's product and for a range pass over w3 that a last round of large tiles would hide; both were dearer
+// when this was set (gate/up at T = 4096, d = 768, f = 2048: 39 us large, 53 small; now 34 and 33), so a few long batches of small width stay in
+// large tiles that small ones would take less for (3440, 256, 848: 22.5 and 17.5).
 static double small_launch_time(const GemmArgs &a, int64_t tiles) {
     const int split = split_line_operands(a);
     const double cost = 3.0 + 0.96 * k_steps(a) * (1.0 + 0.2 * split) + 0.25 * epilogue_cost(a);
@@ -207,9 +211,9 @@ int gemm_wave_blocks(const GemmArgs *const *list, int n, double last) {
 
 // Sets of large tiles that make whole rounds of the chip when the rest is worth a launch of small tiles of its own (5 us):
 // a last round of large tiles that fills a third of the chip takes longer than its share.  0: the GEMM stays whole.
-// (gate/up of the inference form at T = 4096, d = 4096, f = 11008, 5.4 rounds: 303 us whole, 288 as 5 rounds and 384 small
-// tiles.  The training forward at d = 3072, f = 8208, W1, W2 cached: T = 2048, 2.03 rounds, 261 us whole, 247 in two;
-// T = 2064, 2.3 rounds, 264 and 256; T = 1552, 1.8 rounds, 216 and 232.)
+// (gate/up of the inference form at T = 4096, d = 4096, f = 11008, 5.4 rounds: 299 us whole, 282 as 5 rounds and 384 small
+// tiles.  Gate/up of the training forward at d = 3072, f = 8208, W1, W2 cached: T = 2048, 2.03 rounds, 119 us whole, 107 in two;
+// T = 2064, 2.3 rounds, 119 and 114; T = 1552, 1.8 rounds, 82 and 96.)
 static int full_round_sets(const GemmArgs &a, double whole) {
     if (a.a_fmt == kBF16) return 0;
     const int64_t tiles = tile_count(a, 4), rounds = tiles / kComputeUnits, rest = tiles - rounds * kComputeUnits;
@@ -218,12 +222,13 @@ static int full_round_sets(const GemmArgs &a, double whole) {
     return split < 0.98 * whole ? (int)(rounds * kComputeUnits / 8) : 0;
 }
 
-// The input gradient of a hidden width that is no multiple of 128: in one launch of small tiles together with the
-// weight gradients, or as two launches of large tiles through fp32 scratch and the weight gradients each on its own
-// (T = 4096, d = 4096, f = 11024, the whole step: 1982 us against 1870; T = 2048, d = 3072, f = 8208: 745 against 884).
 size_t gemm_arrival_words(int64_t M, int64_t N) {
     return (size_t)(4 * ((M + tile_edge(4) - 1) / tile_edge(4)) * ((N + tile_edge(4) - 1) / tile_edge(4)));
 }
+
+// Without halves.  The input gradient of a hidden width that is no multiple of 128: in one launch of small tiles together with
+// the weight gradients, or as two launches of large tiles through fp32 scratch and the weight gradients each on its own
+// (T = 4096, d = 4096, f = 11024, the whole step: 1945 us against 1776; T = 2048, d = 3072, f = 8208: 704 against 798).
 static int sum_form_unsplit(const GemmArgs &dx, const GemmArgs &dw, double *separate_time) {
     *separate_time = 0.0;
     if (sum_in_large_tile_ok(dx.K)) return 3;

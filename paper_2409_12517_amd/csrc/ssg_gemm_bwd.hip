@@ -19,7 +19,8 @@
 
 namespace ssg {
 
-// Up to four GEMMs in one grid, one after the other in dispatch order, all in the same tile (gemm_wave_blocks).
+// Up to four GEMMs in one grid, one of them perhaps as two members, one after the other in dispatch order, all in the same
+// tile (gemm_wave_blocks).
 // Workgroups are dealt in sets of 8 large tiles (see set_of: one per XCD, so that vblock % 8 stays the XCD inside each
 // GEMM and map_tile's per-XCD patches survive); member i runs sets [first[i], first[i] + sets[i]) of its GEMM -- a GEMM
 // may be split between two launches at a set boundary.

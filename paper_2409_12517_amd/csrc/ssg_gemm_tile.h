@@ -21,9 +21,10 @@
 //
 // Epilogues:
 //   STORE       C = acc / (sa*sb) [* col_scale[n]] [+ addend], bf16 or fp32.  A sum of two
-//               products (the input gradient) runs in one tile (PART = 3), or as two launches:
-//               the first leaves its scaled product as fp32 scratch, the second adds it before
-//               rounding (PART = 1, 2).
+//               products (the input gradient) runs in one tile (PART = 3), as two launches: the
+//               first leaves its scaled product as fp32 scratch, the second adds it before
+//               rounding (PART = 1, 2), or with each product in tiles of its own: of two that
+//               belong together the one that ends later adds (PART = 4).
 //   SWIGLU      B tile = 128 (64) rows of W1 and the same rows of W2, so a wave
 //               holds u and g of the same (t,i): stores bf16 U, G and folds
 //               max_t |u * Swish(g)| into the per-channel maxima (Section 4.4).
