@@ -159,7 +159,8 @@ def test_last_rows_of_the_inference_form_leave_the_tiles_where_that_is_shorter(T
 
 @pytest.mark.parametrize("d,f", [(16, 784), (512, 1360), (2048, 5504), (4096, 11008), (4096, 11024), (20512, 1024)])
 def test_buffers_made_for_the_longest_batch_serve_every_shorter_one(d, f):
-    """Neither size falls as T grows, whichever form dX takes at that T, nor depends on the output types."""
+    """Neither size falls as T grows, whichever form dX takes at that T, nor depends on the output types; and where its products
+    have tiles of their own, there is room for both results (64 K floats for each 256 x 256 tile) beside the codes, dU and dG."""
     for extra in ({}, dict(smooth=0, w3_layer_bf16=1)):
         last = (0, 0)
         for T in range(16, 4096 + 1, 16):
@@ -170,5 +171,7 @@ def test_buffers_made_for_the_longest_batch_serve_every_shorter_one(d, f):
                     sizes.add((ssg.ssg_mlp_saved_bytes(desc), ssg.ssg_mlp_workspace_bytes(desc)))
             assert len(sizes) == 1, (T, sizes)
             now = sizes.pop()
+            if ssg.ssg_mlp_gemm_route(desc, ssg.SSG_PLAN_BWD_SECOND).dx_form == ssg.SSG_DX_HALVES:
+                assert now[1] >= T * d + 6 * T * f + 8 * 65536 * (-(-T // 256)) * (-(-d // 256))
             assert now[0] >= last[0] and now[1] >= last[1], (T, last, now)
             last = now
