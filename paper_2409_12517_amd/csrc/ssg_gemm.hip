@@ -247,7 +247,8 @@ static int sum_form_unsplit(const GemmArgs &dx, const GemmArgs &dw, double *sepa
 // (the one, 256 KB per large tile, out and in) only costs (the group at 2048, 3072, 8192, 96 tiles: 210 us whole, 219 in
 // halves; 4096, 4096, 11008 559 and 590).  Not where a tile of both products takes less than four thirds of a weight
 // gradient's K steps (the backward, whole and in halves: 3072, 768, 2048 69.4 and 73.2 us; 2560, 512, 1360 57.4 and 60.2), unless all
-// tiles together are few (1280, 256, 688 40.6 and 39.0); elsewhere as estimated.
+// tiles together are few (1280, 256, 688 40.6 and 39.0); elsewhere as estimated, up to 2.5 % above whole tiles (3 % with bf16
+// gradients), where the choice came out best over the calls that the estimates are fitted to.
 // Measured, the whole backward in each form, 27 pairs of d and f from 256 x 688 to 8192 x 28672, T = 16 to 4096, fp32 and bf16
 // gradients: over the 1626 calls with up to 128 tiles the choice takes 0.904 of the time without halves, the best of
 // both for every call 0.903.  8 calls take more than 1.5 % longer than without halves, the worst 1.045 times (2048, 2560, 6912,
