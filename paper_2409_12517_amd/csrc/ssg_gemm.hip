@@ -244,8 +244,9 @@ static int sum_form_unsplit(const GemmArgs &dx, const GemmArgs &dw, double *sepa
 // Each product of dX in tiles of its own, which meet where the second of them is done: for short batches, whose few tiles of
 // both products (172 K steps at d = 4096, f = 11008) are still running when the weight gradients have long ended.  Up to 80
 // large tiles, twice that as halves; beyond, the tiles of dX fill the chip by themselves and the products' way through memory
-// (the one, 256 KB per large tile, out and in) only costs (the group at 2048, 3072, 8192, 96 tiles: 210 us whole, 219 in
-// halves; 4096, 4096, 11008 559 and 590).  Not where a tile of both products takes less than four thirds of a weight
+// (the one, 256 KB per large tile, out and in) costs (the group at 2048, 3072, 8192, 96 tiles: 210 us whole, 219 in halves;
+// 4096, 4096, 11008 559 and 590; only where f is no multiple of 128, and whole means small tiles, there would still be a gain: the
+// backward at 4096, 2000, 6000 462 and 371).  Not where a tile of both products takes less than four thirds of a weight
 // gradient's K steps (the backward, whole and in halves: 3072, 768, 2048 69.4 and 73.2 us; 2560, 512, 1360 57.4 and 60.2), unless all
 // tiles together are few (1280, 256, 688 40.6 and 39.0); elsewhere as estimated, up to 2.5 % above whole tiles (3 % with bf16
 // gradients), where the choice came out best over the calls that the estimates are fitted to.
