@@ -280,10 +280,17 @@ int gemm_profile_tag(const GemmArgs &a) {
     return 2 * (a.epilogue == EPI_SWIGLU_BWD_Q ? (int)EPI_SWIGLU_BWD : a.epilogue) + a.a_fmt;
 }
 
-template <int WB, int UNITS, int EPI, int LAY>
-static void launch_fmt(const GemmParams &p, int a_fmt, unsigned blocks, hipStream_t st) {
-    if (a_fmt == kE4M3) hipLaunchKernelGGL((gemm_kernel<WB, EPI, kE4M3, 0, LAY, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((gemm_kernel<WB, EPI, kE5M2, 0, LAY, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
+template <int WB, int UNITS, int EPI, int AFMT, int LAY>
+static void launch_tiles(const GemmParams &p, unsigned blocks, hipStream_t st) {
+    if constexpr (UNITS == kLongRing)
+        hipLaunchKernelGGL((gemm_alone_kernel<EPI, AFMT, LAY>), dim3(blocks), dim3(kThreads), (unsigned)smem_bytes(2, kLongRing), st, p);
+    else
+        hipLaunchKernelGGL((gemm_kernel<WB, EPI, AFMT, 0, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
+}
+template <int WB, int UNITS, int LAY>
+static void launch_store_tiles(const GemmParams &p, int a_fmt, unsigned blocks, hipStream_t st) {
+    if (a_fmt == kE4M3) launch_tiles<WB, UNITS, EPI_STORE, kE4M3, LAY>(p, blocks, st);
+    else launch_tiles<WB, UNITS, EPI_STORE, kE5M2, LAY>(p, blocks, st);
 }
 
 template <int WB, int UNITS>
@@ -298,9 +305,9 @@ static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream
     switch (a.epilogue) {
         case EPI_STORE:
             if (a.a_fmt == kBF16) hipLaunchKernelGGL((gemm_kernel<4, EPI_STORE, kBF16, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
-            else if (a.layout == 2) launch_fmt<WB, UNITS, EPI_STORE, 2>(p, a.a_fmt, blocks, st);
-            else if (a.layout == 1) launch_fmt<WB, UNITS, EPI_STORE, 1>(p, a.a_fmt, blocks, st);
-            else launch_fmt<WB, UNITS, EPI_STORE, 0>(p, a.a_fmt, blocks, st);
+            else if (a.layout == 2) launch_store_tiles<WB, UNITS, 2>(p, a.a_fmt, blocks, st);
+            else if (a.layout == 1) launch_store_tiles<WB, UNITS, 1>(p, a.a_fmt, blocks, st);
+            else launch_store_tiles<WB, UNITS, 0>(p, a.a_fmt, blocks, st);
             break;
         case EPI_SWIGLU:
             if (tail) {
@@ -309,11 +316,11 @@ static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream
                 const unsigned extra = (unsigned)(r.blocks_x * col_range_blocks_y(a.tail_rows));
                 hipLaunchKernelGGL(gemm_swiglu_col_range_kernel<WB>, dim3(blocks + extra), dim3(kThreads), 0, st, p, r);
             } else {
-                hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU, kE4M3, 0, 0, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
+                launch_tiles<WB, UNITS, EPI_SWIGLU, kE4M3, 0>(p, blocks, st);
             }
             break;
         default:   // EPI_SWIGLU_Q
-            hipLaunchKernelGGL((gemm_kernel<WB, EPI_SWIGLU_Q, kE4M3, 0, 0, UNITS>), dim3(blocks), dim3(kThreads), 0, st, p);
+            launch_tiles<WB, UNITS, EPI_SWIGLU_Q, kE4M3, 0>(p, blocks, st);
             break;
     }
     profile_after(st);
@@ -373,7 +380,7 @@ GemmPlan gemm_plan(const GemmArgs &a) {
     // one small tile to a compute unit, so up to 8 large tiles on an XCD of 32: the longer ring, which leaves no room
     // for a second workgroup (M = 528, N = 2048, K = 4096, 80 tiles: 27 us with five units, 21 with nine; 65 large tiles
     // give one XCD a second round: 28 and 34)
-    if (p.wave_blocks == 2 && tile_count(a, 4) - 8 * p.whole_sets <= kComputeUnits / 4) p.units = 9;
+    if (p.wave_blocks == 2 && tile_count(a, 4) - 8 * p.whole_sets <= kComputeUnits / 4) p.units = kLongRing;
     return p;
 }
 
@@ -396,7 +403,7 @@ bool launch_gemm(const GemmArgs &a, hipStream_t st) {
     const int full = plan.whole_sets, rest = sets_of(make_gemm_params(a)) - full;
     if (full > 0) launch_gemm_wb<4, 5>(a, 0, full, st);
     if (plan.wave_blocks == 4) launch_gemm_wb<4, 5>(a, 0, rest, st);
-    else if (plan.units == 9) launch_gemm_wb<2, 9>(a, full, rest, st);
+    else if (plan.units == kLongRing) launch_gemm_wb<2, kLongRing>(a, full, rest, st);
     else launch_gemm_wb<2, 5>(a, full, rest, st);
     return true;
 }

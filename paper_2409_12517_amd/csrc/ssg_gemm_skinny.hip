@@ -18,7 +18,6 @@
 
 namespace ssg {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kBlockBytes = 16 * BK;          // 16 rows of one K step: two DMA instructions
 constexpr int skinny_smem(int MB, int NB, int KW, int STEPS) { return KW * STEPS * (MB + NB) * kBlockBytes; }

@@ -5,15 +5,20 @@
 //
 // (the inner products of Eq. 2, the last linear layer of the display after it,
 // and their gradient contractions).  fp32 accumulation on the matrix cores with
-// v_mfma_f32_32x32x64_f8f6f4, the only FP8 form that reaches the full rate on
-// this chip; its per-operand format selectors take E4M3 or E5M2.
+// v_mfma_f32_16x16x128_f8f6f4; its per-operand format selectors take E4M3 or E5M2.
+// The chip runs these kernels at its power limit, and of the two forms with the full
+// rate this one draws less per product: a loop of nothing but MFMAs on FP8 codes of
+// Gaussian numbers sustains 4500 TFLOP/s with it and 4120 with v_mfma_f32_32x32x64_f8f6f4
+// (4960 both on one repeated code), y at T = 4096, d = 4096, f = 11008 takes 122 us (126),
+// gate/up of the inference form and y together 424 (438).
 //
 // Workgroup: 256 threads = 4 waves as 2 (M) x 2 (N).  Two tile sizes, by the template parameter WB:
-//   WB = 4  256 x 256 x 128, each wave owns 128 x 128 outputs = 4 x 4 MFMA blocks (256 accumulator registers, one wave
-//           per SIMD).  Bound by the matrix cores and the power they draw: 90 % of the cycles of the main loop are MFMA.
+//   WB = 4  256 x 256 x 128, each wave owns 128 x 128 outputs = 8 x 8 MFMA blocks (256 accumulator registers, one wave
+//           per SIMD).  Bound by the power that the matrix cores and the way of the operands into LDS draw: 81 % of the cycles of
+//           that y are MFMA, at 1.8 GHz; without the loads into LDS it would take 106 us of 122, without the fragment reads 118.
 //   WB = 2  128 x 128 x 128, 64 x 64 outputs per wave (64 accumulator registers), two workgroups per compute unit.
-//           Bound by LDS: every 1024 MFMA cycles of a compute unit need 64 KB written and 128 KB read there (1536 cycles
-//           at 128 B); main loop about 60 % MFMA, but one workgroup's prologue and epilogue run under the other's main
+//           Bound by the loads into LDS, twice the bytes per product: 60 % of the cycles are MFMA, at 1.6 GHz (4096 x 2048 x 4096
+//           32 us, 24 without loads), but one workgroup's prologue and epilogue run under the other's main
 //           loop, and four times the tiles fill the chip where the large ones leave most of it idle.
 // Operand tiles are streamed global -> LDS with 16-byte direct-to-LDS loads (no staging registers) into a ring of five
 // 32 KB (16 KB) tiles, or nine of 16 KB where a small tile has its compute unit to itself.  A row of a tile is 128 bytes; the eight 16-byte chunks of a row are stored XOR-permuted by the
@@ -33,17 +38,19 @@
 //   SWIGLU_Q    as SWIGLU, but stores only the E4M3 cast of u * Swish(g) (inference form).
 //   SWIGLU_BWD_Q as SWIGLU_BWD, but dU, dG leave as E5M2 codes under given scales (delayed scaling).
 #pragma once
+#include <type_traits>
+
 #include "ssg_device.h"
 #include "ssg_internal.h"
 
 namespace ssg {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 typedef __attribute__((address_space(1))) const void *global_void_ptr;
 
-// The tile is square, 64 * WB rows and columns, WB = 4 or 2 blocks of 32 x 32 per wave and direction.
+// The tile is square, 64 * WB rows and columns, 2 * WB blocks of 16 x 16 per wave and direction (WB = 4 or 2).
 constexpr int BK = 128;
 constexpr int tile_edge(int WB) { return 64 * WB; }
 constexpr int unit_bytes(int WB) { return tile_edge(WB) * BK; }   // one operand tile of one K step: 32 or 16 KB
@@ -80,10 +87,12 @@ struct GemmParams {
 };
 
 // An LDS row holds the 128 bytes (eight 16-byte chunks, one full cache line) of one matrix row for one
-// K step.  Two rows fill the 256-byte bank period, so rows r, r+2, r+4, ... would collide when 16
-// lanes read the same chunk of 16 consecutive rows; XOR-ing the chunk index with (r >> 1) & 7
-// spreads 16 consecutive rows over the sixteen 16-byte bank groups.
-__device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
+// K step; two rows fill the 256-byte bank period, so the chunks of row r are XOR-ed with a permutation of r >> 1.  A fragment
+// read takes 16 rows by four chunks c, c + 2, c + 4, c + 6, 16 lanes to a quarter, and goes through the banks 16 lanes at a time:
+// lanes 0-3, 12-15 and 20-27, then 4-11, 16-19 and 28-31, and the same of the upper half.  Rows 0-3 and 12-15 of one chunk meet
+// rows 4-11 of the next there, so 2 XOR (r >> 1) has to map each half of the rows onto itself: the two low bits of r >> 1
+// are exchanged.  (With r >> 1 as it stands half of the LDS cycles were conflicts: y at 4096 x 4096 x 11008 124 us, 49 % of them.)
+__device__ __forceinline__ int swz(int row) { return (row >> 1 & 4) | (row & 2) | (row >> 2 & 1); }
 
 // Direct-to-LDS loads are issued through inline assembly: the compiler would otherwise wait for
 // ALL outstanding LDS-DMA loads before every ds_read (it cannot tell the two LDS stages apart),
@@ -108,27 +117,27 @@ __device__ __forceinline__ void dma16_s(const uint8_t *base_uniform, uint32_t la
 #endif
 }
 
-// AFMT = kE4M3 / kE5M2: the 32 bytes of a fragment are 32 FP8 codes of one row, one MFMA with K = 64 per fragment
+// AFMT = kE4M3 / kE5M2: the 32 bytes of a fragment are 32 FP8 codes of one row, one MFMA with K = 128 per fragment
 // pair.  AFMT = kBF16 (both operands bf16, the comparison variant with the last linear layer left unquantized):
 // the same 32 bytes are 16 bf16 of one row -- two 16-byte pieces of 8 elements each -- and a fragment pair feeds two
-// MFMAs with K = 16 (v_mfma_f32_32x32x16_bf16), the first on the low pieces of both operands, the second on the
+// MFMAs with K = 32 (v_mfma_f32_16x16x32_bf16), the first on the low pieces of both operands, the second on the
 // high ones.  Which elements of K meet in which MFMA does not matter as long as A and B agree, and they do: both
 // fragments come from the same LDS layout through the same lane arithmetic.  Per 128 bytes of K this is twice the
 // MFMA instructions at half the duration each, and K in bytes is twice the element count.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
-// The weight's fragment goes first: of a 32 x 32 block a lane then holds row l & 31, and its registers 4q .. 4q+3 are the four
-// neighbouring columns 8q + 4 (l >> 5) .. + 3, which leave in one 16-byte (fp32) or 8-byte (bf16) access to LDS.  (With the
-// operands the other way round a lane holds one column, and every register is an access of its own.)
+// The weight's fragment goes first: of a 16 x 16 block a lane then holds row l & 15 and, in its four registers, the neighbouring
+// columns 4 (l >> 4) .. + 3, which leave in one 16-byte (fp32) or 8-byte (bf16) access to LDS.  (With the operands the other
+// way round a lane holds one column, and every register is an access of its own.)
 template <int AFMT>
-__device__ __forceinline__ v16f mfma(const v8i &a, const v8i &b, const v16f &c) {
+__device__ __forceinline__ v4f mfma(const v8i &a, const v8i &b, const v4f &c) {
     if constexpr (AFMT == kBF16) {
         const v4i a_lo = {a[0], a[1], a[2], a[3]}, a_hi = {a[4], a[5], a[6], a[7]};
         const v4i b_lo = {b[0], b[1], b[2], b[3]}, b_hi = {b[4], b[5], b[6], b[7]};
-        const v16f t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, b_lo), __builtin_bit_cast(v8bf, a_lo), c, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, b_hi), __builtin_bit_cast(v8bf, a_hi), t, 0, 0, 0);
+        const v4f t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, b_lo), __builtin_bit_cast(v8bf, a_lo), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, b_hi), __builtin_bit_cast(v8bf, a_hi), t, 0, 0, 0);
     } else {
-        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b, a, c, kE4M3, AFMT, 0, 0, 0, 0);
+        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b, a, c, kE4M3, AFMT, 0, 0, 0, 0);
     }
 }
 
@@ -176,17 +185,12 @@ __device__ __forceinline__ void map_tile(const GemmParams &p, int vblock, int &t
 }
 
 // ------------------------------------------------------------------------------------------------
-// Large tile: 4 waves (one per SIMD), 128 x 128 wave tiles: 256 accumulator registers per lane (the AGPR half of
-// the register file); every A and B row block is read from LDS by only two waves.  With a single
-// wave per SIMD there is no partner to hide stalls, so the wave software-pipelines itself (the small tile's waves do
-// the same, with 4 MFMAs, 4 fragments and 4 loads where 16, 8 and 8 stand here): while the
-// 16 MFMAs of one 64-wide K half run from one fragment set, the next half's fragments are read into
-// the other set, one fragment after every second MFMA, and one direct-to-LDS load of the new operand
-// tiles follows every pair of MFMAs throughout the K step.  One barrier per K step, in its middle: by
-// then every wave holds both halves of step k in registers, so the barrier both retires step k's ring
-// slots and publishes step k+1 (each wave first waits for its own DMA share).
+// 4 waves, one per SIMD and workgroup; every A and B row block is read from LDS by only two waves.  In the large tile a wave has
+// no partner on its SIMD to hide stalls, so it pipelines itself: fragments are read half a K step or more before their products,
+// loads go out one at a time throughout the step.  See the schedule in gemm_tile.
 constexpr int kThreads = 256;
-constexpr int waves_per_simd(int WB, int UNITS = 5) { return WB == 4 || UNITS > 5 ? 1 : 2; }     // what registers and LDS leave room for
+// What registers and LDS leave room for.
+constexpr int waves_per_simd(int WB) { return WB == 4 ? 1 : 2; }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -195,13 +199,9 @@ constexpr int kThrough = 16;
 constexpr int kBufferWord3 = 0x00020000;              // of a raw buffer's descriptor: 32-bit data
 
 template <int N> __device__ __forceinline__ void wait_dma() {       // at most N direct-to-LDS loads still in flight
-    static_assert(N == 4 || N == 8 || N == 16 || N == 20 || N == 24, "whole units of 4 or 8 loads");
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    if (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    if (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-    if (N == 20) asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
-    if (N == 24) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 #endif
 }
 
@@ -220,7 +220,8 @@ template <int N> __device__ __forceinline__ void wait_dma() {       // at most N
 template <int WB, int EPI, int AFMT, int PART, int LAY, int UNITS = 5>
 __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock, const int sub, uint8_t *smem) {
     constexpr int BM = tile_edge(WB), BN = BM, WN = 32 * WB, kUnitBytes = unit_bytes(WB);
-    constexpr int NI = 2 * WB;                         // DMA instructions of 1 KB per wave and unit; fragment reads per half step
+    constexpr int NI = 2 * WB;                         // DMA instructions of 1 KB per wave and unit
+    constexpr int RB = 2 * WB;                         // blocks of 16 rows (columns) of a wave's tile; fragments of either operand
     constexpr int kUnits = UNITS, AHEAD = (UNITS - 1) / 2;   // operand tiles are issued AHEAD K steps before their use
     constexpr int kChunks = BM / 16;                   // 16-byte chunks of a K-major row
     constexpr bool HALF = PART == 4, ADD = PART == 2;
@@ -250,18 +251,18 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 
     // DMA slots: a unit is 4 * NI instructions of 1 KB, NI per wave.  K-contiguous operand: an instruction is 8 rows x
     // 128 B (rows (NI*w+j)*8 + l/8).  K-major operand: 4 rows of K x 256 B (WB = 4) or 8 x 128 B (WB = 2); the 16-byte
-    // chunks of a row are permuted so that a transposing read is free of bank conflicts.  The 32 lanes of one K group
-    // read eight consecutive K rows of two adjacent chunks, which have to cover all 64 banks once.
+    // chunks of a row are permuted so that a transposing read is free of bank conflicts.  Every 32 lanes read one chunk of
+    // eight consecutive K rows and of the eight that are 32 further on, which have to cover all 64 banks once.
     //   WB = 4 (a row is the 256-byte bank period): chunk c of K row k sits at position
     //     c ^ (k & 7) ^ (((c & 1) ^ (k >> 5 & 1)) << 3): the XOR with k & 7 spreads the rows over the eight positions of
     //     a half row, the chunk's own low bit picks the half.
-    //   WB = 2 (two rows are the period): position c ^ ((k >> 1 & 3) << 1): the row's parity picks the half, the XOR
-    //     spreads the four rows of one parity over four pairs of positions.
+    //   WB = 2 (two rows are the period): position c ^ ((k >> 1 & 3) << 1) ^ (k >> 5 & 1): the row's parity picks the half,
+    //     the XOR spreads the four rows of one parity over four pairs of positions, k >> 5 picks the position of the pair.
     const int lrow = l >> 3;
     const int chunk_even = (l & 7) ^ swz(lrow), chunk_odd = (l & 7) ^ swz(8 + lrow);
     // the chunk that belongs at position `pos` of K row k (the maps are their own inverses in the low three bits)
     auto kmaj_chunk = [](int k, int pos) {
-        if (WB == 2) return pos ^ (((k >> 1) & 3) << 1);
+        if (WB == 2) return pos ^ (((k >> 1) & 3) << 1) ^ ((k >> 5) & 1);
         const int low = (pos ^ k) & 7;
         return low | ((((pos >> 3) ^ (k >> 5) ^ low) & 1) << 3);
     };
@@ -299,51 +300,45 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     if (kDual && w >= 2) b_src = p.B2;      // waves 2, 3 fill the upper half of the tile rows
     const uint32_t lds_w = (uint32_t)(w * NI) * 1024u;
 
-    // LDS byte offset of this lane's two 16-byte chunks of a fragment row, per K half; the row block of a
-    // fragment adds a wave-uniform base and a compile-time multiple of 4 KB (an instruction immediate)
-    uint32_t frag_off[2][2];
+    // LDS byte offset of this lane's two 16-byte chunks of a fragment: row l & 15 of 16, bytes 32 (l >> 4) .. + 31 of its 128; the
+    // row block of a fragment adds a wave-uniform base and a compile-time multiple of 2 KB (an instruction immediate)
+    uint32_t frag_off[2];
 #pragma unroll
-    for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-            frag_off[kh][e] = (uint32_t)((l & 31) * BK + (((kh * 4 + (l >> 5) * 2 + e) ^ swz(l & 31)) << 4));
+    for (int e = 0; e < 2; ++e) frag_off[e] = (uint32_t)((l & 15) * BK + ((((l >> 4) * 2 + e) ^ swz(l & 15)) << 4));
     // K-major operand: lane offsets of the transposing reads.  In every group of 16 lanes the even lanes supply
     // the 8-byte words whose byte j goes to output lane j, the odd lanes those for output lane 8+j; lane p of a
-    // group therefore points at K row p/2 (of eight) and at half p%2 of the 16-byte chunk that holds the group's
-    // 16 rows of the 32-row block.  Four such reads (K rows +0, +8, +16, +24) make one fragment.
-    uint32_t tr_a[WB], tr_b[WB];
+    // group therefore points at K row p/2 (of eight) and at half p%2 of the 16-byte chunk that holds the 16 rows of the
+    // fragment.  Four such reads (K rows +0, +8, +16, +24 from the group's 32) make one fragment.
+    uint32_t tr_a[RB], tr_b[RB];
     {
-        const int g16 = l >> 4, kg = g16 >> 1, g1 = g16 & 1, t = (l & 15) >> 1, e = l & 1;
+        const int kg = l >> 4, t = (l & 15) >> 1, e = l & 1;
 #pragma unroll
-        for (int rb = 0; rb < WB; ++rb) {
-            // position of chunk c in K row k = kg * 32 + t (+ multiples of 8 and 64, which do not enter)
-            const int ca = wm * 2 * WB + rb * 2 + g1, cb = wn * 2 * WB + rb * 2 + g1;
-            auto pos = [&](int c) { return WB == 2 ? c ^ ((t >> 1) << 1) : ((c ^ t) & 7) | ((((c >> 3) ^ kg ^ c) & 1) << 3); };
-            tr_a[rb] = (uint32_t)((kg * 32 + t) * BM + (pos(ca) << 4) + e * 8);
-            tr_b[rb] = (uint32_t)((kg * 32 + t) * BM + (pos(cb) << 4) + e * 8);
+        for (int rb = 0; rb < RB; ++rb) {
+            // position of chunk c in K row k = kg * 32 + t (+ multiples of 8 below 32, which do not enter)
+            auto pos = [&](int c) { return WB == 2 ? c ^ ((t >> 1) << 1) ^ (kg & 1) : ((c ^ t) & 7) | ((((c >> 3) ^ kg ^ c) & 1) << 3); };
+            tr_a[rb] = (uint32_t)((kg * 32 + t) * BM + (pos(wm * RB + rb) << 4) + e * 8);
+            tr_b[rb] = (uint32_t)((kg * 32 + t) * BM + (pos(wn * RB + rb) << 4) + e * 8);
         }
     }
     const uint32_t a_wave_base = (uint32_t)(wm * WN) * BK;
     const uint32_t b_wave_base = (uint32_t)(kDual ? wn * (WN / 2) : wn * WN) * BK;
     auto b_block_off = [](int nb) -> uint32_t {      // SWIGLU: the first half of the blocks from the W1 rows, the others from the W2 rows
-        return (uint32_t)(kDual ? (nb / (WB / 2)) * (BN / 2) + (nb % (WB / 2)) * 32 : nb * 32) * BK;
+        return (uint32_t)(kDual ? (nb / (RB / 2)) * (BN / 2) + (nb % (RB / 2)) * 16 : nb * 16) * BK;
     };
 
-    v16f acc[WB][WB];
+    v4f acc[RB][RB];
 #pragma unroll
-    for (int mb = 0; mb < WB; ++mb)
+    for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < WB; ++nb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[mb][nb][i] = 0.0f;
+        for (int nb = 0; nb < RB; ++nb) acc[mb][nb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int nk = (int)((p.K + BK - 1) / BK);
     // the staging patch of the epilogue (one 32-row slab of a wave's accumulators at a time), also used where a
     // sum of two products changes the units of its accumulators
     constexpr int kPitch = WN + 4;                       // floats; neighbouring rows are one 16-byte bank group apart
     float *stg = reinterpret_cast<float *>(smem) + w * (32 * kPitch);
-    // where accumulator registers 4q .. 4q+3 of column block nb of a slab lie in the patch
-    auto stg_at = [&](int nb, int q) { return reinterpret_cast<float4 *>(stg + (l & 31) * kPitch + (l >> 5) * 4 + nb * 32 + q * 8); };
+    // where this lane's registers of block (r, nb) of a slab (r = 0, 1) lie in the patch
+    auto stg_at = [&](int r, int nb) { return reinterpret_cast<v4f *>(stg + (r * 16 + (l & 15)) * kPitch + nb * 16 + (l >> 4) * 4); };
     // a sum of two products starts with the one whose scales are larger: its accumulators change units by a factor of
     // at most 1, so that they cannot overflow however far apart the scales are
     bool swapped = false;
@@ -377,51 +372,75 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                 }
             }
         };
-        v8i fa[2][WB], fb[2][WB];
-        // The i-th fragment read of a K half, in the order the MFMAs need them (B0 A0 B1 B2 B3 A1 A2 A3:
-        // the first four MFMAs use A0 with B0..B3), from ring slots sa / sb; g = 0..3: A row blocks,
-        // 4..7: B row blocks
-        auto load_frag = [&](int set, uint32_t sa, uint32_t sb, int kh, int i) {
-            constexpr int kOrder4[8] = {4, 0, 5, 6, 7, 1, 2, 3}, kOrder2[4] = {2, 0, 3, 1};
-            const int g = WB == 4 ? kOrder4[i] : kOrder2[i & 3];
-            if ((g < WB && AKM) || (g >= WB && BKM)) {
+        constexpr int H = RB / 2;                            // "lo" and "hi": the first and the second half of a wave's row blocks
+        constexpr int kSets = WB == 4 ? 1 : 2;
+        v8i fa[RB], fb_lo[kSets][H], fb_hi[H];
+        // half e of a fragment, row block g of A (is_b: of B; lo: into `set`), out of ring slot `slot`
+        auto load_half = [&](int set, bool is_b, int g, uint32_t slot, int e) {
+            v8i &f = !is_b ? fa[g] : g < H ? fb_lo[set][g % H] : fb_hi[g % H];
+            if (is_b ? BKM : AKM) {
                 typedef int v2i_t __attribute__((ext_vector_type(2)));
                 typedef __attribute__((address_space(3))) v2i_t *lds_v2i_ptr;
-                const uint8_t *base = smem + (g < WB ? sa * kUnitBytes + tr_a[g % WB] : sb * kUnitBytes + tr_b[g % WB]) + kh * 64 * BM;
+                const uint8_t *base = smem + slot * kUnitBytes + (is_b ? tr_b[g] : tr_a[g]) + e * 16 * BM;
                 const v2i_t q0 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base));
                 const v2i_t q1 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 8 * BM));
-                const v2i_t q2 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 16 * BM));
-                const v2i_t q3 = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + 24 * BM));
-                const v8i f = v8i{q0.x, q0.y, q1.x, q1.y, q2.x, q2.y, q3.x, q3.y};
-                if (g < WB) fa[set][g % WB] = f; else fb[set][g % WB] = f;
-                return;
+                f[4 * e] = q0.x; f[4 * e + 1] = q0.y; f[4 * e + 2] = q1.x; f[4 * e + 3] = q1.y;
+            } else {
+                const uint32_t ub = slot * kUnitBytes + (is_b ? b_wave_base : a_wave_base);   // uniform
+                const uint32_t imm = is_b ? b_block_off(g) : (uint32_t)(g * 16 * BK);
+                const uint4 q = *reinterpret_cast<const uint4 *>(smem + (frag_off[e] + ub) + imm);
+                f[4 * e] = (int)q.x; f[4 * e + 1] = (int)q.y; f[4 * e + 2] = (int)q.z; f[4 * e + 3] = (int)q.w;
             }
-            const uint32_t ub = g < WB ? sa * kUnitBytes + a_wave_base : sb * kUnitBytes + b_wave_base;   // uniform
-            const uint32_t imm = g < WB ? (uint32_t)(g * 32 * BK) : b_block_off(g - WB);
-            const uint4 lo = *reinterpret_cast<const uint4 *>(smem + (frag_off[kh][0] + ub) + imm);
-            const uint4 hi = *reinterpret_cast<const uint4 *>(smem + (frag_off[kh][1] + ub) + imm);
-            const v8i f = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-            if (g < WB) fa[set][g % WB] = f; else fb[set][g % WB] = f;
         };
-        auto mfma_group = [&](int set, int g) {     // the g-th of the NI equal shares of a half step's WB * WB MFMAs
-#pragma unroll
-            for (int q = (WB / 2) * g; q < (WB / 2) * (g + 1); ++q)
-                acc[q / WB][q % WB] = mfma<AFMT>(fa[set][q / WB], fb[set][q % WB], acc[q / WB][q % WB]);
-        };
+        auto mul = [&](int set, int r, int c) { acc[r][c] = mfma<AFMT>(fa[r], c < H ? fb_lo[set][c % H] : fb_hi[c % H], acc[r][c]); };
         // s_waitcnt lgkmcnt(0) through the builtin (gfx9 encoding: vmcnt and expcnt fields at their
         // maxima), so that the compiler's own wait bookkeeping sees it
         auto wait_lds = [&]() { __builtin_amdgcn_s_waitcnt(0xC07F); };
 
-        // Schedule of a K step k (units 2k, 2k+1 in ring slots sa, sb):
-        //   first half   16 MFMAs on fragment set 0 (k, K half 0); reads (k, half 1) into set 1;
-        //                issues unit 2k+4 (A of step k+2) into the slot that B of step k-1 left (units and steps as
-        //                with a ring of five; UNITS - 1 for the 4 and AHEAD for the 2 in general)
-        //   barrier      each wave first waits for its share of units 2k+2, 2k+3 and for its LDS reads:
-        //                step k's slots are free, step k+1 is visible to all
-        //   second half  16 MFMAs on set 1; reads (k+1, half 0) into set 0; issues unit 2k+5 (B of
-        //                step k+2) into the slot of unit 2k
-        // so one DMA instruction follows every pair of MFMAs throughout and the texture path never
-        // sees a burst.
+        // Schedule of a K step k (units 2k, 2k+1 in ring slots sa, sb; units and steps named as with a ring of five): the quarters
+        // of the wave's tile in the order (A lo, B lo), (A lo, B hi) | (A hi, B hi), (A hi, B lo), the barrier in the middle.  Each
+        // wave has waited for its share of units 2k+2, 2k+3 and for its LDS reads there: step k's slots are free, step k+1 is
+        // visible to all.  Before it unit 2k+4 is issued into the slot that B of step k-1 left, after it 2k+5 into that of 2k.
+        // Consecutive MFMAs share a fragment, and no two stand together without what else there is to issue: an MFMA takes 32
+        // cycles, eight issue slots, and nothing may follow it but what these hold.
+        //   Large tile, registers for one step's fragments: B hi, A hi of step k are read before the barrier (all of them two
+        //   groups of four before it), A lo and B lo of step k+1 after it, each in the place of the one whose last product is done.
+        //   Small tile, bound by LDS: all that can be is read after the barrier (A lo, B lo, B hi of step k+1) and A hi right
+        //   before the second quarter, so that nothing is waited for at the barrier and reads are under way all the time.
+        //   B lo is still in use when the next one is read: two sets, and steps in pairs.
+        constexpr int kSlots = 2 * H * H;                   // MFMAs of half a step
+        // the t-th MFMA of a half: by columns, in the third quarter by rows, back and forth
+        auto product = [&](int set, int half, int t) {
+            const int q = 2 * half + t / (H * H), g = t % (H * H) / H, i = t % H;
+            const int up = g & 1 ? H - 1 - i : i, down = H - 1 - up;
+            if (q == 0) mul(set, up, g);
+            if (q == 1) mul(set, up, H + g);
+            if (q == 2) mul(set, H + g, H + down);
+            if (q == 3) mul(set, H + down, g);
+        };
+        // what is read after it, out of slots a and b (first half: of step k, second half: of step k+1)
+        auto reads = [&](int set, int half, int t, uint32_t a, uint32_t b) {
+            if (WB == 2) {
+                if (half == 0 && t < 2 * H) load_half(0, false, H + t / 2, a, t % 2);
+                if (half == 1 && t < 2 * H)
+                    for (int e = 0; e < 2; ++e) load_half(set ^ 1, t % 2 != 0, t / 2, t % 2 ? b : a, e);
+                if (half == 1 && t >= 2 * H) load_half(0, true, H + t / 2 - H, b, t % 2);
+                return;
+            }
+            const int g = t / H, i = t % H;
+            if (half == 0) {
+                const int n = 3 * g + (i == 3 ? 2 : i);     // (the third place of four is a load's)
+                if (i != 2 && n < 2 * H) load_half(0, true, H + n / 2, b, n % 2);
+                else if (i != 2 && n < 4 * H) load_half(0, false, n / 2, a, n % 2);
+            } else if (g < H) {
+                if (i < 2) load_half(0, false, g, a, i);
+            } else if (i == H - 1) {
+                for (int e = 0; e < 2; ++e) load_half(0, true, g - H, b, e);
+            }
+        };
+        // which load of its unit is issued there, -1: none
+        auto load_at = [](int t) { return WB == 2 ? (t % 2 ? t / 2 : -1) : (t % H == 2 ? t / H : -1); };
+
         const int kwhole = (int)(p.K / BK);                 // K steps with all their 128 bytes; a ragged last one is zero filled
         const int64_t a_step = AKM ? (int64_t)BK * p.M : BK, b_step = BKM ? (int64_t)BK * p.N : BK;   // bytes per K step
         if (kTwoWhole || kwhole >= AHEAD) {
@@ -438,69 +457,68 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             for (int u = 0; u < UNITS - 1; ++u) issue_unit(u);
         }
         if (nk >= AHEAD) wait_dma<(UNITS - 3) * NI>();                       // units 0 and 1 have landed
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else wait_dma<0>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < NI; ++g) load_frag(0, 0, 1, 0, g);
+        for (int g = 0; g < H; ++g)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                load_half(0, false, g, 0, e);
+                load_half(0, true, g, 1, e);
+            }
+        if (WB == 2)
+#pragma unroll
+            for (int n = 0; n < 2 * H; ++n) load_half(0, true, H + n / 2, 1, n % 2);
 
-        // Steady state: the steps whose new units are whole run a body without any per-instruction check:
-        // wave-uniform source pointers, lane offsets from registers.  The last AHEAD steps, and one more before
-        // them when the last one is ragged, take the general body.
-        // (a sum of two products in the large tile is launched on whole K steps, at least two, only: no general body)
-        const int kfast = kwhole > AHEAD ? kwhole - AHEAD : 0;
         uint32_t sa = 0, sb = 1, sp = UNITS - 1;     // ring slots of units 2k, 2k+1 and 2k+UNITS-1
         auto next_slot = [](uint32_t s) { const uint32_t t = s + 2; return t >= (uint32_t)kUnits ? t - kUnits : t; };
         // wave-uniform sources of the units issued during step k (K step k+AHEAD): running pointers in scalar registers
         const uint8_t *ua = a_src + AHEAD * a_step, *ub = b_src + AHEAD * b_step;
-        for (int k = 0; k < kfast; ++k) {
+        // FAST: the step's new units are whole, no per-instruction check: wave-uniform source pointers, lane offsets from
+        // registers.  The last AHEAD steps, and one more before them when the last one is ragged, take the general form.
+        // (a sum of two products in the large tile is launched on whole K steps, at least two, only: nothing to issue there)
+        auto step = [&](auto fast, auto parity, int k) {
+            constexpr bool FAST = decltype(fast)::value;
+            constexpr int set = decltype(parity)::value % kSets;
             const uint32_t sa_n = next_slot(sa), sb_n = next_slot(sb);
-            const uint32_t d4 = smem_base + sp * kUnitBytes + lds_w;
-            const uint32_t d5 = smem_base + sa * kUnitBytes + lds_w;
+            const uint32_t d4 = smem_base + sp * kUnitBytes + lds_w, d5 = smem_base + sa * kUnitBytes + lds_w;
 #pragma unroll
-            for (int g = 0; g < NI; ++g) {
-                mfma_group(0, g);
-                load_frag(1, sa, sb, 1, g);
-                dma16_s(ua, a_lane[g], d4 + g * 1024);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            wait_dma<(UNITS - 4) * NI>();                          // units 2k+2, 2k+3 and all before them have landed
-            wait_lds();
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
+            for (int half = 0; half < 2; ++half) {
+                if (!FAST && !kTwoWhole) issue_unit(2 * k + UNITS - 1 + half);
 #pragma unroll
-            for (int g = 0; g < NI; ++g) {
-                mfma_group(1, g);
-                load_frag(0, sa_n, sb_n, 0, g);
-                dma16_s(ub, b_lane[g], d5 + g * 1024);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int t = 0; t < kSlots; ++t) {
+                    product(set, half, t);
+                    __builtin_amdgcn_sched_barrier(0);
+                    reads(set, half, t, half ? sa_n : sa, half ? sb_n : sb);     // (after the last step: a stale slot, never used)
+                    const int j = load_at(t);
+                    if (FAST && j >= 0) dma16_s(half ? ub : ua, half ? b_lane[j % NI] : a_lane[j % NI], (half ? d5 : d4) + j * 1024);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (half == 0) {
+                    if (FAST || k + AHEAD < nk) wait_dma<(UNITS - 4) * NI>();    // units 2k+2, 2k+3 and all before them have landed
+                    else wait_dma<0>();
+                    wait_lds();
+                    __builtin_amdgcn_s_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
             sp = sb; sa = sa_n; sb = sb_n;
             ua += a_step; ub += b_step;
-        }
-        for (int k = kfast; k < nk; ++k) {
-            const uint32_t sa_n = next_slot(sa), sb_n = next_slot(sb);
-            if (!kTwoWhole) issue_unit(2 * k + UNITS - 1);
-#pragma unroll
-            for (int g = 0; g < NI; ++g) {
-                mfma_group(0, g);
-                load_frag(1, sa, sb, 1, g);
-                __builtin_amdgcn_sched_barrier(0);
+        };
+        constexpr std::integral_constant<int, 0> even{};
+        constexpr std::integral_constant<int, 1> odd{};
+        const int kfast = kwhole > AHEAD ? kwhole - AHEAD : 0;
+        int k = 0;
+        if constexpr (kSets == 1) {
+            for (; k < kfast; ++k) step(std::true_type{}, even, k);
+            for (; k < nk; ++k) step(std::false_type{}, even, k);
+        } else {
+            for (; k + 1 < kfast; k += 2) { step(std::true_type{}, even, k); step(std::true_type{}, odd, k + 1); }
+            for (; k < nk; k += 2) {
+                step(std::false_type{}, even, k);
+                if (k + 1 < nk) step(std::false_type{}, odd, k + 1);
             }
-            if (k + AHEAD < nk) wait_dma<(UNITS - 4) * NI>();
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            wait_lds();
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            if (!kTwoWhole) issue_unit(2 * k + UNITS);
-            // (after the last step the fragment reads touch a stale slot and are never used)
-#pragma unroll
-            for (int g = 0; g < NI; ++g) {
-                mfma_group(1, g);
-                load_frag(0, sa_n, sb_n, 0, g);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            sa = sa_n; sb = sb_n;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
@@ -516,12 +534,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             const double ratio = swapped ? s1 / s2 : s2 / s1;
             const float post = ratio < 0x1p-100 ? 0x1p-96f : 1.0f, rho = (float)(ratio / (double)post);
 #pragma unroll
-            for (int mb = 0; mb < WB; ++mb) {
+            for (int slab = 0; slab < WB; ++slab) {
 #pragma unroll
-                for (int nb = 0; nb < WB; ++nb)
+                for (int r = 0; r < 2; ++r)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *stg_at(nb, q) = make_float4(acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]);
+                    for (int nb = 0; nb < RB; ++nb) *stg_at(r, nb) = acc[2 * slab + r][nb];
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int q = 0; q < 4 * WB; ++q) {
@@ -533,14 +550,12 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
-                for (int nb = 0; nb < WB; ++nb) {
+                for (int r = 0; r < 2; ++r)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 v = *stg_at(nb, q);
-                        acc[mb][nb][4 * q] = v.x; acc[mb][nb][4 * q + 1] = v.y; acc[mb][nb][4 * q + 2] = v.z; acc[mb][nb][4 * q + 3] = v.w;
+                    for (int nb = 0; nb < RB; ++nb) {
+                        acc[2 * slab + r][nb] = *stg_at(r, nb);
+                        if (nb % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                     }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
             }
             __syncthreads();            // the patches overlap the ring slots the next product's first loads fill
         }
@@ -562,54 +577,55 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     const int cols_left = (int)(p.N - wcol0 < kSlabN ? p.N - wcol0 : kSlabN);
     const Dequant dq = TWO && !swapped ? inv_scale_product(s_a_ph2, s_b_ph2) : inv_scale_product(s_a, s_b);
     const uint32_t tile = (uint32_t)(vblock * (16 / (WB * WB)) + sub);
-    f32x4 theirs[HALF ? WB : 1][4];                      // HALF: the other product's registers of the slab that comes next
+    f32x4 theirs[HALF ? 2 : 1][RB];                      // HALF: the other product's registers of the slab that comes next
     auto fetch_theirs = [&](int slab) {
         if constexpr (HALF) {
-            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.other) + (size_t)tile * (BM * BN), 0, BM * BN * 4, kBufferWord3);
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.other) + (size_t)tile * (BM * BN), 0, BM * BN * 4, kBufferWord3);
 #pragma unroll
-            for (int nb = 0; nb < WB; ++nb)
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    theirs[nb][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, tid * 16, ((slab * WB + nb) * 4 + q) * (kThreads * 16), kThrough));
+                for (int nb = 0; nb < RB; ++nb)
+                    theirs[r][nb] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, tid * 16, ((slab * 2 + r) * RB + nb) * (kThreads * 16), kThrough));
         }
     };
     // the slab's accumulators, each times a factor, in ordinary registers (one block of code for each slab, which the
     // compiler must not make one that indexes them)
-    auto scaled_slab = [&](int slab, float (&t)[WB][16], float first, float second) {
+    auto scaled_slab = [&](int slab, float (&t)[2][RB][4], float first, float second) {
 #pragma unroll
-        for (int mb = 0; mb < WB; ++mb) {
-            if (slab != mb) continue;
+        for (int s = 0; s < WB; ++s) {
+            if (slab != s) continue;
 #pragma unroll
-            for (int nb = 0; nb < WB; ++nb)
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) t[nb][i] = __fmul_rn(acc[mb][nb][i], nb < WB / 2 ? first : second);
+                for (int nb = 0; nb < RB; ++nb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) t[r][nb][i] = __fmul_rn(acc[2 * s + r][nb][i], nb < RB / 2 ? first : second);
         }
     };
     auto stage_slab = [&](int slab) {
         if constexpr (HALF) {
-            float t[WB][16];
+            float t[2][RB][4];
             scaled_slab(slab, t, dq.a, dq.a);
 #pragma unroll
-            for (int nb = 0; nb < WB; ++nb)
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float v[4];
+                for (int nb = 0; nb < RB; ++nb) {
+                    v4f v;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) v[k] = __fadd_rn(t[nb][4 * q + k] * dq.post, theirs[nb][q][k]);
-                    *stg_at(nb, q) = make_float4(v[0], v[1], v[2], v[3]);
+                    for (int k = 0; k < 4; ++k) v[k] = __fadd_rn(t[r][nb][k] * dq.post, theirs[r][nb][k]);
+                    *stg_at(r, nb) = v;
                 }
             if (32 * (slab + 1) < rows_left) fetch_theirs(slab + 1);
             return;
         }
 #pragma unroll
-        for (int mb = 0; mb < WB; ++mb) {
-            if (slab != mb) continue;
+        for (int s = 0; s < WB; ++s) {
+            if (slab != s) continue;
 #pragma unroll
-            for (int nb = 0; nb < WB; ++nb)
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *stg_at(nb, q) = make_float4(acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]);
-            asm volatile("; slab %0" :: "n"(mb));        // (else the compiler makes one block of them, indexing registers in memory)
+                for (int nb = 0; nb < RB; ++nb) *stg_at(r, nb) = acc[2 * s + r][nb];
+            asm volatile("; slab %0" :: "n"(s));         // (else the compiler makes one block of them, indexing registers in memory)
         }
     };
     // (The sum of two products runs its slabs unrolled: in a loop the compiler spills its accumulators.)
@@ -655,17 +671,17 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             if (!last) {
                 const __amdgpu_buffer_rsrc_t mine = __builtin_amdgcn_make_buffer_rsrc(p.mine + (size_t)tile * (BM * BN), 0, BM * BN * 4, kBufferWord3);
                 for_slabs([&](const int row) {
-                    float t[WB][16];
+                    float t[2][RB][4];
                     scaled_slab(row >> 5, t, dq.a, dq.a);
 #pragma unroll
-                    for (int nb = 0; nb < WB; ++nb)
+                    for (int r = 0; r < 2; ++r)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
+                        for (int nb = 0; nb < RB; ++nb) {
                             f32x4 v;
 #pragma unroll
-                            for (int k = 0; k < 4; ++k) v[k] = t[nb][4 * q + k] * dq.post;
+                            for (int k = 0; k < 4; ++k) v[k] = t[r][nb][k] * dq.post;
                             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), mine, tid * 16,
-                                                                   (((row >> 5) * WB + nb) * 4 + q) * (kThreads * 16), kThrough);
+                                                                   (((row >> 5) * 2 + r) * RB + nb) * (kThreads * 16), kThrough);
                         }
                 });
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's part is where the others see it
@@ -851,33 +867,35 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         const bool post = dq_u.post != 1.0f || dq_g.post != 1.0f;
         // A lane holds u and g of the same elements, so the product is formed in registers; the patch only turns what is
         // stored (U and G side by side, or the codes) into whole pieces of rows.
-        constexpr int NBU = WB / 2;                              // column blocks of u
+        constexpr int NBU = RB / 2;                              // column blocks of u
         constexpr bool kCodes = EPI == EPI_SWIGLU_Q;
         constexpr int kRowBytes = kCodes ? WN / 2 + 8 : 2 * WN + 16;
         uint8_t *patch = smem + w * (32 * kRowBytes);
         const size_t base = (size_t)wrow0 * (size_t)p.N + (size_t)wcol0;
-        float hmaxf[NBU][16];                                    // fmaxf drops NaN
+        float hmaxf[NBU][4];                                     // fmaxf drops NaN
 #pragma unroll
         for (int nb = 0; nb < NBU; ++nb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) hmaxf[nb][i] = 0.0f;
+            for (int i = 0; i < 4; ++i) hmaxf[nb][i] = 0.0f;
 #pragma nounroll
         for (int row = 0; row < rows_left; row += 32) {
-            float t[WB][16];
+            float t[2][RB][4];
             scaled_slab(row >> 5, t, alpha_u, alpha_g);
             if (post) {
 #pragma unroll
-                for (int nb = 0; nb < WB; ++nb)
+                for (int r = 0; r < 2; ++r)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) t[nb][i] *= nb < NBU ? dq_u.post : dq_g.post;
+                    for (int nb = 0; nb < RB; ++nb)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) t[r][nb][i] *= nb < NBU ? dq_u.post : dq_g.post;
             }
 #pragma unroll
-            for (int nb = 0; nb < NBU; ++nb)
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int q = 0; q < 4; q += 2) {                 // eight columns: two groups of four
+                for (int nb = 0; nb < NBU; nb += 2) {            // eight columns: four of two neighbouring blocks
                     float u[8], g[8];
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) { u[k] = t[nb][4 * q + k]; g[k] = t[nb + NBU][4 * q + k]; }
+                    for (int k = 0; k < 8; ++k) { u[k] = t[r][nb + k / 4][k % 4]; g[k] = t[r][nb + k / 4 + NBU][k % 4]; }
                     if (kCodes) {
                         // inference: the factor s_i is already inside u (folded into w1), so the product is cast as
                         // it stands; nothing else is stored
@@ -885,21 +903,21 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 #pragma unroll
                         for (int k = 0; k < 8; ++k) h[k] = swiglu_f32(u[k], g[k]);
                         const uint2 code = satcast_pk8<kE4M3>(h);
-                        uint8_t *at = patch + (l & 31) * kRowBytes + (l >> 5) * 4 + nb * 32 + q * 8;
+                        uint8_t *at = patch + (r * 16 + (l & 15)) * kRowBytes + nb * 16 + (l >> 4) * 4;
                         *reinterpret_cast<uint32_t *>(at) = code.x;
-                        *reinterpret_cast<uint32_t *>(at + 8) = code.y;
+                        *reinterpret_cast<uint32_t *>(at + 16) = code.y;
                         continue;
                     }
                     const uint4 qu = pack_bf16x8(u), qg = pack_bf16x8(g);
-                    uint8_t *at = patch + (l & 31) * kRowBytes + (l >> 5) * 8 + nb * 64 + q * 16;
+                    uint8_t *at = patch + (r * 16 + (l & 15)) * kRowBytes + nb * 32 + (l >> 4) * 8;
                     *reinterpret_cast<uint2 *>(at) = make_uint2(qu.x, qu.y);
-                    *reinterpret_cast<uint2 *>(at + 16) = make_uint2(qu.z, qu.w);
+                    *reinterpret_cast<uint2 *>(at + 32) = make_uint2(qu.z, qu.w);
                     *reinterpret_cast<uint2 *>(at + WN) = make_uint2(qg.x, qg.y);
-                    *reinterpret_cast<uint2 *>(at + WN + 16) = make_uint2(qg.z, qg.w);
+                    *reinterpret_cast<uint2 *>(at + WN + 32) = make_uint2(qg.z, qg.w);
                     unpack_bf16x8(qu, u);
                     unpack_bf16x8(qg, g);
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) hmaxf[nb][4 * q + k] = fmaxf(hmaxf[nb][4 * q + k], fabsf(swiglu_f32(u[k], g[k])));
+                    for (int k = 0; k < 8; ++k) hmaxf[nb + k / 4][k % 4] = fmaxf(hmaxf[nb + k / 4][k % 4], fabsf(swiglu_f32(u[k], g[k])));
                 }
 #pragma unroll
             for (int pass = 0; pass < kPasses; ++pass) {
@@ -914,16 +932,16 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             }
         }
         if (EPI == EPI_SWIGLU) {
-            // The 32 lanes of a half wave hold 16 NBU channels each, over a row each.  At every step a lane keeps half of its
+            // The 16 lanes of a quarter wave hold 4 NBU channels each, over a row each.  At every step a lane keeps half of its
             // channels and gives the other half to its partner, so that in the end each has the maximum of one channel:
             // one atomic instruction for all of them.  (Non-negative floats order like their bit patterns.)
-            uint32_t m[16 * NBU];
+            uint32_t m[4 * NBU];
 #pragma unroll
             for (int nb = 0; nb < NBU; ++nb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) m[16 * nb + i] = __float_as_uint(hmaxf[nb][i]);
+                for (int i = 0; i < 4; ++i) m[4 * nb + i] = __float_as_uint(hmaxf[nb][i]);
 #pragma unroll
-            for (int half = 8 * NBU; half > 0; half >>= 1) {
+            for (int half = 2 * NBU; half > 0; half >>= 1) {
                 const bool upper = (l & half) != 0;
 #pragma unroll
                 for (int i = 0; i < half; ++i) {
@@ -932,13 +950,13 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                     m[i] = keep > got ? keep : got;
                 }
             }
-            if (NBU == 1) {
-                const uint32_t o = (uint32_t)__shfl_xor((int)m[0], 16, 64);
+            if (NBU == 2) {
+                const uint32_t o = (uint32_t)__shfl_xor((int)m[0], 8, 64);
                 m[0] = m[0] > o ? m[0] : o;
             }
-            const int i = l & 15, nb = (l >> 4) & (NBU - 1);
-            const int64_t channel = n0 + wn * (WN / 2) + nb * 32 + (i >> 2) * 8 + (l >> 5) * 4 + (i & 3);
-            if (channel < p.N && m[0] && (NBU == 2 || (l & 16) == 0)) atomicMax(&p.camax_bits[channel], m[0]);
+            const int i = l & (4 * NBU - 1);
+            const int64_t channel = n0 + wn * (WN / 2) + (i >> 2) * 16 + (l >> 4) * 4 + (i & 3);
+            if (channel < p.N && m[0] && (NBU == 4 || (l & 8) == 0)) atomicMax(&p.camax_bits[channel], m[0]);
         }
     }
 }
@@ -951,10 +969,20 @@ inline unsigned set_workgroups(int WB) { return WB == 4 ? 8u : 32u; }
 
 // One GEMM per launch.
 template <int WB, int EPI, int AFMT, int PART = 0, int LAY = 0, int UNITS = 5>
-__global__ void __launch_bounds__(kThreads, waves_per_simd(WB, UNITS)) gemm_kernel(GemmParams p) {
+__global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(WB, UNITS)];
     const int b = (int)blockIdx.x, vb = (p.first_set + set_of<WB>(b)) * 8 + (b & 7);
     if (vb < p.tiles_m * p.tiles_n) gemm_tile<WB, EPI, AFMT, PART, LAY, UNITS>(p, vb, quarter_of<WB>(b), smem);
+}
+// The small tile with its compute unit to itself, a ring of nine.  The LDS is named at the launch: a compiler that sees 144 KB
+// plans for one wave per SIMD, keeps accumulators in both halves of the register file and moves them about in the loop (116 moves
+// to 32 MFMAs: 2048 x 2048 x 11008 50.6 us).
+constexpr int kLongRing = 9;
+extern __shared__ __attribute__((aligned(1024))) uint8_t g_long_ring[];
+template <int EPI, int AFMT, int LAY>
+__global__ void __launch_bounds__(kThreads, waves_per_simd(2)) gemm_alone_kernel(GemmParams p) {
+    const int b = (int)blockIdx.x, vb = (p.first_set + set_of<2>(b)) * 8 + (b & 7);
+    if (vb < p.tiles_m * p.tiles_n) gemm_tile<2, EPI, AFMT, 0, LAY, kLongRing>(p, vb, quarter_of<2>(b), g_long_ring);
 }
 
 // Host side: algorithmic flops of the whole contraction (both weight matrices of the SwiGLU forms, both products
