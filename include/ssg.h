@@ -88,6 +88,13 @@ ssg_status ssg_quantize(const void *src, ssg_dtype src_dtype, int64_t rows, int6
                         ssg_fp8_format fmt, ssg_scale_mode mode, ssg_scale_round rnd,
                         uint8_t *dst, uint8_t *dst_t, float *scale_dev, float *amax_dev, void *stream);
 
+/* As ssg_quantize.  Under current scaling a tensor that fits the chip's registers is quantized in one launch, whose
+ * workgroups look for each other's ranges at most `polls` times (about a microsecond each) and then form what is
+ * missing from the tensor themselves: the results are the same for any value, a negative one stands for the usual. */
+ssg_status ssg_quantize_wait(const void *src, ssg_dtype src_dtype, int64_t rows, int64_t cols,
+                             ssg_fp8_format fmt, ssg_scale_mode mode, ssg_scale_round rnd,
+                             uint8_t *dst, uint8_t *dst_t, float *scale_dev, float *amax_dev, int32_t polls, void *stream);
+
 /* One FP8 contraction with fp32 accumulation (the matrix products of Eq. 2 and
  * of the display that follows it):
  *     C[m,n] = ( sum_k A[m,k] * B[n,k] ) / (sa * sb)

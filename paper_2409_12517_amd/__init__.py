@@ -30,7 +30,7 @@ SSG_SCALE_CURRENT, SSG_SCALE_GIVEN, SSG_SCALE_DELAYED = 0, 1, 2
 SSG_ROUND_EXACT_DIV, SSG_ROUND_POW2 = 0, 1
 
 EXPORTS = [
-    "ssg_last_error", "ssg_version", "ssg_amax", "ssg_quantize", "ssg_gemm_fp8", "ssg_gemm_fp8_layout", "ssg_gemm_fp8_plan", "ssg_swiglu",
+    "ssg_last_error", "ssg_version", "ssg_amax", "ssg_quantize", "ssg_quantize_wait", "ssg_gemm_fp8", "ssg_gemm_fp8_layout", "ssg_gemm_fp8_plan", "ssg_swiglu",
     "ssg_smooth_swiglu_quantize", "ssg_fold_w3", "ssg_mlp_saved_bytes", "ssg_mlp_workspace_bytes",
     "ssg_mlp_fwd", "ssg_mlp_bwd", "ssg_mlp_bwd_plan", "ssg_mlp_gemm_plan", "ssg_mlp_gemm_route", "ssg_mlp_view_saved", "ssg_mlp_view_workspace",
     "ssg_mlp_scaling_state_bytes", "ssg_mlp_scaling_init",
@@ -89,6 +89,8 @@ _lib.ssg_version.restype = c_char_p
 _lib.ssg_amax.argtypes = [c_void_p, c_int, c_size_t, c_void_p, c_void_p]
 _lib.ssg_quantize.argtypes = [c_void_p, c_int, c_int64, c_int64, c_int, c_int, c_int, c_void_p, c_void_p,
                               c_void_p, c_void_p, c_void_p]
+_lib.ssg_quantize_wait.argtypes = [c_void_p, c_int, c_int64, c_int64, c_int, c_int, c_int, c_void_p, c_void_p,
+                                   c_void_p, c_void_p, c_int32, c_void_p]
 _lib.ssg_gemm_fp8.argtypes = [c_void_p, c_int, c_void_p, c_int, c_int64, c_int64, c_int64, c_void_p, c_void_p,
                               c_void_p, c_int, c_void_p]
 _lib.ssg_gemm_fp8_layout.argtypes = [c_void_p, c_int, c_int, c_void_p, c_int, c_int, c_int64, c_int64, c_int64, c_void_p,
@@ -199,6 +201,11 @@ def ssg_amax(src, src_dtype, n, amax_dev, stream=None):
 def ssg_quantize(src, src_dtype, rows, cols, fmt, mode, rnd, dst, dst_t, scale_dev, amax_dev, stream=None):
     _check(_lib.ssg_quantize(_ptr(src), src_dtype, rows, cols, fmt, mode, rnd, _ptr(dst), _ptr(dst_t),
                              _ptr(scale_dev), _ptr(amax_dev), _stream(stream)))
+
+
+def ssg_quantize_wait(src, src_dtype, rows, cols, fmt, mode, rnd, dst, dst_t, scale_dev, amax_dev, polls, stream=None):
+    _check(_lib.ssg_quantize_wait(_ptr(src), src_dtype, rows, cols, fmt, mode, rnd, _ptr(dst), _ptr(dst_t),
+                                  _ptr(scale_dev), _ptr(amax_dev), polls, _stream(stream)))
 
 
 def ssg_gemm_fp8(A, a_fmt, B, b_fmt, M, N, K, sa_dev, sb_dev, C, c_dtype, stream=None):

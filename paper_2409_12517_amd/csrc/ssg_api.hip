@@ -582,6 +582,12 @@ ssg_status ssg_amax(const void *src, ssg_dtype src_dtype, size_t n, float *amax_
 ssg_status ssg_quantize(const void *src, ssg_dtype src_dtype, int64_t rows, int64_t cols, ssg_fp8_format fmt,
                         ssg_scale_mode mode, ssg_scale_round rnd, uint8_t *dst, uint8_t *dst_t,
                         float *scale_dev, float *amax_dev, void *stream) {
+    return ssg_quantize_wait(src, src_dtype, rows, cols, fmt, mode, rnd, dst, dst_t, scale_dev, amax_dev, -1, stream);
+}
+
+ssg_status ssg_quantize_wait(const void *src, ssg_dtype src_dtype, int64_t rows, int64_t cols, ssg_fp8_format fmt,
+                             ssg_scale_mode mode, ssg_scale_round rnd, uint8_t *dst, uint8_t *dst_t,
+                             float *scale_dev, float *amax_dev, int32_t polls, void *stream) {
     hipStream_t st = (hipStream_t)stream;
     if (!dtype_ok(src_dtype)) return fail(SSG_ERR_ARG, "ssg_quantize: bad src_dtype");
     if (!fmt_ok(fmt)) return fail(SSG_ERR_ARG, "ssg_quantize: bad fmt");
@@ -611,6 +617,9 @@ ssg_status ssg_quantize(const void *src, ssg_dtype src_dtype, int64_t rows, int6
             ssg::launch_fill_u32(reinterpret_cast<uint32_t *>(amax_dev), 1, 0u, st);
             ssg::launch_fill_u32(reinterpret_cast<uint32_t *>(scale_dev), 1, 0x3f800000u, st);
         } else {
+            a.amax_out = amax_dev; a.scale_out = scale_dev;
+            if (ssg::launch_quantize_once(a, polls, st)) return check_launch("ssg_quantize");
+            a.amax_out = nullptr; a.scale_out = nullptr;
             ssg::launch_range_scale(src, a.kind, n, words, fmt, a.pow2, amax_dev, scale_dev, st);
         }
     } else if (amax_dev && !empty) {

@@ -61,6 +61,10 @@ void launch_cast_batch(const CastArgs *list, int n, const ZeroWords &zero, hipSt
 // given; one format), in one launch for small tensors, else a range and a cast launch.  Returns how many packed words of
 // each range_words hold its range afterwards.
 int launch_quantize_batch(CastArgs *list, int n, const ZeroWords &zero, hipStream_t st);
+// Q of one tensor, any source kind but the SwiGLU product, from its own range in one launch.  polls: how often a workgroup looks
+// for the others' ranges before it forms them itself, < 0: the usual number.  false: nothing launched, the tensor is too large
+// or the stream is being captured.
+bool launch_quantize_once(const CastArgs &a, int polls, hipStream_t st);
 // camax_bits[c] = max_r |v[r,c]| as float bits (zeroed by the caller).
 void launch_col_amax(const void *src, const void *src2, SrcKind kind, int64_t rows, int64_t cols,
                      uint32_t *camax_bits, hipStream_t st);

@@ -10,6 +10,7 @@
 #include "ssg_col_range.h"
 #include "ssg_device.h"
 #include "ssg_internal.h"
+#include "ssg_meet.h"
 #include "ssg_scaling.h"
 
 namespace ssg {
@@ -687,6 +688,211 @@ __global__ void __launch_bounds__(kSmallThreads) quantize_small_kernel(const Cas
     *reinterpret_cast<uint2 *>(it.dst + (size_t)own * 8) = make_uint2(satcast_pk4<FMT>(v[0], v[1], v[2], v[3]), satcast_pk4<FMT>(v[4], v[5], v[6], v[7]));
 }
 
+// ------------------------------------------------------------------ range and cast of tensors that fit the registers
+// Up to one workgroup per compute unit, each with up to TILES tiles of 128 x 128 in registers (100 MB on the chip) while the
+// workgroups exchange their maxima (ssg_meet.h): the tensor is read once, in one launch.  Bound by HBM, and for small tensors by
+// the latency of the exchange, about 2 us.  ssg_quantize with the transposed copy, in three launches before (range, scale, cast)
+// and this way: 256 x 512 13.9 and 8.0 us, 1040 x 2736 13.6 and 9.7, 4096 x 4096 23.3 and 21.2, 4096 x 11008 50.4 and 41.7; fp32
+// 2048 x 2048 15.4 and 11.0, 4096 x 5504 46.8 and 36.1.  In calls that quantize several tensors: 1040, 1024, 2736 115 and 111 us a step, the inference
+// form at 272 rows, 4096, 11008 82.6 and 80.3.  Tensors of up to 2^18 elements stay with quantize_small_kernel, which has no exchange (a
+// decode step of 16 rows 38.2 us, 39.0 this way).
+constexpr int kHeldThreads = 512;
+template <bool F32> constexpr int held_most_tiles() { return F32 ? 6 : 12; }         // 192 registers of source per lane
+struct HeldItem {
+    const void *src;
+    int64_t rows, cols;
+    uint8_t *dst, *dst_t;
+    float *amax_out, *scale_out;
+    uint32_t *record;                // optional: receives the range's bits
+    int tiles_x, tiles;
+    int first, blocks;               // workgroups (and words) of this item
+};
+struct HeldBatch {
+    HeldItem item[3];
+    int pow2;
+    Meeting meeting;
+    ZeroWords zero;
+};
+template <bool F32, int FMT, bool TRANSPOSED, int TILES>
+__global__ void __launch_bounds__(kHeldThreads, 2) quantize_held_kernel(const HeldBatch batch) {
+    __shared__ uint32_t turn[TRANSPOSED ? 2 : 1][TRANSPOSED ? kTile * kTPitchWords : 1];
+    __shared__ uint32_t words[kMeetBlocks + 8];
+    const int b = (int)blockIdx.x, which = (b >= batch.item[1].first) + (b >= batch.item[2].first);
+    const HeldItem &it = batch.item[which];
+    const int own = b - it.first;
+    zero_words(batch.zero, blockIdx.x * kHeldThreads + threadIdx.x, gridDim.x * kHeldThreads);
+    // a thread has eight columns of four rows of every tile, in PER pieces of 16 bytes
+    constexpr int PER = F32 ? 8 : 4;
+    const int c8 = (threadIdx.x & 15) * 8, r4 = (threadIdx.x >> 4) * 4;
+    auto origin = [&](int k, int t, int64_t &row0, int64_t &col0) {      // of the t-th tile of the item's workgroup k
+        const int tile = k + t * it.blocks;
+        row0 = (int64_t)(tile / it.tiles_x) * kTile;
+        col0 = (int64_t)(tile % it.tiles_x) * kTile;
+        return tile < it.tiles && row0 + r4 < it.rows && col0 + c8 < it.cols;      // (both extents are multiples of 16)
+    };
+    auto load = [&](int64_t row, int64_t col, ssg_u32x4 (&q)[PER]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const size_t at = (size_t)(row + r) * (size_t)it.cols + (size_t)col;
+#pragma unroll
+            for (int p = 0; p < PER / 4; ++p)
+                q[r * (PER / 4) + p] = __builtin_nontemporal_load(reinterpret_cast<const ssg_u32x4 *>(static_cast<const uint8_t *>(it.src) + at * (F32 ? 4 : 2)) + p);
+        }
+    };
+    struct Seen { ssg_i16x2 pk = {0x7f, 0x7f}; uint32_t bits = 0u; };
+    auto see = [&](const ssg_u32x4 (&q)[PER], Seen &seen) {
+#pragma unroll
+        for (int p = 0; p < PER; ++p)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (F32) {
+                    const uint32_t v = abs_bits_ignore_nan(__uint_as_float(q[p][k]));
+                    seen.bits = seen.bits > v ? seen.bits : v;
+                } else seen.pk = __builtin_elementwise_max(seen.pk, biased_abs_pk(q[p][k]));
+            }
+    };
+    ssg_u32x4 held[TILES][PER];
+    Seen seen;
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+        int64_t row0, col0;
+        if (origin(own, t, row0, col0)) load(row0 + r4, col0 + c8, held[t]);
+        else
+#pragma unroll
+            for (int p = 0; p < PER; ++p) held[t][p] = ssg_u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) see(held[t], seen);
+    const uint32_t mine = wave_max_u32(F32 ? seen.bits : unbias_max_pk(seen.pk));
+    if ((threadIdx.x & 63) == 0) words[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t m = mine;
+        for (int w = 1; w < kHeldThreads / 64; ++w) m = m > words[w] ? m : words[w];
+        meet_leave(batch.meeting, b, m);
+    }
+    const uint32_t bits = meet_max<kHeldThreads>(batch.meeting, it.first, it.blocks, own, words, [&](int k) {
+        Seen s;
+        for (int t = 0; k + t * it.blocks < it.tiles; ++t) {
+            int64_t row0, col0;
+            if (!origin(k, t, row0, col0)) continue;
+            ssg_u32x4 q[PER];
+            load(row0 + r4, col0 + c8, q);
+            see(q, s);
+        }
+        return F32 ? s.bits : unbias_max_pk(s.pk);
+    });
+    const float amax = __uint_as_float(bits), sigma = scale_from_amax(amax, Fp8Traits<FMT>::fmax, batch.pow2);
+    if (own == 0 && threadIdx.x == 0) {
+        if (it.amax_out) *it.amax_out = amax;
+        if (it.scale_out) *it.scale_out = sigma;
+        if (it.record) *it.record = bits;
+    }
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+        if (own + t * it.blocks >= it.tiles) break;
+        int64_t row0, col0;
+        const bool inside = origin(own, t, row0, col0);
+        uint32_t code[4][2];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float v[8];
+            if (F32) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[k] = __uint_as_float(held[t][r * (PER / 4) + k / 4 % (PER / 4)][k % 4]);
+            } else {
+                const ssg_u32x4 q = held[t][r * (PER / 4)];
+                LoadBf16::widen(make_uint4(q[0], q[1], q[2], q[3]), v);
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = __fmul_rn(v[k], sigma);
+            code[r][0] = satcast_pk4<FMT>(v[0], v[1], v[2], v[3]);
+            code[r][1] = satcast_pk4<FMT>(v[4], v[5], v[6], v[7]);
+            if (inside)
+                *reinterpret_cast<uint2 *>(it.dst + (size_t)(row0 + r4 + r) * (size_t)it.cols + (size_t)(col0 + c8)) = make_uint2(code[r][0], code[r][1]);
+        }
+        if (TRANSPOSED) {
+            // (two turning buffers by turns: one barrier per tile)
+            uint32_t *at = turn[TRANSPOSED ? t & 1 : 0];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t o[4];
+                transpose4x4_bytes(code[0][h], code[1][h], code[2][h], code[3][h], o);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) at[(c8 + 4 * h + j) * kTPitchWords + (r4 >> 2)] = o[j];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 1024 / kHeldThreads; ++j) {
+                const int q = threadIdx.x + kHeldThreads * j, c = q >> 3, rc = q & 7;       // column of the tile, 16 rows of it
+                if (col0 + c < it.cols && row0 + rc * 16 < it.rows) {
+                    const uint32_t *src = &at[c * kTPitchWords + rc * 4];
+                    *reinterpret_cast<uint4 *>(it.dst_t + (size_t)(col0 + c) * (size_t)it.rows + (size_t)(row0 + rc * 16)) =
+                        make_uint4(src[0], src[1], src[2], src[3]);
+                }
+            }
+        }
+    }
+}
+
+// Tiles a workgroup holds so that all items' workgroups fit the chip at once; 0: they do not.
+static int held_tiles(HeldItem *item, int n, bool f32) {
+    int total = 0;
+    for (int i = 0; i < n; ++i) {
+        item[i].tiles_x = (int)((item[i].cols + kTile - 1) / kTile);
+        const int64_t tiles = (int64_t)item[i].tiles_x * ((item[i].rows + kTile - 1) / kTile);
+        if (tiles > kMeetBlocks * 16) return 0;
+        item[i].tiles = (int)tiles;
+        total += item[i].tiles;
+    }
+    for (int per = (total + kMeetBlocks - 1) / kMeetBlocks; per <= (f32 ? held_most_tiles<true>() : held_most_tiles<false>()); ++per) {
+        int blocks = 0;
+        for (int i = 0; i < n; ++i) { item[i].first = blocks; item[i].blocks = (item[i].tiles + per - 1) / per; blocks += item[i].blocks; }
+        for (int i = n; i < 3; ++i) item[i].first = 1 << 30;
+        if (blocks <= kMeetBlocks) return per;
+    }
+    return 0;
+}
+template <bool F32, int FMT, bool TRANSPOSED>
+static void launch_held(const HeldBatch &batch, int per, unsigned blocks, hipStream_t st) {
+    if (per <= 1) hipLaunchKernelGGL((quantize_held_kernel<F32, FMT, TRANSPOSED, 1>), dim3(blocks), dim3(kHeldThreads), 0, st, batch);
+    else if (per <= 3) hipLaunchKernelGGL((quantize_held_kernel<F32, FMT, TRANSPOSED, 3>), dim3(blocks), dim3(kHeldThreads), 0, st, batch);
+    else hipLaunchKernelGGL((quantize_held_kernel<F32, FMT, TRANSPOSED, held_most_tiles<F32>()>), dim3(blocks), dim3(kHeldThreads), 0, st, batch);
+}
+// false: nothing launched, the tensors do not fit or the call could be replayed
+static bool launch_quantize_held(const CastArgs *list, int n, const ZeroWords &zero, int polls, hipStream_t st) {
+    const bool f32 = list[0].kind == SRC_F32, tr = list[0].dst_t != nullptr;
+    HeldBatch batch;
+    double bytes = 0.0;
+    for (int i = 0; i < 3; ++i) {
+        const CastArgs &a = list[i < n ? i : 0];
+        batch.item[i] = HeldItem{a.src, a.rows, a.cols, a.dst, a.dst_t, a.amax_out, a.scale_out, a.range_words, 0, 0, 0, 0};
+        if (i < n) bytes += cast_bytes(a);
+    }
+    const int per = held_tiles(batch.item, n, f32);
+    if (per == 0 || !meet_ticket(st, &batch.meeting)) return false;
+    if (polls >= 0) batch.meeting.polls = polls;
+    batch.pow2 = list[0].pow2;
+    batch.zero = zero;
+    unsigned blocks = 0;
+    for (int i = 0; i < n; ++i) blocks += (unsigned)batch.item[i].blocks;
+    const int fmt = list[0].fmt;
+    profile_before(kTagCast, st, bytes);
+    auto go = [&](auto f, auto m, auto t) { launch_held<decltype(f)::value, decltype(m)::value, decltype(t)::value>(batch, per, blocks, st); };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr std::integral_constant<int, kE4M3> e4{};
+    constexpr std::integral_constant<int, kE5M2> e5{};
+    auto pick = [&](auto f, auto t) { if (fmt == kE4M3) go(f, e4, t); else go(f, e5, t); };
+    if (f32 && tr) pick(yes, yes);
+    else if (f32) pick(yes, no);
+    else if (tr) pick(no, yes);
+    else pick(no, no);
+    profile_after(st);
+    return true;
+}
+bool launch_quantize_once(const CastArgs &a, int polls, hipStream_t st) { return launch_quantize_held(&a, 1, ZeroWords{}, polls, st); }
+
 // Q of up to three bf16 tensors from their own ranges (Section 2).  Returns the number of packed range words each
 // tensor's `range_words` holds afterwards.
 int launch_quantize_batch(CastArgs *list, int n, const ZeroWords &zero, hipStream_t st) {
@@ -713,6 +919,7 @@ int launch_quantize_batch(CastArgs *list, int n, const ZeroWords &zero, hipStrea
         profile_after(st);
         return 1;
     }
+    if (launch_quantize_held(list, n, zero, -1, st)) return 1;
     const int words = launch_amax_batch(list, n, zero, st);
     for (int i = 0; i < n; ++i) {
         list[i].amax = reinterpret_cast<const float *>(list[i].range_words);
