@@ -36,9 +36,11 @@ __device__ __forceinline__ void zero_words(const ZeroWords &z, const unsigned fi
 }
 
 // ------------------------------------------------------------------ loaders
-// Each loader returns 8 consecutive elements of one row as fp32.
+// Each loader returns 8 consecutive elements of one row as fp32; get and widen do it in two steps, the load and the rest.
 struct LoadBf16 {
     const uint16_t *p;
+    typedef uint4 Raw;
+    __device__ __forceinline__ Raw get(size_t off) const { return load8_raw(off); }
     // (a streaming read: the non-temporal hint keeps the source from displacing what later kernels read again)
     __device__ __forceinline__ uint4 load8_raw(size_t off) const {
         typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -65,23 +67,31 @@ struct LoadBf16 {
 };
 struct LoadF32 {
     const float *p;
-    __device__ __forceinline__ void load8(size_t off, float (&v)[8]) const {
-        float4 a = *reinterpret_cast<const float4 *>(p + off);
-        float4 b = *reinterpret_cast<const float4 *>(p + off + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    struct Raw { float4 a, b; };
+    __device__ __forceinline__ Raw get(size_t off) const {
+        return Raw{*reinterpret_cast<const float4 *>(p + off), *reinterpret_cast<const float4 *>(p + off + 4)};
     }
+    static __device__ __forceinline__ void widen(const Raw &q, float (&v)[8]) {
+        v[0] = q.a.x; v[1] = q.a.y; v[2] = q.a.z; v[3] = q.a.w;
+        v[4] = q.b.x; v[5] = q.b.y; v[6] = q.b.z; v[7] = q.b.w;
+    }
+    __device__ __forceinline__ void load8(size_t off, float (&v)[8]) const { widen(get(off), v); }
 };
 struct LoadSwiglu {          // h = u * Swish(g) from stored bf16 U, G
     const uint16_t *u, *g;
-    __device__ __forceinline__ void load8(size_t off, float (&v)[8]) const {
-        // plain loads: U and G were just written by the GEMM and are read again by the backward pass
+    struct Raw { uint4 u, g; };
+    // plain loads: U and G were just written by the GEMM and are read again by the backward pass
+    __device__ __forceinline__ Raw get(size_t off) const {
+        return Raw{*reinterpret_cast<const uint4 *>(u + off), *reinterpret_cast<const uint4 *>(g + off)};
+    }
+    static __device__ __forceinline__ void widen(const Raw &q, float (&v)[8]) {
         float uu[8], gg[8];
-        LoadBf16::widen(*reinterpret_cast<const uint4 *>(u + off), uu);
-        LoadBf16::widen(*reinterpret_cast<const uint4 *>(g + off), gg);
+        LoadBf16::widen(q.u, uu);
+        LoadBf16::widen(q.g, gg);
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = swiglu_f32(uu[i], gg[i]);
     }
+    __device__ __forceinline__ void load8(size_t off, float (&v)[8]) const { widen(get(off), v); }
 };
 
 // ------------------------------------------------------------------ amax
@@ -313,16 +323,24 @@ struct CastBatch {
     int pow2;
     ZeroWords zero;
 };
-// The work of one workgroup: tile (bx, by) of item `it`.
+// The work of one workgroup: tile (bx, by) of item `it`, ROWS x 128.
 // FACT: the per-column factor is formed here from the per-channel maxima of h that col_scale points to: s_i (kFactS) or
-// s_i^-1 (kFactSinv), and the per-tensor scale, if any, is given as `sigma_known`.
+// s_i^-1 (kFactSinv); none otherwise.  `known`: the per-tensor scale comes from known_scale(), called by all threads, instead of
+// the item.
+// The first loads are under way before the scale is looked for, and small launches take tiles of 64 rows, twice as many with one round
+// of loads each: there nothing but latencies counts, one after the other.
 enum { kFactNone = 0, kFactS = 1, kFactSinv = 2 };
-template <class Loader, int FMT, bool COLSCALE, bool TRANSPOSED, bool RECORD = false, bool COUNT = false, int FACT = kFactNone>
+struct FromItem {};                                      // known_scale: none
+template <class Loader, int FMT, bool COLSCALE, bool TRANSPOSED, bool RECORD = false, bool COUNT = false, int ROWS = kTile, int FACT = kFactNone,
+          class KnownScale = FromItem>
 __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int pow2, const unsigned bx, const unsigned by,
-                                           const float sigma_known = 1.0f) {
+                                           KnownScale known_scale = KnownScale{}) {
+    constexpr bool KNOWN = !std::is_same<KnownScale, FromItem>::value;
+    static_assert(ROWS == kTile || ((ROWS == 64 || ROWS == 16) && !TRANSPOSED), "a tile is two halves of 64 rows, or one, or 16 rows");
+    constexpr int RPT = ROWS < 64 ? ROWS / 16 : 4;         // neighbouring rows of a thread
     const Loader ld = it.ld;
     const int64_t rows = it.rows, cols = it.cols;
-    if ((int64_t)bx * kTile >= cols || (int64_t)by * kTile >= rows) return;
+    if ((int64_t)bx * kTile >= cols || (int64_t)by * ROWS >= rows) return;
     const float *__restrict__ col_scale = it.col_scale;
     const float *__restrict__ amax = it.amax;
     const int amax_slots = it.amax_slots;
@@ -335,9 +353,38 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
     __shared__ uint32_t tile[TRANSPOSED ? kTile * kTPitchWords : 1];
     uint32_t n_sat = 0, n_flush = 0;
 
-    float sigma = sigma_known;
-    bool tensor_scale = FACT == kFactSinv;
-    if (scale_in) { sigma = *scale_in; tensor_scale = true; }
+    const int64_t row0 = (int64_t)by * ROWS;
+    const int64_t col0 = (int64_t)bx * kTile;
+    const int c8 = threadIdx.x & 15;       // which 8-column chunk
+    const int r4 = threadIdx.x >> 4;       // which group of RPT rows (0..15) inside a half
+    const int64_t col = col0 + c8 * 8;
+    const bool col_ok = col < cols;
+
+    // the four row loads of a group together: four requests in flight per lane (measured: one at a time is
+    // 5-10 % slower, all eight of the lane at once is slower again)
+    typename Loader::Raw raw[RPT];
+    auto get = [&](int half) {
+        const int64_t row = row0 + half * 64 + r4 * RPT;
+        if (col_ok && row < rows)                      // rows is a multiple of 16: the group is all in or all out
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) raw[r] = ld.get((size_t)(row + r) * (size_t)cols + (size_t)col);
+    };
+    get(0);
+
+    float cs[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cs[i] = 1.0f;
+    if (COLSCALE && col_ok) {
+        float4 a = *reinterpret_cast<const float4 *>(col_scale + col);
+        float4 b = *reinterpret_cast<const float4 *>(col_scale + col + 4);
+        cs[0] = a.x; cs[1] = a.y; cs[2] = a.z; cs[3] = a.w;
+        cs[4] = b.x; cs[5] = b.y; cs[6] = b.z; cs[7] = b.w;
+    }
+
+    float sigma = 1.0f;
+    bool tensor_scale = false;
+    if constexpr (KNOWN) { sigma = known_scale(); tensor_scale = true; }
+    else if (scale_in) { sigma = *scale_in; tensor_scale = true; }
     else if (amax) {
         // maximum over the words of the range pass, or over the slots the producers folded into: lane i of every wave
         // takes slot i (kAmaxSlots = wave size); then a wave-wide maximum
@@ -362,60 +409,37 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
         if (amax_out && bx == 0 && by == 0 && threadIdx.x == 0) *amax_out = m;
     }
     if (scale_out && bx == 0 && by == 0 && threadIdx.x == 0) *scale_out = sigma;
-
-    const int64_t row0 = (int64_t)by * kTile;
-    const int64_t col0 = (int64_t)bx * kTile;
-    const int c8 = threadIdx.x & 15;       // which 8-column chunk
-    const int r4 = threadIdx.x >> 4;       // which 4-row group (0..15) inside a 64-row half
-    const int64_t col = col0 + c8 * 8;
-    const bool col_ok = col < cols;
-
-    float cs[8];
+    if (FACT != kFactNone && col_ok) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) cs[i] = 1.0f;
-    if (COLSCALE && col_ok) {
-        float4 a = *reinterpret_cast<const float4 *>(col_scale + col);
-        float4 b = *reinterpret_cast<const float4 *>(col_scale + col + 4);
-        cs[0] = a.x; cs[1] = a.y; cs[2] = a.z; cs[3] = a.w;
-        cs[4] = b.x; cs[5] = b.y; cs[6] = b.z; cs[7] = b.w;
-        if (FACT != kFactNone) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) cs[i] = FACT == kFactS ? smooth_factor(cs[i]) : smooth_factor_inv(cs[i]);
-        }
+        for (int i = 0; i < 8; ++i) cs[i] = FACT == kFactS ? smooth_factor(cs[i]) : smooth_factor_inv(cs[i]);
     }
 
     ssg_i16x2 seen2 = {0x7f, 0x7f};                     // RECORD: largest (|bf16 pattern| + 0x7f) this lane met, per half
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const int lr = half * 64 + r4 * 4;             // local row of the 4-row group
-        uint32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
-        if (col_ok && row0 + lr < rows) {              // rows is a multiple of 16: the group is all in or all out
-            // the four row loads of the group first: four requests in flight per lane (measured: one at a time is
-            // 5-10 % slower, all eight of the lane at once is slower again)
-            float v[4][8];
+    for (int half = 0; half < (ROWS + 63) / 64; ++half) {
+        const int lr = half * 64 + r4 * RPT;           // local row of the group
+        uint32_t lo[RPT] = {}, hi[RPT] = {};
+        if (half > 0) get(half);
+        if (col_ok && row0 + lr < rows) {
+            float v[RPT][8];
             if constexpr (RECORD) {
                 // bf16 source: the range is taken on the raw 16-bit patterns, two per operation.  |x| + 0x7f is
                 // below 0x8000 for every number and infinity and at or above it for NaN, so a signed 16-bit
                 // maximum ignores NaN, as the range pass does.
-                uint4 raw[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) raw[r] = ld.load8_raw((size_t)(row0 + lr + r) * (size_t)cols + (size_t)col);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
+                for (int r = 0; r < RPT; ++r) {
                     const uint32_t w4[4] = {raw[r].x, raw[r].y, raw[r].z, raw[r].w};
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const ssg_i16x2 b = __builtin_bit_cast(ssg_i16x2, (w4[i] & 0x7fff7fffu) + 0x007f007fu);
                         seen2 = __builtin_elementwise_max(seen2, b);
                     }
-                    LoadBf16::widen(raw[r], v[r]);
                 }
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) ld.load8((size_t)(row0 + lr + r) * (size_t)cols + (size_t)col, v[r]);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < RPT; ++r) Loader::widen(raw[r], v[r]);
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) {
                 const size_t off = (size_t)(row0 + lr + r) * (size_t)cols + (size_t)col;
                 uint32_t nonzero = 0;
 #pragma unroll
@@ -437,7 +461,7 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
                 *reinterpret_cast<uint2 *>(dst + off) = make_uint2(lo[r], hi[r]);
             }
         }
-        if (TRANSPOSED) {
+        if constexpr (TRANSPOSED) {
             uint32_t t[4];
             transpose4x4_bytes(lo[0], lo[1], lo[2], lo[3], t);
 #pragma unroll
@@ -496,13 +520,13 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
     }
 }
 
-template <class Loader, int FMT, bool COLSCALE, bool TRANSPOSED, bool RECORD = false, bool COUNT = false>
+template <class Loader, int FMT, bool COLSCALE, bool TRANSPOSED, bool RECORD = false, bool COUNT = false, int ROWS = kTile>
 __global__ void __launch_bounds__(256)
 cast_kernel(const CastBatch<Loader> batch) {
     // (the list is read where a recording cast starts a call, and not elsewhere: it costs every cast 0.15 us, 16 x 16 with a
     // given scale 2.7 and 2.55 us)
     if (RECORD && blockIdx.z == 0) zero_words(batch.zero, (blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x, gridDim.x * gridDim.y * 256);
-    cast_block<Loader, FMT, COLSCALE, TRANSPOSED, RECORD, COUNT>(batch.item[blockIdx.z], batch.pow2, blockIdx.x, blockIdx.y);
+    cast_block<Loader, FMT, COLSCALE, TRANSPOSED, RECORD, COUNT, ROWS>(batch.item[blockIdx.z], batch.pow2, blockIdx.x, blockIdx.y);
 }
 
 // The two casts between the gate/up GEMM and the last GEMM of the Smooth-SwiGLU forward in one launch: h^ =
@@ -515,15 +539,20 @@ cast_h_w3_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3, cons
     else cast_block<LoadBf16, kE4M3, true, false, false, false>(w3, pow2, blockIdx.x, blockIdx.y);
 }
 
-// The same with the channel factors formed on the way (Smooth-SwiGLU): h.col_scale and w3.col_scale are the per-channel
-// maxima of h, f.w3_camax those of W3.  Every workgroup of the second cast takes the maximum of s^-1 * w3's range over all
-// channels itself, which saves the launch of channel_factors_kernel (4.7 us) and costs each of them a read of 8 f bytes.
+// The same with the channel factors formed on the way: h.col_scale and w3.col_scale are the per-channel maxima of h, f.w3_camax those
+// of W3.  Saves the launch of channel_factors_kernel (4.7 us; two for the plain block).  Two forms:
+//   cast_h_w3_factors_kernel, Smooth-SwiGLU with few channels: every workgroup of the second cast takes the maximum of s^-1 * w3's
+//     range over all channels itself, a read of 8 f bytes for each of them;
+//   cast_h_w3_meet_kernel: the workgroups of the first row of tiles of h take it over their 128 channels and leave it for the
+//     others (ssg_meet.h).  Their tiles are dealt first, so where there are many workgroups no one has to wait.
 struct InlineFactors {
     const float *h_camax, *w3_camax;
     int64_t f;
     float *s, *sinv, *amax_w3s;
+    float *hmax;                     // plain block: receives h's range
+    const float *h_scale_given;      //              the scale of h as the caller gives it, or null
 };
-template <bool COUNT>
+template <bool COUNT, int ROWS>
 __global__ void __launch_bounds__(256)
 cast_h_w3_factors_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3, const int pow2, const InlineFactors fac) {
     if (blockIdx.z == 0) {
@@ -533,24 +562,103 @@ cast_h_w3_factors_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> 
             fac.s[col] = smooth_factor(a);
             fac.sinv[col] = smooth_factor_inv(a);
         }
-        cast_block<LoadSwiglu, kE4M3, true, false, false, COUNT, kFactS>(h, pow2, blockIdx.x, blockIdx.y);
+        cast_block<LoadSwiglu, kE4M3, true, false, false, COUNT, ROWS, kFactS>(h, pow2, blockIdx.x, blockIdx.y);
         return;
     }
-    if ((int64_t)blockIdx.x * kTile >= w3.cols || (int64_t)blockIdx.y * kTile >= w3.rows) return;
-    uint32_t m = 0;
-    for (int64_t i = threadIdx.x; i < fac.f; i += 256) {
-        const uint32_t b = abs_bits_ignore_nan(__fmul_rn(fac.w3_camax[i], smooth_factor_inv(fac.h_camax[i])));
-        m = m > b ? m : b;
+    cast_block<LoadBf16, kE4M3, true, false, false, false, ROWS, kFactSinv>(w3, pow2, blockIdx.x, blockIdx.y, [&]() {
+        uint32_t m = 0;
+        for (int64_t i = threadIdx.x; i < fac.f; i += 256) {
+            const uint32_t b = abs_bits_ignore_nan(__fmul_rn(fac.w3_camax[i], smooth_factor_inv(fac.h_camax[i])));
+            m = m > b ? m : b;
+        }
+        __shared__ uint32_t wave_m[4];
+        m = wave_max_u32(m);
+        if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = m;
+        __syncthreads();
+        m = wave_max_u32(wave_m[threadIdx.x & 3]);
+        const float amax = __uint_as_float(m);
+        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *fac.amax_w3s = amax;
+        return scale_from_amax(amax, Fp8Traits<kE4M3>::fmax, pow2);
+    });
+}
+
+// `update`: its ranges enter the history of delayed scaling here, a workgroup each (they are complete, and no later kernel of the call
+// reads the state).
+template <bool COUNT, bool SMOOTH, int ROWS>
+__global__ void __launch_bounds__(256)
+cast_h_w3_meet_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3, const int pow2, const InlineFactors fac,
+                      const Meeting meeting, const ScalingUpdate update) {
+    __shared__ uint32_t words[kMeetBlocks + 8];
+    const int t = threadIdx.x, groups = (int)((fac.f + kTile - 1) / kTile), mine = (int)blockIdx.x;
+    // of channel kTile * k + t: the range of s^-1 * w3, and of h
+    auto w3_range = [&](int k) {
+        const int64_t i = (int64_t)k * kTile + t;
+        if (t >= kTile || i >= fac.f) return 0u;
+        return abs_bits_ignore_nan(SMOOTH ? __fmul_rn(fac.w3_camax[i], smooth_factor_inv(fac.h_camax[i])) : fac.w3_camax[i]);
+    };
+    auto h_range = [&](int k) {
+        const int64_t i = (int64_t)k * kTile + t;
+        return t < kTile && i < fac.f ? abs_bits_ignore_nan(fac.h_camax[i]) : 0u;
+    };
+    const bool first_row = blockIdx.z == 0 && blockIdx.y == 0;
+    if (first_row) {
+        const uint32_t a = wave_max_u32(w3_range(mine)), b = SMOOTH ? 0u : wave_max_u32(h_range(mine));
+        if ((t & 63) == 0) { words[t >> 6] = a; words[4 + (t >> 6)] = b; }
+        __syncthreads();
+        if (t == 0) {
+            meet_leave(meeting, mine, words[0] > words[1] ? words[0] : words[1]);
+            if (!SMOOTH) meet_leave(meeting, groups + mine, words[4] > words[5] ? words[4] : words[5]);
+        }
+        __syncthreads();
     }
-    __shared__ uint32_t wave_m[4];
-    m = wave_max_u32(m);
-    if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = m;
-    __syncthreads();
-    m = wave_max_u32(wave_m[threadIdx.x & 3]);
-    const float amax = __uint_as_float(m);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *fac.amax_w3s = amax;
-    cast_block<LoadBf16, kE4M3, true, false, false, false, kFactSinv>(w3, pow2, blockIdx.x, blockIdx.y,
-                                                                      scale_from_amax(amax, Fp8Traits<kE4M3>::fmax, pow2));
+    if (blockIdx.z == 0) {
+        float sigma_h = 1.0f;
+        auto scale_h = [&]() {                           // plain block: one scale for the whole tensor
+            const bool first = first_row && mine == 0;
+            float amax = 0.0f;
+            if (!fac.h_scale_given || first) amax = __uint_as_float(meet_max<256>(meeting, groups, groups, mine, words, h_range));
+            if (first && t == 0) *fac.hmax = amax;
+            return fac.h_scale_given ? *fac.h_scale_given : scale_from_amax(amax, 448.0f, 0);
+        };
+        if constexpr (SMOOTH) {
+            cast_block<LoadSwiglu, kE4M3, true, false, false, COUNT, ROWS, kFactS>(h, pow2, blockIdx.x, blockIdx.y);
+        } else {
+            cast_block<LoadSwiglu, kE4M3, false, false, false, COUNT, ROWS>(h, pow2, blockIdx.x, blockIdx.y, [&]() { return sigma_h = scale_h(); });
+        }
+        if (first_row) {
+            const int64_t i = (int64_t)mine * kTile + t;
+            if (t < kTile && i < fac.f) {
+                const float a = fac.h_camax[i];
+                fac.s[i] = SMOOTH ? smooth_factor(a) : sigma_h;
+                fac.sinv[i] = SMOOTH ? smooth_factor_inv(a) : 1.0f;
+            }
+            for (int k = mine; k < update.count; k += groups)
+                if (t < 64) scaling_update_wave(update, k, t);
+        }
+        return;
+    }
+    auto scale_w3 = [&]() {
+        const float amax = __uint_as_float(meet_max<256>(meeting, 0, groups, mine, words, w3_range));
+        if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) *fac.amax_w3s = amax;
+        return scale_from_amax(amax, Fp8Traits<kE4M3>::fmax, pow2);
+    };
+    if constexpr (SMOOTH) cast_block<LoadBf16, kE4M3, true, false, false, false, ROWS, kFactSinv>(w3, pow2, blockIdx.x, blockIdx.y, scale_w3);
+    else cast_block<LoadBf16, kE4M3, false, false, false, false, ROWS>(w3, pow2, blockIdx.x, blockIdx.y, scale_w3);
+}
+
+// Rows of a launch's tiles, by the number of those of 128.  Small launches are bound by latencies and, where a thread has 64
+// elements, by its own instructions one after the other.  A step in tiles of 128 rows, 64 and 16: 256, 256, 688 60.4 us, 56.4, 54.4;
+// 1408, 256, 848 62.0, 56.3, 53.5; 384, 512, 1664 65.6, 59.8, 57.4; 1040, 1024, 2736 (396 tiles) 110.3, 108.8, 108.8; 384, 2400, 6016 (1786)
+// 152, 146, 146; 2048, 2048, 5504 (1376) 290, 287; beyond 4096 tiles no difference.
+static int cast_tile_rows(int64_t rows, int64_t cols, int64_t items) {
+    const int64_t tiles = items * ((rows + kTile - 1) / kTile) * ((cols + kTile - 1) / kTile);
+    return tiles <= 512 ? 16 : tiles <= 4096 ? 64 : kTile;
+}
+// f with the number as a constant
+template <class F> static void with_tile_rows(int rows, F &&f) {
+    if (rows == 16) f(std::integral_constant<int, 16>{});
+    else if (rows == 64) f(std::integral_constant<int, 64>{});
+    else f(std::integral_constant<int, kTile>{});
 }
 
 template <class Loader>
@@ -579,13 +687,19 @@ static void launch_cast_l(const CastArgs *list, int n, MakeLoader make, const Ze
     }
     batch.pow2 = a.pow2;
     batch.zero = zero;
-    dim3 grid((unsigned)((cols + kTile - 1) / kTile), (unsigned)((rows + kTile - 1) / kTile), (unsigned)n);
     const bool cs = a.col_scale != nullptr, tr = a.dst_t != nullptr;
+    // (the forms of the block's own calls without a transposed copy are built for both)
+    const int edge = std::is_same<Loader, LoadBf16>::value && !cs && !tr && !a.counters ? cast_tile_rows(rows, cols, n) : kTile;
+    dim3 grid((unsigned)((cols + kTile - 1) / kTile), (unsigned)((rows + edge - 1) / edge), (unsigned)n);
 #define SSG_CAST(...) hipLaunchKernelGGL((cast_kernel<Loader, FMT, __VA_ARGS__>), grid, dim3(256), 0, st, batch)
     if constexpr (std::is_same<Loader, LoadBf16>::value) {
         if (a.record && !cs) {
             if (tr) SSG_CAST(false, true, true);
-            else SSG_CAST(false, false, true);
+            else with_tile_rows(edge, [&](auto r) { SSG_CAST(false, false, true, false, decltype(r)::value); });
+            return;
+        }
+        if (edge < kTile) {
+            with_tile_rows(edge, [&](auto r) { SSG_CAST(false, false, false, false, decltype(r)::value); });
             return;
         }
     }
@@ -935,12 +1049,22 @@ bool cast_h_w3_ok(const CastArgs &h, const CastArgs &w3) {
            w3.cols > 0;
 }
 
+template <bool COUNT, int ROWS>
+static void launch_h_w3_factors(dim3 grid, bool smooth, const CastItem<LoadSwiglu> &h, const CastItem<LoadBf16> &w3, int pow2,
+                                const InlineFactors &in, const Meeting *meeting, const ScalingUpdate &update, hipStream_t st) {
+    if (!meeting) hipLaunchKernelGGL((cast_h_w3_factors_kernel<COUNT, ROWS>), grid, dim3(256), 0, st, h, w3, pow2, in);
+    else if (smooth) hipLaunchKernelGGL((cast_h_w3_meet_kernel<COUNT, true, ROWS>), grid, dim3(256), 0, st, h, w3, pow2, in, *meeting, update);
+    else hipLaunchKernelGGL((cast_h_w3_meet_kernel<COUNT, false, ROWS>), grid, dim3(256), 0, st, h, w3, pow2, in, *meeting, update);
+}
+
 void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, const ChannelFactors &fac, hipStream_t st) {
     const bool pair = cast_h_w3_ok(h, w3);
-    // the line: 8 f bytes read by every workgroup of the w3 cast against a launch (f = 688: 64.5 us a step with the launch,
-    // 62.6 without; f = 2736: 126 either way)
-    const bool inline_factors = pair && fac.smooth && fac.update.count == 0 && fac.f <= 1024;
-    if (!inline_factors) launch_channel_factors(fac, st);
+    // the line between the two forms that need no launch of their own for the factors: 8 f bytes read by every workgroup of the w3 cast
+    // against the exchange
+    const bool few = pair && fac.smooth && fac.update.count == 0 && fac.f <= 1024;
+    Meeting meeting;
+    const bool meet = pair && !few && (fac.smooth ? 1 : 2) * ((fac.f + kTile - 1) / kTile) <= kMeetBlocks && meet_ticket(st, &meeting);
+    if (!few && !meet) launch_channel_factors(fac, st);
     if (!pair) {                            // not the pair this launch is built for: one after the other
         launch_cast(h, st);
         launch_cast(w3, st);
@@ -949,14 +1073,19 @@ void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, const ChannelFactor
     CastItem<LoadSwiglu> hi = cast_item<LoadSwiglu>(LoadSwiglu{(const uint16_t *)h.src, (const uint16_t *)h.src2}, h);
     CastItem<LoadBf16> wi = cast_item<LoadBf16>(LoadBf16{(const uint16_t *)w3.src}, w3);
     const int64_t rows = h.rows > w3.rows ? h.rows : w3.rows, cols = h.cols > w3.cols ? h.cols : w3.cols;
-    dim3 grid((unsigned)((cols + kTile - 1) / kTile), (unsigned)((rows + kTile - 1) / kTile), 2u);
+    const int edge = few || meet ? cast_tile_rows(rows, cols, 2) : kTile;
+    const dim3 grid((unsigned)((cols + kTile - 1) / kTile), (unsigned)((rows + edge - 1) / edge), 2u);
     profile_before(kTagCastHW3, st, cast_bytes(h) + cast_bytes(w3));
-    if (inline_factors) {
+    if (few || meet) {
         hi.col_scale = wi.col_scale = fac.h_camax;
         wi.amax = nullptr;
-        const InlineFactors in{fac.h_camax, fac.w3_camax, fac.f, fac.s, fac.sinv, reinterpret_cast<float *>(fac.amax_w3s_bits)};
-        if (h.counters) hipLaunchKernelGGL(cast_h_w3_factors_kernel<true>, grid, dim3(256), 0, st, hi, wi, w3.pow2, in);
-        else hipLaunchKernelGGL(cast_h_w3_factors_kernel<false>, grid, dim3(256), 0, st, hi, wi, w3.pow2, in);
+        const InlineFactors in{fac.h_camax, fac.w3_camax, fac.f, fac.s, fac.sinv, reinterpret_cast<float *>(fac.amax_w3s_bits),
+                               reinterpret_cast<float *>(fac.hmax_bits), fac.h_scale_given};
+        const Meeting *m = meet ? &meeting : nullptr;
+        with_tile_rows(edge, [&](auto r) {
+            if (h.counters) launch_h_w3_factors<true, decltype(r)::value>(grid, fac.smooth, hi, wi, w3.pow2, in, m, fac.update, st);
+            else launch_h_w3_factors<false, decltype(r)::value>(grid, fac.smooth, hi, wi, w3.pow2, in, m, fac.update, st);
+        });
     } else if (h.counters) hipLaunchKernelGGL(cast_h_w3_kernel<true>, grid, dim3(256), 0, st, hi, wi, w3.pow2);
     else hipLaunchKernelGGL(cast_h_w3_kernel<false>, grid, dim3(256), 0, st, hi, wi, w3.pow2);
     profile_after(st);
