@@ -354,6 +354,11 @@ size_t ssg_adam_state_bytes(int64_t n);
 ssg_status ssg_adam_init(int64_t n, void *state, void *stream);
 ssg_status ssg_adam_step(const ssg_adam_desc *desc, const void *grad, float *w, void *w_bf16, void *state,
                          void *stream);
+/* As ssg_adam_step.  A tensor whose gradient and moments fit the chip's registers takes its step in one launch, whose workgroups look
+ * for each other's ranges at most `polls` times and then form what is missing themselves (see ssg_quantize_wait): the results
+ * are the same for any value. */
+ssg_status ssg_adam_step_wait(const ssg_adam_desc *desc, const void *grad, float *w, void *w_bf16, void *state,
+                              int32_t polls, void *stream);
 /* pointers into `state` as left by step `step` (0 = after ssg_adam_init) */
 ssg_status ssg_adam_view_state(int64_t n, int32_t step, const void *state, ssg_adam_state_view *out);
 

@@ -36,7 +36,7 @@ EXPORTS = [
     "ssg_mlp_scaling_state_bytes", "ssg_mlp_scaling_init",
     "ssg_infer_prepared_bytes", "ssg_infer_workspace_bytes", "ssg_infer_prepare", "ssg_infer_fwd", "ssg_infer_view",
     "ssg_infer_noalloc_max_bytes", "ssg_infer_fwd_noalloc",
-    "ssg_adam_state_bytes", "ssg_adam_init", "ssg_adam_step", "ssg_adam_view_state",
+    "ssg_adam_state_bytes", "ssg_adam_init", "ssg_adam_step", "ssg_adam_step_wait", "ssg_adam_view_state",
     "ssg_profile_enable", "ssg_profile_select", "ssg_profile_read",
 ]
 
@@ -132,6 +132,7 @@ _lib.ssg_adam_state_bytes.argtypes = [c_int64]
 _lib.ssg_adam_state_bytes.restype = c_size_t
 _lib.ssg_adam_init.argtypes = [c_int64, c_void_p, c_void_p]
 _lib.ssg_adam_step.argtypes = [POINTER(ssg_adam_desc), c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]
+_lib.ssg_adam_step_wait.argtypes = [POINTER(ssg_adam_desc), c_void_p, c_void_p, c_void_p, c_void_p, c_int32, c_void_p]
 _lib.ssg_adam_view_state.argtypes = [c_int64, c_int32, c_void_p, POINTER(ssg_adam_state_view)]
 for _n in EXPORTS[2:]:
     if not _n.endswith("_bytes"):          # the size queries return size_t, everything else a status
@@ -370,6 +371,10 @@ def ssg_adam_init(n: int, state, stream=None) -> None:
 
 def ssg_adam_step(desc, grad, w, w_bf16, state, stream=None) -> None:
     _check(_lib.ssg_adam_step(ctypes.byref(desc), _ptr(grad), _ptr(w), _ptr(w_bf16), _ptr(state), _stream(stream)))
+
+
+def ssg_adam_step_wait(desc, grad, w, w_bf16, state, polls, stream=None) -> None:
+    _check(_lib.ssg_adam_step_wait(ctypes.byref(desc), _ptr(grad), _ptr(w), _ptr(w_bf16), _ptr(state), polls, _stream(stream)))
 
 
 def ssg_adam_view_state(n: int, step: int, state) -> ssg_adam_state_view:

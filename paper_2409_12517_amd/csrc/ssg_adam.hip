@@ -1,6 +1,6 @@
 // Adam step with the first moment stored in E4M3 and the second in E5M2 (Section 5).
 //
-// Two HBM-bound passes over a flat parameter tensor:
+// Two HBM-bound passes over a flat parameter tensor (one launch for up to 4 M elements, see adam_held_kernel):
 //   pass 1  new moments from the stored codes and the gradient, their ranges (max|m|, max v)
 //           into 64 slotted atomics each;
 //   pass 2  the same moments again (bit-identical: same inputs, same operations), the
@@ -18,8 +18,11 @@
 //
 // State scalars are kept twice, by step parity, so that pass 2 can read the old scales and
 // range slots while workgroup 0 writes the new ones and clears the slots of the next step.
+#include <type_traits>
+
 #include "ssg_device.h"
 #include "ssg_internal.h"
+#include "ssg_meet.h"
 
 namespace ssg {
 
@@ -44,22 +47,28 @@ typedef float ssg_f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int ssg_u32x2 __attribute__((ext_vector_type(2)));
 // A lane takes four neighbouring elements at a time: 16 bytes of an fp32 gradient or of the weights, 4 bytes of each code, so
 // that the lanes of a wave lie side by side in every access.
+template <bool GRAD_BF16> using Packed = std::conditional_t<GRAD_BF16, ssg_u32x2, ssg_f32x4>;
 template <bool GRAD_BF16>
-__device__ __forceinline__ void load_grad4(const void *grad, size_t i, float (&g)[4]) {
-    if (GRAD_BF16) {
-        const ssg_u32x2 q = __builtin_nontemporal_load(reinterpret_cast<const ssg_u32x2 *>(reinterpret_cast<const uint16_t *>(grad) + i));
+__device__ __forceinline__ Packed<GRAD_BF16> load_packed4(const void *grad, size_t i) {
+    return __builtin_nontemporal_load(reinterpret_cast<const Packed<GRAD_BF16> *>(static_cast<const uint8_t *>(grad) + i * (GRAD_BF16 ? 2 : 4)));
+}
+template <bool GRAD_BF16>
+__device__ __forceinline__ void unpack4(const Packed<GRAD_BF16> &q, float (&g)[4]) {
+    if constexpr (GRAD_BF16) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             g[2 * k] = __uint_as_float(q[k] << 16);
             g[2 * k + 1] = __uint_as_float(q[k] & 0xffff0000u);
         }
     } else {
-        const ssg_f32x4 q = __builtin_nontemporal_load(reinterpret_cast<const ssg_f32x4 *>(reinterpret_cast<const float *>(grad) + i));
 #pragma unroll
         for (int k = 0; k < 4; ++k) g[k] = q[k];
     }
 }
-
+template <bool GRAD_BF16>
+__device__ __forceinline__ void load_grad4(const void *grad, size_t i, float (&g)[4]) {
+    unpack4<GRAD_BF16>(load_packed4<GRAD_BF16>(grad, i), g);
+}
 // four stored moments from a word of codes each, as fp32: decode(code) * (1 / scale)
 __device__ __forceinline__ void decode_moments4(uint32_t mw, uint32_t vw, float inv_sm, float inv_sv, float (&m)[4], float (&v)[4]) {
     m[0] = __fmul_rn(__builtin_amdgcn_cvt_f32_fp8((int)mw, 0), inv_sm);
@@ -70,6 +79,37 @@ __device__ __forceinline__ void decode_moments4(uint32_t mw, uint32_t vw, float 
     v[1] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw, 1), inv_sv);
     v[2] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw, 2), inv_sv);
     v[3] = __fmul_rn(__builtin_amdgcn_cvt_f32_bf8((int)vw, 3), inv_sv);
+}
+
+// the step of four elements, stored: weights, their copy, the codes of the new moments m, v under the new scales
+__device__ __forceinline__ void finish4(const AdamParams &p, size_t i, const float (&m)[4], const float (&v)[4], float sm, float sv, ssg_f32x4 w) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        // bias-corrected step, decoupled decay
+        const float mhat = __fmul_rn(m[k], p.c1);
+        const float vhat = __fmul_rn(v[k], p.c2);
+        const float denom = __fadd_rn(sqrtf(vhat), p.eps);   // sqrtf, not __fsqrt_rn: only the former is correctly rounded here
+        float upd = __fdiv_rn(mhat, denom);
+        upd = __fadd_rn(upd, __fmul_rn(p.wd, w[k]));
+        w[k] = __fsub_rn(w[k], __fmul_rn(p.lr, upd));
+    }
+    __builtin_nontemporal_store(w, reinterpret_cast<ssg_f32x4 *>(p.w + i));
+    if (p.w_bf16) *reinterpret_cast<ssg_u32x2 *>(p.w_bf16 + i) = ssg_u32x2{pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3])};
+    *reinterpret_cast<uint32_t *>(p.m_q + i) = satcast_pk4<kE4M3>(__fmul_rn(m[0], sm), __fmul_rn(m[1], sm), __fmul_rn(m[2], sm), __fmul_rn(m[3], sm));
+    *reinterpret_cast<uint32_t *>(p.v_q + i) = satcast_pk4<kE5M2>(__fmul_rn(v[0], sv), __fmul_rn(v[1], sv), __fmul_rn(v[2], sv), __fmul_rn(v[3], sv));
+}
+
+// what one workgroup leaves behind for the call and for the next step: the scales and ranges, the other parity's slots cleared (they
+// were last read by the previous step's update pass)
+__device__ __forceinline__ void leave_scalars(const AdamParams &p, float sm, float sv, float amax_m, float amax_v) {
+    uint32_t *cur = p.scalars + 8 * p.parity;
+    if (threadIdx.x == 0) {
+        cur[kAdamScaleM] = __float_as_uint(sm); cur[kAdamScaleV] = __float_as_uint(sv);
+        cur[kAdamAmaxM] = __float_as_uint(amax_m); cur[kAdamAmaxV] = __float_as_uint(amax_v);
+    }
+    uint32_t *next = p.scalars + kAdamSlotsM + (size_t)(p.parity ^ 1) * 2 * kAmaxSlotWords;
+    if (threadIdx.x < 2 * kAmaxSlots)
+        next[(threadIdx.x >> 6) * kAmaxSlotWords + (threadIdx.x & 63) * kAmaxSlotStride] = 0u;
 }
 
 // exponential moving averages of the gradient and of its square
@@ -140,17 +180,7 @@ __global__ void __launch_bounds__(kAdamThreads) adam_update_kernel(AdamParams p)
     const float amax_v = __uint_as_float(wave_max_u32(slots_v[lane * kAmaxSlotStride]));
     const float sm = scale_from_amax(amax_m, Fp8Traits<kE4M3>::fmax, p.pow2);
     const float sv = scale_from_amax(amax_v, Fp8Traits<kE5M2>::fmax, p.pow2);
-    if (blockIdx.x == 0) {
-        uint32_t *cur = p.scalars + 8 * p.parity;
-        if (threadIdx.x == 0) {
-            cur[kAdamScaleM] = __float_as_uint(sm); cur[kAdamScaleV] = __float_as_uint(sv);
-            cur[kAdamAmaxM] = __float_as_uint(amax_m); cur[kAdamAmaxV] = __float_as_uint(amax_v);
-        }
-        // the other parity's slots were last read by the previous step's update pass: clear them for the next step
-        uint32_t *next = p.scalars + kAdamSlotsM + (size_t)(p.parity ^ 1) * 2 * kAmaxSlotWords;
-        if (threadIdx.x < 2 * kAmaxSlots)
-            next[(threadIdx.x >> 6) * kAmaxSlotWords + (threadIdx.x & 63) * kAmaxSlotStride] = 0u;
-    }
+    if (blockIdx.x == 0) leave_scalars(p, sm, sv, amax_m, amax_v);
     constexpr int kChunk = 4 * kAdamThreads;
     const size_t stride = (size_t)gridDim.x * kChunk * CHUNKS;
     for (size_t i = (size_t)blockIdx.x * kChunk * CHUNKS + 4 * threadIdx.x; i < (size_t)p.n; i += stride) {
@@ -173,21 +203,124 @@ __global__ void __launch_bounds__(kAdamThreads) adam_update_kernel(AdamParams p)
             float m[4], v[4];
             decode_moments4(mq[c], vq[c], inv_sm, inv_sv, m, v);
             new_moments4(p, g[c], m, v);
+            finish4(p, j, m, v, sm, sv, w[c]);
+        }
+    }
+}
+
+// ---- both passes in one launch
+// Up to 4 M elements: every workgroup keeps its share of the gradient and the codes in registers, eight groups of four elements to a
+// lane at most, while they exchange the two ranges (ssg_meet.h), then updates it.  Bound by the latency of the launch and of the exchange; the
+// two passes cost 4 to 6 us more from the first's drain to the second's first load: 1 M elements 15.9 us with them, 10.4 in one
+// launch, 4 M 25.9 and 19.7.  With more groups per lane it gains nothing, one workgroup per compute unit streams no faster than two launches
+// that fill it: 8 M 38.4 and 38.5 (bf16 gradient 35.1 and 36.1), 16 M bf16 62.4 and 61.0.
+constexpr int kHeldThreads = 512, kHeldGroups = 4, kHeldBatches = 2;
+template <bool GRAD_BF16>
+__global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p, Meeting meeting) {
+    constexpr int HELD = kHeldGroups * kHeldBatches, kChunk = 4 * kHeldThreads;
+    __shared__ uint32_t words[kMeetBlocks + 8];
+    const uint32_t *old = p.scalars + 8 * (p.parity ^ 1);
+    const float inv_sm = __fdiv_rn(1.0f, __uint_as_float(old[kAdamScaleM])), inv_sv = __fdiv_rn(1.0f, __uint_as_float(old[kAdamScaleV]));
+    const int own = (int)blockIdx.x, blocks = (int)gridDim.x, t = threadIdx.x;
+    // the j-th group of this thread in workgroup k's share; one beyond the end is the tensor's first, for reading
+    auto group_at = [&](int k, int j) { return ((size_t)j * blocks + k) * kChunk + 4 * t; };
+    auto share = [&](int k) { return (int)(((size_t)p.n + kChunk - 1) / kChunk - k + blocks - 1) / blocks; };      // groups of it
+    struct Group { float g[4]; uint32_t mq, vq; };
+    auto load = [&](size_t i) {
+        Group x;
+        const size_t at = i < (size_t)p.n ? i : 0;
+        load_grad4<GRAD_BF16>(p.grad, at, x.g);
+        x.mq = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.m_q + at));
+        x.vq = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.v_q + at));
+        return x;
+    };
+    auto moments = [&](const Group &x, float (&m)[4], float (&v)[4]) {
+        decode_moments4(x.mq, x.vq, inv_sm, inv_sv, m, v);
+        new_moments4(p, x.g, m, v);
+    };
+    uint32_t mmax = 0, vmax = 0;
+    auto see = [&](const Group &x, uint32_t &mm, uint32_t &vm) {
+        float m[4], v[4];
+        moments(x, m, v);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                // bias-corrected step, decoupled decay
-                const float mhat = __fmul_rn(m[k], p.c1);
-                const float vhat = __fmul_rn(v[k], p.c2);
-                const float denom = __fadd_rn(sqrtf(vhat), p.eps);   // sqrtf, not __fsqrt_rn: only the former is correctly rounded here
-                float upd = __fdiv_rn(mhat, denom);
-                upd = __fadd_rn(upd, __fmul_rn(p.wd, w[c][k]));
-                w[c][k] = __fsub_rn(w[c][k], __fmul_rn(p.lr, upd));
-            }
-            __builtin_nontemporal_store(w[c], reinterpret_cast<ssg_f32x4 *>(p.w + j));
-            if (p.w_bf16)
-                *reinterpret_cast<ssg_u32x2 *>(p.w_bf16 + j) = ssg_u32x2{pack_bf16x2(w[c][0], w[c][1]), pack_bf16x2(w[c][2], w[c][3])};
-            *reinterpret_cast<uint32_t *>(p.m_q + j) = satcast_pk4<kE4M3>(__fmul_rn(m[0], sm), __fmul_rn(m[1], sm), __fmul_rn(m[2], sm), __fmul_rn(m[3], sm));
-            *reinterpret_cast<uint32_t *>(p.v_q + j) = satcast_pk4<kE5M2>(__fmul_rn(v[0], sv), __fmul_rn(v[1], sv), __fmul_rn(v[2], sv), __fmul_rn(v[3], sv));
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t a = abs_bits_ignore_nan(m[k]), b = abs_bits_ignore_nan(v[k]);
+            mm = mm > a ? mm : a;
+            vm = vm > b ? vm : b;
+        }
+    };
+    const int mine = share(own);
+    Packed<GRAD_BF16> held_g[HELD];
+    uint32_t held_m[HELD], held_v[HELD];
+#pragma unroll
+    for (int j = 0; j < HELD; ++j) {
+        if (j < mine) {
+            const size_t i = group_at(own, j), at = i < (size_t)p.n ? i : 0;
+            held_g[j] = load_packed4<GRAD_BF16>(p.grad, at);
+            held_m[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.m_q + at));
+            held_v[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.v_q + at));
+        } else {
+            held_g[j] = Packed<GRAD_BF16>{};
+            held_m[j] = held_v[j] = 0u;
+        }
+    }
+    auto group_of = [&](int j) {
+        Group x;
+        unpack4<GRAD_BF16>(held_g[j], x.g);
+        x.mq = held_m[j]; x.vq = held_v[j];
+        return x;
+    };
+    // (groups that are not there: zero gradient and moments)
+#pragma unroll
+    for (int j = 0; j < HELD; ++j)
+        if (j < mine) see(group_of(j), mmax, vmax);
+    // the weights of the first batch come in while the ranges are exchanged
+    ssg_f32x4 w[kHeldGroups];
+    auto load_w = [&](int batch) {
+#pragma unroll
+        for (int c = 0; c < kHeldGroups; ++c) {
+            const size_t i = group_at(own, kHeldGroups * batch + c);
+            w[c] = __builtin_nontemporal_load(reinterpret_cast<const ssg_f32x4 *>(p.w + (i < (size_t)p.n ? i : 0)));
+        }
+    };
+    load_w(0);
+    mmax = wave_max_u32(mmax);
+    vmax = wave_max_u32(vmax);
+    if ((t & 63) == 0) { words[t >> 6] = mmax; words[8 + (t >> 6)] = vmax; }
+    __syncthreads();
+    if (t < 2) {
+        uint32_t r = 0;
+#pragma unroll
+        for (int k = 0; k < kHeldThreads / 64; ++k) r = r > words[8 * t + k] ? r : words[8 * t + k];
+        meet_leave(meeting, t * kMeetBlocks + own, r);
+    }
+    __syncthreads();
+    auto share_max = [&](int k, bool second) {
+        uint32_t mm = 0, vm = 0;
+        for (int j = 0; j < share(k); ++j) see(load(group_at(k, j)), mm, vm);
+        return second ? vm : mm;
+    };
+    const float amax_m = __uint_as_float(meet_max<kHeldThreads>(meeting, 0, blocks, own, words, [&](int k) { return share_max(k, false); }));
+    const float amax_v = __uint_as_float(meet_max<kHeldThreads>(meeting, kMeetBlocks, blocks, own, words, [&](int k) { return share_max(k, true); }));
+    const float sm = scale_from_amax(amax_m, Fp8Traits<kE4M3>::fmax, p.pow2);
+    const float sv = scale_from_amax(amax_v, Fp8Traits<kE5M2>::fmax, p.pow2);
+    if (own == 0) leave_scalars(p, sm, sv, amax_m, amax_v);
+#pragma nounroll
+    for (int batch = 0; kHeldGroups * batch < mine; ++batch) {
+        ssg_f32x4 now[kHeldGroups];
+#pragma unroll
+        for (int c = 0; c < kHeldGroups; ++c) now[c] = w[c];
+        if (kHeldGroups * (batch + 1) < mine) load_w(batch + 1);
+#pragma unroll
+        for (int c = 0; c < kHeldGroups; ++c) {
+            const size_t i = group_at(own, kHeldGroups * batch + c);
+            float m[4], v[4];
+            moments(group_of(c), m, v);
+            if (i < (size_t)p.n) finish4(p, i, m, v, sm, sv, now[c]);
+        }
+#pragma unroll
+        for (int j = 0; j + kHeldGroups < HELD; ++j) {
+            held_g[j] = held_g[j + kHeldGroups]; held_m[j] = held_m[j + kHeldGroups]; held_v[j] = held_v[j + kHeldGroups];
         }
     }
 }
@@ -214,6 +347,20 @@ void launch_adam_step(const AdamArgs &a, hipStream_t st) {
     p.grad = a.grad; p.w = a.w; p.w_bf16 = (uint16_t *)a.w_bf16; p.m_q = a.m_q; p.v_q = a.v_q; p.scalars = a.scalars;
     p.n = a.n; p.b1 = a.beta1; p.b2 = a.beta2; p.omb1 = a.one_minus_beta1; p.omb2 = a.one_minus_beta2;
     p.c1 = a.c1; p.c2 = a.c2; p.lr = a.lr; p.eps = a.eps; p.wd = a.weight_decay; p.parity = a.step & 1; p.pow2 = a.pow2;
+    const double gbytes = a.grad_bf16 ? 2.0 : 4.0;       // algorithmic bytes per element: gradient + two codes; update: + w in/out, bf16 copy, codes out
+    const double update_bytes = gbytes + 2.0 + 4.0 + 4.0 + (a.w_bf16 ? 2.0 : 0.0) + 2.0;
+    constexpr size_t kHeldChunk = 4 * kHeldThreads;
+    const size_t chunks = ((size_t)a.n + kHeldChunk - 1) / kHeldChunk;
+    Meeting meeting;
+    if (chunks <= (size_t)kMeetBlocks * kHeldGroups * kHeldBatches && meet_ticket(st, &meeting)) {
+        if (a.polls >= 0) meeting.polls = a.polls;
+        const dim3 grid((unsigned)(chunks < kMeetBlocks ? chunks : kMeetBlocks));
+        profile_before(33, st, update_bytes * (double)a.n);
+        if (a.grad_bf16) hipLaunchKernelGGL(adam_held_kernel<true>, grid, dim3(kHeldThreads), 0, st, p, meeting);
+        else hipLaunchKernelGGL(adam_held_kernel<false>, grid, dim3(kHeldThreads), 0, st, p, meeting);
+        profile_after(st);
+        return;
+    }
     // 16 elements per lane in the range pass, one trip; 8 in the update pass, 2048 looping workgroups
     constexpr int kRangeChunks = 4, kUpdateChunks = 2;
     auto grid = [&](int chunks, size_t cap) {
@@ -222,12 +369,11 @@ void launch_adam_step(const AdamArgs &a, hipStream_t st) {
     };
     const unsigned grid_r = grid(kRangeChunks, (size_t)1 << 20), grid_u = grid(kUpdateChunks, 2048);
     // timing records (when enabled): tag 32 = range pass, 33 = update pass
-    const double gbytes = a.grad_bf16 ? 2.0 : 4.0;       // algorithmic bytes per element: gradient + two codes; update: + w in/out, bf16 copy, codes out
     profile_before(32, st, (gbytes + 2.0) * (double)a.n);
     if (a.grad_bf16) hipLaunchKernelGGL((adam_range_kernel<true, kRangeChunks>), dim3(grid_r), dim3(kAdamThreads), 0, st, p);
     else hipLaunchKernelGGL((adam_range_kernel<false, kRangeChunks>), dim3(grid_r), dim3(kAdamThreads), 0, st, p);
     profile_after(st);
-    profile_before(33, st, (gbytes + 2.0 + 4.0 + 4.0 + (a.w_bf16 ? 2.0 : 0.0) + 2.0) * (double)a.n);
+    profile_before(33, st, update_bytes * (double)a.n);
     if (a.grad_bf16) hipLaunchKernelGGL((adam_update_kernel<true, kUpdateChunks>), dim3(grid_u), dim3(kAdamThreads), 0, st, p);
     else hipLaunchKernelGGL((adam_update_kernel<false, kUpdateChunks>), dim3(grid_u), dim3(kAdamThreads), 0, st, p);
     profile_after(st);

@@ -525,6 +525,11 @@ ssg_status ssg_adam_init(int64_t n, void *state, void *stream) {
 
 ssg_status ssg_adam_step(const ssg_adam_desc *desc, const void *grad, float *w, void *w_bf16, void *state,
                          void *stream) {
+    return ssg_adam_step_wait(desc, grad, w, w_bf16, state, -1, stream);
+}
+
+ssg_status ssg_adam_step_wait(const ssg_adam_desc *desc, const void *grad, float *w, void *w_bf16, void *state,
+                              int32_t polls, void *stream) {
     if (!desc) return fail(SSG_ERR_ARG, "ssg_adam_step: desc is NULL");
     if (!adam_n_ok(desc->n)) return fail(SSG_ERR_SHAPE, "ssg_adam_step: n = %lld must be a positive multiple of 16", (long long)desc->n);
     if (desc->step < 1) return fail(SSG_ERR_ARG, "ssg_adam_step: step %d (steps count from 1)", desc->step);
@@ -552,6 +557,7 @@ ssg_status ssg_adam_step(const ssg_adam_desc *desc, const void *grad, float *w, 
     a.c1 = (float)(1.0 / (1.0 - std::pow((double)desc->beta1, (double)desc->step)));
     a.c2 = (float)(1.0 / (1.0 - std::pow((double)desc->beta2, (double)desc->step)));
     a.lr = desc->lr; a.eps = desc->eps; a.weight_decay = desc->weight_decay; a.pow2 = desc->rnd == SSG_ROUND_POW2;
+    a.polls = polls;
     ssg::launch_adam_step(a, static_cast<hipStream_t>(stream));
     return check_launch("ssg_adam_step");
 }

@@ -12,6 +12,10 @@
 // launch that happens to use the same row, are told from this launch's by it, and nothing is cleared.  (64-bit accesses are
 // whole; a word is a pair of them, each with half of the ticket and the maximum, which have to agree.)  A graph launches the same ticket
 // every time, so calls under capture take the launches without an exchange.
+//
+// A workgroup may write over its share of the tensor once it has all the maxima: its own word is where the others see it before
+// it looks for theirs, and one that forms a missing maximum looks for the word again after its last read of the share.  What it formed counts only if
+// the word was not there then, and so nothing of the share was written yet.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -20,7 +24,8 @@
 
 namespace ssg {
 
-constexpr int kMeetRows = 64, kMeetBlocks = 256;            // launches under way at once before two share a row; words of a row
+constexpr int kMeetRows = 64;                               // launches under way at once before two share a row of words
+constexpr int kMeetBlocks = 256;                            // workgroups that exchange a maximum, each maybe two
 constexpr int kMeetPolls = 400;                             // each takes about a microsecond
 
 // what one launch needs to know
@@ -30,12 +35,13 @@ struct Meeting {
 };
 
 // the words of a translation unit's launches
-static __device__ uint64_t g_meet[kMeetRows][kMeetBlocks][2];
+static __device__ uint64_t g_meet[kMeetRows][2 * kMeetBlocks][2];
 
 __device__ __forceinline__ void meet_leave(const Meeting &m, int word, uint32_t v) {
     uint64_t *w = g_meet[m.ticket % kMeetRows][word];
     __hip_atomic_store(w, (m.ticket << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(w + 1, (m.ticket & ~(uint64_t)0xffffffffu) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 __device__ __forceinline__ bool meet_look(const Meeting &m, int word, uint32_t &v) {
     uint64_t *w = g_meet[m.ticket % kMeetRows][word];
@@ -77,12 +83,19 @@ __device__ __forceinline__ uint32_t meet_max(const Meeting &m, int first, int co
     for (int n = 1; n <= count; ++n) {
         const int k = (own + n) % count;
         if (lds[k] != kMissing) continue;
-        uint32_t late = kMissing;
-        if (t == 0 && !meet_look(m, first + k, late)) late = kMissing;
-        late = over_workgroup(t == 0 ? late : 0u);           // by now it may have come
+        auto look_again = [&]() {                            // by now it may have come
+            uint32_t x = kMissing;
+            if (t == 0 && !meet_look(m, first + k, x)) x = kMissing;
+            return over_workgroup(t == 0 ? x : 0u);
+        };
+        uint32_t late = look_again();
         if (late == kMissing) {
-            late = over_workgroup(share_max(k));
-            if (t == 0) meet_leave(m, first + k, late);
+            const uint32_t formed = over_workgroup(share_max(k));
+            late = look_again();
+            if (late == kMissing) {
+                late = formed;
+                if (t == 0) meet_leave(m, first + k, late);
+            }
         }
         all = all > late ? all : late;
     }
