@@ -449,8 +449,9 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
                     if (tensor_scale) v[r][i] = __fmul_rn(v[r][i], sigma);
                     if (COUNT) n_sat += fabsf(v[r][i]) > Fp8Traits<FMT>::overflow_above ? 1u : 0u;
                 }
-                lo[r] = satcast_pk4<FMT>(v[r][0], v[r][1], v[r][2], v[r][3]);
-                hi[r] = satcast_pk4<FMT>(v[r][4], v[r][5], v[r][6], v[r][7]);
+                const uint2 codes = satcast_pk8<FMT>(v[r]);
+                lo[r] = codes.x;
+                hi[r] = codes.y;
                 if (COUNT) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
@@ -458,7 +459,7 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
                         n_flush += (code == 0u && ((nonzero >> i) & 1u)) ? 1u : 0u;
                     }
                 }
-                *reinterpret_cast<uint2 *>(dst + off) = make_uint2(lo[r], hi[r]);
+                *reinterpret_cast<uint2 *>(dst + off) = codes;
             }
         }
         if constexpr (TRANSPOSED) {
@@ -799,7 +800,7 @@ __global__ void __launch_bounds__(kSmallThreads) quantize_small_kernel(const Cas
     LoadBf16::widen(make_uint4(mine[0], mine[1], mine[2], mine[3]), v);
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = __fmul_rn(v[k], sigma);
-    *reinterpret_cast<uint2 *>(it.dst + (size_t)own * 8) = make_uint2(satcast_pk4<FMT>(v[0], v[1], v[2], v[3]), satcast_pk4<FMT>(v[4], v[5], v[6], v[7]));
+    *reinterpret_cast<uint2 *>(it.dst + (size_t)own * 8) = satcast_pk8<FMT>(v);
 }
 
 // ------------------------------------------------------------------ range and cast of tensors that fit the registers
@@ -920,10 +921,11 @@ __global__ void __launch_bounds__(kHeldThreads, 2) quantize_held_kernel(const He
             }
 #pragma unroll
             for (int k = 0; k < 8; ++k) v[k] = __fmul_rn(v[k], sigma);
-            code[r][0] = satcast_pk4<FMT>(v[0], v[1], v[2], v[3]);
-            code[r][1] = satcast_pk4<FMT>(v[4], v[5], v[6], v[7]);
+            const uint2 codes = satcast_pk8<FMT>(v);
+            code[r][0] = codes.x;
+            code[r][1] = codes.y;
             if (inside)
-                *reinterpret_cast<uint2 *>(it.dst + (size_t)(row0 + r4 + r) * (size_t)it.cols + (size_t)(col0 + c8)) = make_uint2(code[r][0], code[r][1]);
+                *reinterpret_cast<uint2 *>(it.dst + (size_t)(row0 + r4 + r) * (size_t)it.cols + (size_t)(col0 + c8)) = codes;
         }
         if (TRANSPOSED) {
             // (two turning buffers by turns: one barrier per tile)
@@ -1354,8 +1356,7 @@ rowscale_cast_kernel(const uint16_t *__restrict__ w, const float *__restrict__ r
         const float f = rs[i / (size_t)cols];
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = __fmul_rn(__fmul_rn(v[k], f), sigma);
-        *reinterpret_cast<uint2 *>(dst + i) = make_uint2(satcast_pk4<kE4M3>(v[0], v[1], v[2], v[3]),
-                                                         satcast_pk4<kE4M3>(v[4], v[5], v[6], v[7]));
+        *reinterpret_cast<uint2 *>(dst + i) = satcast_pk8<kE4M3>(v);
     }
 }
 void launch_rowscale_quantize(const void *w, const float *row_scale, int64_t rows, int64_t cols, uint32_t *slots,
