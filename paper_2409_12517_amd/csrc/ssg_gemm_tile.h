@@ -829,8 +829,15 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                                 du[k] = __fmul_rn(du[k], q_su);
                                 dg[k] = __fmul_rn(dg[k], q_sg);
                             }
-                            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C) + o) = satcast_pk8<kE5M2>(du);
-                            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C2) + o) = satcast_pk8<kE5M2>(dg);
+                            // (empty statements: what is rounded to bf16 is so before, what becomes codes does so in between)
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(du[k]), "+v"(dg[k]));
+                            saturating_conversions();
+                            uint2 cu = satcast_pk8<kE5M2>(du), cg = satcast_pk8<kE5M2>(dg);
+                            asm volatile("" : "+v"(cu.x), "+v"(cu.y), "+v"(cg.x), "+v"(cg.y));
+                            saturating_conversions<0>();
+                            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C) + o) = cu;
+                            *reinterpret_cast<uint2 *>(reinterpret_cast<uint8_t *>(p.C2) + o) = cg;
                             if (p.keep_u) {
                                 *reinterpret_cast<uint4 *>(p.keep_u + o) = qu;
                                 *reinterpret_cast<uint4 *>(p.keep_g + o) = qg;
@@ -872,6 +879,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         constexpr int kRowBytes = kCodes ? WN / 2 + 8 : 2 * WN + 16;
         uint8_t *patch = smem + w * (32 * kRowBytes);
         const size_t base = (size_t)wrow0 * (size_t)p.N + (size_t)wcol0;
+        if (kCodes) saturating_conversions();
         float hmaxf[NBU][4];                                     // fmaxf drops NaN
 #pragma unroll
         for (int nb = 0; nb < NBU; ++nb)

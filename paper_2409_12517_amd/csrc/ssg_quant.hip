@@ -341,6 +341,7 @@ __device__ __forceinline__ void cast_block(const CastItem<Loader> &it, const int
     const Loader ld = it.ld;
     const int64_t rows = it.rows, cols = it.cols;
     if ((int64_t)bx * kTile >= cols || (int64_t)by * ROWS >= rows) return;
+    saturating_conversions();
     const float *__restrict__ col_scale = it.col_scale;
     const float *__restrict__ amax = it.amax;
     const int amax_slots = it.amax_slots;
@@ -796,6 +797,7 @@ __global__ void __launch_bounds__(kSmallThreads) quantize_small_kernel(const Cas
         if (it.record) *it.record = bits;
     }
     if (own >= n16) return;
+    saturating_conversions();
     float v[8];
     LoadBf16::widen(make_uint4(mine[0], mine[1], mine[2], mine[3]), v);
 #pragma unroll
@@ -835,6 +837,7 @@ __global__ void __launch_bounds__(kHeldThreads, 2) quantize_held_kernel(const He
     const int b = (int)blockIdx.x, which = (b >= batch.item[1].first) + (b >= batch.item[2].first);
     const HeldItem &it = batch.item[which];
     const int own = b - it.first;
+    saturating_conversions();
     zero_words(batch.zero, blockIdx.x * kHeldThreads + threadIdx.x, gridDim.x * kHeldThreads);
     // a thread has eight columns of four rows of every tile, in PER pieces of 16 bytes
     constexpr int PER = F32 ? 8 : 4;
@@ -1350,6 +1353,7 @@ rowscale_cast_kernel(const uint16_t *__restrict__ w, const float *__restrict__ r
     const float sigma = scale_from_amax(amax, Fp8Traits<kE4M3>::fmax, pow2);
     if (blockIdx.x == 0 && threadIdx.x == 0) { *scale_out = sigma; if (amax_out) *amax_out = amax; }
     const size_t n = (size_t)rows * (size_t)cols, stride = (size_t)gridDim.x * 256 * 8;
+    saturating_conversions();
     for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8; i < n; i += stride) {
         float v[8];
         LoadBf16{w}.load8(i, v);
