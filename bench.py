@@ -43,10 +43,10 @@ TAG_ROLES = {0: "y = h^ w3~^T", 2: "U, G + SwiGLU + channel maxima",
              10: "dX, second product + scratch"}
 # elementwise passes: tag -> (kernel family as rocprofv3 prints it, role)
 ELEMENTWISE = {40: ("amax_bf16_kernel", "per-tensor range of x, W1, W2, dY"),
-               41: ("cast_kernel<LoadBf16, *, false, ...>", "per-tensor cast of x, W1, W2, dY, dU, dG"),
+               41: ("cast_kernel<LoadBf16, *, false, ...>", "per-tensor cast of x, W1, W2, dU, dG (dY: range and cast, quantize_held_kernel)"),
                42: ("cast_kernel<LoadSwiglu, 0, true, ...>", "h^ = cast(s_i h) from bf16 U, G"),
                43: ("cast_kernel<LoadBf16, 0, true, ...>", "w3~ = Q(s^-1 w3)"),
-               47: ("cast_h_w3_kernel", "h^ = cast(s_i h) from bf16 U, G and w3~ = Q(s^-1 w3), one launch"),
+               47: ("cast_h_w3_meet_kernel", "channel factors, h^ = cast(s_i h) from bf16 U, G and w3~ = Q(s^-1 w3), one launch"),
                44: ("col_amax_bf16_kernel", "per-channel range of W3"),
                45: ("fill / channel_factors kernels", "bookkeeping")}
 PEAK_HBM_GBS = 8000.0             # MI355X HBM3E (published: 8 TB/s)
@@ -243,7 +243,7 @@ def summarize_profiles(src: str) -> int:
               "1 = E5M2; part 3 = a sum of two products in one launch; layout 0 = both operands K-contiguous, 1 = B K-major, 2 = A and B "
               "K-major.  gemm_group_dh_dw3_kernel = dH then the first part of dW3 in one grid; gemm_group_dx_dw_kernel = dX, then dW1, dW2 and "
               "the rest of dW3 in one grid; gemm_swiglu_col_range_kernel = the gate/up GEMM with the per-channel range pass over W3 "
-              "as extra workgroups of the same grid; cast_h_w3_kernel = the casts of h and w3 in one launch.")
+              "as extra workgroups of the same grid; cast_h_w3_meet_kernel = the channel factors and the casts of h and w3 in one launch.")
     # 1. per-kernel durations
     stats = find("stats", "kernel_stats.csv")
     if stats:

@@ -190,7 +190,7 @@ void launch_gemm_rest(const GemmArgs &a, int rows, hipStream_t st);
 void gemm_skinny_extent(const GemmArgs &a, int form, int *rows, int *cols, int *steps);
 bool launch_gemm_bwd(const GemmArgs &a, hipStream_t st);       // the backward forms (called by launch_gemm)
 constexpr int kComputeUnits = 256;      // of an MI355X; the estimates of a launch's time are in its rounds
-// Tile of a launch that runs these GEMMs in one grid: 32 x 32 blocks per wave and direction, 4 (256 x 256 tiles) or 2 (128 x 128)
+// Tile of a launch that runs these GEMMs in one grid: 4 (256 x 256) or 2 (128 x 128), half the 16 x 16 blocks per wave and direction
 // (of the last one: the share `last` of its tiles)
 int gemm_wave_blocks(const GemmArgs *const *list, int n, double last = 1.0);
 double gemm_tile_cost(const GemmArgs &a, int WB);               // estimated microseconds of one tile
