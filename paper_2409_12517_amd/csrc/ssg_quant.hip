@@ -809,7 +809,7 @@ __global__ void __launch_bounds__(kSmallThreads) quantize_small_kernel(const Cas
 // Up to one workgroup per compute unit, each with up to TILES tiles of 128 x 128 in registers (100 MB on the chip) while the
 // workgroups exchange their maxima (ssg_meet.h): the tensor is read once, in one launch.  Bound by HBM, and for small tensors by
 // the latency of the exchange, about 2 us.  ssg_quantize with the transposed copy, in three launches before (range, scale, cast)
-// and this way: 256 x 512 13.9 and 8.0 us, 1040 x 2736 13.6 and 9.7, 4096 x 4096 23.3 and 21.2, 4096 x 11008 50.4 and 41.7; fp32
+// and this way: 256 x 512 13.9 and 8.0 us, 1040 x 2736 13.6 and 9.7, 4096 x 4096 23.3 and 21.2, 4096 x 11008 50.4 and 41.7 (35.2 since the encode takes fewer instructions); fp32
 // 2048 x 2048 15.4 and 11.0, 4096 x 5504 46.8 and 36.1.  In calls that quantize several tensors: 1040, 1024, 2736 115 and 111 us a step, the inference
 // form at 272 rows, 4096, 11008 82.6 and 80.3.  Tensors of up to 2^18 elements stay with quantize_small_kernel, which has no exchange (a
 // decode step of 16 rows 38.2 us, 39.0 this way).
