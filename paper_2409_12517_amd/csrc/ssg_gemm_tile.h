@@ -680,8 +680,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                             f32x4 v;
 #pragma unroll
                             for (int k = 0; k < 4; ++k) v[k] = t[r][nb][k] * dq.post;
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), mine, tid * 16,
-                                                                   (((row >> 5) * 2 + r) * RB + nb) * (kThreads * 16), kThrough);
+                            // (No scalar offset: with one, neither the compiler nor this chip waits for the store to have read its
+                            // registers, and the next vector instruction can put another piece's numbers into them, 16 lanes of one
+                            // register at a time.)
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), mine,
+                                                                   tid * 16 + (((row >> 5) * 2 + r) * RB + nb) * (kThreads * 16), 0, kThrough);
                         }
                 });
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's part is where the others see it

@@ -50,6 +50,23 @@ def test_dx_in_halves(T, d, f, tile, mode):
         assert torch.equal(first.view(torch.int32), blk.dx.view(torch.int32))
 
 
+# more halves than an XCD has compute units for, so that some share one and leave their results while it stores others
+@pytest.mark.parametrize("T,d,f", [(2688, 608, 2272), (640, 3456, 12800), (896, 3072, 10240)])
+def test_dx_in_halves_with_compute_units_shared(T, d, f):
+    blk = tp._training(T, d, f)
+    blk.desc = ssg.make_desc(T, d, f, y_dtype=ssg.SSG_F32)
+    assert ssg.ssg_mlp_gemm_plan(blk.desc, ssg.SSG_PLAN_BWD_SECOND).tile == 128
+    assert ssg.ssg_mlp_gemm_route(blk.desc, ssg.SSG_PLAN_BWD_SECOND).dx_form == ssg.SSG_DX_HALVES
+    blk.fwd()
+    blk.bwd()
+    tp._check_backward(blk, False)
+    first = blk.dx.clone()
+    for _ in range(40):
+        blk.dx.fill_(float("nan"))
+        blk.bwd()
+        assert torch.equal(first.view(torch.int32), blk.dx.view(torch.int32))
+
+
 def test_dx_in_halves_in_bf16_and_on_its_own(tmp_path):
     """bf16 dX from the same sum; and launched without the weight gradients (the switch that takes the groups apart), the
     same bits."""
