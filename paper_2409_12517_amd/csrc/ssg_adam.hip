@@ -222,16 +222,16 @@ __global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p
     const uint32_t *old = p.scalars + 8 * (p.parity ^ 1);
     const float inv_sm = __fdiv_rn(1.0f, __uint_as_float(old[kAdamScaleM])), inv_sv = __fdiv_rn(1.0f, __uint_as_float(old[kAdamScaleV]));
     const int own = (int)blockIdx.x, blocks = (int)gridDim.x, t = threadIdx.x;
-    // the j-th group of this thread in workgroup k's share; one beyond the end is the tensor's first, for reading
+    // the j-th group of this thread in workgroup k's share.  One beyond the end of the tensor counts for nothing and nothing is read
+    // for it: whatever other group stood in for it would belong to a workgroup that may have stored its new codes by then
     auto group_at = [&](int k, int j) { return ((size_t)j * blocks + k) * kChunk + 4 * t; };
     auto share = [&](int k) { return (int)(((size_t)p.n + kChunk - 1) / kChunk - k + blocks - 1) / blocks; };      // groups of it
     struct Group { float g[4]; uint32_t mq, vq; };
     auto load = [&](size_t i) {
         Group x;
-        const size_t at = i < (size_t)p.n ? i : 0;
-        load_grad4<GRAD_BF16>(p.grad, at, x.g);
-        x.mq = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.m_q + at));
-        x.vq = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.v_q + at));
+        load_grad4<GRAD_BF16>(p.grad, i, x.g);
+        x.mq = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.m_q + i));
+        x.vq = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.v_q + i));
         return x;
     };
     auto moments = [&](const Group &x, float (&m)[4], float (&v)[4]) {
@@ -254,11 +254,11 @@ __global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p
     uint32_t held_m[HELD], held_v[HELD];
 #pragma unroll
     for (int j = 0; j < HELD; ++j) {
-        if (j < mine) {
-            const size_t i = group_at(own, j), at = i < (size_t)p.n ? i : 0;
-            held_g[j] = load_packed4<GRAD_BF16>(p.grad, at);
-            held_m[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.m_q + at));
-            held_v[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.v_q + at));
+        const size_t i = group_at(own, j);
+        if (j < mine && i < (size_t)p.n) {
+            held_g[j] = load_packed4<GRAD_BF16>(p.grad, i);
+            held_m[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.m_q + i));
+            held_v[j] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p.v_q + i));
         } else {
             held_g[j] = Packed<GRAD_BF16>{};
             held_m[j] = held_v[j] = 0u;
@@ -270,7 +270,7 @@ __global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p
         x.mq = held_m[j]; x.vq = held_v[j];
         return x;
     };
-    // (groups that are not there: zero gradient and moments)
+    // (groups that are not there: zero gradient and moments, no new ones)
 #pragma unroll
     for (int j = 0; j < HELD; ++j)
         if (j < mine) see(group_of(j), mmax, vmax);
@@ -280,7 +280,7 @@ __global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p
 #pragma unroll
         for (int c = 0; c < kHeldGroups; ++c) {
             const size_t i = group_at(own, kHeldGroups * batch + c);
-            w[c] = __builtin_nontemporal_load(reinterpret_cast<const ssg_f32x4 *>(p.w + (i < (size_t)p.n ? i : 0)));
+            w[c] = i < (size_t)p.n ? __builtin_nontemporal_load(reinterpret_cast<const ssg_f32x4 *>(p.w + i)) : ssg_f32x4{};
         }
     };
     load_w(0);
@@ -297,7 +297,8 @@ __global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p
     __syncthreads();
     auto share_max = [&](int k, bool second) {
         uint32_t mm = 0, vm = 0;
-        for (int j = 0; j < share(k); ++j) see(load(group_at(k, j)), mm, vm);
+        for (int j = 0; j < share(k); ++j)
+            if (group_at(k, j) < (size_t)p.n) see(load(group_at(k, j)), mm, vm);
         return second ? vm : mm;
     };
     const float amax_m = __uint_as_float(meet_max<kHeldThreads>(meeting, 0, blocks, own, words, [&](int k) { return share_max(k, false); }));
