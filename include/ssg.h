@@ -332,7 +332,8 @@ ssg_status ssg_infer_view(const ssg_mlp_desc *desc, const void *prepared, const 
  * The paper fixes the two formats; the rest is this library's reading.
  *
  * state (device, caller-owned, ssg_adam_state_bytes(n) bytes, 256-byte aligned): scale and range
- * words kept twice by step parity, the range slots of the reduction, then m_q[n] and v_q[n].
+ * words kept twice by step parity, the words in which the ranges are formed (also by parity, cleared by the
+ * step before), then m_q[n] and v_q[n].
  * ssg_adam_init writes zero moments (codes 0, scales 1).  ssg_adam_step takes step = 1, 2, 3, ...
  * in order (the parity of `step` selects which scalar set is read and which is written).
  * grad: [n] device, grad_dtype SSG_F32 or SSG_BF16.  w: [n] fp32 device, updated in place.

@@ -17,7 +17,8 @@
 // weights can be compared bit for bit with a binary32 reference.
 //
 // State scalars are kept twice, by step parity, so that pass 2 can read the old scales and
-// range slots while workgroup 0 writes the new ones and clears the slots of the next step.
+// range slots while workgroup 0 writes the new ones and clears the slots of the next step, and the words between them in which the
+// workgroups of the one launch exchange their ranges.
 #include <type_traits>
 
 #include "ssg_device.h"
@@ -41,6 +42,7 @@ struct AdamParams {
 // word offsets in the scalar block
 constexpr int kAdamScaleM = 0, kAdamScaleV = 1, kAdamAmaxM = 2, kAdamAmaxV = 3;   // + 8 * parity
 constexpr int kAdamSlotsM = 64;                                                  // + parity * 2 * kAmaxSlotWords
+static_assert(kAmaxSlotStride == 32 && kMeetOwnedLines <= kAmaxSlots, "the words of the exchange lie between the slots, a run beside each moment's");
 constexpr int kAdamThreads = 256;
 
 typedef float ssg_f32x4 __attribute__((ext_vector_type(4)));
@@ -99,17 +101,16 @@ __device__ __forceinline__ void finish4(const AdamParams &p, size_t i, const flo
     *reinterpret_cast<uint32_t *>(p.v_q + i) = satcast_pk4<kE5M2>(__fmul_rn(v[0], sv), __fmul_rn(v[1], sv), __fmul_rn(v[2], sv), __fmul_rn(v[3], sv));
 }
 
-// what one workgroup leaves behind for the call and for the next step: the scales and ranges, the other parity's slots cleared (they
-// were last read by the previous step's update pass)
+// what one workgroup leaves behind for the call and for the next step: the scales and ranges, the other parity's slots and words cleared
+// (they were last read by the previous step)
 __device__ __forceinline__ void leave_scalars(const AdamParams &p, float sm, float sv, float amax_m, float amax_v) {
     uint32_t *cur = p.scalars + 8 * p.parity;
     if (threadIdx.x == 0) {
         cur[kAdamScaleM] = __float_as_uint(sm); cur[kAdamScaleV] = __float_as_uint(sv);
         cur[kAdamAmaxM] = __float_as_uint(amax_m); cur[kAdamAmaxV] = __float_as_uint(amax_v);
     }
-    uint32_t *next = p.scalars + kAdamSlotsM + (size_t)(p.parity ^ 1) * 2 * kAmaxSlotWords;
-    if (threadIdx.x < 2 * kAmaxSlots)
-        next[(threadIdx.x >> 6) * kAmaxSlotWords + (threadIdx.x & 63) * kAmaxSlotStride] = 0u;
+    uint4 *next = reinterpret_cast<uint4 *>(p.scalars + kAdamSlotsM + (size_t)(p.parity ^ 1) * 2 * kAmaxSlotWords);
+    for (unsigned i = threadIdx.x; i < 2 * kAmaxSlotWords / 4; i += blockDim.x) next[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // exponential moving averages of the gradient and of its square
@@ -216,7 +217,7 @@ __global__ void __launch_bounds__(kAdamThreads) adam_update_kernel(AdamParams p)
 // that fill it: 8 M 38.4 and 38.5 (bf16 gradient 35.1 and 36.1), 16 M bf16 62.4 and 61.0.
 constexpr int kHeldThreads = 512, kHeldGroups = 4, kHeldBatches = 2;
 template <bool GRAD_BF16>
-__global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p, Meeting meeting) {
+__global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p, MeetOwned meeting) {
     constexpr int HELD = kHeldGroups * kHeldBatches, kChunk = 4 * kHeldThreads;
     __shared__ uint32_t words[kMeetBlocks + 8];
     const uint32_t *old = p.scalars + 8 * (p.parity ^ 1);
@@ -292,7 +293,7 @@ __global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p
         uint32_t r = 0;
 #pragma unroll
         for (int k = 0; k < kHeldThreads / 64; ++k) r = r > words[8 * t + k] ? r : words[8 * t + k];
-        meet_leave(meeting, t * kMeetBlocks + own, r);
+        meeting.leave(t * kMeetBlocks + own, r);
     }
     __syncthreads();
     auto share_max = [&](int k, bool second) {
@@ -352,9 +353,9 @@ void launch_adam_step(const AdamArgs &a, hipStream_t st) {
     const double update_bytes = gbytes + 2.0 + 4.0 + 4.0 + (a.w_bf16 ? 2.0 : 0.0) + 2.0;
     constexpr size_t kHeldChunk = 4 * kHeldThreads;
     const size_t chunks = ((size_t)a.n + kHeldChunk - 1) / kHeldChunk;
-    Meeting meeting;
-    if (chunks <= (size_t)kMeetBlocks * kHeldGroups * kHeldBatches && meet_ticket(st, &meeting)) {
-        if (a.polls >= 0) meeting.polls = a.polls;
+    if (chunks <= (size_t)kMeetBlocks * kHeldGroups * kHeldBatches && !launch_recorded(st)) {
+        const MeetOwned meeting{p.scalars + kAdamSlotsM + (size_t)p.parity * 2 * kAmaxSlotWords, kAmaxSlots, (uint32_t)a.step,
+                                a.polls >= 0 ? a.polls : kMeetPolls};
         const dim3 grid((unsigned)(chunks < kMeetBlocks ? chunks : kMeetBlocks));
         profile_before(33, st, update_bytes * (double)a.n);
         if (a.grad_bf16) hipLaunchKernelGGL(adam_held_kernel<true>, grid, dim3(kHeldThreads), 0, st, p, meeting);

@@ -6,16 +6,23 @@
 //
 // Nobody depends on another workgroup being on the chip: one that has looked `polls` times in vain forms the maxima that are
 // missing from the tensor itself (and leaves them for the others), so every workgroup ends whatever the rest do -- when two
-// such launches share the chip, when other work holds the compute units, when the words are overwritten.
+// such launches share the chip, when other work holds the compute units.
 //
-// A word belongs to a launch by its ticket, a number that no other launch of the process has: stale words, and those of a
-// launch that happens to use the same row, are told from this launch's by it, and nothing is cleared.  (64-bit accesses are
-// whole; a word is a pair of them, each with half of the ticket and the maximum, which have to agree.)  A graph launches the same ticket
-// every time, so calls under capture take the launches without an exchange.
+// Two places for the words:
+//   MeetRing   rows of words that all launches of a translation unit share, for launches that leave their source as it is.  A word belongs
+//     to a launch by its ticket, a number that no other launch of the process has: what an earlier launch left is told from this
+//     launch's by it, and nothing is cleared.  Tickets are dealt where a call is enqueued, so two launches whose tickets are
+//     kMeetRows apart can be under way at once, however few there are, and write over each other's words: that costs them the wait and
+//     another read of the tensor, no more, since the source still holds what the word held.
+//   MeetOwned  words that nothing else writes while the launch runs, for launches that overwrite their shares.  They are
+//     part of memory whose calls the caller orders, zeroed before the launch, and tagged by a number that says which call wrote them.
 //
-// A workgroup may write over its share of the tensor once it has all the maxima: its own word is where the others see it before
-// it looks for theirs, and one that forms a missing maximum looks for the word again after its last read of the share.  What it formed counts only if
-// the word was not there then, and so nothing of the share was written yet.
+// Where a workgroup overwrites its share once it has all the maxima: its own word is where the others see it before it looks for
+// theirs, and stays; one that forms a missing maximum looks for the word again after its last read of the share.  What it formed counts only
+// if the word is not there then: then nothing of the share was written yet.  (With words that another launch may write over
+// this does not hold: the word may be missing because of that.)
+//
+// A graph launches the same ticket every time, so calls under capture take the launches without an exchange.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -24,44 +31,66 @@
 
 namespace ssg {
 
-constexpr int kMeetRows = 64;                               // launches under way at once before two share a row of words
+constexpr int kMeetRows = 64;                               // launches enqueued in a row before two share a row of words
 constexpr int kMeetBlocks = 256;                            // workgroups that exchange a maximum, each maybe two
 constexpr int kMeetPolls = 400;                             // each takes about a microsecond
-
-// what one launch needs to know
-struct Meeting {
-    uint64_t ticket;
-    int polls;
-};
 
 // the words of a translation unit's launches
 static __device__ uint64_t g_meet[kMeetRows][2 * kMeetBlocks][2];
 
-__device__ __forceinline__ void meet_leave(const Meeting &m, int word, uint32_t v) {
-    uint64_t *w = g_meet[m.ticket % kMeetRows][word];
-    __hip_atomic_store(w, (m.ticket << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(w + 1, (m.ticket & ~(uint64_t)0xffffffffu) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
-__device__ __forceinline__ bool meet_look(const Meeting &m, int word, uint32_t &v) {
-    uint64_t *w = g_meet[m.ticket % kMeetRows][word];
-    const uint64_t a = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t b = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v = (uint32_t)a;
-    return a == ((m.ticket << 32) | v) && b == ((m.ticket & ~(uint64_t)0xffffffffu) | v);
-}
+// (64-bit accesses are whole; a word is a pair of them, each with half of the ticket and the maximum, which have to agree)
+struct MeetRing {
+    uint64_t ticket;
+    int polls;
+    __device__ __forceinline__ void leave(int word, uint32_t v) const {
+        uint64_t *w = g_meet[ticket % kMeetRows][word];
+        __hip_atomic_store(w, (ticket << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(w + 1, (ticket & ~(uint64_t)0xffffffffu) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    __device__ __forceinline__ bool look(int word, uint32_t &v) const {
+        uint64_t *w = g_meet[ticket % kMeetRows][word];
+        const uint64_t a = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t b = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v = (uint32_t)a;
+        return a == ((ticket << 32) | v) && b == ((ticket & ~(uint64_t)0xffffffffu) | v);
+    }
+};
+
+// 15 words in the upper 120 bytes of each 128-byte line from `base` on, 2 * kMeetBlocks of them in two runs `second` lines apart.
+struct MeetOwned {
+    uint32_t *base;
+    int second;
+    uint32_t tag;                                            // not zero
+    int polls;
+    __device__ __forceinline__ uint64_t *at(int word) const {
+        const int run = word / kMeetBlocks, i = word % kMeetBlocks;
+        return reinterpret_cast<uint64_t *>(base + (run * second + i / 15) * 32) + 1 + i % 15;
+    }
+    __device__ __forceinline__ void leave(int word, uint32_t v) const {
+        // (with the old value returned: the word is in its place before anything after it is stored)
+        const uint64_t old = __hip_atomic_exchange(at(word), (uint64_t)tag << 32 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("; %0" :: "v"(old) : "memory");
+    }
+    __device__ __forceinline__ bool look(int word, uint32_t &v) const {
+        const uint64_t a = __hip_atomic_load(at(word), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v = (uint32_t)a;
+        return (uint32_t)(a >> 32) == tag;
+    }
+};
+constexpr int kMeetOwnedLines = (kMeetBlocks + 14) / 15;    // of a run
 
 // The maximum over words first .. first + count - 1 (count <= kMeetBlocks <= the workgroup's threads), for all threads.  `own`:
 // this workgroup's word among them; share_max(k): this thread's part of the k-th one's maximum, formed from the tensor.
 // lds: kMeetBlocks + 8 words.  Called by all threads of the workgroup.
-template <int THREADS, class ShareMax>
-__device__ __forceinline__ uint32_t meet_max(const Meeting &m, int first, int count, int own, uint32_t *lds, ShareMax &&share_max) {
+template <int THREADS, class Place, class ShareMax>
+__device__ __forceinline__ uint32_t meet_max(const Place &m, int first, int count, int own, uint32_t *lds, ShareMax &&share_max) {
     const int t = threadIdx.x;
     constexpr uint32_t kMissing = 0xffffffffu;               // no maximum of magnitudes: above every number and infinity
     uint32_t v = 0u;
     bool have = t >= count;
     for (int n = 0; n < m.polls && !have; ++n) {
-        have = meet_look(m, first + t, v);
+        have = m.look(first + t, v);
         if (!have) __builtin_amdgcn_s_sleep(2);
     }
     if (!have) v = kMissing;
@@ -85,7 +114,7 @@ __device__ __forceinline__ uint32_t meet_max(const Meeting &m, int first, int co
         if (lds[k] != kMissing) continue;
         auto look_again = [&]() {                            // by now it may have come
             uint32_t x = kMissing;
-            if (t == 0 && !meet_look(m, first + k, x)) x = kMissing;
+            if (t == 0 && !m.look(first + k, x)) x = kMissing;
             return over_workgroup(t == 0 ? x : 0u);
         };
         uint32_t late = look_again();
@@ -94,7 +123,7 @@ __device__ __forceinline__ uint32_t meet_max(const Meeting &m, int first, int co
             late = look_again();
             if (late == kMissing) {
                 late = formed;
-                if (t == 0) meet_leave(m, first + k, late);
+                if (t == 0) m.leave(first + k, late);
             }
         }
         all = all > late ? all : late;
@@ -102,15 +131,19 @@ __device__ __forceinline__ uint32_t meet_max(const Meeting &m, int first, int co
     return all;
 }
 
-// Host: a ticket for a launch on `st`, or false where the launch could be replayed.
-inline bool meet_ticket(hipStream_t st, Meeting *m) {
-    static std::atomic<uint64_t> next{1};
+// Host: whether a launch on `st` would be recorded and could be replayed.
+inline bool launch_recorded(hipStream_t st) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &status) != hipSuccess) {
         (void)hipGetLastError();                             // (the null stream while another one is captured)
-        return false;
+        return true;
     }
-    if (status != hipStreamCaptureStatusNone) return false;
+    return status != hipStreamCaptureStatusNone;
+}
+// A ticket for a launch on `st`, or false where the launch could be replayed.
+inline bool meet_ticket(hipStream_t st, MeetRing *m) {
+    static std::atomic<uint64_t> next{1};
+    if (launch_recorded(st)) return false;
     m->ticket = next.fetch_add(1, std::memory_order_relaxed);
     m->polls = kMeetPolls;
     return true;

@@ -589,7 +589,7 @@ cast_h_w3_factors_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> 
 template <bool COUNT, bool SMOOTH, int ROWS>
 __global__ void __launch_bounds__(256)
 cast_h_w3_meet_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3, const int pow2, const InlineFactors fac,
-                      const Meeting meeting, const ScalingUpdate update) {
+                      const MeetRing meeting, const ScalingUpdate update) {
     __shared__ uint32_t words[kMeetBlocks + 8];
     const int t = threadIdx.x, groups = (int)((fac.f + kTile - 1) / kTile), mine = (int)blockIdx.x;
     // of channel kTile * k + t: the range of s^-1 * w3, and of h
@@ -608,8 +608,8 @@ cast_h_w3_meet_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3,
         if ((t & 63) == 0) { words[t >> 6] = a; words[4 + (t >> 6)] = b; }
         __syncthreads();
         if (t == 0) {
-            meet_leave(meeting, mine, words[0] > words[1] ? words[0] : words[1]);
-            if (!SMOOTH) meet_leave(meeting, groups + mine, words[4] > words[5] ? words[4] : words[5]);
+            meeting.leave(mine, words[0] > words[1] ? words[0] : words[1]);
+            if (!SMOOTH) meeting.leave(groups + mine, words[4] > words[5] ? words[4] : words[5]);
         }
         __syncthreads();
     }
@@ -827,7 +827,7 @@ struct HeldItem {
 struct HeldBatch {
     HeldItem item[3];
     int pow2;
-    Meeting meeting;
+    MeetRing meeting;
     ZeroWords zero;
 };
 template <bool F32, int FMT, bool TRANSPOSED, int TILES>
@@ -887,7 +887,7 @@ __global__ void __launch_bounds__(kHeldThreads, 2) quantize_held_kernel(const He
     if (threadIdx.x == 0) {
         uint32_t m = mine;
         for (int w = 1; w < kHeldThreads / 64; ++w) m = m > words[w] ? m : words[w];
-        meet_leave(batch.meeting, b, m);
+        batch.meeting.leave(b, m);
     }
     const uint32_t bits = meet_max<kHeldThreads>(batch.meeting, it.first, it.blocks, own, words, [&](int k) {
         Seen s;
@@ -1056,7 +1056,7 @@ bool cast_h_w3_ok(const CastArgs &h, const CastArgs &w3) {
 
 template <bool COUNT, int ROWS>
 static void launch_h_w3_factors(dim3 grid, bool smooth, const CastItem<LoadSwiglu> &h, const CastItem<LoadBf16> &w3, int pow2,
-                                const InlineFactors &in, const Meeting *meeting, const ScalingUpdate &update, hipStream_t st) {
+                                const InlineFactors &in, const MeetRing *meeting, const ScalingUpdate &update, hipStream_t st) {
     if (!meeting) hipLaunchKernelGGL((cast_h_w3_factors_kernel<COUNT, ROWS>), grid, dim3(256), 0, st, h, w3, pow2, in);
     else if (smooth) hipLaunchKernelGGL((cast_h_w3_meet_kernel<COUNT, true, ROWS>), grid, dim3(256), 0, st, h, w3, pow2, in, *meeting, update);
     else hipLaunchKernelGGL((cast_h_w3_meet_kernel<COUNT, false, ROWS>), grid, dim3(256), 0, st, h, w3, pow2, in, *meeting, update);
@@ -1067,7 +1067,7 @@ void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, const ChannelFactor
     // the line between the two forms that need no launch of their own for the factors: 8 f bytes read by every workgroup of the w3 cast
     // against the exchange
     const bool few = pair && fac.smooth && fac.update.count == 0 && fac.f <= 1024;
-    Meeting meeting;
+    MeetRing meeting;
     const bool meet = pair && !few && (fac.smooth ? 1 : 2) * ((fac.f + kTile - 1) / kTile) <= kMeetBlocks && meet_ticket(st, &meeting);
     if (!few && !meet) launch_channel_factors(fac, st);
     if (!pair) {                            // not the pair this launch is built for: one after the other
@@ -1086,7 +1086,7 @@ void launch_cast_h_w3(const CastArgs &h, const CastArgs &w3, const ChannelFactor
         wi.amax = nullptr;
         const InlineFactors in{fac.h_camax, fac.w3_camax, fac.f, fac.s, fac.sinv, reinterpret_cast<float *>(fac.amax_w3s_bits),
                                reinterpret_cast<float *>(fac.hmax_bits), fac.h_scale_given};
-        const Meeting *m = meet ? &meeting : nullptr;
+        const MeetRing *m = meet ? &meeting : nullptr;
         with_tile_rows(edge, [&](auto r) {
             if (h.counters) launch_h_w3_factors<true, decltype(r)::value>(grid, fac.smooth, hi, wi, w3.pow2, in, m, fac.update, st);
             else launch_h_w3_factors<false, decltype(r)::value>(grid, fac.smooth, hi, wi, w3.pow2, in, m, fac.update, st);

@@ -1,5 +1,6 @@
-"""The exchange of maxima between the workgroups of one launch (csrc/ssg_meet.h) where a workgroup overwrites its share of the tensor
-afterwards, as the Adam step does: a model of it, run through every interleaving at small sizes on the CPU.
+"""The exchange of maxima between the workgroups of one launch (csrc/ssg_meet.h), a model of it, run through every interleaving at small
+sizes on the CPU: where a workgroup overwrites its share of the tensor afterwards, as the Adam step does, and where the source stays
+and another launch may write over the words.
 
 A share is two cells, read and written one at a time.  A workgroup reads its share, leaves its maximum in its word, and looks at the
 words until it has all maxima; at any time it may give up on one that is missing, form it from the share's cells and look again:
@@ -10,9 +11,10 @@ import pytest
 CELLS = 2
 
 
-def explore(count, reads):
+def explore(count, reads, in_place=True, lost_words=False):
     """Every outcome of `count` workgroups: the set of the maxima they ended with.  reads(k): the cells (share, index) that
-    workgroup k reads for its own maximum, later ones for another's."""
+    workgroup k reads for its own maximum, later ones for another's.  in_place: shares are overwritten; lost_words: another launch
+    writes over words at any time."""
     true = {(k, c): 1 + CELLS * k + c for k in range(count) for c in range(CELLS)}
     written = 1000                                            # a new code under the old scale: larger than any true value
     # a workgroup: (stage, position in the stage, running maximum, which share it forms, maxima it has, its result)
@@ -45,10 +47,13 @@ def explore(count, reads):
                 for i in missing:
                     if words[i] is not None:
                         yield to(("look", 0, 0, k, have[:i] + (words[i],) + have[i + 1:], None))
-                    elif i != k:
+                    else:
                         yield to(("form", 0, 0, i, have, None))
             elif stage == "write" and at < CELLS:
-                yield to((stage, at + 1, 0, k, have, result), words, new | {(k, at)})
+                yield to((stage, at + 1, 0, k, have, result), words, new | {(k, at)} if in_place else new)
+        for i in range(count):
+            if lost_words and words[i] is not None and any(g[0] != "write" for g in groups):
+                yield groups, words[:i] + (None,) + words[i + 1:], new
 
     while todo:
         state = todo.pop()
@@ -71,6 +76,18 @@ def own_cells(k):
 def test_every_workgroup_gets_the_maximum(count):
     results, top = explore(count, own_cells)
     assert results == {(top,) * count}
+
+
+def test_words_of_the_ring_may_be_lost_where_the_source_stays():
+    results, top = explore(2, own_cells, in_place=False, lost_words=True)
+    assert results == {(top,) * 2}
+
+
+def test_losing_words_where_shares_are_overwritten_is_found():
+    """Why launches that overwrite their shares have words of their own: in the ring, where another launch can take a word away,
+    a maximum would be formed from new codes."""
+    results, top = explore(2, own_cells, lost_words=True)
+    assert any(r != (top,) * 2 for r in results)
 
 
 def test_reading_a_cell_of_another_share_is_found():

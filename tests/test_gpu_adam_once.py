@@ -35,7 +35,7 @@ class Tensor:
 
 @pytest.mark.parametrize("n,bf16", CASES)
 def test_one_launch_equals_two(n, bf16):
-    """Weights, their copy and the whole state (codes, scales; the range slots but for those of the two launches) after each of three steps."""
+    """Weights, their copy and the state (codes, scales; not the slots and words in which the ranges were formed) after each of three steps."""
     ref, once = Tensor(n, bf16, n), [Tensor(n, bf16, n) for _ in range(3)]
     torch.cuda.synchronize()
     for k in (1, 2, 3):
@@ -72,6 +72,34 @@ def test_steps_of_both_kinds_alternate():
             b.step(k)
         torch.cuda.synchronize()
         assert torch.equal(a.w.view(torch.int32), b.w.view(torch.int32)), k
+
+
+def test_many_tensors_on_one_stream_then_on_another():
+    """As a program does that enqueues the steps of a group of tensors on one stream and those of another group on another: every
+    exchange has words of its own.  Cut last chunks, so that workgroups have lanes without elements."""
+    sizes = [16 * (1 + 37 * i) for i in range(32)] + [CHUNK // 2 + 1040 * i for i in range(32)]
+    groups = [[Tensor(n, i % 3 == 0, 2 * i + s) for i, n in enumerate(sizes)] for s in range(2)]
+    want = [[Tensor(n, i % 3 == 0, 2 * i + s) for i, n in enumerate(sizes)] for s in range(2)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for k in (1, 2, 3):
+        for s in range(2):
+            with torch.cuda.stream(streams[s]):
+                for t in groups[s]:
+                    t.step(k)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()                       # two launches each
+        with torch.cuda.graph(graph):
+            for s in range(2):
+                for t in want[s]:
+                    t.step(k)
+        graph.replay()
+        torch.cuda.synchronize()
+        for s in range(2):
+            for a, b in zip(groups[s], want[s]):
+                codes = a.state.numel() - 2 * ((a.n + 255) // 256 * 256)
+                assert torch.equal(a.state[:256], b.state[:256]) and torch.equal(a.state[codes:], b.state[codes:]), (k, s, a.n)
+                assert torch.equal(a.w.view(torch.int32), b.w.view(torch.int32)) and torch.equal(a.wb.view(torch.int16), b.wb.view(torch.int16)), (k, s, a.n)
 
 
 def test_two_streams_at_once():
