@@ -89,8 +89,9 @@ ssg_status ssg_quantize(const void *src, ssg_dtype src_dtype, int64_t rows, int6
                         uint8_t *dst, uint8_t *dst_t, float *scale_dev, float *amax_dev, void *stream);
 
 /* As ssg_quantize.  Under current scaling a tensor that fits the chip's registers is quantized in one launch, whose
- * workgroups look for each other's ranges at most `polls` times (about a microsecond each) and then form what is
- * missing from the tensor themselves: the results are the same for any value, a negative one stands for the usual. */
+ * workgroups look for each other's ranges at most `polls` times (about a fifth of a microsecond each) and then form what is
+ * missing from the tensor themselves: the results are the same for any value.  A negative one stands for the usual number, 200,
+ * which is also the most. */
 ssg_status ssg_quantize_wait(const void *src, ssg_dtype src_dtype, int64_t rows, int64_t cols,
                              ssg_fp8_format fmt, ssg_scale_mode mode, ssg_scale_round rnd,
                              uint8_t *dst, uint8_t *dst_t, float *scale_dev, float *amax_dev, int32_t polls, void *stream);

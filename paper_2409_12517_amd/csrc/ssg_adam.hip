@@ -302,8 +302,8 @@ __global__ void __launch_bounds__(kHeldThreads, 2) adam_held_kernel(AdamParams p
             if (group_at(k, j) < (size_t)p.n) see(load(group_at(k, j)), mm, vm);
         return second ? vm : mm;
     };
-    const float amax_m = __uint_as_float(meet_max<kHeldThreads>(meeting, 0, blocks, own, words, [&](int k) { return share_max(k, false); }));
-    const float amax_v = __uint_as_float(meet_max<kHeldThreads>(meeting, kMeetBlocks, blocks, own, words, [&](int k) { return share_max(k, true); }));
+    const float amax_m = __uint_as_float(meet_max<kHeldThreads>(meeting, 0, blocks, (unsigned)own, words, [&](int k) { return share_max(k, false); }));
+    const float amax_v = __uint_as_float(meet_max<kHeldThreads>(meeting, kMeetBlocks, blocks, (unsigned)own, words, [&](int k) { return share_max(k, true); }));
     const float sm = scale_from_amax(amax_m, Fp8Traits<kE4M3>::fmax, p.pow2);
     const float sv = scale_from_amax(amax_v, Fp8Traits<kE5M2>::fmax, p.pow2);
     if (own == 0) leave_scalars(p, sm, sv, amax_m, amax_v);
@@ -354,8 +354,7 @@ void launch_adam_step(const AdamArgs &a, hipStream_t st) {
     constexpr size_t kHeldChunk = 4 * kHeldThreads;
     const size_t chunks = ((size_t)a.n + kHeldChunk - 1) / kHeldChunk;
     if (chunks <= (size_t)kMeetBlocks * kHeldGroups * kHeldBatches && !launch_recorded(st)) {
-        const MeetOwned meeting{p.scalars + kAdamSlotsM + (size_t)p.parity * 2 * kAmaxSlotWords, kAmaxSlots, (uint32_t)a.step,
-                                a.polls >= 0 ? a.polls : kMeetPolls};
+        const MeetOwned meeting{p.scalars + kAdamSlotsM + (size_t)p.parity * 2 * kAmaxSlotWords, kAmaxSlots, (uint32_t)a.step, meet_polls(a.polls)};
         const dim3 grid((unsigned)(chunks < kMeetBlocks ? chunks : kMeetBlocks));
         profile_before(33, st, update_bytes * (double)a.n);
         if (a.grad_bf16) hipLaunchKernelGGL(adam_held_kernel<true>, grid, dim3(kHeldThreads), 0, st, p, meeting);

@@ -257,7 +257,7 @@ struct AdamArgs {
     float beta1 = 0, beta2 = 0, one_minus_beta1 = 0, one_minus_beta2 = 0, c1 = 1, c2 = 1;
     float lr = 0, eps = 0, weight_decay = 0;
     int pow2 = 0;
-    int polls = -1;                  // looks at the others' ranges where the step is one launch, < 0: the usual number
+    int polls = -1;                  // looks at the others' ranges where the step is one launch, < 0: the usual number, the most
 };
 size_t adam_scalar_words();
 void launch_adam_init(uint32_t *scalars, uint8_t *codes, size_t code_bytes, hipStream_t st);

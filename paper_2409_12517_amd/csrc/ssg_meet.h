@@ -5,8 +5,9 @@
 // in a word of its own and looks at the words of the others until all are there.
 //
 // Nobody depends on another workgroup being on the chip: one that has looked `polls` times in vain forms the maxima that are
-// missing from the tensor itself (and leaves them for the others), so every workgroup ends whatever the rest do -- when two
-// such launches share the chip, when other work holds the compute units.
+// missing from the tensor itself and leaves them for the others, so every workgroup ends whatever the rest do -- when two
+// such launches share the chip, when other work holds the compute units.  Those that wait share this work, so it comes to about
+// another read of the tensor by all of them together.
 //
 // Two places for the words:
 //   MeetRing   rows of words that all launches of a translation unit share, for launches that leave their source as it is.  A word belongs
@@ -33,13 +34,20 @@ namespace ssg {
 
 constexpr int kMeetRows = 64;                               // launches enqueued in a row before two share a row of words
 constexpr int kMeetBlocks = 256;                            // workgroups that exchange a maximum, each maybe two
-constexpr int kMeetPolls = 400;                             // each takes about a microsecond
+// Looks before a workgroup forms what is missing, about a fifth of a microsecond each.  Alone no launch needs 20; where others hold the chip a
+// waiting workgroup holds a compute unit that the missing ones may need, but of two such launches at once one is done in less than
+// this wait.  Q of 4096 x 11008 with the transposed copy, on one stream, two and four at once, with 32 looks, 200 and 600: 35.6 us a call,
+// 47.4 and 56.9; 35.5, 33.9 and 62.9; 35.5, 33.9 and 84.6 (the separate launches 49.9, 43.0 and 47.6).
+constexpr int kMeetPolls = 200;
+// how often a caller may have them look (< 0: the usual number)
+inline int meet_polls(int asked) { return asked >= 0 && asked < kMeetPolls ? asked : kMeetPolls; }
 
 // the words of a translation unit's launches
 static __device__ uint64_t g_meet[kMeetRows][2 * kMeetBlocks][2];
 
 // (64-bit accesses are whole; a word is a pair of them, each with half of the ticket and the maximum, which have to agree)
 struct MeetRing {
+    static constexpr bool kOverwritten = false;
     uint64_t ticket;
     int polls;
     __device__ __forceinline__ void leave(int word, uint32_t v) const {
@@ -59,6 +67,7 @@ struct MeetRing {
 
 // 15 words in the upper 120 bytes of each 128-byte line from `base` on, 2 * kMeetBlocks of them in two runs `second` lines apart.
 struct MeetOwned {
+    static constexpr bool kOverwritten = true;
     uint32_t *base;
     int second;
     uint32_t tag;                                            // not zero
@@ -80,11 +89,13 @@ struct MeetOwned {
 };
 constexpr int kMeetOwnedLines = (kMeetBlocks + 14) / 15;    // of a run
 
-// The maximum over words first .. first + count - 1 (count <= kMeetBlocks <= the workgroup's threads), for all threads.  `own`:
-// this workgroup's word among them; share_max(k): this thread's part of the k-th one's maximum, formed from the tensor.
+// The maximum over words first .. first + count - 1 (count <= kMeetBlocks <= the workgroup's threads), for all threads.
+// share_max(k): this thread's part of the k-th one's maximum, formed from the tensor.  `salt`: a number that differs between
+// the workgroups that wait: each forms another one of what is missing, leaves it and looks at all again, so that they share the work.
 // lds: kMeetBlocks + 8 words.  Called by all threads of the workgroup.
 template <int THREADS, class Place, class ShareMax>
-__device__ __forceinline__ uint32_t meet_max(const Place &m, int first, int count, int own, uint32_t *lds, ShareMax &&share_max) {
+__device__ __forceinline__ uint32_t meet_max(const Place &m, int first, int count, unsigned salt, uint32_t *lds, ShareMax &&share_max) {
+    static_assert(THREADS >= kMeetBlocks && THREADS <= 512, "a thread looks at one word; a word of lds for each wave's maximum");
     const int t = threadIdx.x;
     constexpr uint32_t kMissing = 0xffffffffu;               // no maximum of magnitudes: above every number and infinity
     uint32_t v = 0u;
@@ -93,7 +104,6 @@ __device__ __forceinline__ uint32_t meet_max(const Place &m, int first, int coun
         have = m.look(first + t, v);
         if (!have) __builtin_amdgcn_s_sleep(2);
     }
-    if (!have) v = kMissing;
     auto over_workgroup = [&](uint32_t x) {
         x = wave_max_u32(x);
         __syncthreads();                                     // (whoever read lds before is done)
@@ -104,31 +114,35 @@ __device__ __forceinline__ uint32_t meet_max(const Place &m, int first, int coun
         for (int w = 0; w < THREADS / 64; ++w) r = r > lds[kMeetBlocks + w] ? r : lds[kMeetBlocks + w];
         return r;
     };
-    uint32_t all = over_workgroup(v);
-    if (all != kMissing) return all;
-    // some did not come in time: form theirs, beginning after this workgroup's own, so that several that wait share the work
-    if (t < count) lds[t] = v;
-    all = over_workgroup(v == kMissing ? 0u : v);
-    for (int n = 1; n <= count; ++n) {
-        const int k = (own + n) % count;
-        if (lds[k] != kMissing) continue;
-        auto look_again = [&]() {                            // by now it may have come
-            uint32_t x = kMissing;
-            if (t == 0 && !m.look(first + k, x)) x = kMissing;
-            return over_workgroup(t == 0 ? x : 0u);
-        };
-        uint32_t late = look_again();
-        if (late == kMissing) {
-            const uint32_t formed = over_workgroup(share_max(k));
-            late = look_again();
-            if (late == kMissing) {
-                late = formed;
-                if (t == 0) m.leave(first + k, late);
-            }
+    for (;;) {                                               // (at most `count` times: each adds one)
+        const uint32_t all = over_workgroup(have ? v : kMissing);
+        if (all != kMissing) return all;
+        // the (salt % missing)-th of those that are missing
+        const unsigned long long gone = __ballot(!have);
+        if ((t & 63) == 0 && t < kMeetBlocks) lds[t >> 6] = (uint32_t)__popcll(gone);
+        __syncthreads();
+        unsigned before = 0, missing = 0;
+#pragma unroll
+        for (int w = 0; w < kMeetBlocks / 64; ++w) {
+            before += w < t >> 6 ? lds[w] : 0u;
+            missing += lds[w];
         }
-        all = all > late ? all : late;
+        if (!have && before + (unsigned)__popcll(gone & ((1ull << (t & 63)) - 1)) == salt % missing) lds[kMeetBlocks / 64] = (uint32_t)t;
+        __syncthreads();
+        const int k = (int)lds[kMeetBlocks / 64];
+        uint32_t one = over_workgroup(share_max(k));
+        if (Place::kOverwritten) {                           // by now it may have come, and its share with it
+            uint32_t late = kMissing;
+            if (t == 0 && !m.look(first + k, late)) late = kMissing;
+            late = over_workgroup(t == 0 ? late : 0u);
+            if (late != kMissing) one = late;
+            else if (t == 0) m.leave(first + k, one);
+        } else if (t == 0) {
+            m.leave(first + k, one);
+        }
+        if (t == k) { v = one; have = true; }
+        if (!have) have = m.look(first + t, v);
     }
-    return all;
 }
 
 // Host: whether a launch on `st` would be recorded and could be replayed.

@@ -592,6 +592,7 @@ cast_h_w3_meet_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3,
                       const MeetRing meeting, const ScalingUpdate update) {
     __shared__ uint32_t words[kMeetBlocks + 8];
     const int t = threadIdx.x, groups = (int)((fac.f + kTile - 1) / kTile), mine = (int)blockIdx.x;
+    const unsigned salt = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     // of channel kTile * k + t: the range of s^-1 * w3, and of h
     auto w3_range = [&](int k) {
         const int64_t i = (int64_t)k * kTile + t;
@@ -618,7 +619,7 @@ cast_h_w3_meet_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3,
         auto scale_h = [&]() {                           // plain block: one scale for the whole tensor
             const bool first = first_row && mine == 0;
             float amax = 0.0f;
-            if (!fac.h_scale_given || first) amax = __uint_as_float(meet_max<256>(meeting, groups, groups, mine, words, h_range));
+            if (!fac.h_scale_given || first) amax = __uint_as_float(meet_max<256>(meeting, groups, groups, salt, words, h_range));
             if (first && t == 0) *fac.hmax = amax;
             return fac.h_scale_given ? *fac.h_scale_given : scale_from_amax(amax, 448.0f, 0);
         };
@@ -640,7 +641,7 @@ cast_h_w3_meet_kernel(const CastItem<LoadSwiglu> h, const CastItem<LoadBf16> w3,
         return;
     }
     auto scale_w3 = [&]() {
-        const float amax = __uint_as_float(meet_max<256>(meeting, 0, groups, mine, words, w3_range));
+        const float amax = __uint_as_float(meet_max<256>(meeting, 0, groups, salt, words, w3_range));
         if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) *fac.amax_w3s = amax;
         return scale_from_amax(amax, Fp8Traits<kE4M3>::fmax, pow2);
     };
@@ -889,7 +890,7 @@ __global__ void __launch_bounds__(kHeldThreads, 2) quantize_held_kernel(const He
         for (int w = 1; w < kHeldThreads / 64; ++w) m = m > words[w] ? m : words[w];
         batch.meeting.leave(b, m);
     }
-    const uint32_t bits = meet_max<kHeldThreads>(batch.meeting, it.first, it.blocks, own, words, [&](int k) {
+    const uint32_t bits = meet_max<kHeldThreads>(batch.meeting, it.first, it.blocks, (unsigned)own, words, [&](int k) {
         Seen s;
         for (int t = 0; k + t * it.blocks < it.tiles; ++t) {
             int64_t row0, col0;
@@ -990,7 +991,7 @@ static bool launch_quantize_held(const CastArgs *list, int n, const ZeroWords &z
     }
     const int per = held_tiles(batch.item, n, f32);
     if (per == 0 || !meet_ticket(st, &batch.meeting)) return false;
-    if (polls >= 0) batch.meeting.polls = polls;
+    batch.meeting.polls = meet_polls(polls);
     batch.pow2 = list[0].pow2;
     batch.zero = zero;
     unsigned blocks = 0;
