@@ -405,8 +405,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         // cycles, eight issue slots, and nothing may follow it but what these hold.
         //   Large tile, registers for one step's fragments: B hi, A hi of step k are read before the barrier (all of them two
         //   groups of four before it), A lo and B lo of step k+1 after it, each in the place of the one whose last product is done.
-        //   Small tile, bound by LDS: all that can be is read after the barrier (A lo, B lo, B hi of step k+1) and A hi right
-        //   before the second quarter, so that nothing is waited for at the barrier and reads are under way all the time.
+        //   Small tile, bound by LDS: half a fragment after every MFMA, B hi and A hi of step k before the barrier and A lo, B lo of step
+        //   k+1 after it, so that neither half has more to read or to issue than its MFMAs take.  (With B hi of step k+1 after
+        //   the barrier too, three quarters of the reads in one half: K-major operands, whose fragments take twice the
+        //   instructions, 48 x 896 x 10368 31.0 us and 29.5; 29 training steps in small tiles .4 % longer.)
         //   B lo is still in use when the next one is read: two sets, and steps in pairs.
         constexpr int kSlots = 2 * H * H;                   // MFMAs of half a step
         // the t-th MFMA of a half: by columns, in the third quarter by rows, back and forth
@@ -421,10 +423,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         // what is read after it, out of slots a and b (first half: of step k, second half: of step k+1)
         auto reads = [&](int set, int half, int t, uint32_t a, uint32_t b) {
             if (WB == 2) {
-                if (half == 0 && t < 2 * H) load_half(0, false, H + t / 2, a, t % 2);
-                if (half == 1 && t < 2 * H)
-                    for (int e = 0; e < 2; ++e) load_half(set ^ 1, t % 2 != 0, t / 2, t % 2 ? b : a, e);
-                if (half == 1 && t >= 2 * H) load_half(0, true, H + t / 2 - H, b, t % 2);
+                if (half == 0 && t < 2 * H) load_half(0, true, H + t / 2, b, t % 2);
+                if (half == 0 && t >= 2 * H) load_half(0, false, H + t / 2 - H, a, t % 2);
+                if (half == 1) load_half(set ^ 1, (t / 2) % 2 != 0, t / 4, (t / 2) % 2 ? b : a, t % 2);
                 return;
             }
             const int g = t / H, i = t % H;
@@ -467,9 +468,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                 load_half(0, false, g, 0, e);
                 load_half(0, true, g, 1, e);
             }
-        if (WB == 2)
-#pragma unroll
-            for (int n = 0; n < 2 * H; ++n) load_half(0, true, H + n / 2, 1, n % 2);
 
         uint32_t sa = 0, sb = 1, sp = UNITS - 1;     // ring slots of units 2k, 2k+1 and 2k+UNITS-1
         auto next_slot = [](uint32_t s) { const uint32_t t = s + 2; return t >= (uint32_t)kUnits ? t - kUnits : t; };
