@@ -281,20 +281,25 @@ int gemm_profile_tag(const GemmArgs &a) {
 }
 
 template <int WB, int UNITS, int EPI, int AFMT, int LAY>
-static void launch_tiles(const GemmParams &p, unsigned blocks, hipStream_t st) {
+static void launch_tiles(const GemmParams &p, bool wide, unsigned blocks, hipStream_t st) {
+    if constexpr (UNITS == kLongRing && EPI == EPI_STORE)
+        if (wide) {
+            hipLaunchKernelGGL((gemm_wide_kernel<AFMT, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
+            return;
+        }
     if constexpr (UNITS == kLongRing)
         hipLaunchKernelGGL((gemm_alone_kernel<EPI, AFMT, LAY>), dim3(blocks), dim3(kThreads), (unsigned)smem_bytes(2, kLongRing), st, p);
     else
         hipLaunchKernelGGL((gemm_kernel<WB, EPI, AFMT, 0, LAY>), dim3(blocks), dim3(kThreads), 0, st, p);
 }
 template <int WB, int UNITS, int LAY>
-static void launch_store_tiles(const GemmParams &p, int a_fmt, unsigned blocks, hipStream_t st) {
-    if (a_fmt == kE4M3) launch_tiles<WB, UNITS, EPI_STORE, kE4M3, LAY>(p, blocks, st);
-    else launch_tiles<WB, UNITS, EPI_STORE, kE5M2, LAY>(p, blocks, st);
+static void launch_store_tiles(const GemmParams &p, int a_fmt, bool wide, unsigned blocks, hipStream_t st) {
+    if (a_fmt == kE4M3) launch_tiles<WB, UNITS, EPI_STORE, kE4M3, LAY>(p, wide, blocks, st);
+    else launch_tiles<WB, UNITS, EPI_STORE, kE5M2, LAY>(p, wide, blocks, st);
 }
 
 template <int WB, int UNITS>
-static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream_t st) {
+static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream_t st, bool wide = false) {
     GemmParams p = make_gemm_params(a);
     const int tiles = p.tiles_m * p.tiles_n, hi = std::min((first_set + sets) * 8, tiles);
     p.first_set = first_set;
@@ -305,9 +310,9 @@ static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream
     switch (a.epilogue) {
         case EPI_STORE:
             if (a.a_fmt == kBF16) hipLaunchKernelGGL((gemm_kernel<4, EPI_STORE, kBF16, 0, 0>), dim3(blocks), dim3(kThreads), 0, st, p);
-            else if (a.layout == 2) launch_store_tiles<WB, UNITS, 2>(p, a.a_fmt, blocks, st);
-            else if (a.layout == 1) launch_store_tiles<WB, UNITS, 1>(p, a.a_fmt, blocks, st);
-            else launch_store_tiles<WB, UNITS, 0>(p, a.a_fmt, blocks, st);
+            else if (a.layout == 2) launch_store_tiles<WB, UNITS, 2>(p, a.a_fmt, wide, blocks, st);
+            else if (a.layout == 1) launch_store_tiles<WB, UNITS, 1>(p, a.a_fmt, wide, blocks, st);
+            else launch_store_tiles<WB, UNITS, 0>(p, a.a_fmt, wide, blocks, st);
             break;
         case EPI_SWIGLU:
             if (tail) {
@@ -316,11 +321,11 @@ static void launch_gemm_wb(const GemmArgs &a, int first_set, int sets, hipStream
                 const unsigned extra = (unsigned)(r.blocks_x * col_range_blocks_y(a.tail_rows));
                 hipLaunchKernelGGL(gemm_swiglu_col_range_kernel<WB>, dim3(blocks + extra), dim3(kThreads), 0, st, p, r);
             } else {
-                launch_tiles<WB, UNITS, EPI_SWIGLU, kE4M3, 0>(p, blocks, st);
+                launch_tiles<WB, UNITS, EPI_SWIGLU, kE4M3, 0>(p, false, blocks, st);
             }
             break;
         default:   // EPI_SWIGLU_Q
-            launch_tiles<WB, UNITS, EPI_SWIGLU_Q, kE4M3, 0>(p, blocks, st);
+            launch_tiles<WB, UNITS, EPI_SWIGLU_Q, kE4M3, 0>(p, false, blocks, st);
             break;
     }
     profile_after(st);
@@ -380,7 +385,16 @@ GemmPlan gemm_plan(const GemmArgs &a) {
     // one small tile to a compute unit, so up to 8 large tiles on an XCD of 32: the longer ring, which leaves no room
     // for a second workgroup (M = 528, N = 2048, K = 4096, 80 tiles: 27 us with five units, 21 with nine; 65 large tiles
     // give one XCD a second round: 28 and 34)
-    if (p.wave_blocks == 2 && tile_count(a, 4) - 8 * p.whole_sets <= kComputeUnits / 4) p.units = kLongRing;
+    const int64_t rest = tile_count(a, 4) - 8 * p.whole_sets;
+    if (p.wave_blocks == 2 && rest <= kComputeUnits / 4) p.units = kLongRing;
+    // The wide products but where power bounds these launches too: most of the chip at it, whole cache lines and enough K steps.
+    // Short and wide, of the time on wide products alone (before the short form): 256 tiles, K = 4096, .97 and 1.00 (both K-major), .95 and
+    // .98; 192 tiles .98 and .99, 1.02 and 1.01; K = 11008 .97 and 1.00, .99 and 1.00; 160 tiles, K = 4096, 1.00 and 1.00.  Lines split:
+    // 198 tiles, K = 1040, 4112 and 11024 1.025, 1.009 and 1.001, wide 1.002, 1.001 and .997; 7 tiles, K-major, 1.06 to 1.10
+    // and 1.02.  K = 1024: short .5 to 2 % longer than wide up to 256 tiles.
+    const int64_t small = p.whole_sets > 0 ? 4 * rest : tile_count(a, 2);
+    p.wide = a.epilogue == EPI_STORE && a.a_fmt != kBF16 && p.units == kLongRing &&
+             !(small > kComputeUnits * 5 / 8 && split_line_operands(a) == 0 && a.K >= 16 * BK);
     return p;
 }
 
@@ -403,7 +417,7 @@ bool launch_gemm(const GemmArgs &a, hipStream_t st) {
     const int full = plan.whole_sets, rest = sets_of(make_gemm_params(a)) - full;
     if (full > 0) launch_gemm_wb<4, 5>(a, 0, full, st);
     if (plan.wave_blocks == 4) launch_gemm_wb<4, 5>(a, 0, rest, st);
-    else if (plan.units == kLongRing) launch_gemm_wb<2, kLongRing>(a, full, rest, st);
+    else if (plan.units == kLongRing) launch_gemm_wb<2, kLongRing>(a, full, rest, st, plan.wide);
     else launch_gemm_wb<2, 5>(a, full, rest, st);
     return true;
 }

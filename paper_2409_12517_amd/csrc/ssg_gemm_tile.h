@@ -12,6 +12,8 @@
 // (4960 both on one repeated code), y at T = 4096, d = 4096, f = 11008 takes 122 us (126),
 // gate/up of the inference form and y together 424 (438).
 //
+// The small tile with its compute unit to itself is bound by latencies and takes the other form for plain stores (WIDE, in gemm_tile).
+//
 // Workgroup: 256 threads = 4 waves as 2 (M) x 2 (N).  Two tile sizes, by the template parameter WB:
 //   WB = 4  256 x 256 x 128, each wave owns 128 x 128 outputs = 8 x 8 MFMA blocks (256 accumulator registers, one wave
 //           per SIMD).  Bound by the power that the matrix cores and the way of the operands into LDS draw: 81 % of the cycles of
@@ -47,6 +49,7 @@ namespace ssg {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 typedef __attribute__((address_space(1))) const void *global_void_ptr;
 
@@ -92,7 +95,8 @@ struct GemmParams {
 // lanes 0-3, 12-15 and 20-27, then 4-11, 16-19 and 28-31, and the same of the upper half.  Rows 0-3 and 12-15 of one chunk meet
 // rows 4-11 of the next there, so 2 XOR (r >> 1) has to map each half of the rows onto itself: the two low bits of r >> 1
 // are exchanged.  (With r >> 1 as it stands half of the LDS cycles were conflicts: y at 4096 x 4096 x 11008 124 us, 49 % of them.)
-__device__ __forceinline__ int swz(int row) { return (row >> 1 & 4) | (row & 2) | (row >> 2 & 1); }
+// WIDE: a read takes 32 rows by two chunks c, c + 2, for which r >> 1 as it stands is right.
+template <bool WIDE = false> __device__ __forceinline__ int swz(int row) { return WIDE ? row >> 1 & 7 : (row >> 1 & 4) | (row & 2) | (row >> 2 & 1); }
 
 // Direct-to-LDS loads are issued through inline assembly: the compiler would otherwise wait for
 // ALL outstanding LDS-DMA loads before every ds_read (it cannot tell the two LDS stages apart),
@@ -139,6 +143,10 @@ __device__ __forceinline__ v4f mfma(const v8i &a, const v8i &b, const v4f &c) {
     } else {
         return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b, a, c, kE4M3, AFMT, 0, 0, 0, 0);
     }
+}
+template <int AFMT>
+__device__ __forceinline__ v16f mfma_wide(const v8i &a, const v8i &b, const v16f &c) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b, a, c, kE4M3, AFMT, 0, 0, 0, 0);
 }
 
 // The dequantization factor 1 / (sa * sb).  The product of two binary32 scales can leave the binary32 range
@@ -217,7 +225,14 @@ template <int N> __device__ __forceinline__ void wait_dma() {       // at most N
 // PART = 3: the sum of two products in one tile -- the K loop runs twice, over (A, B) and then over (A_ph2, B_ph2)
 // of the same shapes (or the other way round), and the accumulators are rescaled by the ratio of the two dequantization
 // factors in between, so that one epilogue with the last factor finishes both.
-template <int WB, int EPI, int AFMT, int PART, int LAY, int UNITS = 5>
+//
+// WIDE: the products on v_mfma_f32_32x32x64_f8f6f4, half as many of twice the length and half a K step each, 2 x 2 blocks of
+// 32 x 32 per wave.  With one workgroup of one wave per SIMD no other wave fills the gaps between MFMAs: 32 cycles do not hold the reads
+// and loads that go with one, 64 do.  (1040 x 2736 x 4112 23.9 us with the short form and 23.7; 48 x 896 x 10368, both K-major,
+// 29.6 and 27.7; 69 drawn contractions with one small tile to a compute unit and a K-major operand 1.026 and 1.005 times what they took
+// before there was the short form.)  Where the chip is full, power bounds the small tiles too: see gemm_plan.
+constexpr int kLongRing = 9;                          // operand tiles of the ring of a small tile with its compute unit to itself
+template <int WB, int EPI, int AFMT, int PART, int LAY, int UNITS = 5, bool WIDE = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock, const int sub, uint8_t *smem) {
     constexpr int BM = tile_edge(WB), BN = BM, WN = 32 * WB, kUnitBytes = unit_bytes(WB);
     constexpr int NI = 2 * WB;                         // DMA instructions of 1 KB per wave and unit
@@ -229,6 +244,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     constexpr bool kTwoWhole = TWO && WB == 4;         // no general loop body there (see sum_in_large_tile_ok)
     static_assert(!TWO || EPI == EPI_STORE, "a sum of two products ends in the plain store epilogue");
     constexpr bool AKM = LAY == 2, BKM = LAY >= 1;
+    static_assert(!WIDE || (WB == 2 && EPI == EPI_STORE && PART == 0 && AFMT != kBF16), "plain stores of the small tile");
     constexpr bool kBwd = EPI == EPI_SWIGLU_BWD || EPI == EPI_SWIGLU_BWD_Q;     // dH -> dU, dG through the SwiGLU derivative
     static_assert(!(BKM && (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_Q)), "the dual-B forms take K-contiguous operands");
     constexpr bool kDual = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_Q;     // B tile = half rows of W1, half of W2
@@ -258,11 +274,12 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     //     a half row, the chunk's own low bit picks the half.
     //   WB = 2 (two rows are the period): position c ^ ((k >> 1 & 3) << 1) ^ (k >> 5 & 1): the row's parity picks the half,
     //     the XOR spreads the four rows of one parity over four pairs of positions, k >> 5 picks the position of the pair.
+    //     (WIDE: 32 lanes read two adjacent chunks of eight K rows, and k >> 5 does not enter.)
     const int lrow = l >> 3;
-    const int chunk_even = (l & 7) ^ swz(lrow), chunk_odd = (l & 7) ^ swz(8 + lrow);
+    const int chunk_even = (l & 7) ^ swz<WIDE>(lrow), chunk_odd = (l & 7) ^ swz<WIDE>(8 + lrow);
     // the chunk that belongs at position `pos` of K row k (the maps are their own inverses in the low three bits)
     auto kmaj_chunk = [](int k, int pos) {
-        if (WB == 2) return pos ^ (((k >> 1) & 3) << 1) ^ ((k >> 5) & 1);
+        if (WB == 2) return pos ^ (((k >> 1) & 3) << 1) ^ (WIDE ? 0 : (k >> 5) & 1);
         const int low = (pos ^ k) & 7;
         return low | ((((pos >> 3) ^ (k >> 5) ^ low) & 1) << 3);
     };
@@ -302,18 +319,31 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 
     // LDS byte offset of this lane's two 16-byte chunks of a fragment: row l & 15 of 16, bytes 32 (l >> 4) .. + 31 of its 128; the
     // row block of a fragment adds a wave-uniform base and a compile-time multiple of 2 KB (an instruction immediate)
-    uint32_t frag_off[2];
+    // (WIDE: row l & 31 of 32, bytes 64 kh + 32 (l >> 5) .. + 31)
+    uint32_t frag_off[2], wide_off[2][2];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) frag_off[e] = (uint32_t)((l & 15) * BK + ((((l >> 4) * 2 + e) ^ swz(l & 15)) << 4));
+    for (int e = 0; e < 2; ++e) {
+        frag_off[e] = (uint32_t)((l & 15) * BK + ((((l >> 4) * 2 + e) ^ swz(l & 15)) << 4));
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh) wide_off[kh][e] = (uint32_t)((l & 31) * BK + (((kh * 4 + (l >> 5) * 2 + e) ^ swz<true>(l & 31)) << 4));
+    }
     // K-major operand: lane offsets of the transposing reads.  In every group of 16 lanes the even lanes supply
     // the 8-byte words whose byte j goes to output lane j, the odd lanes those for output lane 8+j; lane p of a
     // group therefore points at K row p/2 (of eight) and at half p%2 of the 16-byte chunk that holds the 16 rows of the
-    // fragment.  Four such reads (K rows +0, +8, +16, +24 from the group's 32) make one fragment.
+    // fragment.  Four such reads (K rows +0, +8, +16, +24 from the group's 32) make one fragment.  (WIDE: two groups read the two
+    // chunks of 32 rows, the other two the K rows 32 further on.)
     uint32_t tr_a[RB], tr_b[RB];
     {
-        const int kg = l >> 4, t = (l & 15) >> 1, e = l & 1;
+        const int kg = WIDE ? l >> 5 : l >> 4, t = (l & 15) >> 1, e = l & 1;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
+            if (WIDE) {
+                if (rb >= WB) break;
+                const int ca = (wm * WB + rb) * 2 + (l >> 4 & 1), cb = (wn * WB + rb) * 2 + (l >> 4 & 1), turn = (t >> 1) << 1;
+                tr_a[rb] = (uint32_t)((kg * 32 + t) * BM + ((ca ^ turn) << 4) + e * 8);
+                tr_b[rb] = (uint32_t)((kg * 32 + t) * BM + ((cb ^ turn) << 4) + e * 8);
+                continue;
+            }
             // position of chunk c in K row k = kg * 32 + t (+ multiples of 8 below 32, which do not enter)
             auto pos = [&](int c) { return WB == 2 ? c ^ ((t >> 1) << 1) ^ (kg & 1) : ((c ^ t) & 7) | ((((c >> 3) ^ kg ^ c) & 1) << 3); };
             tr_a[rb] = (uint32_t)((kg * 32 + t) * BM + (pos(wm * RB + rb) << 4) + e * 8);
@@ -331,6 +361,11 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
     for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < RB; ++nb) acc[mb][nb] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    v16f wide[WB][WB];                                  // WIDE: in the place of acc
+#pragma unroll
+    for (int mb = 0; mb < WB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < WB; ++nb) wide[mb][nb] = v16f{};
 
     const int nk = (int)((p.K + BK - 1) / BK);
     // the staging patch of the epilogue (one 32-row slab of a wave's accumulators at a time), also used where a
@@ -373,7 +408,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             }
         };
         constexpr int H = RB / 2;                            // "lo" and "hi": the first and the second half of a wave's row blocks
-        constexpr int kSets = WB == 4 ? 1 : 2;
+        constexpr int kSets = WB == 4 || WIDE ? 1 : 2;
         v8i fa[RB], fb_lo[kSets][H], fb_hi[H];
         // half e of a fragment, row block g of A (is_b: of B; lo: into `set`), out of ring slot `slot`
         auto load_half = [&](int set, bool is_b, int g, uint32_t slot, int e) {
@@ -391,6 +426,31 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
                 const uint4 q = *reinterpret_cast<const uint4 *>(smem + (frag_off[e] + ub) + imm);
                 f[4 * e] = (int)q.x; f[4 * e + 1] = (int)q.y; f[4 * e + 2] = (int)q.z; f[4 * e + 3] = (int)q.w;
             }
+        };
+        // WIDE: fragment i of four (in the order of use) of K half kh, out of slots a and b
+        v8i wa[2][WB], wb[2][WB];
+        auto load_wide = [&](int kh, int i, uint32_t a, uint32_t b) {
+            const bool is_b = i % 2 == 0;
+            const int rb = i / 2;
+            v8i f;
+            if (is_b ? BKM : AKM) {
+                typedef int v2i_t __attribute__((ext_vector_type(2)));
+                typedef __attribute__((address_space(3))) v2i_t *lds_v2i_ptr;
+                const uint8_t *base = smem + (is_b ? b : a) * kUnitBytes + (is_b ? tr_b[rb] : tr_a[rb]) + kh * 64 * BM;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const v2i_t q = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i_ptr)(base + k * 8 * BM));
+                    f[2 * k] = q.x; f[2 * k + 1] = q.y;
+                }
+            } else {
+                const uint32_t ub = (is_b ? b : a) * kUnitBytes + (is_b ? b_wave_base : a_wave_base);   // uniform
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const uint4 q = *reinterpret_cast<const uint4 *>(smem + (wide_off[kh][e] + ub) + rb * 32 * BK);
+                    f[4 * e] = (int)q.x; f[4 * e + 1] = (int)q.y; f[4 * e + 2] = (int)q.z; f[4 * e + 3] = (int)q.w;
+                }
+            }
+            (is_b ? wb : wa)[kh][rb] = f;
         };
         auto mul = [&](int set, int r, int c) { acc[r][c] = mfma<AFMT>(fa[r], c < H ? fb_lo[set][c % H] : fb_hi[c % H], acc[r][c]); };
         // s_waitcnt lgkmcnt(0) through the builtin (gfx9 encoding: vmcnt and expcnt fields at their
@@ -410,9 +470,14 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         //   the barrier too, three quarters of the reads in one half: K-major operands, whose fragments take twice the
         //   instructions, 48 x 896 x 10368 31.0 us and 29.5; 29 training steps in small tiles .4 % longer.)
         //   B lo is still in use when the next one is read: two sets, and steps in pairs.
-        constexpr int kSlots = 2 * H * H;                   // MFMAs of half a step
+        //   WIDE: the second half of step k is read before the barrier, the first half of step k+1 after it.
+        constexpr int kSlots = WIDE ? WB * WB : 2 * H * H;  // MFMAs of half a step
         // the t-th MFMA of a half: by columns, in the third quarter by rows, back and forth
         auto product = [&](int set, int half, int t) {
+            if constexpr (WIDE) {
+                wide[t / WB][t % WB] = mfma_wide<AFMT>(wa[half][t / WB], wb[half][t % WB], wide[t / WB][t % WB]);
+                return;
+            }
             const int q = 2 * half + t / (H * H), g = t % (H * H) / H, i = t % H;
             const int up = g & 1 ? H - 1 - i : i, down = H - 1 - up;
             if (q == 0) mul(set, up, g);
@@ -422,6 +487,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         };
         // what is read after it, out of slots a and b (first half: of step k, second half: of step k+1)
         auto reads = [&](int set, int half, int t, uint32_t a, uint32_t b) {
+            if constexpr (WIDE) {
+                load_wide(half ^ 1, t, a, b);
+                return;
+            }
             if (WB == 2) {
                 if (half == 0 && t < 2 * H) load_half(0, true, H + t / 2, b, t % 2);
                 if (half == 0 && t >= 2 * H) load_half(0, false, H + t / 2 - H, a, t % 2);
@@ -440,7 +509,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
             }
         };
         // which load of its unit is issued there, -1: none
-        auto load_at = [](int t) { return WB == 2 ? (t % 2 ? t / 2 : -1) : (t % H == 2 ? t / H : -1); };
+        auto load_at = [](int t) { return WIDE ? t : WB == 2 ? (t % 2 ? t / 2 : -1) : (t % H == 2 ? t / H : -1); };
 
         const int kwhole = (int)(p.K / BK);                 // K steps with all their 128 bytes; a ragged last one is zero filled
         const int64_t a_step = AKM ? (int64_t)BK * p.M : BK, b_step = BKM ? (int64_t)BK * p.N : BK;   // bytes per K step
@@ -461,13 +530,18 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
         else wait_dma<0>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int g = 0; g < H; ++g)
+            for (int i = 0; i < 2 * WB; ++i) load_wide(0, i, 0, 1);
+        } else {
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                load_half(0, false, g, 0, e);
-                load_half(0, true, g, 1, e);
-            }
+            for (int g = 0; g < H; ++g)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    load_half(0, false, g, 0, e);
+                    load_half(0, true, g, 1, e);
+                }
+        }
 
         uint32_t sa = 0, sb = 1, sp = UNITS - 1;     // ring slots of units 2k, 2k+1 and 2k+UNITS-1
         auto next_slot = [](uint32_t s) { const uint32_t t = s + 2; return t >= (uint32_t)kUnits ? t - kUnits : t; };
@@ -619,10 +693,20 @@ __device__ __forceinline__ void gemm_tile(const GemmParams &p, const int vblock,
 #pragma unroll
         for (int s = 0; s < WB; ++s) {
             if (slab != s) continue;
+            if constexpr (WIDE) {
+                // a lane holds row l & 31 and, four registers at a time, columns 8 q + 4 (l >> 5) .. + 3 of a block
 #pragma unroll
-            for (int r = 0; r < 2; ++r)
+                for (int nb = 0; nb < WB; ++nb)
 #pragma unroll
-                for (int nb = 0; nb < RB; ++nb) *stg_at(r, nb) = acc[2 * s + r][nb];
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<v4f *>(stg + (l & 31) * kPitch + (l >> 5) * 4 + nb * 32 + q * 8) =
+                            v4f{wide[s][nb][4 * q], wide[s][nb][4 * q + 1], wide[s][nb][4 * q + 2], wide[s][nb][4 * q + 3]};
+            } else {
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int nb = 0; nb < RB; ++nb) *stg_at(r, nb) = acc[2 * s + r][nb];
+            }
             asm volatile("; slab %0" :: "n"(s));         // (else the compiler makes one block of them, indexing registers in memory)
         }
     };
@@ -985,13 +1069,18 @@ __global__ void __launch_bounds__(kThreads, waves_per_simd(WB)) gemm_kernel(Gemm
 }
 // The small tile with its compute unit to itself, a ring of nine.  The LDS is named at the launch: a compiler that sees 144 KB
 // plans for one wave per SIMD, keeps accumulators in both halves of the register file and moves them about in the loop (116 moves
-// to 32 MFMAs: 2048 x 2048 x 11008 50.6 us).
-constexpr int kLongRing = 9;
+// to 32 MFMAs: 2048 x 2048 x 11008 50.6 us).  With the wide products it keeps them in one half.
 extern __shared__ __attribute__((aligned(1024))) uint8_t g_long_ring[];
 template <int EPI, int AFMT, int LAY>
 __global__ void __launch_bounds__(kThreads, waves_per_simd(2)) gemm_alone_kernel(GemmParams p) {
     const int b = (int)blockIdx.x, vb = (p.first_set + set_of<2>(b)) * 8 + (b & 7);
     if (vb < p.tiles_m * p.tiles_n) gemm_tile<2, EPI, AFMT, 0, LAY, kLongRing>(p, vb, quarter_of<2>(b), g_long_ring);
+}
+template <int AFMT, int LAY>
+__global__ void __launch_bounds__(kThreads, 1) gemm_wide_kernel(GemmParams p) {
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[smem_bytes(2, kLongRing)];
+    const int b = (int)blockIdx.x, vb = (p.first_set + set_of<2>(b)) * 8 + (b & 7);
+    if (vb < p.tiles_m * p.tiles_n) gemm_tile<2, EPI_STORE, AFMT, 0, LAY, kLongRing, true>(p, vb, quarter_of<2>(b), smem);
 }
 
 // Host side: algorithmic flops of the whole contraction (both weight matrices of the SwiGLU forms, both products

@@ -175,6 +175,7 @@ bool launch_gemm(const GemmArgs &a, hipStream_t st);
 struct GemmPlan {
     int wave_blocks = 4;        // 4: tiles of 256 x 256, 2: tiles of 128 x 128, 0: few rows
     int units = 5;              // operand tiles of the ring
+    bool wide = false;          // the long ring: the products on the wide MFMA (see gemm_tile)
     int whole_sets = 0;         // > 0: so many sets of 8 large tiles in a launch before that of the small ones
     int form = 0;               // few rows: which of its forms
     int rest_rows = 0;          // > 0: the batch's last rows, in the few-rows form in the grid of the small tiles
