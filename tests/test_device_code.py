@@ -11,8 +11,7 @@ import subprocess
 
 import pytest
 
-import paper_2409_12517_amd as ssg
-
+LIB = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2409_12517_amd", "libssg.so")
 OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 WAIT_STATES = 2
@@ -77,7 +76,7 @@ def test_finder():
 def test_no_store_data_is_overwritten_early(tmp_path):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
-    objects = list(code_objects(ssg.LIB_PATH))
+    objects = list(code_objects(LIB))
     assert objects, "no gfx950 code in the library"
     stores, bad = 0, []
     for i, code in enumerate(objects):
