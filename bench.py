@@ -201,7 +201,7 @@ def mfma_ceiling(ssg, torch, saved_view_bytes, stream):
             best = max(best, flops / (e0.elapsed_time(e1) * 1e-3) / 1e12)
         out[name] = best
     out["unit"] = "TFLOP/s"
-    out["note"] = "256 workgroups x 4 waves x 16 accumulator blocks of v_mfma_f32_32x32x64_f8f6f4, best of 2 launches of about 8 ms (long enough for the clock to settle)"
+    out["note"] = "256 workgroups x 4 waves x 32 accumulator blocks of v_mfma_f32_16x16x128_f8f6f4, best of 2 launches of about 8 ms (long enough for the clock to settle)"
     return out
 
 
@@ -238,7 +238,7 @@ def summarize_profiles(src: str) -> int:
 
     shape = "Llama2-7B MLP shape, fwd+bwd, T=4096 d=4096 f=11008"
     legend = ("gemm_kernel<blocks per wave, epilogue, A format, part, layout, ring units>: 4 blocks per wave = 256 x 256 tile, "
-              "2 = 128 x 128; gemm_skinny_kernel = few rows; epilogue 0 = store, 1 = SwiGLU forward (U, G, channel maxima), 2 = SwiGLU "
+              "2 = 128 x 128; gemm_alone_kernel and gemm_wide_kernel = 128 x 128 with the long ring; gemm_skinny_kernel = few rows; epilogue 0 = store, 1 = SwiGLU forward (U, G, channel maxima), 2 = SwiGLU "
               "backward, 3 = SwiGLU + E4M3 cast (inference form), 4 = SwiGLU backward + E5M2 cast (delayed scaling); A format 0 = E4M3, "
               "1 = E5M2; part 3 = a sum of two products in one launch; layout 0 = both operands K-contiguous, 1 = B K-major, 2 = A and B "
               "K-major.  gemm_group_dh_dw3_kernel = dH then the first part of dW3 in one grid; gemm_group_dx_dw_kernel = dX, then dW1, dW2 and "
