@@ -35,11 +35,12 @@ def code_objects(path):
 
 
 def registers(operand):
-    """Numbers of the vector registers of an operand such as v7 or v[4:7]; empty: something else."""
-    m = re.fullmatch(r"v(\d+)|v\[(\d+):(\d+)\]", operand)
+    """The vector registers of an operand such as v7, v[4:7] or a[0:3] (accumulation registers); empty: something else."""
+    m = re.fullmatch(r"([va])(?:(\d+)|\[(\d+):(\d+)\])", operand)
     if not m:
         return set()
-    return {int(m[1])} if m[1] else set(range(int(m[2]), int(m[3]) + 1))
+    numbers = [int(m[2])] if m[2] else range(int(m[3]), int(m[4]) + 1)
+    return {(m[1], n) for n in numbers}
 
 
 def early_overwrites(lines):
@@ -70,6 +71,8 @@ def test_finder():
     assert not early_overwrites([scalar, "\tv_add_f32_e32 v6, s4, v2", "\tv_mov_b32_e32 v7, v2", "\tv_mov_b32_e32 v2, v7"])
     assert not early_overwrites([scalar, "\ts_nop 1", "\tv_mov_b32_e32 v2, v7"])
     assert early_overwrites(["\tglobal_store_dwordx4 v[18:19], v[2:5], off", "\tv_mov_b32_e32 v5, v7"])
+    assert early_overwrites(["\tglobal_store_dwordx4 v[18:19], a[2:5], off", "\tv_accvgpr_write_b32 a3, v7"])
+    assert not early_overwrites(["\tglobal_store_dwordx4 v[18:19], a[2:5], off", "\tv_mov_b32_e32 v3, v7"])
     assert not early_overwrites(["\tglobal_store_dwordx2 v[18:19], v[2:3], off", "\tv_mov_b32_e32 v2, v7"])
 
 
